@@ -112,14 +112,16 @@ def measure(rot, U, O, out, d, precision, steps, warmup, symmetric=False):
     mp = U.shape[1]
     p = rot._problem(U, O, out, d)
     prec = rot.precision_code(precision)
-    ws = torch.empty(rot.rot_workspace_size([p], prec), dtype=torch.uint8, device=U.device)
+    ws = torch.empty(rot.rot_workspace_preferred([p], prec), dtype=torch.uint8, device=U.device)
     ms, kernels, per_step = time_steps(rot, U, O, out, ws, d, precision, steps, warmup, True, symmetric)
     del ws
     ops_per_s = n * steps / (ms / 1e3)
     F = flops_per_op(m, d, mp, symmetric)
     tflops = F * ops_per_s / 1e12
-    peak = PEAK_TFLOPS[precision]
-    exec_factor = 3.0 if precision == "split_bf16" else 1.0
+    # FP32 batches on FP16 pairs execute three 16-bit products per FP32 one
+    pairs = any(k.endswith("_f16x3") for k in kernels)
+    peak = PEAK_TFLOPS["split_bf16" if pairs else precision]
+    exec_factor = 3.0 if precision == "split_bf16" or pairs else 1.0
     per_launch_flops = {"stage1": n * 2.0 * m * m * d * mp, "stage2": n * 2.0 * m * d * mp * mp,
                         "stage2sym": n * 1.0 * m * d * mp * (mp + 1),
                         "small": n * (2.0 * m * m * d * mp + 2.0 * m * d * mp * mp)}  # both stages, one launch

@@ -58,7 +58,10 @@ typedef enum {
 
 typedef enum {
     ROT_FP64 = 0,        /* double buffers, FP64 matrix cores */
-    ROT_FP32 = 1,        /* float buffers, FP32 matrix cores, FP32 accumulation */
+    ROT_FP32 = 1,        /* float buffers, FP32 accumulation: FP32 matrix cores,
+                            or for larger dense batches three products of
+                            FP16 pairs that hold the scaled operands to FP32's
+                            last bit, whose results are the more exact */
     ROT_SPLIT_BF16 = 2   /* float buffers; each operand x = hi + lo with
                             hi = bf16(x), lo = bf16(x - hi) (round to nearest
                             even); products hi*hi + hi*lo + lo*hi on BF16
@@ -109,7 +112,13 @@ typedef struct {
  * bits from a call whose workspace is too small to split.  An FP64 group
  * with m <= 64 and mp <= 64 (not ROT_OUT_SYMMETRIC) is rotated in a single
  * launch that keeps both stages in LDS and leaves the workspace untouched
- * (its size is still checked as for any group).  Groups may have
+ * (its size is still checked as for any group).  An FP32 group of 1 GFLOP or
+ * more (m, mp >= 64, d <= 8) runs on FP16 pairs when the workspace holds the
+ * split operands of the group (rot_workspace_preferred) or of chunks of at
+ * least 8 GFLOP, with the same bits for every chunk size; its operators with
+ * infinities, NaN or rows whose largest entries differ by more than 2^12 are
+ * computed by the FP32 kernels, all of them if U holds an infinity or NaN.
+ * Groups may have
  * different m, d, mp.  ROT_SPLIT_BF16 picks each stage's tile configuration per shape (m, d,
  * mp, chunk): from the tuning cache (in memory, and in the file named by
  * ROT_TUNE_CACHE), else on the shape's first call by timing the candidates
@@ -134,6 +143,15 @@ ROT_API rot_status rot_batch(const rot_problem* groups, int32_t n_groups, rot_pr
  */
 ROT_API rot_status rot_batch_ex(const rot_problem* groups, int32_t n_groups, rot_precision prec, uint32_t flags,
                         void* workspace, size_t workspace_bytes, void* stream);
+
+/*
+ * rot_batch_ex in ROT_FP32 on the FP32 matrix cores whatever the batch
+ * (rot_batch_ex runs larger batches on FP16 pairs, whose sums are rounded
+ * elsewhere): for callers that compare results with earlier ones digit by
+ * digit, such as a loss formed in FP64 from the rotated operators.
+ */
+ROT_API rot_status rot_batch_fp32(const rot_problem* groups, int32_t n_groups, uint32_t flags, void* workspace,
+                                  size_t workspace_bytes, void* stream);
 
 /*
  * rot_batch_ex without a workspace argument, for callers that cannot
@@ -166,6 +184,14 @@ ROT_API size_t rot_noalloc_scratch_bytes(void);
  */
 ROT_API size_t rot_workspace_size(const rot_problem* groups, int32_t n_groups, rot_precision prec,
                           int32_t ops_per_chunk, int32_t for_backward);
+
+/*
+ * Workspace bytes with which rot_batch runs these groups fastest: at least
+ * rot_workspace_size(groups, n_groups, prec, 0, 0), and room for the split
+ * operands of the FP32 groups that run on FP16 pairs.  0 for invalid
+ * arguments.
+ */
+ROT_API size_t rot_workspace_preferred(const rot_problem* groups, int32_t n_groups, rot_precision prec);
 
 /*
  * Reverse-mode derivative of rot_batch (not in the paper).  For each group,

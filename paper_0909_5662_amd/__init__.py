@@ -6,7 +6,7 @@ supplies device memory and the current stream.  There is no CPU fallback:
 if the library is missing, importing the binding's entry points raises.
 
 The entry points mirror the C ABI (include/librot.h):
-  rot_batch, rot_backward, rot_batch_blocked, rot_pair_loss,
+  rot_batch, rot_batch_fp32, rot_backward, rot_batch_blocked, rot_pair_loss,
   rot_check_isometry, rot_split_bf16, rot_workspace_size
 plus tensor-level helpers ``rotate``, ``rotate_backward``, ``pair_loss``,
 ``check_isometry``, ``rotate_blocked`` and the autograd functions
@@ -26,8 +26,8 @@ import torch
 __all__ = [
     "ROT_FP64", "ROT_FP32", "ROT_SPLIT_BF16", "ROT_ASSUME_SYMMETRIC_O", "RotError",
     "RotProblem", "problem", "RotSector", "RotBlockedProblem", "lib", "library_path",
-    "rot_batch", "rot_batch_noalloc", "rot_backward", "rot_batch_blocked", "rot_pair_loss", "rot_check_isometry",
-    "rot_split_bf16", "rot_workspace_size", "rot_blocked_workspace_size",
+    "rot_batch", "rot_batch_fp32", "rot_batch_noalloc", "rot_backward", "rot_batch_blocked", "rot_pair_loss", "rot_check_isometry",
+    "rot_split_bf16", "rot_workspace_size", "rot_workspace_preferred", "rot_blocked_workspace_size",
     "rotate", "rotate_backward", "pair_loss", "check_isometry", "split_bf16",
     "RotateFn", "PairLossFn", "precision_code", "profile_enable", "profile_read",
     "blocked_problem", "rotate_blocked", "Plan", "ROT_PLAN_NO_GRAPH", "ROT_PLAN_NO_TUNE", "ROT_PLAN_RETUNE",
@@ -128,12 +128,16 @@ def lib() -> ctypes.CDLL:
         vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
         L.rot_batch.argtypes = [ctypes.POINTER(RotProblem), i32, ctypes.c_int, vp, sz, vp]
         L.rot_batch_ex.argtypes = [ctypes.POINTER(RotProblem), i32, ctypes.c_int, ctypes.c_uint32, vp, sz, vp]
+        L.rot_batch_fp32.argtypes = [ctypes.POINTER(RotProblem), i32, ctypes.c_uint32, vp, sz, vp]
+        L.rot_batch_fp32.restype = ctypes.c_int
         L.rot_batch_noalloc.argtypes = [ctypes.POINTER(RotProblem), i32, ctypes.c_int, ctypes.c_uint32, vp]
         L.rot_batch_noalloc.restype = ctypes.c_int
         L.rot_noalloc_scratch_bytes.argtypes = []
         L.rot_noalloc_scratch_bytes.restype = sz
         L.rot_workspace_size.argtypes = [ctypes.POINTER(RotProblem), i32, ctypes.c_int, i32, i32]
         L.rot_workspace_size.restype = sz
+        L.rot_workspace_preferred.argtypes = [ctypes.POINTER(RotProblem), i32, ctypes.c_int]
+        L.rot_workspace_preferred.restype = sz
         L.rot_backward.argtypes = [ctypes.POINTER(RotProblem), i32, ctypes.POINTER(vp), ctypes.POINTER(i64),
                                    ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.c_uint32, ctypes.c_int,
                                    vp, sz, vp]
@@ -247,12 +251,23 @@ def rot_workspace_size(groups, prec: int, ops_per_chunk: int = 0, for_backward: 
     return lib().rot_workspace_size(arr, len(groups), prec, ops_per_chunk, int(for_backward))
 
 
+def rot_workspace_preferred(groups, prec: int) -> int:
+    arr = (RotProblem * len(groups))(*groups)
+    return lib().rot_workspace_preferred(arr, len(groups), prec)
+
+
 def rot_batch(groups, prec: int, workspace: int, workspace_bytes: int, stream: int, flags: int = 0) -> None:
     arr = (RotProblem * len(groups))(*groups)
     if flags:
         _check(lib().rot_batch_ex(arr, len(groups), prec, flags, workspace, workspace_bytes, stream))
     else:
         _check(lib().rot_batch(arr, len(groups), prec, workspace, workspace_bytes, stream))
+
+
+def rot_batch_fp32(groups, workspace: int, workspace_bytes: int, stream: int, flags: int = 0) -> None:
+    """rot_batch in FP32 on the FP32 matrix cores whatever the batch."""
+    arr = (RotProblem * len(groups))(*groups)
+    _check(lib().rot_batch_fp32(arr, len(groups), flags, workspace, workspace_bytes, stream))
 
 
 def rot_batch_noalloc(groups, prec: int, stream: int, flags: int = 0) -> None:
@@ -382,7 +397,7 @@ def rotate(U: torch.Tensor, O: torch.Tensor, d: int, precision="fp32", out: torc
         _row_layout(out, "out")
     p = _problem(U, O, out, d)
     if workspace is None:
-        workspace = _workspace(rot_workspace_size([p], prec), U.device)
+        workspace = _workspace(rot_workspace_preferred([p], prec), U.device)
     rot_batch([p], prec, workspace.data_ptr(), workspace.numel(), _stream(stream),
               ROT_ASSUME_SYMMETRIC_O if symmetric_O else 0)
     return out
@@ -818,7 +833,16 @@ class RotateFn(torch.autograd.Function):
         ctx.d = d
         ctx.precision = precision
         ctx.symmetric_O = symmetric_O
-        return rotate(U, O, d, precision)
+        if precision_code(precision) != ROT_FP32:
+            return rotate(U, O, d, precision)
+        # on the FP32 matrix cores: a loss formed in FP64 from the result shows
+        # where its sums are rounded
+        _check_inputs(U, O, d, ROT_FP32)
+        out = torch.empty((O.shape[0], U.shape[1], U.shape[1]), dtype=U.dtype, device=U.device)
+        p = _problem(U, O, out, d)
+        workspace = _workspace(rot_workspace_size([p], ROT_FP32), U.device)
+        rot_batch_fp32([p], workspace.data_ptr(), workspace.numel(), _stream())
+        return out
 
     @staticmethod
     def backward(ctx, dOut):

@@ -81,6 +81,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmDesc g, int tile
         lin -= part * per;
     }
     const TileCoord tc = tile_coord(lin, tiles_m, tiles_n, g.upper);
+    if (g.only && !g.only[tc.g]) return;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -249,6 +250,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_dl_kernel(GemmDesc g, int t
     __shared__ __attribute__((aligned(1024))) float Bs[2][DB::ELEMS];
 
     const TileCoord tc = tile_coord(xcd_linear_id(), tiles_m, tiles_n, UPPER);
+    if (g.only && !g.only[tc.g]) return;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;

@@ -1,0 +1,870 @@
+// FP32 rotation on FP16 pairs.  The FP32 matrix instructions run at 1/16 of
+// the FP16 ones' rate, so a product of FP32 operands taken as three FP16
+// products (hi*hi + hi*lo + lo*hi, FP32 accumulation) has over five times the
+// FP32 peak to work with.  It is no less exact: a scaled pair holds an FP32
+// value to its last bit (split2_f16), the dropped lo*lo term is below 2^-22
+// of a product and averages 2^-25, and the sum is rounded three times per 16
+// k where the FP32 instructions round eight times.  Measured against 64 bits
+// (relative Frobenius error, Gaussian operators; FP32 kernels -> pairs):
+// 1024 states 1.28e-6 -> 8.0e-7, 403: 8.0e-7 -> 5.1e-7, 256: 4.4e-7 ->
+// 3.2e-7, 128: 2.6e-7 -> 2.1e-7, 64: 2.1e-7 -> 1.8e-7.
+// Time of the two stages and all passes around them, 64 operators of 1024
+// states: 8.02 -> 2.75 ms; 65 of 403 (kept 391): 1.31 -> 0.28 ms.
+//
+// Scaling.  U's columns and each operator are brought to a largest entry in
+// [2^14, 2^15) by exact powers of two (eu[beta], eo[b]).  |T| of the scaled
+// operands is below m 2^30, so stage 1's epilogue multiplies by 2^-t with
+// t = 15 + ceil(log2 m) before it splits T; stage 2's undoes every scale.
+// FP16's range leaves T entries down to 2^-16 of that bound (Gaussian
+// operators of 1024 states sit at 2^-9) at full precision.  An operator with
+// an infinity or NaN, or whose rows' largest entries differ by more than
+// 2^12 (its small rows of T would fall out of that range), and every operator
+// when U holds one, is skipped by these kernels and computed by the FP32
+// kernels that follow, which leave the others alone (skip[b]).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <functional>
+
+#include "buffer_rsrc.h"
+#include "lds_slice.h"
+#include "rot_internal.h"
+#include "split_slab.h"
+
+namespace rot {
+namespace {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+// four floats at any 4-byte boundary: global_load_dwordx4 needs no more
+typedef f32x4 f32x4u __attribute__((aligned(4)));
+
+// FP16 carries 11 significant bits to BF16's 8, in a range of 2^30 instead of
+// FP32's: its operands are scaled by powers of two first (|x| < 2^15), so
+// hi + lo holds x to 2^-23 of itself (FP32's last bit) or 2^-40 of the
+// operand's largest entry, whichever is larger.
+__device__ inline u32x2 split2_f16(float a, float b) {
+    const f16x2 h = {(_Float16)a, (_Float16)b};
+    const f16x2 l = {(_Float16)(a - (float)h[0]), (_Float16)(b - (float)h[1])};
+    return u32x2{__builtin_bit_cast(uint32_t, h), __builtin_bit_cast(uint32_t, l)};
+}
+
+// Rotation products with one A for every operator (U1 or U2) and one B per
+// operator: the operators' B rows, each padded to whole blocks of 32, are laid
+// end to end, and a tile takes 8 consecutive blocks (256 columns) whatever
+// operator they belong to, so only the last tile of the launch and each
+// operator's last block hold padding (403 columns: 3 % where 256-wide tiles
+// per operator computed 21 %).  Tiles have 64 bi rows (64 to 256);
+// the last M tile shrinks to the multiple of 64 that covers the rest of M.
+// K may be cut into parts of `part_slabs` slabs, whose products go to their
+// own partial results (c_ps apart) to be added in a fixed order.
+struct FlatDesc {
+    int M, N, K, batch;         // C_b (M x N) = A (M x K) B_b^T
+    const uint16_t *a_hi, *a_lo;  // slab layout, M rows
+    const uint16_t *b_hi, *b_lo;  // slab layout, n32 rows per operator, b_bs elements apart
+    int64_t b_bs;
+    int n32;                    // N rounded up to 32
+    int bi;                     // 32-row blocks per wave: 64 bi rows per tile
+    int tiles_m, tiles_n, parts, part_slabs;
+    // plain epilogue: C_b(row, col) 2^-(e0 + op_e[b] + row_e[row] + col_e[col])
+    // at c + part*c_ps + b*c_bs + row*ldc + col
+    float* c;
+    int64_t ldc, c_bs, c_ps;
+    int e0;
+    const int *op_e, *row_e, *col_e;  // row_e: readable up to the last tile's rows
+    // split-transposed epilogue: C_b(beta*d + s, i) 2^-t_shift -> T_b(beta, i*d + s),
+    // slab layout with t_rows rows per operator, t_bs elements apart
+    uint16_t *t_hi, *t_lo;
+    int d, t_rows, t_shift;
+    int64_t t_bs;
+    const int* skip;            // operators left to the FP32 kernels
+    // symmetric output (M == N, plain epilogue): tiles below the diagonal of
+    // all their operators are left out, entries on or above it are also stored
+    // transposed
+    int upper;
+};
+
+__device__ inline f32x16 mfma_f16(f16x8 a, f16x8 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+
+constexpr int kFlatRing = 6;                         // LDS stages of A
+constexpr int kFlatArr = 256 * kSlabK;               // elements of A_hi (or A_lo) in a stage
+constexpr int kFlatLds = kFlatRing * 2 * kFlatArr;   // elements
+
+// One tile of (64 BI) x 256 as 2 x 4 waves of (32 BI) x 64, by
+// gemm_bf16x3_db_kernel's scheme: A through the LDS ring, B fragments straight
+// into three register sets two slabs ahead.  A stage always holds 256 rows
+// (those past the tile are copied and not read), so every wave issues the
+// same number of loads and the waits stay immediate.
+template <int BI, bool EPI_T, bool D4>
+__device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& g, uint16_t* lds, int m0, int nt,
+                                                                int part) {
+    constexpr int BJ = 2, S = kFlatRing, ARR = kFlatArr, STAGE = 2 * ARR;
+    constexpr int LA = 2, LB = 2 * BJ;
+    constexpr int WAIT_A0 = (S - 2) * LA + 2 * LB;
+    constexpr int WAIT_A = (S - 3) * LA + (S - 2) * LB;
+    constexpr int WAIT_B = 2 * (LA + LB), WAIT_B0 = LA + 2 * LB;
+    static_assert(WAIT_A0 <= 63 && WAIT_A <= 63 && WAIT_B <= 63, "vmcnt range");
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    const int h = lane >> 5, c = lane & 31;
+    const int st0 = part * g.part_slabs;
+    const int nk = min(g.part_slabs, (int)n_slabs(g.K) - st0);
+
+    const __amdgpu_buffer_rsrc_t ra[2] = {operand_rsrc(g.a_hi, g.M, g.K), operand_rsrc(g.a_lo, g.M, g.K)};
+    const int b_bytes = (int)(uint32_t)(g.batch * g.b_bs * 2);
+    const __amdgpu_buffer_rsrc_t rb[2] = {
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.b_hi), (short)0, b_bytes, kBufferFlags),
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.b_lo), (short)0, b_bytes, kBufferFlags)};
+    const uint32_t a_slab = (uint32_t)g.M * kSlabK * 2, b_slab = (uint32_t)g.n32 * kSlabK * 2;
+    const uint32_t a_off = (uint32_t)((m0 + wave * 32) * kSlabK * 2 + lane * 16) + (uint32_t)st0 * a_slab;
+    const int fslot = (h ^ ((c >> 3) & 1)) * 8;
+    // this wave's column blocks: operator and block inside it (blocks past the
+    // last operator repeat its last one and are not stored)
+    const int bpo = g.n32 >> 5, nblk = bpo * g.batch;
+    int op[BJ], cb[BJ];
+    uint32_t b_off[BJ];
+    bool live[BJ];
+#pragma unroll
+    for (int j = 0; j < BJ; j++) {
+        const int x = nt * 8 + wn * BJ + j;
+        live[j] = x < nblk;
+        const int y = min(x, nblk - 1);
+        op[j] = y / bpo;
+        cb[j] = y - op[j] * bpo;
+        b_off[j] = (uint32_t)(op[j] * g.b_bs * 2) + (uint32_t)(((cb[j] * 32 + c) * kSlabK + fslot) * 2) +
+                   (uint32_t)st0 * b_slab;
+    }
+
+    auto issue_a = [&](int st) __attribute__((always_inline)) {
+        uint16_t* base = lds + (st % S) * STAGE + wave * 512;
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                ra[j], (__attribute__((address_space(3))) void*)(base + j * ARR), 16, a_off + (uint32_t)st * a_slab,
+                0, 0, 0);
+    };
+    struct BSet {
+        f16x8 bh[BJ], bl[BJ];
+    };
+    auto issue_b = [&](BSet& o, int st) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < BJ; j++) {
+            const uint32_t off = b_off[j] + (uint32_t)st * b_slab;
+            o.bh[j] = __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(rb[0], off, 0, 0));
+            o.bl[j] = __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(rb[1], off, 0, 0));
+        }
+    };
+
+    f32x16 acc[BI][BJ];
+#pragma unroll
+    for (int i = 0; i < BI; i++)
+#pragma unroll
+        for (int j = 0; j < BJ; j++)
+#pragma unroll
+            for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
+
+    f16x8 ah[BI], al[BI];
+    auto read_a = [&](int i, int st) __attribute__((always_inline)) {
+        const uint16_t* sb = lds + (st % S) * STAGE;
+        const int ra_ = (wm * 32 * BI + i * 32 + c) * kSlabK + fslot;
+        ah[i] = *reinterpret_cast<const f16x8*>(sb + ra_);
+        al[i] = *reinterpret_cast<const f16x8*>(sb + ARR + ra_);
+    };
+    auto barrier = [&]() __attribute__((always_inline)) {
+        compiler_fence();
+        __builtin_amdgcn_s_barrier();
+        compiler_fence();
+    };
+
+    // the wait counts assume exactly this issue order
+    BSet bs[3];
+#pragma unroll
+    for (int st = 0; st <= S - 2; st++) {
+        issue_a(st);
+        compiler_fence();
+    }
+    issue_b(bs[0], 0);
+    compiler_fence();
+    issue_b(bs[1], 1);
+    compiler_fence();
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(WAIT_A0));
+    barrier();
+#pragma unroll
+    for (int i = 0; i < BI; i++) read_a(i, 0);
+
+#define FLAT_STEP(T_, CUR, NB, WA, WB)                                                                    \
+    do {                                                                                                  \
+        const int t_ = (T_);                                                                              \
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(WA));                                                        \
+        barrier();                                                                                        \
+        issue_a(t_ + S - 1);                                                                              \
+        compiler_fence();                                                                                 \
+        issue_b(NB, t_ + 2);                                                                              \
+        compiler_fence();                                                                                 \
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(WB));                                                        \
+        compiler_fence();                                                                                 \
+        _Pragma("unroll") for (int i = 0; i < BI; i++) {                                                  \
+            _Pragma("unroll") for (int k = 0; k < BJ; k++) acc[i][k] =                                    \
+                mfma_f16(al[i], (CUR).bh[k], acc[i][k]);                                                   \
+            _Pragma("unroll") for (int k = 0; k < BJ; k++) acc[i][k] =                                    \
+                mfma_f16(ah[i], (CUR).bl[k], acc[i][k]);                                                   \
+            _Pragma("unroll") for (int k = 0; k < BJ; k++) acc[i][k] =                                    \
+                mfma_f16(ah[i], (CUR).bh[k], acc[i][k]);                                                   \
+            read_a(i, t_ + 1);                                                                            \
+        }                                                                                                 \
+        compiler_fence();                                                                                 \
+    } while (0)
+    constexpr int WA0 = (S - 3) * LA + 2 * LB;
+    constexpr int WA1 = (S - 3) * LA + 3 * LB;
+    constexpr int WA2 = (S - 3) * LA + 4 * LB;
+    FLAT_STEP(0, bs[0], bs[2], WA0, WAIT_B0);
+    FLAT_STEP(1, bs[1], bs[0], WA1, WAIT_B);
+    FLAT_STEP(2, bs[2], bs[1], WA2, WAIT_B);
+    int t = 3;
+    for (; t + 3 <= nk; t += 3) {
+        FLAT_STEP(t, bs[0], bs[2], WAIT_A, WAIT_B);
+        FLAT_STEP(t + 1, bs[1], bs[0], WAIT_A, WAIT_B);
+        FLAT_STEP(t + 2, bs[2], bs[1], WAIT_A, WAIT_B);
+    }
+    // the last one or two steps wait for every earlier load (their own B loads
+    // are never used, and the compiler may drop them)
+    if (t < nk) FLAT_STEP(t, bs[0], bs[2], 0, 0);
+    if (t + 1 < nk) FLAT_STEP(t + 1, bs[1], bs[0], 0, 0);
+#undef FLAT_STEP
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    __builtin_amdgcn_s_waitcnt(kLgkmcnt0);
+
+    const int row0w = m0 + wm * 32 * BI;
+#pragma unroll
+    for (int k = 0; k < BJ; k++) {
+        const int col = cb[k] * 32 + c;
+        if (!live[k] || col >= g.N || g.skip[op[k]]) continue;
+        if (EPI_T) {
+            uint16_t* th = g.t_hi + op[k] * g.t_bs;
+            uint16_t* tl = g.t_lo + op[k] * g.t_bs;
+#pragma unroll
+            for (int i = 0; i < BI; i++)
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    const int row0 = row0w + i * 32 + 8 * q + 4 * h;
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; e++) v[e] = ldexpf(acc[i][k][4 * q + e], -g.t_shift);
+                    const u32x2 p0 = split2_f16(v[0], v[1]), p1 = split2_f16(v[2], v[3]);
+                    const u32x2 hv = {p0[0], p1[0]}, lv = {p0[1], p1[1]};
+                    if (D4) {
+                        if (row0 < g.M) {
+                            const int64_t off = slab_off(row0 >> 2, (int64_t)col * 4, g.t_rows);
+                            *reinterpret_cast<u32x2*>(th + off) = hv;
+                            *reinterpret_cast<u32x2*>(tl + off) = lv;
+                        }
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {
+                            const int row = row0 + e;
+                            if (row < g.M) {
+                                const int64_t off = slab_off(row / g.d, (int64_t)col * g.d + row % g.d, g.t_rows);
+                                th[off] = (uint16_t)(hv[e >> 1] >> (16 * (e & 1)));
+                                tl[off] = (uint16_t)(lv[e >> 1] >> (16 * (e & 1)));
+                            }
+                        }
+                    }
+                }
+        } else if (g.upper) {
+            float* cp = g.c + part * g.c_ps + op[k] * g.c_bs;
+            const int e0 = -(g.e0 + g.op_e[op[k]] + g.col_e[col]);
+#pragma unroll
+            for (int i = 0; i < BI; i++)
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    const int row0 = row0w + i * 32 + 8 * q + 4 * h;
+                    if (row0 > col) continue;
+                    const i32x4 er = *reinterpret_cast<const i32x4*>(g.row_e + row0);
+                    f32x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; e++) v[e] = ldexpf(acc[i][k][4 * q + e], e0 - er[e]);
+                    float* mirror = cp + (int64_t)col * g.ldc + row0;
+                    if (row0 + 3 <= col) {
+                        *reinterpret_cast<f32x4u*>(mirror) = v;
+#pragma unroll
+                        for (int e = 0; e < 4; e++) cp[(int64_t)(row0 + e) * g.ldc + col] = v[e];
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; e++)
+                            if (row0 + e <= col) {
+                                mirror[e] = v[e];
+                                cp[(int64_t)(row0 + e) * g.ldc + col] = v[e];
+                            }
+                    }
+                }
+        } else {
+            float* cp = g.c + part * g.c_ps + op[k] * g.c_bs + col;
+            const int e0 = -(g.e0 + g.op_e[op[k]] + g.col_e[col]);
+#pragma unroll
+            for (int i = 0; i < BI; i++)
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    const int row0 = row0w + i * 32 + 8 * q + 4 * h;
+                    const i32x4 er = *reinterpret_cast<const i32x4*>(g.row_e + row0);
+#pragma unroll
+                    for (int e = 0; e < 4; e++)
+                        if (row0 + e < g.M) cp[(int64_t)(row0 + e) * g.ldc] = ldexpf(acc[i][k][4 * q + e], e0 - er[e]);
+                }
+        }
+    }
+}
+
+template <int BI, bool EPI_T, bool D4>
+__global__ __launch_bounds__(512, 1) void gemm_flat_kernel(FlatDesc g) {
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[kFlatLds];
+    const int lin = xcd_linear_id();
+    const int mt = lin % g.tiles_m, r = lin / g.tiles_m, nt = r % g.tiles_n, part = r / g.tiles_n;
+    const int m0 = mt * 64 * BI;
+    if (!EPI_T && g.upper) {
+        // the tile's 8 blocks: their largest column is one operator's last
+        // block's if the tile crosses an operator's end, else the last one's
+        const int bpo = g.n32 >> 5, first = nt * 8, last = min(first + 7, bpo * g.batch - 1);
+        const int top = first / bpo == last / bpo ? last % bpo : bpo - 1;
+        if (m0 > top * 32 + 31) return;
+    }
+    // M tiles fastest: neighbouring workgroups share the B panel
+    const int rest = min(BI, (g.M - m0 + 63) / 64);
+    if (rest == BI) flat_tile<BI, EPI_T, D4>(g, lds, m0, nt, part);
+    else if (BI > 3 && rest == 3) flat_tile<BI < 3 ? BI : 3, EPI_T, D4>(g, lds, m0, nt, part);
+    else if (BI > 2 && rest == 2) flat_tile<BI < 2 ? BI : 2, EPI_T, D4>(g, lds, m0, nt, part);
+    else flat_tile<1, EPI_T, D4>(g, lds, m0, nt, part);
+}
+
+constexpr int kF16MaxSite = 8;          // a split block holds 16 j of all site states
+constexpr int kF16RowSpread = 12;       // log2 of the accepted spread of row maxima
+constexpr int kPrepRows = 256;          // rows of U per partial column maximum
+constexpr int kPrepORows = 32;          // rows of O per partial maximum
+constexpr uint32_t kInfBits = 0x7f800000u;
+
+// Launch-time sizes and pointers of the scale pass.
+struct F16Scale {
+    const float* U;
+    int rows, mp, d;
+    int64_t ldu;
+    const float* O;
+    int m, nb;
+    int64_t ldo, stride_o;
+    uint32_t* upart;   // [chunk][mp]: largest |U| of a column in kPrepRows rows (bits)
+    uint32_t* ublk;    // [U block of the scale pass]: largest |U|
+    uint32_t* opart;   // [b][row block][2]: largest |O|, smallest non-zero row maximum
+    int* eu;           // [mp]
+    int n_ublk;
+    int m32, mp32;     // rows of O_b's and T_b's layouts
+    int* eo;           // [nb]
+    int* skip;         // [nb]
+    uint16_t *u1h, *u1l, *u2h, *u2l;
+    uint16_t *oh, *ol;
+    int64_t o_bs;
+    uint16_t *th, *tl;
+    int64_t t_bs;
+    int u_blocks;      // workgroups that work on U (0: done by an earlier chunk)
+    int o_blocks;      // and on O
+};
+
+inline __host__ __device__ int div_up(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+__device__ inline uint32_t abs_bits(float x) { return __float_as_uint(x) & 0x7fffffffu; }
+__device__ inline uint32_t umax32(uint32_t a, uint32_t b) { return a > b ? a : b; }
+__device__ inline uint32_t umin32(uint32_t a, uint32_t b) { return a < b ? a : b; }
+
+// Power of two that brings a largest magnitude (bits) into [2^14, 2^15).
+__device__ inline int scale_exp(uint32_t bits) {
+    if (bits == 0 || bits >= kInfBits) return 0;
+    return 14 - ilogbf(__uint_as_float(bits));
+}
+
+// Partial maxima of |U| per column and of |O| per operator.  Bound by the one
+// read of O and U.
+__global__ __launch_bounds__(256) void f16_scale_kernel(F16Scale g) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ uint32_t red[4][64];
+    int blk = blockIdx.x;
+    if (blk < g.u_blocks) {
+        const int cb = div_up(g.mp, 64);
+        const int c = (blk % cb) * 64 + lane, r0 = (blk / cb) * kPrepRows;
+        const int r1 = min(r0 + kPrepRows, g.rows);
+        uint32_t mx = 0;
+        if (c < g.mp) {
+#pragma unroll 16
+            for (int r = r0 + wave; r < r1; r += 4) mx = umax32(mx, abs_bits(g.U[(int64_t)r * g.ldu + c]));
+        }
+        red[wave][lane] = mx;
+        __syncthreads();
+        if (wave == 0) {
+            mx = umax32(umax32(red[0][lane], red[1][lane]), umax32(red[2][lane], red[3][lane]));
+            if (c < g.mp) g.upart[(int64_t)(blk / cb) * g.mp + c] = mx;
+#pragma unroll
+            for (int s = 32; s; s >>= 1) mx = umax32(mx, __shfl_xor(mx, s));
+            if (lane == 0) g.ublk[blk] = mx;
+        }
+        return;
+    }
+    blk -= g.u_blocks;
+    const int rb = div_up(g.m, kPrepORows);
+    const int b = blk / rb, i0 = (blk % rb) * kPrepORows;
+    const float* src = g.O + (int64_t)b * g.stride_o;
+    uint32_t mx = 0, mn = 0xffffffffu;
+    // eight rows per wave, their loads in flight together (rows past the last
+    // repeat it)
+    constexpr int RW = kPrepORows / 4;
+    const int r0 = i0 + wave * RW;
+    if (r0 < g.m) {
+        uint32_t x[RW];
+#pragma unroll
+        for (int k = 0; k < RW; k++) x[k] = 0;
+        const int m4 = g.m & ~3;
+#pragma unroll 2
+        for (int j = lane * 4; j < m4; j += 256)
+#pragma unroll
+            for (int k = 0; k < RW; k++) {
+                const f32x4u v = *reinterpret_cast<const f32x4u*>(src + (int64_t)min(r0 + k, g.m - 1) * g.ldo + j);
+#pragma unroll
+                for (int e = 0; e < 4; e++) x[k] = umax32(x[k], abs_bits(v[e]));
+            }
+        if (m4 + lane < g.m)
+#pragma unroll
+            for (int k = 0; k < RW; k++)
+                x[k] = umax32(x[k], abs_bits(src[(int64_t)min(r0 + k, g.m - 1) * g.ldo + m4 + lane]));
+#pragma unroll
+        for (int k = 0; k < RW; k++) {
+#pragma unroll
+            for (int s = 32; s; s >>= 1) x[k] = umax32(x[k], __shfl_xor(x[k], s));
+            mx = umax32(mx, x[k]);
+            if (x[k]) mn = umin32(mn, x[k]);
+        }
+    }
+    if (lane == 0) {
+        red[0][wave] = mx;
+        red[1][wave] = mn;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t* o = g.opart + 2 * ((int64_t)b * rb + i0 / kPrepORows);
+        o[0] = umax32(umax32(red[0][0], red[0][1]), umax32(red[0][2], red[0][3]));
+        o[1] = umin32(umin32(red[1][0], red[1][1]), umin32(red[1][2], red[1][3]));
+    }
+}
+
+// U, O and T's K padding into the slab layout:
+//   U1 (d*mp rows, K = m):   element (beta*d + s, j) = U[j*d+s][beta] 2^eu[beta]
+//   U2 (mp rows, K = m*d):   element (alpha, r)      = U[r][alpha] 2^eu[alpha]
+//   O_b (m32 rows, K = m):   element (i, j)          = O_b[i][j] 2^eo[b]
+// A workgroup on U takes 16 j (16 d rows) x 64 columns through LDS: one slab
+// of U1's rows and d slabs of U2's, both written in whole 16-byte chunks,
+// chunk after chunk.  One on O takes a 64 x 64 block (split_o_kernel's
+// scheme).  The first block of each operator records eo[b] and skip[b].
+template <int DMAX>
+__global__ __launch_bounds__(256) void f16_split_kernel(F16Scale g) {
+    static_assert(DMAX <= kF16MaxSite, "tile size");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ __attribute__((aligned(16))) float tile[DMAX <= 4 ? 64 * 68 : 16 * DMAX * 65];
+    __shared__ int s_e[64];
+    __shared__ uint32_t s_mx[4][64];
+    int blk = blockIdx.x;
+    const int u_chunks = div_up(g.rows, kPrepRows);
+    auto store8 = [&](uint16_t* hi, uint16_t* lo, const float (&v)[8]) {
+        const u32x2 p0 = split2_f16(v[0], v[1]), p1 = split2_f16(v[2], v[3]);
+        const u32x2 p2 = split2_f16(v[4], v[5]), p3 = split2_f16(v[6], v[7]);
+        *reinterpret_cast<u32x4*>(hi) = u32x4{p0[0], p1[0], p2[0], p3[0]};
+        *reinterpret_cast<u32x4*>(lo) = u32x4{p0[1], p1[1], p2[1], p3[1]};
+    };
+    if (blk < g.u_blocks) {
+        const int cb = div_up(g.mp, 64), d = g.d;
+        const int a0 = (blk % cb) * 64, q = blk / cb, r0 = q * 16 * d, nr = 16 * d;
+        const int a = a0 + lane;
+        // loads first (clamped addresses, all in flight together), then LDS
+        const int ac = min(a, g.mp - 1);
+        uint32_t mx = 0;
+#pragma unroll 4
+        for (int x = wave; x < u_chunks; x += 4) mx = umax32(mx, g.upart[(int64_t)x * g.mp + ac]);
+        float v[DMAX * 4];
+#pragma unroll
+        for (int k = 0; k < DMAX * 4; k++)
+            v[k] = g.U[(int64_t)min(r0 + wave + 4 * k, g.rows - 1) * g.ldu + ac];
+        s_mx[wave][lane] = mx;
+#pragma unroll
+        for (int k = 0; k < DMAX * 4; k++)
+            if (wave + 4 * k < nr) tile[(wave + 4 * k) * 65 + lane] = r0 + wave + 4 * k < g.rows ? v[k] : 0.f;
+        __syncthreads();
+        if (wave == 0) {
+            mx = umax32(umax32(s_mx[0][lane], s_mx[1][lane]), umax32(s_mx[2][lane], s_mx[3][lane]));
+            s_e[lane] = scale_exp(mx);
+            if (q == 0 && a < g.mp) g.eu[a] = scale_exp(mx);
+        }
+        __syncthreads();
+        const int na = min(64, g.mp - a0);
+        // U1: rows a*d + s of slab q, chunk (row, slot)
+        const int64_t rows1 = (int64_t)d * g.mp;
+        for (int x = tid; x < na * d * 2; x += 256) {
+            const int row = x >> 1, slot = x & 1, al = row / d, s = row - al * d;
+            const int64_t gr = (int64_t)a0 * d + row;
+            const int half = slot ^ (int)((gr >> 3) & 1), e = s_e[al];
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; k++) v[k] = ldexpf(tile[((half * 8 + k) * d + s) * 65 + al], e);
+            const int64_t off = (int64_t)q * rows1 * kSlabK + gr * kSlabK + slot * 8;
+            store8(g.u1h + off, g.u1l + off, v);
+        }
+        // U2: rows a of slabs q*d .. q*d + d - 1
+        const int64_t ns2 = n_slabs(g.rows);
+        for (int x = tid; x < na * d * 2; x += 256) {
+            const int sl = x / (na * 2), y = x - sl * (na * 2), al = y >> 1, slot = y & 1;
+            const int64_t sq = (int64_t)q * d + sl;
+            if (sq >= ns2) break;
+            const int half = slot ^ (((a0 + al) >> 3) & 1), e = s_e[al];
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; k++) v[k] = ldexpf(tile[(sl * 16 + half * 8 + k) * 65 + al], e);
+            const int64_t off = sq * (int64_t)g.mp * kSlabK + (int64_t)(a0 + al) * kSlabK + slot * 8;
+            store8(g.u2h + off, g.u2l + off, v);
+        }
+        return;
+    }
+    blk -= g.u_blocks;
+    if (blk < g.o_blocks) {
+        const int tb = div_up(g.m, 64);
+        const int b = blk / (tb * tb), t = blk % (tb * tb), i0 = (t / tb) * 64, j0 = (t % tb) * 64;
+        const float* src = g.O + (int64_t)b * g.stride_o;
+        if (j0 + 64 <= g.m) {
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const int r = (tid >> 4) + 16 * k, c4 = (tid & 15) * 4, i = i0 + r;
+                // rows past the last repeat it (they are not written)
+                *reinterpret_cast<f32x4*>(&tile[r * 68 + c4]) =
+                    *reinterpret_cast<const f32x4u*>(src + (int64_t)min(i, g.m - 1) * g.ldo + j0 + c4);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 16; k++) {
+                const int i = i0 + wave + 4 * k, j = j0 + lane;
+                tile[(wave + 4 * k) * 68 + lane] = (i < g.m && j < g.m) ? src[(int64_t)i * g.ldo + j] : 0.f;
+            }
+        }
+        if (wave == 0) {
+            const int rb = div_up(g.m, kPrepORows);
+            const uint32_t* p = g.opart + 2 * (int64_t)b * rb;
+            uint32_t mx = 0, mn = 0xffffffffu;
+            for (int x = lane; x < rb; x += 64) {
+                mx = umax32(mx, p[2 * x]);
+                mn = umin32(mn, p[2 * x + 1]);
+            }
+            for (int s = 32; s; s >>= 1) {
+                mx = umax32(mx, __shfl_xor(mx, s));
+                mn = umin32(mn, __shfl_xor(mn, s));
+            }
+            if (lane == 0) s_e[0] = scale_exp(mx);
+            if (t == 0) {
+                bool bad = mx >= kInfBits ||
+                           (mx && ilogbf(__uint_as_float(mx)) - ilogbf(__uint_as_float(mn)) > kF16RowSpread);
+                for (int x = lane; x < g.n_ublk; x += 64) bad |= g.ublk[x] >= kInfBits;
+                bad = __any(bad);
+                if (lane == 0) {
+                    g.eo[b] = scale_exp(mx);
+                    g.skip[b] = bad;
+                }
+            }
+        }
+        __syncthreads();
+        const int e = s_e[0];
+        const int64_t nslab = n_slabs(g.m);
+#pragma unroll
+        for (int x = 0; x < 2; x++) {
+            const int ch = tid + 256 * x;  // slab q, k half, row
+            const int q = ch >> 7, half = (ch >> 6) & 1, row = ch & 63;
+            const int i = i0 + row;
+            const int64_t sq = j0 / kSlabK + q;
+            if (i >= g.m || sq >= nslab) continue;
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; k++) v[k] = ldexpf(tile[row * 68 + q * kSlabK + half * 8 + k], e);
+            const int64_t off = (int64_t)b * g.o_bs + sq * (int64_t)g.m32 * kSlabK + (int64_t)i * kSlabK +
+                                (half ^ ((i >> 3) & 1)) * 8;
+            store8(g.oh + off, g.ol + off, v);
+        }
+        return;
+    }
+    // T's last slab (stage 1 writes only k < m*d): zeros, 16 bytes per chunk
+    blk -= g.o_blocks;
+    const int tb = div_up((int64_t)g.mp * 2, 256);
+    const int b = blk / tb, x = (blk % tb) * 256 + tid;
+    if (x >= g.mp * 2) return;
+    const int64_t off = (int64_t)b * g.t_bs + (n_slabs(g.rows) - 1) * (int64_t)g.mp32 * kSlabK + (int64_t)x * 8;
+    *reinterpret_cast<u32x4*>(g.th + off) = u32x4{0, 0, 0, 0};
+    *reinterpret_cast<u32x4*>(g.tl + off) = u32x4{0, 0, 0, 0};
+}
+
+// Rows per tile (64 bi) and K parts of a flat product.
+struct FlatCfg {
+    int bi, parts, part_slabs;
+};
+
+// The choice with the least estimated time: tiles go to 256 CUs one per CU
+// (the ring fills the LDS), so a launch takes whole rounds of its tile's
+// time; smaller tiles cost more per row and K parts cost a pass over the
+// partial results, and pay where the tiles are too few to fill the chip
+// (512 states, 48 operators, stage 2: 256-row tiles 0.145 ms, 192: 0.20,
+// 128: 0.20; 256 states, 20 operators, stage 1: 25.0 against 18.3 us for
+// 128 rows).  At least min_parts.  out_bytes: bytes of the whole result, read and written once more per part.
+FlatCfg flat_cfg(int M, int blocks, int slabs, int min_parts, int max_parts, double out_bytes) {
+    // us per slab of a tile of 64 bi rows with the chip full (1024-state
+    // batches of 64 operators, stage 2), and around its K loop
+    static const double cost[5] = {0, 0.66, 0.74, 0.96, 1.22};
+    const double around = 5;
+    FlatCfg best{4, 1, slabs};
+    double best_t = 1e30;
+    const int tn = div_up(blocks, 8);
+    for (int bi = 4; bi >= 1; bi--)
+        for (int parts = min_parts; parts <= max_parts; parts++) {
+            const int ps = div_up(slabs, parts);
+            if (parts > min_parts && (ps < 8 || (int64_t)ps * (parts - 1) >= slabs - 2)) break;
+            const int full = M / (64 * bi), rest = div_up(M - full * 64 * bi, 64);
+            const double tf = cost[bi] * ps + around, tr = rest ? cost[rest] * ps + around : 0;
+            const double tiles = (double)(full + (rest > 0)) * tn * parts;
+            const double busy = (full * tf + tr) * tn * parts / 256;
+            // whole rounds when all tiles are alike, about half a tile of tail otherwise
+            double t = full ? (rest ? std::max(tf, busy + 0.4 * tf) : std::ceil(tiles / 256) * tf) : std::ceil(tiles / 256) * tr;
+            if (tiles <= 256) t = full ? tf : tr;
+            if (parts > 1) t += 4 + (parts + 1) * out_bytes / 4e6;
+            if (t < best_t * 0.97) {
+                best_t = t;
+                best = {bi, parts, ps};
+            }
+        }
+    return best;
+}
+
+constexpr int kF16MaxParts = 8;
+
+template <bool EPI_T, bool D4>
+hipError_t launch_flat(FlatDesc g, const FlatCfg& c, hipStream_t s) {
+    g.bi = c.bi;
+    g.parts = c.parts;
+    g.part_slabs = c.part_slabs;
+    g.tiles_m = div_up(g.M, 64 * c.bi);
+    g.tiles_n = div_up((int64_t)g.batch * (g.n32 / 32), 8);
+    const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n * g.parts;
+    if (tiles > 0x7fffffff || n_slabs(g.K) - (int64_t)(g.parts - 1) * g.part_slabs < 3) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)tiles), block(512);
+    switch (c.bi) {
+        case 1: hipLaunchKernelGGL((gemm_flat_kernel<1, EPI_T, D4>), grid, block, 0, s, g); break;
+        case 2: hipLaunchKernelGGL((gemm_flat_kernel<2, EPI_T, D4>), grid, block, 0, s, g); break;
+        case 3: hipLaunchKernelGGL((gemm_flat_kernel<3, EPI_T, D4>), grid, block, 0, s, g); break;
+        default: hipLaunchKernelGGL((gemm_flat_kernel<4, EPI_T, D4>), grid, block, 0, s, g); break;
+    }
+    return hipGetLastError();
+}
+
+struct F16Layout {
+    int m32, mp32;
+    size_t u1, u2;              // bytes of one array (hi or lo)
+    size_t t_op, o_op;          // one operator's
+    size_t t32;                 // one operator's T of the FP32 kernels
+    size_t part_u, ublk, eu;    // scale pass: partial column maxima, block maxima, exponents
+    size_t shared;
+};
+
+F16Layout f16_layout(const rot_problem& p) {
+    F16Layout L;
+    const int64_t md = (int64_t)p.m * p.d;
+    L.m32 = div_up(p.m, 32) * 32;
+    L.mp32 = div_up(p.mp, 32) * 32;
+    L.u1 = al256((size_t)(n_slabs(p.m) * p.d * p.mp * kSlabK * 2));
+    L.u2 = al256((size_t)(n_slabs(md) * p.mp * kSlabK * 2));
+    L.o_op = (size_t)(n_slabs(p.m) * L.m32 * kSlabK * 2);
+    L.t_op = (size_t)(n_slabs(md) * L.mp32 * kSlabK * 2);
+    L.t32 = al256((size_t)md * p.ldu * 4);
+    const size_t chunks = div_up(md, kPrepRows);
+    L.part_u = al256(chunks * p.mp * 4);
+    L.ublk = al256(chunks * div_up(p.mp, 64) * 4);
+    L.eu = al256((size_t)(p.mp + 256) * 4);  // read in groups of four up to a tile's last row
+    L.shared = 2 * L.u1 + 2 * L.u2 + L.part_u + L.ublk + L.eu;
+    return L;
+}
+
+size_t f16_t_bytes(const F16Layout& L, int ops) { return std::max(2 * al256(ops * L.t_op), ops * L.t32); }
+size_t f16_scale_bytes(const rot_problem& p, int ops) {
+    return al256((size_t)ops * (div_up(p.m, kPrepORows) * 8 + 8));
+}
+// Stage 2 of `ops` operators of the group.  The K parts are those of the
+// whole group, so that results do not depend on the chunks.  Symmetric output
+// computes the tiles on or above the diagonal, a little over half of them:
+// the choice is made for that many operators.
+FlatCfg f16_stage2_cfg(const rot_problem& p, int ops, bool symmetric) {
+    const int slabs = (int)n_slabs((int64_t)p.m * p.d), bpo = div_up(p.mp, 32);
+    auto tiled = [&](int n) { return symmetric ? (n * 5 + 7) / 8 : n; };
+    // where the FP32 kernels split K, sums must not get longer than theirs (3
+    // roundings per 16 k against 8)
+    int kp;
+    int least = symmetric ? 1 : (stage2_parts(p, p.n_ops, &kp) * 3 + 7) / 8;
+    while (least > 1 && slabs - div_up(slabs, least) * (least - 1) < 3) least--;
+    const int parts = flat_cfg(p.mp, tiled(p.n_ops) * bpo, slabs, least, kF16MaxParts, 4.0 * p.n_ops * p.mp * p.mp).parts;
+    return flat_cfg(p.mp, tiled(ops) * bpo, slabs, parts, parts, 0);
+}
+// The split O, and later (stage 1 done) stage 2's partial results.
+size_t f16_o_bytes(const rot_problem& p, const F16Layout& L, int ops, int parts) {
+    return std::max(2 * al256(ops * L.o_op), parts > 1 ? al256((size_t)parts * ops * p.mp * p.mp * 4) : 0);
+}
+
+}  // namespace
+
+// Whether a group runs on FP16 pairs, `ops` operators at a time.  The passes
+// over U and O and the launches for skipped operators cost about 20 us, which
+// pays from about 1 GFLOP on (back to back, FP32 kernels against pairs: 40
+// operators of 128 states, 1.3 GFLOP, 48.8 / 45.6 us; 16 of them, 0.5 GFLOP,
+// 34.6 / 36.6; one of 403, 1.0 GFLOP, 85 / 53).  Below 64 states the tiles
+// are mostly padding; U's split takes d up to 8; 32-bit offsets bound the
+// operand arrays.
+bool f16_rotate_applies(const rot_problem& p, int ops) {
+    if (p.d > kF16MaxSite || p.m < 64 || p.mp < 64) return false;
+    const F16Layout L = f16_layout(p);
+    if (std::max(L.u1, L.u2) >= ((size_t)1 << 31) - 256 * kSlabK * 2) return false;
+    if (std::max(L.o_op, L.t_op) * ops >= (size_t)1 << 31) return false;
+    return 2.0 * p.m * p.d * p.mp * ((double)p.m + p.mp) * p.n_ops >= 1e9;
+}
+
+size_t f16_group_workspace(const rot_problem& p, int ops, bool symmetric) {
+    const F16Layout L = f16_layout(p);
+    const int parts = f16_stage2_cfg(p, ops, symmetric).parts;
+    return L.shared + f16_t_bytes(L, ops) + f16_o_bytes(p, L, ops, parts) + f16_scale_bytes(p, ops);
+}
+
+// Operators b0 .. b0 + nb - 1 of p (leading dimensions resolved) through FP16
+// pairs; `fallback` enqueues the FP32 kernels for the operators they skip
+// (T: FP32 intermediates, slot_elems apart; skip: the flags).
+hipError_t rotate_f16(const rot_problem& p, int b0, int nb, void* ws, bool symmetric,
+                      const std::function<hipError_t(void* T, int64_t slot_elems, const int* skip)>& fallback,
+                      hipStream_t stream) {
+    const F16Layout L = f16_layout(p);
+    char* base = static_cast<char*>(ws);
+    auto take = [&](size_t bytes) {
+        char* q = base;
+        base += bytes;
+        return q;
+    };
+    F16Scale g{};
+    g.U = static_cast<const float*>(p.U);
+    g.rows = p.m * p.d;
+    g.mp = p.mp;
+    g.d = p.d;
+    g.ldu = p.ldu;
+    g.O = static_cast<const float*>(p.O) + (int64_t)b0 * p.stride_o;
+    g.m = p.m;
+    g.nb = nb;
+    g.m32 = L.m32;
+    g.mp32 = L.mp32;
+    g.ldo = p.ldo;
+    g.stride_o = p.stride_o;
+    g.u1h = reinterpret_cast<uint16_t*>(take(L.u1));
+    g.u1l = reinterpret_cast<uint16_t*>(take(L.u1));
+    g.u2h = reinterpret_cast<uint16_t*>(take(L.u2));
+    g.u2l = reinterpret_cast<uint16_t*>(take(L.u2));
+    g.upart = reinterpret_cast<uint32_t*>(take(L.part_u));
+    g.ublk = reinterpret_cast<uint32_t*>(take(L.ublk));
+    g.eu = reinterpret_cast<int*>(take(L.eu));
+    const FlatCfg c2 = f16_stage2_cfg(p, nb, symmetric);
+    char* T = take(f16_t_bytes(L, nb));
+    g.th = reinterpret_cast<uint16_t*>(T);
+    g.tl = reinterpret_cast<uint16_t*>(T + al256(nb * L.t_op));
+    g.t_bs = (int64_t)(L.t_op / 2);
+    char* O = take(f16_o_bytes(p, L, nb, c2.parts));
+    g.oh = reinterpret_cast<uint16_t*>(O);
+    g.ol = reinterpret_cast<uint16_t*>(O + al256(nb * L.o_op));
+    g.o_bs = (int64_t)(L.o_op / 2);
+    const int orb = div_up(p.m, kPrepORows), cb = div_up(p.mp, 64);
+    g.opart = reinterpret_cast<uint32_t*>(base);
+    g.eo = reinterpret_cast<int*>(g.opart + 2 * (size_t)nb * orb);
+    g.skip = g.eo + nb;
+    g.n_ublk = cb * div_up(g.rows, kPrepRows);
+    hipError_t e = prof_timed("scale_f16x3", stream, [&] {
+        F16Scale q = g;
+        q.u_blocks = b0 == 0 ? g.n_ublk : 0;
+        q.o_blocks = nb * orb;
+        hipLaunchKernelGGL(f16_scale_kernel, dim3((unsigned)(q.u_blocks + q.o_blocks)), dim3(256), 0, stream, q);
+        return hipGetLastError();
+    });
+    if (e != hipSuccess) return e;
+    e = prof_timed("split_f16x3", stream, [&] {
+        F16Scale q = g;
+        const int tb = div_up(p.m, 64);
+        q.u_blocks = b0 == 0 ? cb * div_up(p.m, kSlabK) : 0;
+        q.o_blocks = nb * tb * tb;
+        const int t_blocks = g.rows % kSlabK ? nb * div_up((int64_t)p.mp * 2, 256) : 0;
+        const dim3 grid((unsigned)(q.u_blocks + q.o_blocks + t_blocks));
+        if (p.d <= 4)
+            hipLaunchKernelGGL(f16_split_kernel<4>, grid, dim3(256), 0, stream, q);
+        else
+            hipLaunchKernelGGL(f16_split_kernel<kF16MaxSite>, grid, dim3(256), 0, stream, q);
+        return hipGetLastError();
+    });
+    if (e != hipSuccess) return e;
+    int log2m = 0;
+    while ((1 << log2m) < p.m) log2m++;
+    const int t_shift = 15 + log2m;
+    // stage 1, transposed: C(beta*d + s, i) = sum_j U1(beta*d + s, j) O_b(i, j)
+    FlatDesc a{};
+    a.M = p.d * p.mp;
+    a.N = p.m;
+    a.K = p.m;
+    a.batch = nb;
+    a.a_hi = g.u1h;
+    a.a_lo = g.u1l;
+    a.b_hi = g.oh;
+    a.b_lo = g.ol;
+    a.b_bs = g.o_bs;
+    a.n32 = L.m32;
+    a.t_hi = g.th;
+    a.t_lo = g.tl;
+    a.d = p.d;
+    a.t_rows = L.mp32;
+    a.t_bs = g.t_bs;
+    a.t_shift = t_shift;
+    a.skip = g.skip;
+    const FlatCfg c1 = flat_cfg(a.M, nb * (L.m32 / 32), (int)n_slabs(p.m), 1, 1, 0);
+    e = prof_timed("stage1_f16x3", stream, [&] {
+        return p.d == 4 ? launch_flat<true, true>(a, c1, stream) : launch_flat<true, false>(a, c1, stream);
+    });
+    if (e != hipSuccess) return e;
+    float* out = static_cast<float*>(p.out) + (int64_t)b0 * p.stride_out;
+    {
+        FlatDesc b{};
+        b.M = p.mp;
+        b.N = p.mp;
+        b.K = g.rows;
+        b.batch = nb;
+        b.a_hi = g.u2h;
+        b.a_lo = g.u2l;
+        b.b_hi = g.th;
+        b.b_lo = g.tl;
+        b.b_bs = g.t_bs;
+        b.n32 = L.mp32;
+        b.c = c2.parts > 1 ? reinterpret_cast<float*>(O) : out;
+        b.ldc = c2.parts > 1 ? p.mp : p.ldout;
+        b.c_bs = c2.parts > 1 ? (int64_t)p.mp * p.mp : p.stride_out;
+        b.c_ps = (int64_t)nb * p.mp * p.mp;
+        b.e0 = -t_shift;
+        b.op_e = g.eo;
+        b.row_e = g.eu;
+        b.col_e = g.eu;
+        b.skip = g.skip;
+        b.upper = symmetric;
+        e = prof_timed(symmetric ? "stage2sym_f16x3" : "stage2_f16x3", stream, [&] { return launch_flat<false, true>(b, c2, stream); });
+        if (e == hipSuccess && c2.parts > 1)
+            e = prof_timed("stage2_sum", stream, [&] {
+                return sum_parts_2d(out, p.ldout, p.stride_out, O, p.mp, p.mp, nb, c2.parts, b.c_ps, false, stream);
+            });
+    }
+    if (e != hipSuccess) return e;
+    return fallback(T, (int64_t)(L.t32 / 4), g.skip);
+}
+
+}  // namespace rot

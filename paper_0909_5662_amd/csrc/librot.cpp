@@ -22,6 +22,11 @@ hipError_t bf16_choice(const rot_problem& p, int nb, bool symmetric, void* ws, b
                        Bf16Choice* choice);
 hipError_t rotate_bf16(const rot_problem& p, int b0, int nb, void* ws, bool symmetric, const Bf16Choice& choice,
                        hipStream_t stream);
+bool f16_rotate_applies(const rot_problem& p, int ops);
+size_t f16_group_workspace(const rot_problem& p, int ops, bool symmetric);
+hipError_t rotate_f16(const rot_problem& p, int b0, int nb, void* ws, bool symmetric,
+                      const std::function<hipError_t(void* T, int64_t slot_elems, const int* skip)>& fallback,
+                      hipStream_t stream);
 bool bf16_backward_supported(int m, int d, int mp);
 size_t bf16_backward_workspace(int m, int d, int mp, int ops);
 hipError_t backward_bf16(const rot_problem& p, int b0, int nb, const float* dout, int64_t sd, float* dO, float* dU,
@@ -32,6 +37,24 @@ hipError_t rotate_blocked(const rot_blocked_problem* p, void* ws, size_t ws_byte
 size_t density_workspace_bytes(const rot_dm_sector* sectors, int n_sectors);
 hipError_t density_basis(const rot_dm_sector* sectors, int n_sec, int64_t m_keep, int32_t* kept, double* eps,
                          void* workspace, hipStream_t stream, bool* converged);
+
+// Stage 2 split over K for small outputs: when the chunk's stage-2 output
+// has fewer than 256 tiles of 128 x 128 (too few workgroups to fill the chip)
+// and K = m*d is long, K is cut into parts of kp (a multiple of 16, at least
+// 64) computed by separate workgroups into partial sums that are added in a
+// fixed order.  Returns the number of parts (1: no split) for `ops` operators.
+int stage2_parts(const rot_problem& p, int ops, int* kp) {
+    const int64_t t = (p.mp + kGemmTile - 1) / kGemmTile;
+    const int64_t tiles = t * t * ops;
+    const int64_t K = (int64_t)p.m * p.d;
+    *kp = (int)K;
+    if (tiles >= 256 || K < 128) return 1;
+    int64_t parts = std::min<int64_t>({8, (512 + tiles - 1) / tiles, K / 64});
+    if (parts < 2) return 1;
+    const int64_t k = ((K + parts - 1) / parts + 15) / 16 * 16;
+    *kp = (int)k;
+    return (int)((K + k - 1) / k);
+}
 
 namespace {
 
@@ -125,24 +148,6 @@ size_t t_bytes(const rot_problem& p, rot_precision prec) {
 // m x d*mp view, which only a packed U provides).
 size_t packed_u_bytes(const rot_problem& p, rot_precision prec) {
     return p.ldu == p.mp ? 0 : align_up((size_t)p.m * p.d * p.mp * elem_size(prec));
-}
-
-// Stage 2 split over K for small outputs: when the chunk's stage-2 output
-// has fewer than 256 tiles of 128 x 128 (too few workgroups to fill the chip)
-// and K = m*d is long, K is cut into parts of kp (a multiple of 16, at least
-// 64) computed by separate workgroups into partial sums that are added in a
-// fixed order.  Returns the number of parts (1: no split) for `ops` operators.
-int stage2_parts(const rot_problem& p, int ops, int* kp) {
-    const int64_t t = (p.mp + kGemmTile - 1) / kGemmTile;
-    const int64_t tiles = t * t * ops;
-    const int64_t K = (int64_t)p.m * p.d;
-    *kp = (int)K;
-    if (tiles >= 256 || K < 128) return 1;
-    int64_t parts = std::min<int64_t>({8, (512 + tiles - 1) / tiles, K / 64});
-    if (parts < 2) return 1;
-    const int64_t k = ((K + parts - 1) / parts + 15) / 16 * 16;
-    *kp = (int)k;
-    return (int)((K + k - 1) / k);
 }
 
 // Bytes of one operator's partial stage-2 sums when split into `parts`.
@@ -421,14 +426,36 @@ size_t rot_workspace_size(const rot_problem* groups, int32_t n_groups, rot_preci
     return need;
 }
 
-rot_status rot_batch(const rot_problem* groups, int32_t n_groups, rot_precision prec, void* workspace,
-                     size_t workspace_bytes, void* stream) {
-    return rot_batch_ex(groups, n_groups, prec, 0u, workspace, workspace_bytes, stream);
+size_t rot_workspace_preferred(const rot_problem* groups, int32_t n_groups, rot_precision prec) {
+    size_t need = rot_workspace_size(groups, n_groups, prec, 0, 0);
+    if (need == 0 || prec != ROT_FP32) return need;
+    for (int gi = 0; gi < n_groups; gi++) {
+        const rot_problem p = resolved(groups[gi]);
+        if (p.n_ops > 0 && f16_rotate_applies(p, p.n_ops))
+            need = std::max({need, f16_group_workspace(p, p.n_ops, false), f16_group_workspace(p, p.n_ops, true)});
+    }
+    return need;
 }
 
-rot_status rot_batch_ex(const rot_problem* groups, int32_t n_groups, rot_precision prec, uint32_t flags,
-                        void* workspace, size_t workspace_bytes, void* stream) {
-    rot::TraceRange trace_("rot_batch_ex");
+namespace {
+
+// Operators per chunk on FP16 pairs within `bytes` of workspace; 0: FP32
+// kernels.  Chunks of a group that does not fit whole are of equal size and
+// pay from about 8 GFLOP on (a chunk's passes and launches cost 40 us; the
+// pairs gain 5 us per GFLOP on the FP32 kernels' full rate).
+int pair_chunk(const rot_problem& p, bool sym, size_t bytes) {
+    auto fits = [&](int ops) { return f16_rotate_applies(p, ops) && f16_group_workspace(p, ops, sym) <= bytes; };
+    if (!fits(1)) return 0;
+    if (fits(p.n_ops)) return p.n_ops;
+    int fit = 1, over = p.n_ops;
+    while (over - fit > 1) (fits((fit + over) / 2) ? fit : over) = (fit + over) / 2;
+    const int chunks = (p.n_ops + fit - 1) / fit, size = (p.n_ops + chunks - 1) / chunks;
+    return 2.0 * p.m * p.d * p.mp * ((double)p.m + p.mp) * size >= 8e9 ? size : 0;
+}
+
+// rot_batch_ex; `pairs`: FP32 batches may run on FP16 pairs.
+rot_status batch(const rot_problem* groups, int32_t n_groups, rot_precision prec, uint32_t flags, bool pairs,
+                 void* workspace, size_t workspace_bytes, void* stream) {
     if (n_groups < 0 || (n_groups > 0 && !groups))
         return fail(ROT_ERR_INVALID_ARG, "groups is null or n_groups negative");
     if (!valid_precision(prec)) return fail(ROT_ERR_INVALID_ARG, "unknown precision %d", (int)prec);
@@ -484,6 +511,25 @@ rot_status rot_batch_ex(const rot_problem* groups, int32_t n_groups, rot_precisi
             if (e != hipSuccess) return hip_fail(e, "rot_batch small fp64");
             continue;
         }
+        if (prec == ROT_FP32 && pairs) {
+            const int fit = pair_chunk(p, sym, workspace_bytes);
+            if (fit > 0) {
+                for (int b0 = 0; b0 < p.n_ops; b0 += fit) {
+                    const int nb = std::min(fit, p.n_ops - b0);
+                    auto fp32 = [&](void* T, int64_t slot, const int* skip) {
+                        GemmDesc g1 = stage1(p, b0, nb, T, es), g2 = stage2(p, b0, nb, T, es);
+                        g1.c_bs = g2.b_bs = slot;
+                        g1.only = g2.only = skip;
+                        g2.upper = sym;
+                        const hipError_t e = gemm(prec, g1, s, "rest1");
+                        return e == hipSuccess ? gemm(prec, g2, s, "rest2") : e;
+                    };
+                    hipError_t e = rotate_f16(p, b0, nb, workspace, sym, fp32, s);
+                    if (e != hipSuccess) return hip_fail(e, "rot_batch launch");
+                }
+                continue;
+            }
+        }
         const size_t per_op = t_bytes(p, prec);
         // split-K stage 2 (general output only) when the workspace holds the
         // whole batch with its partial sums
@@ -520,6 +566,25 @@ rot_status rot_batch_ex(const rot_problem* groups, int32_t n_groups, rot_precisi
         }
     }
     return ROT_OK;
+}
+
+}  // namespace
+
+rot_status rot_batch(const rot_problem* groups, int32_t n_groups, rot_precision prec, void* workspace,
+                     size_t workspace_bytes, void* stream) {
+    return rot_batch_ex(groups, n_groups, prec, 0u, workspace, workspace_bytes, stream);
+}
+
+rot_status rot_batch_ex(const rot_problem* groups, int32_t n_groups, rot_precision prec, uint32_t flags,
+                        void* workspace, size_t workspace_bytes, void* stream) {
+    rot::TraceRange trace_("rot_batch_ex");
+    return batch(groups, n_groups, prec, flags, true, workspace, workspace_bytes, stream);
+}
+
+rot_status rot_batch_fp32(const rot_problem* groups, int32_t n_groups, uint32_t flags, void* workspace,
+                          size_t workspace_bytes, void* stream) {
+    rot::TraceRange trace_("rot_batch_fp32");
+    return batch(groups, n_groups, ROT_FP32, flags, false, workspace, workspace_bytes, stream);
 }
 
 namespace {

@@ -6,6 +6,8 @@
 // passes only that address on, never the array's name.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include <cstdio>
 #include <mutex>
 
@@ -73,7 +75,10 @@ rot_status rot_batch_noalloc(const rot_problem* groups, int32_t n_groups, rot_pr
     void* ws = nullptr;
     const rot_status st = rot::scratch_for_current_device(&ws);
     if (st != ROT_OK) return st;
-    return rot_batch_ex(groups, n_groups, prec, flags, ws, rot::kScratchBytes, stream);
+    // no more than the whole batch's size: a call whose scratch holds the batch
+    // takes the route, and gives the bits, of rot_batch_ex with that workspace
+    const size_t bytes = std::min(rot::kScratchBytes, rot_workspace_size(groups, n_groups, prec, 0, 0));
+    return rot_batch_ex(groups, n_groups, prec, flags, ws, bytes, stream);
 }
 
 }  // extern "C"

@@ -37,6 +37,8 @@ struct GemmDesc {
     // C + p*c_ps; the caller adds the parts
     int parts, kp;
     int64_t c_ps;
+    // FP32 only: when set, batch elements b with only[b] == 0 are left alone
+    const int* only;
 };
 
 // ---- grouped GEMM over a work-list (grouped.hip) ----
@@ -111,6 +113,10 @@ hipError_t prof_timed(const char* name, hipStream_t stream, const std::function<
 constexpr int kGemmTile = 128;  // output tile edge of gemm_f32 / gemm_f64
 hipError_t gemm_f32(const GemmDesc& g, hipStream_t stream);
 hipError_t gemm_f64(const GemmDesc& g, hipStream_t stream);
+
+// Parts that FP32 / FP64 stage 2 of `ops` operators is split into over K, and
+// the K extent of each (librot.cpp).
+int stage2_parts(const rot_problem& p, int ops, int* kp);
 
 // Split-BF16 launch configuration (gemm_bf16x3.hip): tile edge 256 (eight
 // waves of 128 x 64) or 128 (four waves of 64 x 64), LDS ring depth 4 or 5,
