@@ -870,5 +870,5 @@ class PairLossFn(torch.autograd.Function):
     @staticmethod
     def backward(ctx, gl):
         (grad,) = ctx.saved_tensors
-        g = grad if bool(gl == 1) else grad * gl.to(grad.dtype)
+        g = grad * gl.to(grad.dtype)  # reading gl on the host would wait for the forward
         return g.unsqueeze(0).expand(ctx.n, *grad.shape), None

@@ -234,7 +234,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmDesc g, int tile
 // products and stores as gemm_f32_kernel, so the same bits.  MODE 0: one K
 // batch, plain stores; 1: symmetric output; 2: K batches (the slices of
 // batch kb after those of kb - 1) and, with g.accumulate, C += result.
-// Requires K a multiple of 16, 16-byte aligned rows, no split, and each
+// Requires K (and a part's) a multiple of 16, 16-byte aligned rows, and each
 // operand's batch entry (all its K batches) under 4 GiB (direct_lds_ok).
 // EDGE (M or N not a multiple of 128): slices of a last, partial tile read
 // whatever lies past the operand's rows or columns (zero past the batch
@@ -249,7 +249,13 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_dl_kernel(GemmDesc g, int t
     __shared__ __attribute__((aligned(1024))) float As[2][DA::ELEMS];
     __shared__ __attribute__((aligned(1024))) float Bs[2][DB::ELEMS];
 
-    const TileCoord tc = tile_coord(xcd_linear_id(), tiles_m, tiles_n, UPPER);
+    int lin = xcd_linear_id(), part = 0;
+    if (MODE == 0 && g.parts > 1) {
+        const int per = gridDim.x / g.parts;
+        part = lin / per;
+        lin -= part * per;
+    }
+    const TileCoord tc = tile_coord(lin, tiles_m, tiles_n, UPPER);
     if (g.only && !g.only[tc.g]) return;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -279,7 +285,9 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_dl_kernel(GemmDesc g, int t
             for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
 
     const int nk = g.K / kSlice;
-    const int total = MODE == 2 ? nk * g.kbatch : nk;
+    // a part's K range: slices s0 .. s0 + total - 1
+    const int s0 = MODE == 0 && g.parts > 1 ? part * (g.kp / kSlice) : 0;
+    const int total = MODE == 2 ? nk * g.kbatch : MODE == 0 && g.parts > 1 ? min(g.kp / kSlice, nk - s0) : nk;
     // slice t: K batch t / nk, slice t % nk of it
     auto issue = [&](int t, int buf) __attribute__((always_inline)) {
         if (MODE == 2) {
@@ -287,8 +295,8 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_dl_kernel(GemmDesc g, int t
             da.issue_at(ra, As[buf], (uint32_t)kb * (uint32_t)(g.a_ks * 4) + (uint32_t)kt * da.step, wave);
             db.issue_at(rb, Bs[buf], (uint32_t)kb * (uint32_t)(g.b_ks * 4) + (uint32_t)kt * db.step, wave);
         } else {
-            da.issue(ra, As[buf], t, wave);
-            db.issue(rb, Bs[buf], t, wave);
+            da.issue(ra, As[buf], s0 + t, wave);
+            db.issue(rb, Bs[buf], s0 + t, wave);
         }
     };
     issue(0, 0);
@@ -338,7 +346,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_dl_kernel(GemmDesc g, int t
         dma_slice_sync();
     }
 
-    float* Cb = static_cast<float*>(g.C) + (int64_t)tc.g * g.c_bs;
+    float* Cb = static_cast<float*>(g.C) + (int64_t)tc.g * g.c_bs + (int64_t)part * g.c_ps;
     // symmetric output: a diagonal tile keeps row <= col and mirrors it; an
     // off-diagonal tile is also stored transposed (a lane's rows 8q + 4h ..
     // +3 become four consecutive entries of row `col`)
@@ -423,8 +431,9 @@ __global__ __launch_bounds__(kThreads) void gemm_f64_kernel(GemmDesc g, int tile
     const int wm = wave >> 1, wn = wave & 1;
     const int h = lane >> 4, c = lane & 15;
 
-    const double* Ab = static_cast<const double*>(g.A) + (int64_t)tc.g * g.a_bs;
-    const double* Bb = static_cast<const double*>(g.B) + (int64_t)tc.g * g.b_bs;
+    const int go = g.inner > 1 ? tc.g / g.inner : tc.g, gi = tc.g - go * (g.inner > 1 ? g.inner : 1);
+    const double* Ab = static_cast<const double*>(g.A) + (int64_t)go * g.a_bs + (int64_t)gi * g.a_is;
+    const double* Bb = static_cast<const double*>(g.B) + (int64_t)go * g.b_bs + (int64_t)gi * g.b_is;
     int K = g.K;
     if (g.parts > 1) {
         // this part's K range
@@ -529,7 +538,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f64_kernel(GemmDesc g, int tile
 // destination (DmaSlice128D, the LdsSlice layouts of gemm_f64_kernel), K
 // batches, accumulation and symmetric output as there; same fragment reads,
 // products and stores, so the same bits.  Requires K a multiple of 16,
-// 16-byte aligned rows, no split, and each operand's batch entry (with the
+// 16-byte aligned rows, and each operand's batch entry (with the
 // rows or columns a partial tile reads past it) under 4 GiB; a partial
 // tile's extra rows and columns read zeros or unused data and are not
 // stored.
@@ -543,14 +552,21 @@ __global__ __launch_bounds__(kThreads) void gemm_f64_dl_kernel(GemmDesc g, int t
     __shared__ __attribute__((aligned(1024))) double As[2][DA::ELEMS];
     __shared__ __attribute__((aligned(1024))) double Bs[2][DB::ELEMS];
 
-    const TileCoord tc = tile_coord(xcd_linear_id(), tiles_m, tiles_n, g.upper);
+    int lin = xcd_linear_id(), part = 0;
+    if (g.parts > 1) {
+        const int per = gridDim.x / g.parts;
+        part = lin / per;
+        lin -= part * per;
+    }
+    const TileCoord tc = tile_coord(lin, tiles_m, tiles_n, g.upper);
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int h = lane >> 4, c = lane & 15;
 
-    const double* Ab = static_cast<const double*>(g.A) + (int64_t)tc.g * g.a_bs;
-    const double* Bb = static_cast<const double*>(g.B) + (int64_t)tc.g * g.b_bs;
+    const int go = g.inner > 1 ? tc.g / g.inner : tc.g, gi = tc.g - go * (g.inner > 1 ? g.inner : 1);
+    const double* Ab = static_cast<const double*>(g.A) + (int64_t)go * g.a_bs + (int64_t)gi * g.a_is;
+    const double* Bb = static_cast<const double*>(g.B) + (int64_t)go * g.b_bs + (int64_t)gi * g.b_is;
     const int64_t ea = (AK ? (int64_t)(g.M - 1) * g.lda + g.K : (int64_t)(g.K - 1) * g.lda + g.M) +
                        (int64_t)(g.kbatch - 1) * g.a_ks;
     const int64_t eb = (BK ? (int64_t)(g.N - 1) * g.ldb + g.K : (int64_t)(g.K - 1) * g.ldb + g.N) +
@@ -573,9 +589,12 @@ __global__ __launch_bounds__(kThreads) void gemm_f64_dl_kernel(GemmDesc g, int t
             for (int v = 0; v < 4; v++) acc[i][j][v] = 0.0;
 
     const int nk = g.K / kSlice;
-    const int total = nk * g.kbatch;
+    // a part's K range (one K batch): slices s0 .. s0 + total - 1
+    const int s0 = g.parts > 1 ? part * (g.kp / kSlice) : 0;
+    const int total = g.parts > 1 ? min(g.kp / kSlice, nk - s0) : nk * g.kbatch;
     // slice t: K batch t / nk, slice t % nk of it
-    auto issue = [&](int t, int buf) __attribute__((always_inline)) {
+    auto issue = [&](int t_, int buf) __attribute__((always_inline)) {
+        const int t = s0 + t_;
         const int kb = t / nk, kt = t - kb * nk;
         da.issue_at(ra, As[buf], (uint32_t)kb * (uint32_t)(g.a_ks * 8) + (uint32_t)kt * da.step, wave);
         db.issue_at(rb, Bs[buf], (uint32_t)kb * (uint32_t)(g.b_ks * 8) + (uint32_t)kt * db.step, wave);
@@ -625,7 +644,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f64_dl_kernel(GemmDesc g, int t
         dma_slice_sync();
     }
 
-    double* Cb = static_cast<double*>(g.C) + (int64_t)tc.g * g.c_bs;
+    double* Cb = static_cast<double*>(g.C) + (int64_t)tc.g * g.c_bs + (int64_t)part * g.c_ps;
     // symmetric output: off-diagonal tiles are also stored transposed; a
     // diagonal tile keeps row <= col and mirrors it (exactly symmetric)
     const bool mirror = !ACC && g.upper && tc.m0 != tc.n0;
@@ -653,15 +672,16 @@ bool vector_ok(const GemmDesc& g) {
     const int64_t vw = 16 / sizeof(T);
     auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
     return al(g.A) && al(g.B) && g.lda % vw == 0 && g.ldb % vw == 0 && g.a_bs % vw == 0 &&
-           g.b_bs % vw == 0 && g.a_ks % vw == 0 && g.b_ks % vw == 0 && (g.parts <= 1 || g.kp % vw == 0);
+           g.b_bs % vw == 0 && g.a_ks % vw == 0 && g.b_ks % vw == 0 && g.a_is % vw == 0 && g.b_is % vw == 0 &&
+           (g.parts <= 1 || g.kp % vw == 0);
 }
 
 // The direct-to-LDS FP32 kernel's conditions (16-byte alignment is checked
-// by vector_ok): whole K slices, no split, and every byte offset of an
+// by vector_ok): whole K slices (also of a part), and every byte offset of an
 // operand's batch entry (over all K batches, and the rows or columns a last
 // partial tile reads) below 2^32.
 bool direct_lds_ok(const GemmDesc& g, int64_t es = 4) {
-    if (g.parts > 1 || g.kbatch < 1) return false;
+    if (g.kbatch < 1 || (g.parts > 1 && (g.kp % kSlice != 0 || g.accumulate))) return false;
     if (g.K % kSlice != 0 || g.K <= 0) return false;
     if (g.kbatch > 1 && (g.a_ks < 0 || g.b_ks < 0)) return false;
     const int64_t ea = (g.a_kcontig ? (int64_t)(g.M - 1) * g.lda + g.K : (int64_t)(g.K - 1) * g.lda + g.M) +

@@ -39,6 +39,10 @@ struct GemmDesc {
     int64_t c_ps;
     // FP32 only: when set, batch elements b with only[b] == 0 are left alone
     const int* only;
+    // FP64 only: with inner > 1, batch element g reads A at (g / inner)*a_bs +
+    // (g % inner)*a_is (B likewise)
+    int inner;
+    int64_t a_is, b_is;
 };
 
 // ---- grouped GEMM over a work-list (grouped.hip) ----
@@ -159,6 +163,14 @@ hipError_t site_mix(const void* U, int m, int d, int mp, const SiteMatrix& S, co
 // sum over p of the packed matrices at src + p*pstride, in ascending p.
 hipError_t sum_parts_2d(void* dst, int64_t ld, int64_t bs, const void* src, int rows, int cols, int nmat, int parts,
                         int64_t pstride, bool is_double, hipStream_t stream);
+// dst (m x m packed) = sum of n matrices at src (row stride ld, matrix stride
+// bs), added in FP64 in a fixed order.
+hipError_t sum_matrices(void* dst, const void* src, int m, int64_t ld, int64_t bs, int n, bool is_double,
+                        hipStream_t stream);
+// The first `count` elements at dst repeated n - 1 times behind them.
+hipError_t repeat(void* dst, int64_t count, int n, bool is_double, hipStream_t stream);
+// dst = G + G^T (mp x mp, packed).
+hipError_t add_transpose(void* dst, const void* G, int mp, bool is_double, hipStream_t stream);
 // dst (+)= sum of `parts` arrays of n elements at src + p*stride, summed in
 // ascending p (deterministic).
 hipError_t sum_parts(void* dst, const void* src, int64_t n, int parts, int64_t stride, bool accumulate,
