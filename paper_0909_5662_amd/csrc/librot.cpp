@@ -785,6 +785,12 @@ rot_status rot_expect_cross(const double* psi, int32_t m, int32_t d, int32_t mR,
                                             (workspace_bytes - q_bytes - split_bytes) / (t_bytes_op + qq_bytes_op));
     char* T = base + q_bytes + split_bytes;
     char* Q = T + (size_t)chunk * t_bytes_op;
+    // K parts of the products with psi^T: enough tiles for the chip, at most
+    // dR (their results then fit the mp x mp slot), the same for every chunk
+    const int64_t tr = (mR + kGemmTile - 1) / kGemmTile;
+    int parts = (int)std::max<int64_t>(1, std::min({(int64_t)dR, 512 / (tr * tr * dR * n_left), md / 256}));
+    const int kp = parts > 1 ? (int)((md + parts - 1) / parts + 15) / 16 * 16 : (int)md;
+    parts = (int)((md + kp - 1) / kp);
     hipError_t err = hipSuccess;
     for (int b0 = 0; b0 < n_left && err == hipSuccess; b0 += chunk) {
         const int nb = std::min(chunk, n_left - b0);
@@ -798,17 +804,34 @@ rot_status rot_expect_cross(const double* psi, int32_t m, int32_t d, int32_t mR,
         g1.c_bs = (int64_t)(t_bytes_op / 8);
         err = gemm(ROT_FP64, g1, s, "expect_stage1");
         if (err == hipSuccess) {
-            GemmDesc g2 = stage2(p, 0, nb, T, 8);
+            // q_b(j, j') = sum over s' and r of psi(r, s' mR + j) T_b(r, s' mR + j'):
+            // the blocks of psi^T T_b on the diagonal in s' and no others, as
+            // products per (b, s') and K part, then added
+            GemmDesc g2{};
+            g2.M = g2.N = mR;
+            g2.K = (int)md;
+            g2.batch = nb * dR;
+            g2.inner = dR;
+            g2.kbatch = 1;
+            g2.A = psi;
+            g2.lda = mp;
+            g2.a_is = mR;
+            g2.B = T;
+            g2.ldb = mp;
             g2.b_bs = (int64_t)(t_bytes_op / 8);
-            g2.c_bs = (int64_t)(qq_bytes_op / 8);
+            g2.b_is = mR;
+            g2.C = Q;
+            g2.ldc = mR;
+            g2.c_bs = (int64_t)parts * mR * mR;
+            g2.parts = parts;
+            g2.kp = kp;
+            g2.c_ps = (int64_t)mR * mR;
             err = gemm(ROT_FP64, g2, s, "expect_stage2");
         }
-        if (err == hipSuccess) {
-            err = prof_timed("expect_trace", s, [&] {
-                return partial_trace(reinterpret_cast<const double*>(Q), (int64_t)(qq_bytes_op / 8), mR, dR, nb,
-                                     q + (size_t)b0 * mR * mR, s);
+        if (err == hipSuccess)
+            err = prof_timed("expect_sum", s, [&] {
+                return sum_groups(q + (size_t)b0 * mR * mR, Q, (int64_t)mR * mR, dR * parts, nb, s);
             });
-        }
     }
     if (err == hipSuccess) {
         // c[b][k] = sum_e q_b[e] W_k[e]

@@ -3,14 +3,12 @@
 // products done by the GEMM kernels.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-
 #include "rot_internal.h"
 
 namespace rot {
 namespace {
 
-constexpr int kDotParts = 8;
+constexpr int kDotParts = 8;  // workgroups per operator
 
 // partial[b][p] = sum over elements e = p*256*... of Z_b[e] * rho[e] in FP64:
 // workgroup (p, b) takes the strided elements tid + 256*(p + kDotParts*q).
@@ -40,19 +38,16 @@ __global__ void dot_final_kernel(const double* __restrict__ partial, int n_ops, 
     e[b] = acc;
 }
 
-// q_b[j][j'] = sum_s Q_b[s*mR + j][s*mR + j'] (Q_b of side dR*mR at
-// Q + b*q_stride, q_b of side mR)
-__global__ __launch_bounds__(256) void partial_trace_kernel(const double* __restrict__ Q, int64_t q_stride, int mR,
-                                                            int dR, double* __restrict__ q) {
-    const int64_t side = (int64_t)dR * mR, n = (int64_t)mR * mR;
+__global__ __launch_bounds__(256) void sum_groups_kernel(double* __restrict__ dst, const double* __restrict__ src,
+                                                         int64_t count, int groups) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= count) return;
     const int b = blockIdx.y;
-    const double* Qb = Q + (int64_t)b * q_stride;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
-        const int64_t j = e / mR, jp = e % mR;
-        double acc = 0.0;
-        for (int s = 0; s < dR; s++) acc += Qb[((int64_t)s * mR + j) * side + (int64_t)s * mR + jp];
-        q[(int64_t)b * n + e] = acc;
-    }
+    const double* p = src + (int64_t)b * groups * count + i;
+    double acc = 0.0;
+#pragma unroll 4
+    for (int x = 0; x < groups; x++) acc += p[(int64_t)x * count];
+    dst[(int64_t)b * count + i] = acc;
 }
 
 }  // namespace
@@ -75,11 +70,10 @@ hipError_t expect_dots(const void* Z, bool z_double, int64_t stride_z, int64_t n
     return hipGetLastError();
 }
 
-hipError_t partial_trace(const double* Q, int64_t q_stride, int mR, int dR, int n_ops, double* q, hipStream_t s) {
-    if (n_ops <= 0) return hipSuccess;
-    const int64_t n = (int64_t)mR * mR;
-    const dim3 grid((unsigned)std::min<int64_t>((n + 255) / 256, 1024), (unsigned)n_ops);
-    hipLaunchKernelGGL(partial_trace_kernel, grid, dim3(256), 0, s, Q, q_stride, mR, dR, q);
+hipError_t sum_groups(double* dst, const void* src, int64_t count, int groups, int nmat, hipStream_t s) {
+    if (nmat <= 0) return hipSuccess;
+    const dim3 grid((unsigned)((count + 255) / 256), (unsigned)nmat);
+    hipLaunchKernelGGL(sum_groups_kernel, grid, dim3(256), 0, s, dst, static_cast<const double*>(src), count, groups);
     return hipGetLastError();
 }
 

@@ -37,9 +37,9 @@ struct GemmDesc {
     // C + p*c_ps; the caller adds the parts
     int parts, kp;
     int64_t c_ps;
-    // FP32 only: when set, batch elements b with only[b] == 0 are left alone
+    // when set, batch elements b with only[b] == 0 are left alone
     const int* only;
-    // FP64 only: with inner > 1, batch element g reads A at (g / inner)*a_bs +
+    // with inner > 1, batch element g reads A at (g / inner)*a_bs +
     // (g % inner)*a_is (B likewise)
     int inner;
     int64_t a_is, b_is;
@@ -114,9 +114,10 @@ class TraceRange {
 hipError_t prof_timed(const char* name, hipStream_t stream, const std::function<hipError_t()>& launch);
 
 // Enqueue on `stream`; returns hipSuccess or the launch error.
-constexpr int kGemmTile = 128;  // output tile edge of gemm_f32 / gemm_f64
+constexpr int kGemmTile = 128;  // output tile edge that the K splits are counted in
 hipError_t gemm_f32(const GemmDesc& g, hipStream_t stream);
 hipError_t gemm_f64(const GemmDesc& g, hipStream_t stream);
+hipError_t gemm_tile64(const GemmDesc& g, bool is_double, hipStream_t stream);  // gemm_tile64.hip
 
 // Parts that FP32 / FP64 stage 2 of `ops` operators is split into over K, and
 // the K extent of each (librot.cpp).
@@ -144,12 +145,13 @@ hipError_t fill_zero(void* p, int64_t bytes, hipStream_t stream);
 
 // Superblock measurements (measure.hip): e_b = sum_e Z_b[e] rho[e] in FP64
 // (n elements per operator, fixed summation order; partial needs
-// expect_dot_scratch(n_ops) bytes), and q_b = partial trace of Q_b over the
-// right site (Q_b of side dR*mR at Q + b*q_stride, q_b of side mR).
+// expect_dot_scratch(n_ops) bytes).
 size_t expect_dot_scratch(int n_ops);
 hipError_t expect_dots(const void* Z, bool z_double, int64_t stride_z, int64_t n, int n_ops, const double* rho,
                        double* partial, double* e, hipStream_t s);
-hipError_t partial_trace(const double* Q, int64_t q_stride, int mR, int dR, int n_ops, double* q, hipStream_t s);
+// dst[b][i] = sum over x < groups of src[(b*groups + x)*count + i], i < count,
+// b < nmat, in ascending x.
+hipError_t sum_groups(double* dst, const void* src, int64_t count, int groups, int nmat, hipStream_t s);
 
 // A d x d site operator passed by value to kernels (d <= kMaxSite).
 constexpr int kMaxSite = 16;
