@@ -112,7 +112,7 @@ typedef struct {
  * bits from a call whose workspace is too small to split.  An FP64 group
  * with m <= 64 and mp <= 64 (not ROT_OUT_SYMMETRIC) is rotated in a single
  * launch that keeps both stages in LDS and leaves the workspace untouched
- * (its size is still checked as for any group).  An FP32 group of 1 GFLOP or
+ * (its size is still checked as for any group).  An FP32 group of 4 GFLOP or
  * more (m, mp >= 64, d <= 8) runs on FP16 pairs when the workspace holds the
  * split operands of the group (rot_workspace_preferred) or of chunks of at
  * least 8 GFLOP, with the same bits for every chunk size; its operators with

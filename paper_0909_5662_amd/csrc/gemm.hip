@@ -1,17 +1,16 @@
-// Batched GEMM kernels on CDNA4 matrix cores (FP32 and FP64), the two
-// contractions of the operator rotation (stage 1: T_b = O_b U_r; stage 2:
-// out_b = U^T T_b) and of its adjoint.
+// Batched FP32 products of the operator rotation (stage 1: T_b = O_b U_r;
+// stage 2: out_b = U^T T_b) and its adjoint in 128 x 128 tiles, and the
+// dispatch between them and the 64 x 64 tiles of gemm_tile64.hip.
 //
-// Tiling: a 256-thread workgroup (four 64-wide waves in a 2 x 2 grid) owns a
-// 128 x 128 tile of C and walks K in slices of 16 (FP32) or 16 (FP64)
-// elements, double-buffered in LDS.  Each operand slice is stored in LDS in
-// the same orientation it has in global memory, so the global -> LDS copy
-// is a plain 16-byte vector copy; the assignment of k to matrix-instruction
-// slots is permuted instead: in every slice, lane group h of a wave handles
-// k = h*(slice/groups) + j for step j, for both operands.  A K-contiguous
-// operand is then read with 128-bit LDS loads (all steps of the slice at
-// once) and an M/N-contiguous one with 32/64-bit loads that are contiguous
-// across the 32 (or 16) lanes of a group.
+// A 256-thread workgroup (four 64-wide waves in a 2 x 2 grid) owns a
+// 128 x 128 tile of C and walks K in slices of 16 elements, double-buffered in
+// LDS.  Each operand slice is stored in LDS in the same orientation it has in
+// global memory; the assignment of k to matrix-instruction slots is permuted
+// instead: in every slice, lane group h of a wave handles k = h*8 + j for step
+// j, for both operands (as in gemm_tile64.hip, so both give the same bits).  A
+// K-contiguous operand is then read with 128-bit LDS loads (all steps of the
+// slice at once) and an M/N-contiguous one with 32-bit loads that are
+// contiguous across the 32 lanes of a group.
 //
 // Workgroup ids are remapped so that each of the 8 XCDs (hardware assigns
 // consecutive ids round-robin over them) processes a contiguous range of
@@ -29,13 +28,10 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 constexpr int kTile = kGemmTile;   // BM = BN
 constexpr int kSlice = 16;   // K elements per LDS slice
-static_assert(kSlice == LdsSlice<float, kTile, kThreads, true>::SK, "slice depth");
 
 struct TileCoord {
     int g, m0, n0;
@@ -64,174 +60,10 @@ __device__ inline TileCoord tile_coord(int lin, int tiles_m, int tiles_n, bool u
     return t;
 }
 
-// ---------------------------------------------------------------- FP32 ----
-// v_mfma_f32_32x32x2f32: lane l supplies A(row l%32, k l/32), B(k l/32, col
-// l%32); accumulator element v of lane l is C(8*(v/4) + 4*(l/32) + v%4, l%32).
-template <bool AK, bool BK, bool VEC, bool ACC>
-__global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmDesc g, int tiles_m, int tiles_n) {
-    typedef LdsSlice<float, kTile, kThreads, AK> SA;
-    typedef LdsSlice<float, kTile, kThreads, BK> SB;
-    __shared__ __attribute__((aligned(16))) float As[2][SA::ELEMS];
-    __shared__ __attribute__((aligned(16))) float Bs[2][SB::ELEMS];
-
-    int lin = xcd_linear_id(), part = 0;
-    if (g.parts > 1) {
-        const int per = gridDim.x / g.parts;
-        part = lin / per;
-        lin -= part * per;
-    }
-    const TileCoord tc = tile_coord(lin, tiles_m, tiles_n, g.upper);
-    if (g.only && !g.only[tc.g]) return;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int h = lane >> 5, c = lane & 31;
-
-    const float* Ab = static_cast<const float*>(g.A) + (int64_t)tc.g * g.a_bs;
-    const float* Bb = static_cast<const float*>(g.B) + (int64_t)tc.g * g.b_bs;
-    int K = g.K;
-    if (g.parts > 1) {
-        // this part's K range
-        const int k0 = part * g.kp;
-        K = min(g.kp, g.K - k0);
-        Ab += g.a_kcontig ? (int64_t)k0 : (int64_t)k0 * g.lda;
-        Bb += g.b_kcontig ? (int64_t)k0 : (int64_t)k0 * g.ldb;
-    }
-    const int nk = (K + kSlice - 1) / kSlice;
-    const int total = nk * g.kbatch;
-
-    SA la;
-    SB lb;
-    f32x16 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-            for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
-
-    auto fetch = [&](int t) {
-        const int kb = t / nk, k0 = (t % nk) * kSlice;
-        la.template load<VEC>(Ab + (int64_t)kb * g.a_ks, g.lda, tc.m0, g.M, k0, K, true, tid);
-        lb.template load<VEC>(Bb + (int64_t)kb * g.b_ks, g.ldb, tc.n0, g.N, k0, K, true, tid);
-    };
-
-    fetch(0);
-    la.store(As[0], tid);
-    lb.store(Bs[0], tid);
-    __syncthreads();
-
-    for (int t = 0; t < total; t++) {
-        const int cur = t & 1;
-        if (t + 1 < total) fetch(t + 1);
-        const float* a_s = As[cur];
-        const float* b_s = Bs[cur];
-        // 8 steps of k = 2: lane group h takes k = h*8 + j at step j
-        float av[2][8], bv[2][8];
-#pragma unroll
-        for (int i = 0; i < 2; i++) {
-            const int row = wm * 64 + i * 32 + c;
-            if (AK) {
-                const f32x4 x0 = *reinterpret_cast<const f32x4*>(a_s + SA::kc_off(row, 2 * h));
-                const f32x4 x1 = *reinterpret_cast<const f32x4*>(a_s + SA::kc_off(row, 2 * h + 1));
-#pragma unroll
-                for (int e = 0; e < 4; e++) { av[i][e] = x0[e]; av[i][4 + e] = x1[e]; }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; j++) av[i][j] = a_s[(h * 8 + j) * SA::PITCH + row];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 2; i++) {
-            const int col = wn * 64 + i * 32 + c;
-            if (BK) {
-                const f32x4 x0 = *reinterpret_cast<const f32x4*>(b_s + SB::kc_off(col, 2 * h));
-                const f32x4 x1 = *reinterpret_cast<const f32x4*>(b_s + SB::kc_off(col, 2 * h + 1));
-#pragma unroll
-                for (int e = 0; e < 4; e++) { bv[i][e] = x0[e]; bv[i][4 + e] = x1[e]; }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; j++) bv[i][j] = b_s[(h * 8 + j) * SB::PITCH + col];
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 8; j++)
-#pragma unroll
-            for (int i = 0; i < 2; i++)
-#pragma unroll
-                for (int k = 0; k < 2; k++)
-                    acc[i][k] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i][j], bv[k][j], acc[i][k], 0, 0, 0);
-        if (t + 1 < total) {
-            la.store(As[cur ^ 1], tid);
-            lb.store(Bs[cur ^ 1], tid);
-        }
-        __syncthreads();
-    }
-
-    float* Cb = static_cast<float*>(g.C) + (int64_t)tc.g * g.c_bs + (int64_t)part * g.c_ps;
-    // symmetric output: a diagonal tile keeps row <= col and mirrors it, so
-    // the result is exactly symmetric.  Accumulating: the previous values of
-    // each group of four rows are loaded before the group's stores
-    // (unconditionally, from element 0 outside C), so four loads are in
-    // flight together instead of one load-add-store at a time.
-    const bool diag = !ACC && g.upper && tc.m0 == tc.n0;
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int k = 0; k < 2; k++) {
-            const int col = tc.n0 + wn * 64 + k * 32 + c;
-            if (col >= g.N) continue;
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const int row0 = tc.m0 + wm * 64 + i * 32 + 8 * q + 4 * h;
-                float old[4];
-                if (ACC) {
-#pragma unroll
-                    for (int e = 0; e < 4; e++)
-                        old[e] = Cb[row0 + e < g.M ? (int64_t)(row0 + e) * g.ldc + col : 0];
-                }
-#pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const int row = row0 + e, v = 4 * q + e;
-                    if (row < g.M && (!diag || row <= col)) {
-                        float* p = Cb + (int64_t)row * g.ldc + col;
-                        *p = ACC ? old[e] + acc[i][k][v] : acc[i][k][v];
-                        if (diag && row < col) Cb[(int64_t)col * g.ldc + row] = acc[i][k][v];
-                    }
-                }
-            }
-        }
-    if (!ACC && g.upper && tc.m0 != tc.n0) {
-        // the transposed tile: a lane's rows 8q + 4h .. +3 become four
-        // consecutive entries of row `col`
-        const bool vec4 = (g.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(Cb) & 15) == 0;
-#pragma unroll
-        for (int i = 0; i < 2; i++)
-#pragma unroll
-            for (int k = 0; k < 2; k++) {
-                const int col = tc.n0 + wn * 64 + k * 32 + c;
-                if (col >= g.N) continue;
-#pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    const int row0 = tc.m0 + wm * 64 + i * 32 + 8 * q + 4 * h;
-                    float* p = Cb + (int64_t)col * g.ldc + row0;
-                    if (vec4 && row0 + 4 <= g.M) {
-                        *reinterpret_cast<f32x4*>(p) =
-                            f32x4{acc[i][k][4 * q], acc[i][k][4 * q + 1], acc[i][k][4 * q + 2], acc[i][k][4 * q + 3]};
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; e++)
-                            if (row0 + e < g.M) p[e] = acc[i][k][4 * q + e];
-                    }
-                }
-            }
-    }
-}
-
 // FP32 product of whole tiles with both K slices filled by buffer loads with
 // LDS destination (DmaSlice128): no staging registers, no per-slice address
 // arithmetic, one wait and barrier per slice.  Same fragment reads,
-// products and stores as gemm_f32_kernel, so the same bits.  MODE 0: one K
+// products and stores as gemm_tile64_kernel, so the same bits.  MODE 0: one K
 // batch, plain stores; 1: symmetric output; 2: K batches (the slices of
 // batch kb after those of kb - 1) and, with g.accumulate, C += result.
 // Requires K (and a part's) a multiple of 16, 16-byte aligned rows, and each
@@ -409,278 +241,15 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_dl_kernel(GemmDesc g, int t
     }
 }
 
-// ---------------------------------------------------------------- FP64 ----
-// v_mfma_f64_16x16x4f64: lane l supplies A(row l%16, k l/16), B(k l/16, col
-// l%16); accumulator element v of lane l is C(4*v + l/16, l%16).
-template <bool AK, bool BK, bool VEC, bool ACC>
-__global__ __launch_bounds__(kThreads) void gemm_f64_kernel(GemmDesc g, int tiles_m, int tiles_n) {
-    typedef LdsSlice<double, kTile, kThreads, AK> SA;
-    typedef LdsSlice<double, kTile, kThreads, BK> SB;
-    __shared__ __attribute__((aligned(16))) double As[2][SA::ELEMS];
-    __shared__ __attribute__((aligned(16))) double Bs[2][SB::ELEMS];
-
-    int lin = xcd_linear_id(), part = 0;
-    if (g.parts > 1) {
-        const int per = gridDim.x / g.parts;
-        part = lin / per;
-        lin -= part * per;
-    }
-    const TileCoord tc = tile_coord(lin, tiles_m, tiles_n, g.upper);
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int h = lane >> 4, c = lane & 15;
-
-    const int go = g.inner > 1 ? tc.g / g.inner : tc.g, gi = tc.g - go * (g.inner > 1 ? g.inner : 1);
-    const double* Ab = static_cast<const double*>(g.A) + (int64_t)go * g.a_bs + (int64_t)gi * g.a_is;
-    const double* Bb = static_cast<const double*>(g.B) + (int64_t)go * g.b_bs + (int64_t)gi * g.b_is;
-    int K = g.K;
-    if (g.parts > 1) {
-        // this part's K range
-        const int k0 = part * g.kp;
-        K = min(g.kp, g.K - k0);
-        Ab += g.a_kcontig ? (int64_t)k0 : (int64_t)k0 * g.lda;
-        Bb += g.b_kcontig ? (int64_t)k0 : (int64_t)k0 * g.ldb;
-    }
-    const int nk = (K + kSlice - 1) / kSlice;
-    const int total = nk * g.kbatch;
-
-    SA la;
-    SB lb;
-    f64x4 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-#pragma unroll
-            for (int v = 0; v < 4; v++) acc[i][j][v] = 0.0;
-
-    auto fetch = [&](int t) {
-        const int kb = t / nk, k0 = (t % nk) * kSlice;
-        la.template load<VEC>(Ab + (int64_t)kb * g.a_ks, g.lda, tc.m0, g.M, k0, K, true, tid);
-        lb.template load<VEC>(Bb + (int64_t)kb * g.b_ks, g.ldb, tc.n0, g.N, k0, K, true, tid);
-    };
-
-    fetch(0);
-    la.store(As[0], tid);
-    lb.store(Bs[0], tid);
-    __syncthreads();
-
-    for (int t = 0; t < total; t++) {
-        const int cur = t & 1;
-        if (t + 1 < total) fetch(t + 1);
-        const double* a_s = As[cur];
-        const double* b_s = Bs[cur];
-        // 4 steps of k = 4: lane group h takes k = h*4 + j at step j
-        double av[4][4], bv[4][4];
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int row = wm * 64 + i * 16 + c;
-            if (AK) {
-                const f64x2 x0 = *reinterpret_cast<const f64x2*>(a_s + SA::kc_off(row, 2 * h));
-                const f64x2 x1 = *reinterpret_cast<const f64x2*>(a_s + SA::kc_off(row, 2 * h + 1));
-                av[i][0] = x0[0]; av[i][1] = x0[1]; av[i][2] = x1[0]; av[i][3] = x1[1];
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; j++) av[i][j] = a_s[(h * 4 + j) * SA::PITCH + row];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int col = wn * 64 + i * 16 + c;
-            if (BK) {
-                const f64x2 x0 = *reinterpret_cast<const f64x2*>(b_s + SB::kc_off(col, 2 * h));
-                const f64x2 x1 = *reinterpret_cast<const f64x2*>(b_s + SB::kc_off(col, 2 * h + 1));
-                bv[i][0] = x0[0]; bv[i][1] = x0[1]; bv[i][2] = x1[0]; bv[i][3] = x1[1];
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; j++) bv[i][j] = b_s[(h * 4 + j) * SB::PITCH + col];
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-#pragma unroll
-                for (int k = 0; k < 4; k++)
-                    acc[i][k] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i][j], bv[k][j], acc[i][k], 0, 0, 0);
-        if (t + 1 < total) {
-            la.store(As[cur ^ 1], tid);
-            lb.store(Bs[cur ^ 1], tid);
-        }
-        __syncthreads();
-    }
-
-    double* Cb = static_cast<double*>(g.C) + (int64_t)tc.g * g.c_bs + (int64_t)part * g.c_ps;
-    // symmetric output: off-diagonal tiles are also stored transposed; a
-    // diagonal tile keeps row <= col and mirrors it (exactly symmetric)
-    const bool mirror = !ACC && g.upper && tc.m0 != tc.n0;
-    const bool diag = !ACC && g.upper && tc.m0 == tc.n0;
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const int col = tc.n0 + wn * 64 + k * 16 + c;
-            if (col >= g.N) continue;
-#pragma unroll
-            for (int v = 0; v < 4; v++) {
-                const int row = tc.m0 + wm * 64 + i * 16 + 4 * v + h;
-                if (row < g.M && (!diag || row <= col)) {
-                    double* p = Cb + (int64_t)row * g.ldc + col;
-                    *p = ACC ? *p + acc[i][k][v] : acc[i][k][v];
-                    if (mirror || (diag && row < col)) Cb[(int64_t)col * g.ldc + row] = acc[i][k][v];
-                }
-            }
-        }
-}
-
-// The FP64 product with both K slices filled by buffer loads with LDS
-// destination (DmaSlice128D, the LdsSlice layouts of gemm_f64_kernel), K
-// batches, accumulation and symmetric output as there; same fragment reads,
-// products and stores, so the same bits.  Requires K a multiple of 16,
-// 16-byte aligned rows, and each operand's batch entry (with the
-// rows or columns a partial tile reads past it) under 4 GiB; a partial
-// tile's extra rows and columns read zeros or unused data and are not
-// stored.
-template <bool AK, bool BK, bool ACC>
-__global__ __launch_bounds__(kThreads) void gemm_f64_dl_kernel(GemmDesc g, int tiles_m, int tiles_n) {
-    typedef DmaSlice128D<AK> DA;
-    typedef DmaSlice128D<BK> DB;
-    typedef LdsSlice<double, kTile, kThreads, AK> SA;
-    typedef LdsSlice<double, kTile, kThreads, BK> SB;
-    static_assert(DA::ELEMS == SA::ELEMS && DB::ELEMS == SB::ELEMS && DA::PITCH == SA::PITCH, "layouts");
-    __shared__ __attribute__((aligned(1024))) double As[2][DA::ELEMS];
-    __shared__ __attribute__((aligned(1024))) double Bs[2][DB::ELEMS];
-
-    int lin = xcd_linear_id(), part = 0;
-    if (g.parts > 1) {
-        const int per = gridDim.x / g.parts;
-        part = lin / per;
-        lin -= part * per;
-    }
-    const TileCoord tc = tile_coord(lin, tiles_m, tiles_n, g.upper);
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int h = lane >> 4, c = lane & 15;
-
-    const int go = g.inner > 1 ? tc.g / g.inner : tc.g, gi = tc.g - go * (g.inner > 1 ? g.inner : 1);
-    const double* Ab = static_cast<const double*>(g.A) + (int64_t)go * g.a_bs + (int64_t)gi * g.a_is;
-    const double* Bb = static_cast<const double*>(g.B) + (int64_t)go * g.b_bs + (int64_t)gi * g.b_is;
-    const int64_t ea = (AK ? (int64_t)(g.M - 1) * g.lda + g.K : (int64_t)(g.K - 1) * g.lda + g.M) +
-                       (int64_t)(g.kbatch - 1) * g.a_ks;
-    const int64_t eb = (BK ? (int64_t)(g.N - 1) * g.ldb + g.K : (int64_t)(g.K - 1) * g.ldb + g.N) +
-                       (int64_t)(g.kbatch - 1) * g.b_ks;
-    const __amdgpu_buffer_rsrc_t ra =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(Ab), (short)0, (int)(uint32_t)(ea * 8), kBufferFlags);
-    const __amdgpu_buffer_rsrc_t rb =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(Bb), (short)0, (int)(uint32_t)(eb * 8), kBufferFlags);
-    DA da;
-    DB db;
-    da.init(g.lda, tc.m0, wave, lane);
-    db.init(g.ldb, tc.n0, wave, lane);
-
-    f64x4 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-#pragma unroll
-            for (int v = 0; v < 4; v++) acc[i][j][v] = 0.0;
-
-    const int nk = g.K / kSlice;
-    // a part's K range (one K batch): slices s0 .. s0 + total - 1
-    const int s0 = g.parts > 1 ? part * (g.kp / kSlice) : 0;
-    const int total = g.parts > 1 ? min(g.kp / kSlice, nk - s0) : nk * g.kbatch;
-    // slice t: K batch t / nk, slice t % nk of it
-    auto issue = [&](int t_, int buf) __attribute__((always_inline)) {
-        const int t = s0 + t_;
-        const int kb = t / nk, kt = t - kb * nk;
-        da.issue_at(ra, As[buf], (uint32_t)kb * (uint32_t)(g.a_ks * 8) + (uint32_t)kt * da.step, wave);
-        db.issue_at(rb, Bs[buf], (uint32_t)kb * (uint32_t)(g.b_ks * 8) + (uint32_t)kt * db.step, wave);
-    };
-    issue(0, 0);
-    dma_slice_sync();
-    for (int t = 0; t < total; t++) {
-        const int cur = t & 1;
-        if (t + 1 < total) issue(t + 1, cur ^ 1);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        const double* a_s = As[cur];
-        const double* b_s = Bs[cur];
-        // 4 steps of k = 4: lane group h takes k = h*4 + j at step j
-        double av[4][4], bv[4][4];
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int row = wm * 64 + i * 16 + c;
-            if (AK) {
-                const f64x2 x0 = *reinterpret_cast<const f64x2*>(a_s + SA::kc_off(row, 2 * h));
-                const f64x2 x1 = *reinterpret_cast<const f64x2*>(a_s + SA::kc_off(row, 2 * h + 1));
-                av[i][0] = x0[0]; av[i][1] = x0[1]; av[i][2] = x1[0]; av[i][3] = x1[1];
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; j++) av[i][j] = a_s[(h * 4 + j) * SA::PITCH + row];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int col = wn * 64 + i * 16 + c;
-            if (BK) {
-                const f64x2 x0 = *reinterpret_cast<const f64x2*>(b_s + SB::kc_off(col, 2 * h));
-                const f64x2 x1 = *reinterpret_cast<const f64x2*>(b_s + SB::kc_off(col, 2 * h + 1));
-                bv[i][0] = x0[0]; bv[i][1] = x0[1]; bv[i][2] = x1[0]; bv[i][3] = x1[1];
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; j++) bv[i][j] = b_s[(h * 4 + j) * SB::PITCH + col];
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-#pragma unroll
-                for (int k = 0; k < 4; k++)
-                    acc[i][k] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i][j], bv[k][j], acc[i][k], 0, 0, 0);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        dma_slice_sync();
-    }
-
-    double* Cb = static_cast<double*>(g.C) + (int64_t)tc.g * g.c_bs + (int64_t)part * g.c_ps;
-    // symmetric output: off-diagonal tiles are also stored transposed; a
-    // diagonal tile keeps row <= col and mirrors it (exactly symmetric)
-    const bool mirror = !ACC && g.upper && tc.m0 != tc.n0;
-    const bool diag = !ACC && g.upper && tc.m0 == tc.n0;
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const int col = tc.n0 + wn * 64 + k * 16 + c;
-            if (col >= g.N) continue;
-#pragma unroll
-            for (int v = 0; v < 4; v++) {
-                const int row = tc.m0 + wm * 64 + i * 16 + 4 * v + h;
-                if (row < g.M && (!diag || row <= col)) {
-                    double* p = Cb + (int64_t)row * g.ldc + col;
-                    *p = ACC ? *p + acc[i][k][v] : acc[i][k][v];
-                    if (mirror || (diag && row < col)) Cb[(int64_t)col * g.ldc + row] = acc[i][k][v];
-                }
-            }
-        }
-}
-
-template <typename T>
-bool vector_ok(const GemmDesc& g) {
-    const int64_t vw = 16 / sizeof(T);
+// Conditions of the direct-to-LDS kernel: 16-byte aligned rows, whole K slices
+// (also of a part), no two-level batch, and every byte offset of an operand's
+// batch entry (over all K batches, and the rows or columns a last partial
+// tile reads) below 2^32.
+bool direct_lds_ok(const GemmDesc& g) {
     auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    return al(g.A) && al(g.B) && g.lda % vw == 0 && g.ldb % vw == 0 && g.a_bs % vw == 0 &&
-           g.b_bs % vw == 0 && g.a_ks % vw == 0 && g.b_ks % vw == 0 && g.a_is % vw == 0 && g.b_is % vw == 0 &&
-           (g.parts <= 1 || g.kp % vw == 0);
-}
-
-// The direct-to-LDS FP32 kernel's conditions (16-byte alignment is checked
-// by vector_ok): whole K slices (also of a part), and every byte offset of an
-// operand's batch entry (over all K batches, and the rows or columns a last
-// partial tile reads) below 2^32.
-bool direct_lds_ok(const GemmDesc& g, int64_t es = 4) {
+    if (!(al(g.A) && al(g.B) && g.lda % 4 == 0 && g.ldb % 4 == 0 && g.a_bs % 4 == 0 && g.b_bs % 4 == 0 &&
+          g.a_ks % 4 == 0 && g.b_ks % 4 == 0 && g.inner <= 1))
+        return false;
     if (g.kbatch < 1 || (g.parts > 1 && (g.kp % kSlice != 0 || g.accumulate))) return false;
     if (g.K % kSlice != 0 || g.K <= 0) return false;
     if (g.kbatch > 1 && (g.a_ks < 0 || g.b_ks < 0)) return false;
@@ -692,87 +261,48 @@ bool direct_lds_ok(const GemmDesc& g, int64_t es = 4) {
     // past the operand
     const int64_t ra = g.a_kcontig ? (int64_t)kTile * g.lda : kTile;
     const int64_t rb = g.b_kcontig ? (int64_t)kTile * g.ldb : kTile;
-    return (ea + ra) * es < ((int64_t)1 << 32) && (eb + rb) * es < ((int64_t)1 << 32);
+    return (ea + ra) * 4 < ((int64_t)1 << 32) && (eb + rb) * 4 < ((int64_t)1 << 32);
 }
 
-#define ROT_DISPATCH(KERNEL)                                                                       \
-    template <bool AK, bool BK, bool VEC>                                                          \
-    hipError_t launch_##KERNEL##_acc(const GemmDesc& g, dim3 grid, int tm, int tn, hipStream_t s) { \
-        if (g.accumulate)                                                                          \
-            hipLaunchKernelGGL((KERNEL<AK, BK, VEC, true>), grid, dim3(kThreads), 0, s, g, tm, tn); \
-        else                                                                                       \
-            hipLaunchKernelGGL((KERNEL<AK, BK, VEC, false>), grid, dim3(kThreads), 0, s, g, tm, tn); \
-        return hipGetLastError();                                                                  \
-    }                                                                                              \
-    template <bool AK, bool BK>                                                                    \
-    hipError_t launch_##KERNEL##_vec(const GemmDesc& g, bool vec, dim3 grid, int tm, int tn,       \
-                                     hipStream_t s) {                                              \
-        return vec ? launch_##KERNEL##_acc<AK, BK, true>(g, grid, tm, tn, s)                       \
-                   : launch_##KERNEL##_acc<AK, BK, false>(g, grid, tm, tn, s);                     \
-    }                                                                                              \
-    hipError_t launch_##KERNEL(const GemmDesc& g, bool vec, dim3 grid, int tm, int tn, hipStream_t s) { \
-        if (g.a_kcontig)                                                                           \
-            return g.b_kcontig ? launch_##KERNEL##_vec<true, true>(g, vec, grid, tm, tn, s)        \
-                               : launch_##KERNEL##_vec<true, false>(g, vec, grid, tm, tn, s);      \
-        return g.b_kcontig ? launch_##KERNEL##_vec<false, true>(g, vec, grid, tm, tn, s)           \
-                           : launch_##KERNEL##_vec<false, false>(g, vec, grid, tm, tn, s);         \
-    }
+// Tiles of 128 x 128 from which the direct-to-LDS kernel is the faster one:
+// four of its workgroups share a CU, so fewer than 4 x 256 leave room that
+// 64 x 64 tiles fill (both stages, 128 against 64 wide: 48 operators of 512
+// states, 3072 and 768 tiles, 787 / 833 us; 40 of 256, 640: 131 / 132; 10 of
+// 500, 600: 203 / 194; 2 of 512, 128: 78 / 55).
+constexpr int64_t kWideTiles = 1024;
 
-ROT_DISPATCH(gemm_f32_kernel)
-ROT_DISPATCH(gemm_f64_kernel)
-#undef ROT_DISPATCH
-
-template <typename T>
-hipError_t gemm_any(const GemmDesc& g, hipStream_t stream) {
+hipError_t gemm_any(const GemmDesc& g, bool is_double, hipStream_t stream) {
     if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
-    const int tm = (g.M + kTile - 1) / kTile, tn = (g.N + kTile - 1) / kTile;
     if (g.upper && (g.M != g.N || g.accumulate)) return hipErrorInvalidValue;
     const int parts = g.parts > 1 ? g.parts : 1;
-    if (parts > 1 && (g.upper || g.accumulate || g.kbatch != 1 || g.kp <= 0 || (int64_t)g.kp * (parts - 1) >= g.K))
+    if (parts > 1 && (g.upper || g.accumulate || g.kbatch != 1 || g.kp <= 0 || g.kp % kSlice != 0 ||
+                      (int64_t)g.kp * (parts - 1) >= g.K))
         return hipErrorInvalidValue;
+    const int tm = (g.M + kTile - 1) / kTile, tn = (g.N + kTile - 1) / kTile;
     const int64_t tiles = (g.upper ? (int64_t)tm * (tm + 1) / 2 : (int64_t)tm * tn) * g.batch * parts;
+    if (is_double || tiles < kWideTiles || !direct_lds_ok(g)) return gemm_tile64(g, is_double, stream);
     if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)tiles);
-    const bool vec = vector_ok<T>(g);
-    if (sizeof(T) == 4 && vec && direct_lds_ok(g)) {
-        const bool edge = g.M % kTile != 0 || g.N % kTile != 0;
-        auto pick = [&](auto mode, auto e) {
-            constexpr int MD = decltype(mode)::value;
-            constexpr bool E = decltype(e)::value;
-            if (g.a_kcontig)
-                return g.b_kcontig ? gemm_f32_dl_kernel<true, true, MD, E> : gemm_f32_dl_kernel<true, false, MD, E>;
-            return g.b_kcontig ? gemm_f32_dl_kernel<false, true, MD, E> : gemm_f32_dl_kernel<false, false, MD, E>;
-        };
-        auto pick_mode = [&](auto e) {
-            if (g.upper) return pick(std::integral_constant<int, 1>{}, e);
-            if (g.accumulate || g.kbatch > 1) return pick(std::integral_constant<int, 2>{}, e);
-            return pick(std::integral_constant<int, 0>{}, e);
-        };
-        hipLaunchKernelGGL((edge ? pick_mode(std::true_type{}) : pick_mode(std::false_type{})), grid,
-                           dim3(kThreads), 0, stream, g, tm, tn);
-        return hipGetLastError();
-    }
-    if (sizeof(T) == 4) return launch_gemm_f32_kernel(g, vec, grid, tm, tn, stream);
-    // FP64: only with a K-contiguous operand (with both slices M/N-contiguous
-    // the register-staged kernel is faster: 18.1 against 19.4 ms for the
-    // measurement's psi^T T product)
-    if (vec && (g.a_kcontig || g.b_kcontig) && direct_lds_ok(g, sizeof(T))) {
-        auto pick = [&](auto acc) {
-            constexpr bool A = decltype(acc)::value;
-            if (g.a_kcontig)
-                return g.b_kcontig ? gemm_f64_dl_kernel<true, true, A> : gemm_f64_dl_kernel<true, false, A>;
-            return gemm_f64_dl_kernel<false, true, A>;
-        };
-        hipLaunchKernelGGL((g.accumulate ? pick(std::true_type{}) : pick(std::false_type{})), grid, dim3(kThreads),
-                           0, stream, g, tm, tn);
-        return hipGetLastError();
-    }
-    return launch_gemm_f64_kernel(g, vec, grid, tm, tn, stream);
+    const bool edge = g.M % kTile != 0 || g.N % kTile != 0;
+    auto pick = [&](auto mode, auto e) {
+        constexpr int MD = decltype(mode)::value;
+        constexpr bool E = decltype(e)::value;
+        if (g.a_kcontig)
+            return g.b_kcontig ? gemm_f32_dl_kernel<true, true, MD, E> : gemm_f32_dl_kernel<true, false, MD, E>;
+        return g.b_kcontig ? gemm_f32_dl_kernel<false, true, MD, E> : gemm_f32_dl_kernel<false, false, MD, E>;
+    };
+    auto pick_mode = [&](auto e) {
+        if (g.upper) return pick(std::integral_constant<int, 1>{}, e);
+        if (g.accumulate || g.kbatch > 1) return pick(std::integral_constant<int, 2>{}, e);
+        return pick(std::integral_constant<int, 0>{}, e);
+    };
+    hipLaunchKernelGGL((edge ? pick_mode(std::true_type{}) : pick_mode(std::false_type{})), dim3((unsigned)tiles),
+                       dim3(kThreads), 0, stream, g, tm, tn);
+    return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t gemm_f32(const GemmDesc& g, hipStream_t stream) { return gemm_any<float>(g, stream); }
-hipError_t gemm_f64(const GemmDesc& g, hipStream_t stream) { return gemm_any<double>(g, stream); }
+hipError_t gemm_f32(const GemmDesc& g, hipStream_t stream) { return gemm_any(g, false, stream); }
+hipError_t gemm_f64(const GemmDesc& g, hipStream_t stream) { return gemm_any(g, true, stream); }
 
 }  // namespace rot

@@ -718,18 +718,18 @@ size_t f16_o_bytes(const rot_problem& p, const F16Layout& L, int ops, int parts)
 }  // namespace
 
 // Whether a group runs on FP16 pairs, `ops` operators at a time.  The passes
-// over U and O and the launches for skipped operators cost about 20 us, which
-// pays from about 1 GFLOP on (back to back, FP32 kernels against pairs: 40
-// operators of 128 states, 1.3 GFLOP, 48.8 / 45.6 us; 16 of them, 0.5 GFLOP,
-// 34.6 / 36.6; one of 403, 1.0 GFLOP, 85 / 53).  Below 64 states the tiles
-// are mostly padding; U's split takes d up to 8; 32-bit offsets bound the
-// operand arrays.
+// over U and O and the launches for skipped operators cost about 30 us, which
+// pays from about 4 GFLOP on (back to back, FP32 kernels against pairs: 80
+// operators of 128 states, 2.7 GFLOP, 52 / 52 us, 200 of them 97 / 78; 3 of
+// 403, 3.0 GFLOP, 59 / 59; 2 of 512, 4.3 GFLOP, 56 / 56, 4 of them 94 / 75).
+// Below 64 states the tiles are mostly padding; U's split takes d up to 8;
+// 32-bit offsets bound the operand arrays.
 bool f16_rotate_applies(const rot_problem& p, int ops) {
     if (p.d > kF16MaxSite || p.m < 64 || p.mp < 64) return false;
     const F16Layout L = f16_layout(p);
     if (std::max(L.u1, L.u2) >= ((size_t)1 << 31) - 256 * kSlabK * 2) return false;
     if (std::max(L.o_op, L.t_op) * ops >= (size_t)1 << 31) return false;
-    return 2.0 * p.m * p.d * p.mp * ((double)p.m + p.mp) * p.n_ops >= 1e9;
+    return 2.0 * p.m * p.d * p.mp * ((double)p.m + p.mp) * p.n_ops >= 4e9;
 }
 
 size_t f16_group_workspace(const rot_problem& p, int ops, bool symmetric) {

@@ -23,6 +23,11 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).float().cuda()
 
 
+def smallest_batch(m, d, mp):
+    """Operators of a shape from which a batch takes the pairs (4 GFLOP)."""
+    return int(4e9 / (2 * m * d * mp * (m + mp))) + 1
+
+
 def used_pairs(rot, call):
     rot.profile_enable(True)
     out = call()
@@ -43,7 +48,7 @@ EDGES = [(64, 4, 64), (65, 4, 97), (79, 4, 129), (96, 3, 191), (129, 1, 128), (1
 @pytest.mark.parametrize("symmetric", [False, True])
 def test_pairs_parity(rot, oracle_mod, shape, symmetric):
     m, d, mp = shape
-    n = int(1e9 / (2 * m * d * mp * (m + mp))) + 1  # the smallest batch of the shape that takes the pairs
+    n = smallest_batch(m, d, mp)
     case = workloads.dense_case(m, d, mp, n, cfg=700 + m, symmetric=symmetric)
     U, O = dev(case.U), dev(case.O)
     out, pairs = used_pairs(rot, lambda: rot.rotate(U, O, d, "fp32", symmetric_O=symmetric))
@@ -57,7 +62,8 @@ def test_pairs_parity(rot, oracle_mod, shape, symmetric):
 def test_pairs_padded_layouts(rot, oracle_mod, symmetric):
     """Padded rows and matrices filled with NaN, odd leading dimensions; the
     output's padding is kept."""
-    m, d, mp, n = 131, 4, 118, 40
+    m, d, mp = 131, 4, 118
+    n = smallest_batch(m, d, mp)
     case = workloads.dense_case(m, d, mp, n, cfg=730, symmetric=symmetric)
     Ub = torch.full((m * d, mp + 3), float("nan"), device="cuda")
     Ob = torch.full((n, m + 2, m + 5), float("nan"), device="cuda")
@@ -77,7 +83,8 @@ def test_pairs_leave_out_of_range_operators(rot, oracle_mod):
     """Operators with infinities, NaN or rows of very different size are
     computed by the FP32 kernels, the others of the batch are not affected;
     scaled operators keep their accuracy over FP32's range."""
-    m, d, mp, n = 150, 4, 130, 24
+    m, d, mp = 150, 4, 130
+    n = smallest_batch(m, d, mp)
     case = workloads.dense_case(m, d, mp, n, cfg=740, symmetric=False)
     O = case.O.copy()
     O[3] *= 2.0 ** -116
@@ -131,7 +138,7 @@ def test_pairs_chunks_and_column_scales(rot, oracle_mod):
 def test_pairs_in_a_graph(rot):
     """Captured once and replayed with eager work in between: every replay
     equals the eager result."""
-    m, d, mp, n = 260, 4, 200, 12
+    m, d, mp, n = 260, 4, 200, 24
     case = workloads.dense_case(m, d, mp, n, cfg=760, symmetric=False)
     U, O = dev(case.U), dev(case.O)
     out = torch.empty((n, mp, mp), device="cuda")
