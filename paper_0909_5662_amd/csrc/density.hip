@@ -5,13 +5,20 @@
 // rho_k = psi_k psi_k^T is formed tile by tile into a zero-padded n_pad x n_pad
 // matrix (n_pad a multiple of 64) and diagonalised by two-sided block Jacobi:
 // the matrix is cut into 32-wide blocks; in each round the blocks are paired
-// by the circle method, every pair's 64 x 64 principal submatrix is swept once
-// by scalar Jacobi in LDS (one workgroup per pair, the 32 disjoint rotations
-// of a step applied together), and the accumulated 64 x 64 rotations Q are
-// applied to the rest of the matrix (A_{P1,P2} <- Q1^T A_{P1,P2} Q2 for every
-// two pairs) and to the eigenvector matrix (V_{:,P} <- V_{:,P} Q).  Padded
-// rows and columns are exactly zero and never rotate, so they stay decoupled.
-// A sector is finished after a full cycle of rounds without any rotation.
+// by the circle method and every pair's 64 x 64 principal submatrix is swept
+// once by scalar Jacobi in LDS (one workgroup per pair, the 32 disjoint rotations
+// of a step applied together): all its index pairs in the first round of a
+// sweep, those between its two blocks in the others.
+//
+// A round is one launch.  A pair's workgroup first brings its own 32 x 32 block
+// between the two blocks up to date with the rotations of the round before
+// (Q1^T X Q2 of the last full matrix) and then sweeps; beside it, on the CUs
+// that the few pairs leave idle, the last round's rotations are applied to the
+// whole matrix (into a second copy) and to the eigenvectors (V_{:,P} <- V_{:,P}
+// Q), so neither is on the path from round to round.  Everything a round leaves
+// behind alternates between two buffers.  Padded rows and columns are exactly
+// zero and never rotate, so they stay decoupled.  A sector is finished after a
+// full cycle of rounds without any rotation.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,18 +45,18 @@ struct DmSector {
     double* w;
     double* V;
     int64_t ld_v;
-    int64_t a_off;  // doubles, into the working matrix and the eigenvector matrix
-    int64_t q_off;  // doubles, into the pair rotations (nb/2 blocks of 64 x 64)
-    int64_t w_off;  // doubles, into the concatenated sorted eigenvalues
-    int flag_off;   // ints, into the per-pair rotation flags
+    int64_t a_off;   // doubles, into a copy of the working matrix and the eigenvector matrix
+    int64_t q_off;   // doubles, into a round's pair submatrices or rotations (nb/2 blocks of 64 x 64)
+    int64_t w_off;   // doubles, into the concatenated sorted eigenvalues
+    int64_t d_off;   // doubles, into the diagonals
+    int flag_off;    // ints, into a round's per-pair rotation flags
     int pad;
 };
 
 struct DmState {
-    double floor;  // |a_pq| <= floor counts as zero
-    int quiet;     // consecutive rounds without a rotation
-    int converged;
-    int rounds;
+    double floor;  // |a_pq| <= floor of the scaled rho counts as zero
+    int quiet[2];  // consecutive rounds without a rotation, before the last one of each parity
+    int exponent;  // rho is swept scaled by 2^-exponent (trace in [1, 2))
     int pad;
 };
 
@@ -57,7 +64,16 @@ struct DmItem {
     int sec, a, b, kind;
 };
 
-enum : int { kItemA = 0, kItemV = 1, kItemBook = 2 };
+enum : int { kItemPair = 0, kItemA = 1, kItemV = 2 };
+
+// The buffers of one call; index 1 of a pair starts `..._round` elements on.
+struct DmBuffers {
+    double *A, *V, *S, *Q, *diag;
+    DmState* st;
+    int* flags;
+    int64_t a_round, q_round;
+    int f_round;
+};
 
 // Round t of the circle method for nb players (nb even): player 0 is fixed,
 // players 1..nb-1 sit on a circle turned by t; pair k is (0, c_0) for k = 0
@@ -76,6 +92,21 @@ __host__ __device__ inline void circle_pair(int nb, int t, int k, int& i, int& j
     }
     i = a < b ? a : b;
     j = a < b ? b : a;
+}
+
+// Pair (and which half of it, 0 or 1) that holds block b in round t.
+__device__ inline void circle_where(int nb, int t, int b, int& k, int& half) {
+    const int m = nb - 1;
+    if (b == 0) {
+        k = half = 0;
+        return;
+    }
+    int j = b - 1 - t;
+    if (j < 0) j += m;
+    k = j <= m / 2 ? j : m - j;
+    int i0, i1;
+    circle_pair(nb, t, k, i0, i1);
+    half = b == i1;
 }
 
 // Global row of local index l (0..63) of the pair of blocks (I, J).
@@ -158,349 +189,611 @@ __global__ __launch_bounds__(256) void dm_prep_kernel(const DmSector* __restrict
     }
     if (threadIdx.x == 0) {
         DmState x;
-        x.floor = ldexp(red[0], -52);
-        x.quiet = 0;
-        x.converged = 0;
-        x.rounds = 0;
+        x.exponent = red[0] > 0.0 && red[0] < INFINITY ? ilogb(red[0]) : 0;
+        x.floor = ldexp(red[0], -52 - x.exponent);
+        x.quiet[0] = x.quiet[1] = 0;
         x.pad = 0;
         st[blockIdx.x] = x;
     }
 }
 
 // ---------------------------------------------------------------------------
-// One Jacobi sweep over the 64 x 64 principal submatrix of pair k of round t:
-// 63 steps of 32 disjoint rotations (circle order over the 64 local indices).
-// Rotation (p, q) with tau = (a_qq - a_pp) / (2 a_pq), t = sign(tau) /
-// (|tau| + sqrt(1 + tau^2)), c = 1/sqrt(1 + t^2), s = t c zeroes a_pq of
-// J^T A J, J = [[c, s], [-s, c]] on rows/columns (p, q).  Each 2 x 2 block
-// (kx <= ky) of the step's pairs is rotated once, so the submatrix stays exactly
-// symmetric.  Schedule per step: all 528 blocks are rotated (one per thread),
-// then wave 0 derives the next step's rotations while the other waves apply
-// this step's to the accumulated Q (parameters double-buffered).
-constexpr int kPairThreads = 1024;
-constexpr int kSteps = kPair - 1;
-constexpr int kBlocks2 = 32 * 33 / 2;
+// One Jacobi sweep over the 64 x 64 principal submatrix S of a pair of blocks,
+// in steps of 32 disjoint rotations.  The 64 indices sit in 32 slots of a top
+// and a bottom one; a step rotates every slot's pair, then the indices move to
+// the next step's slots:
+//   full sweep (63 steps, circle order): top of slot 0 stays, the other 63
+//     indices turn one place: top k <- top k+1, top 31 <- bottom 31,
+//     bottom 0 <- top 1, bottom k <- bottom k-1;
+//   cross sweep (32 steps, the pairs between the two blocks): tops stay,
+//     bottom k <- bottom k+1 cyclically.
+// Both return every index to its first slot at the end.
+//
+// Rotation (p, q) zeroes a_pq of J^T S J, J = [[c, s], [-s, c]] on rows and
+// columns (p, q): with d = a_qq - a_pp and r = sqrt(d^2 + 4 a_pq^2),
+// c^2 = (1 + |d| / r) / 2, s = sign(d) a_pq / (r c), t = s / c (|t| <= 1).
+//
+// A step is bound by its chain of LDS round trips and dependent FP64
+// operations, so it has one barrier: each of the 496 two-slot blocks is
+// rotated by one thread, and the 32 blocks that hold the next step's a_pq
+// belong to the lanes of one wave, which go on from the updated entry to the
+// next rotation (square roots by Newton steps from the hardware's estimate;
+// the diagonal lives apart, double-buffered, written by those lanes only).
+// S is held as its upper triangle.  The accumulated Q never touches the LDS:
+// four waves hold 8 slots of every row each in registers and hand one value
+// per neighbour and step on.  1.1 us per step with two barriers and Q in LDS,
+// 0.5 us so; what is left is the LDS: after each barrier all waves read their
+// blocks at once (about 700 of 1250 cycles).  60 sectors of up to 246 states
+// (3 939 in all, 13 sweeps): 7.1 ms before, 3.5 ms now.
+constexpr int kQWaves = 4;
+constexpr int kSWaves = 9;
+constexpr int kPairThreads = 64 * (kQWaves + kSWaves);
+constexpr int kParamWave = 7;   // shares its SIMD with the fewest others
+constexpr int kCross = 32;      // steps
+constexpr int kFull = kPair - 1;
 
-struct Rot2 {
-    double c, s, t;
+struct DmBlocks {
+    // blocks (kx, ky), kx <= ky, by thread of the 8 plain S waves, then those of
+    // the next step's pairs by lane, for a full (0) and a cross (1) sweep;
+    // 255: none.  entry: which of (top, top), (top, bottom), (bottom, top),
+    // (bottom, bottom) of (kx, ky) is the next pair's a_pq.
+    unsigned char x[2][512], y[2][512], nx[2][32], ny[2][32], entry[2][32];
 };
 
-__device__ inline Rot2 jacobi_rotation(double app, double aqq, double apq, double floor) {
-    Rot2 r{1.0, 0.0, 0.0};
+constexpr DmBlocks dm_blocks() {
+    DmBlocks b{};
+    for (int k = 0; k < 32; k++) {
+        // full: (top 0, top 1); (top 2, bottom 0); (top k+1, bottom k-1); (bottom 31, bottom 30)
+        b.nx[0][k] = (unsigned char)(k == 0 ? 0 : k == 31 ? 30 : k - 1);
+        b.ny[0][k] = (unsigned char)(k == 0 ? 1 : k == 31 ? 31 : k + 1);
+        b.entry[0][k] = (unsigned char)(k == 0 ? 0 : k == 31 ? 3 : 2);
+        // cross: (top k, bottom k+1); (top 31, bottom 0)
+        b.nx[1][k] = (unsigned char)(k == 31 ? 0 : k);
+        b.ny[1][k] = (unsigned char)(k == 31 ? 31 : k + 1);
+        b.entry[1][k] = (unsigned char)(k == 31 ? 2 : 1);
+    }
+    for (int m = 0; m < 2; m++) {
+        int n = 0;
+        for (int ky = 0; ky < 32; ky++)
+            for (int kx = 0; kx <= ky; kx++) {
+                bool next = false;
+                for (int k = 0; k < 32; k++) next = next || (b.nx[m][k] == kx && b.ny[m][k] == ky);
+                if (next) continue;
+                b.x[m][n] = (unsigned char)kx;
+                b.y[m][n] = (unsigned char)ky;
+                n++;
+            }
+        for (; n < 512; n++) b.x[m][n] = b.y[m][n] = 255;
+    }
+    return b;
+}
+
+__constant__ DmBlocks kDmBlocks = dm_blocks();
+
+// Index in the top (bottom) of slot k at step u.
+__device__ inline int slot_index(bool full, int k, bool bottom, int u) {
+    if (!full) return bottom ? 32 + ((k + u) & 31) : k;
+    if (k == 0 && !bottom) return 0;
+    const int j = (bottom ? (k == 0 ? 0 : 63 - k) : k) + u;
+    return 1 + (j >= 63 ? j - 63 : j);
+}
+
+__device__ inline int su(unsigned a, unsigned b) { return (int)(__umul24(min(a, b), kLs) + max(a, b)); }
+
+// 1 / sqrt(x), x in a range without under- or overflow: the hardware's
+// estimate and two Newton steps.
+__device__ inline double dm_rsqrt(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    const double h = 0.5 * x;
+    y = fma(y, fma(-h * y, y, 0.5), y);
+    return fma(y, fma(-h * y, y, 0.5), y);
+}
+
+struct DmRot {
+    double c, s;
+};
+
+// The rotation that zeroes apq; the diagonal becomes app - t apq, aqq + t apq.
+__device__ inline DmRot dm_rotation(double& app, double& aqq, double apq, double floor) {
+    DmRot r{1.0, 0.0};
     if (fabs(apq) > floor) {
-        const double tau = (aqq - app) / (2.0 * apq);
-        r.t = fabs(tau) > 1e150 ? 0.5 / tau : copysign(1.0, tau) / (fabs(tau) + sqrt(1.0 + tau * tau));
-        r.c = 1.0 / sqrt(1.0 + r.t * r.t);
-        r.s = r.t * r.c;
+        const double d = aqq - app, y = dm_rsqrt(fma(d, d, 4.0 * apq * apq));
+        const double c2 = fma(0.5 * fabs(d), y, 0.5), z = dm_rsqrt(c2);
+        r.c = c2 * z;
+        r.s = copysign(apq, d < 0.0 ? -apq : apq) * (y * z);
+        const double t = r.s * z;
+        app = fma(-t, apq, app);
+        aqq = fma(t, apq, aqq);
     }
     return r;
 }
 
-// S is held as its upper triangle (entry (a, b) and (b, a) at su(min, max)):
-// at every step each unordered pair of indices lies in exactly one 2 x 2
-// block, so no mirrored copy has to be written.  Q is held transposed, row
-// stride kLq, so a rotation of columns (p, q) of Q updates two rows of Q^T
-// with 16-byte LDS accesses.
-constexpr int kLq = kPair + 2;
+constexpr int kHalf = kBlk + 1;  // LDS row stride of 64 x 32 operands
 
-__device__ inline int su(int a, int b) { return a < b ? a * kLs + b : b * kLs + a; }
+struct DmPairLds {
+    double S[kPair * kLs];                // before the sweep: X, then X Q2
+    double L1[kPair * kHalf], R2[kPair * kHalf];  // Q1's and Q2's columns of the two blocks
+    double2 rot[2][32];                   // (c, s) of a step's slots
+    double D[2][kPair];                   // diagonal after a step's rotations, by index
+    double hand[2][kQWaves][2][kPair];    // what the Q waves hand on, by row
+    int any, work;
+};
 
-__global__ __launch_bounds__(kPairThreads) void dm_pair_kernel(const DmSector* __restrict__ secs,
-                                                               const DmItem* __restrict__ items,
-                                                               double* __restrict__ A, double* __restrict__ Qw,
-                                                               const DmState* __restrict__ st,
-                                                               int* __restrict__ rotated, int round) {
-    const DmItem it = items[blockIdx.x];
-    const DmSector s = secs[it.sec];
-    const int k = it.a;
-    const int tid = threadIdx.x;
-    int* flag = rotated + s.flag_off + k;
-    if (st[it.sec].converged) {
-        if (tid == 0) *flag = 0;
-        return;
-    }
-    const double floor = st[it.sec].floor;
-    int I, J;
-    circle_pair(s.nb, round, k, I, J);
-    __shared__ double S[kPair * kLs];
-    __shared__ __attribute__((aligned(16))) double Qt[kPair * kLq];
-    __shared__ double rc[2][32], rs[2][32], rt[2][32];
-    __shared__ unsigned char tp[kSteps][32], tq[kSteps][32];
-    __shared__ int any;
-    double* a = A + s.a_off;
-    const int64_t np = s.npad;
-    {
-        constexpr int kPer = kPair * kPair / kPairThreads;
-        double sv[kPer];
+template <bool FULL>
+__device__ __attribute__((always_inline)) inline void dm_sweep(DmPairLds& L, double floor, int tid,
+                                                               double (&qt)[8], double (&qb)[8]) {
+    constexpr int NS = FULL ? kFull : kCross, M = FULL ? 0 : 1;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (wave < kQWaves) {
+        for (int u = 0; u < NS; u++) {
+            const int cur = u & 1;
 #pragma unroll
-        for (int j = 0; j < kPer; j++) {
-            const int e = tid + kPairThreads * j, x = e >> 6, y = e & 63;
-            sv[j] = a[(int64_t)pair_row(I, J, x) * np + pair_row(I, J, y)];
-        }
+            for (int j = 0; j < 8; j++) {
+                const double2 r = L.rot[cur][8 * wave + j];
+                const double a = qt[j], b = qb[j];
+                qt[j] = fma(r.x, a, -r.y * b);
+                qb[j] = fma(r.y, a, r.x * b);
+            }
+            // hand on to the neighbours, move the own ones
+            L.hand[cur][wave][0][lane] = FULL ? qt[0] : qb[0];
+            if (FULL) L.hand[cur][wave][1][lane] = qb[7];
+            __syncthreads();
+            const double up = L.hand[cur][(wave + 1) & 3][0][lane];
+            if (FULL) {
+                const double down = L.hand[cur][(wave + 3) & 3][1][lane];
+                const double t0 = qt[0], t1 = qt[1], last = qb[7];
 #pragma unroll
-        for (int j = 0; j < kPer; j++) {
-            const int e = tid + kPairThreads * j, x = e >> 6, y = e & 63;
-            if (x <= y) S[x * kLs + y] = sv[j];
-            Qt[x * kLq + y] = x == y ? 1.0 : 0.0;
-        }
-    }
-    for (int e = tid; e < kSteps * 32; e += kPairThreads) {
-        int p, q;
-        circle_pair(kPair, e >> 5, e & 31, p, q);
-        tp[e >> 5][e & 31] = (unsigned char)p;
-        tq[e >> 5][e & 31] = (unsigned char)q;
-    }
-    if (tid == 0) any = 0;
-    __syncthreads();
-    if (tid < 32) {
-        const int p = tp[0][tid], q = tq[0][tid];
-        const Rot2 r = jacobi_rotation(S[p * kLs + p], S[q * kLs + q], S[p * kLs + q], floor);
-        rc[0][tid] = r.c;
-        rs[0][tid] = r.s;
-        rt[0][tid] = r.t;
-        if (r.s != 0.0) any = 1;
-    }
-    // this thread's 2 x 2 block: b = ky (ky + 1) / 2 + kx, kx <= ky
-    int kx = 0, ky = 0;
-    if (tid < kBlocks2) {
-        ky = (int)((sqrtf(8.0f * tid + 1.0f) - 1.0f) * 0.5f);
-        while (ky * (ky + 1) / 2 > tid) ky--;
-        while ((ky + 1) * (ky + 2) / 2 <= tid) ky++;
-        kx = tid - ky * (ky + 1) / 2;
-    }
-    __syncthreads();
-    for (int u = 0; u < kSteps; u++) {
-        const int cur = u & 1;
-        if (tid < kBlocks2) {
-            const int px = tp[u][kx], qx = tq[u][kx];  // px < qx
-            if (kx == ky) {
-                const double t = rt[cur][kx];
-                if (t != 0.0) {
-                    const double apq = S[px * kLs + qx];
-                    S[px * kLs + px] -= t * apq;
-                    S[qx * kLs + qx] += t * apq;
-                    S[px * kLs + qx] = 0.0;
+                for (int j = 0; j < 7; j++) qt[j] = qt[j + 1];
+                qt[7] = wave == 3 ? last : up;
+#pragma unroll
+                for (int j = 7; j > 0; j--) qb[j] = qb[j - 1];
+                qb[0] = down;
+                if (wave == 0) {
+                    qt[0] = t0;
+                    qb[0] = t1;
                 }
             } else {
-                const double sx = rs[cur][kx], sy = rs[cur][ky];
-                if (sx != 0.0 || sy != 0.0) {
-                    const int py = tp[u][ky], qy = tq[u][ky];
-                    const double cx = rc[cur][kx], cy = rc[cur][ky];
-                    const int iu = su(px, py), iv = su(px, qy), ix = su(qx, py), iy = su(qx, qy);
-                    const double u0 = S[iu], v0 = S[iv], x0 = S[ix], y0 = S[iy];
-                    const double u1 = cx * u0 - sx * x0, x1 = sx * u0 + cx * x0;
-                    const double v1 = cx * v0 - sx * y0, y1 = sx * v0 + cx * y0;
-                    S[iu] = cy * u1 - sy * v1;
-                    S[iv] = sy * u1 + cy * v1;
-                    S[ix] = cy * x1 - sy * y1;
-                    S[iy] = sy * x1 + cy * y1;
+#pragma unroll
+                for (int j = 0; j < 7; j++) qb[j] = qb[j + 1];
+                qb[7] = up;
+            }
+        }
+        return;
+    }
+    const bool param = wave == kParamWave;
+    const int plain = (wave - kQWaves - (wave > kParamWave ? 1 : 0)) * 64 + lane;
+    unsigned kx, ky, entry = 0;
+    if (param) {
+        kx = lane < 32 ? kDmBlocks.nx[M][lane] : 255;
+        ky = lane < 32 ? kDmBlocks.ny[M][lane] : 255;
+        entry = kDmBlocks.entry[M][lane & 31];
+        __builtin_amdgcn_s_setprio(3);  // the step waits for this wave
+    } else {
+        kx = kDmBlocks.x[M][plain];
+        ky = kDmBlocks.y[M][plain];
+    }
+    const bool live = kx < 32, diagonal = kx == ky;
+    if (!live) kx = ky = 0;
+    // this thread's indices, and (lanes of the next rotations) the next pair's,
+    // carried from step to step
+    unsigned px = slot_index(FULL, kx, false, 0), qx = slot_index(FULL, kx, true, 0);
+    unsigned py = slot_index(FULL, ky, false, 0), qy = slot_index(FULL, ky, true, 0);
+    unsigned p = slot_index(FULL, lane & 31, false, 1), q = slot_index(FULL, lane & 31, true, 1);
+    auto advance = [](unsigned i, bool bottom) -> unsigned {
+        if (FULL) return i == 0 ? 0 : i == 63 ? 1 : i + 1;
+        return bottom ? 32 + ((i + 1) & 31) : i;
+    };
+    for (int u = 0; u < NS; u++) {
+        const int cur = u & 1;
+        if (live) {
+            if (diagonal) {
+                if (L.rot[cur][kx].y != 0.0) L.S[su(px, qx)] = 0.0;
+            } else {
+                const int iu = su(px, py), iv = su(px, qy), ix = su(qx, py), iy = su(qx, qy);
+                const double2 rx = L.rot[cur][kx], ry = L.rot[cur][ky];
+                double u0 = L.S[iu], v0 = L.S[iv], x0 = L.S[ix], y0 = L.S[iy];
+                double app = 0.0, aqq = 0.0;
+                if (param) {
+                    app = L.D[cur][p];
+                    aqq = L.D[cur][q];
+                }
+                if (rx.y != 0.0 || ry.y != 0.0) {
+                    const double u1 = fma(rx.x, u0, -rx.y * x0), x1 = fma(rx.y, u0, rx.x * x0);
+                    const double v1 = fma(rx.x, v0, -rx.y * y0), y1 = fma(rx.y, v0, rx.x * y0);
+                    u0 = fma(ry.x, u1, -ry.y * v1);
+                    v0 = fma(ry.y, u1, ry.x * v1);
+                    x0 = fma(ry.x, x1, -ry.y * y1);
+                    y0 = fma(ry.y, x1, ry.x * y1);
+                    L.S[iu] = u0;
+                    L.S[iv] = v0;
+                    L.S[ix] = x0;
+                    L.S[iy] = y0;
+                }
+                if (param) {
+                    const double apq = entry & 2 ? (entry & 1 ? y0 : x0) : (entry & 1 ? v0 : u0);
+                    DmRot r{1.0, 0.0};
+                    if (u + 1 < NS) r = dm_rotation(app, aqq, apq, floor);
+                    L.rot[cur ^ 1][lane] = double2{r.c, r.s};
+                    L.D[cur ^ 1][p] = app;
+                    L.D[cur ^ 1][q] = aqq;
+                    if (r.s != 0.0) L.any = 1;
+                    p = advance(p, false);
+                    q = advance(q, true);
                 }
             }
-        }
-        __syncthreads();
-        if (tid < 64) {
-            if (tid < 32 && u + 1 < kSteps) {
-                const int p = tp[u + 1][tid], q = tq[u + 1][tid];
-                const Rot2 r = jacobi_rotation(S[p * kLs + p], S[q * kLs + q], S[p * kLs + q], floor);
-                rc[cur ^ 1][tid] = r.c;
-                rs[cur ^ 1][tid] = r.s;
-                rt[cur ^ 1][tid] = r.t;
-                if (r.s != 0.0) any = 1;
-            }
-        } else {
-            // Q <- Q J: rows p, q of Q^T, two entries per access; 32 pairs x 32
-            // row pairs over the 960 threads past wave 0
-            for (int wq = tid - 64; wq < 32 * 32; wq += kPairThreads - 64) {
-                const int kq = wq >> 5, rq2 = wq & 31;
-                const double sn = rs[cur][kq];
-                if (sn == 0.0) continue;
-                const double c = rc[cur][kq];
-                double2* rp = reinterpret_cast<double2*>(Qt + tp[u][kq] * kLq) + rq2;
-                double2* rq = reinterpret_cast<double2*>(Qt + tq[u][kq] * kLq) + rq2;
-                const double2 vp = *rp, vq = *rq;
-                *rp = double2{c * vp.x - sn * vq.x, c * vp.y - sn * vq.y};
-                *rq = double2{sn * vp.x + c * vq.x, sn * vp.y + c * vq.y};
-            }
+            px = advance(px, false);
+            qx = advance(qx, true);
+            py = advance(py, false);
+            qy = advance(qy, true);
         }
         __syncthreads();
     }
-    for (int e = tid; e < kPair * kPair; e += kPairThreads) {
-        const int x = e >> 6, y = e & 63;
-        a[(int64_t)pair_row(I, J, x) * np + pair_row(I, J, y)] = S[su(x, y)];
-        Qw[s.q_off + (int64_t)k * kPair * kPair + e] = Qt[y * kLq + x];
-    }
-    if (tid == 0) *flag = any;
+    if (param) __builtin_amdgcn_s_setprio(0);
 }
 
 typedef double dm_f64x4 __attribute__((ext_vector_type(4)));
 
-// Y = op(L) * R (64 x 64, op(L) = L or L^T, operands in LDS with row stride
-// kLs) on v_mfma_f64_16x16x4f64: wave w owns rows 32 (w / 2) .. and columns
-// 32 (w % 2) .. as 2 x 2 blocks of 16 x 16.  Lane l supplies A(row l%16, k l/16)
-// and B(k l/16, col l%16); element v of block (bi, bj) is row
-// 32 wr + 16 bi + 4 v + l/16, column 32 wc + 16 bj + l%16.
+// 16 x 16 block of op(L) R over K = 64 on v_mfma_f64_16x16x4f64, operands in LDS
+// with row strides ls and rs: L at element (row, k) or, kTransL, (k, row).
+// Lane l supplies A(row l%16, k l/16) and B(k l/16, col l%16); element v is row
+// 4 v + l/16, column l%16.
 template <bool kTransL>
-__device__ inline void mm64(const double* L, const double* R, dm_f64x4 (&acc)[2][2], int wr, int wc, int h,
-                            int c) {
+__device__ inline dm_f64x4 mm16(const double* L, int ls, int row0, const double* R, int rs, int col0, int lane) {
+    const int h = lane >> 4, c = lane & 15;
+    dm_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int bi = 0; bi < 2; bi++)
-#pragma unroll
-        for (int bj = 0; bj < 2; bj++) acc[bi][bj] = dm_f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
     for (int k4 = 0; k4 < kPair / 4; k4++) {
         const int k = 4 * k4 + h;
-        double a[2], b[2];
-#pragma unroll
-        for (int bi = 0; bi < 2; bi++) {
-            const int row = 32 * wr + 16 * bi + c;
-            a[bi] = kTransL ? L[k * kLs + row] : L[row * kLs + k];
-        }
-#pragma unroll
-        for (int bj = 0; bj < 2; bj++) b[bj] = R[k * kLs + 32 * wc + 16 * bj + c];
-#pragma unroll
-        for (int bi = 0; bi < 2; bi++)
-#pragma unroll
-            for (int bj = 0; bj < 2; bj++)
-                acc[bi][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[bi], b[bj], acc[bi][bj], 0, 0, 0);
+        const double x = kTransL ? L[k * ls + row0 + c] : L[(row0 + c) * ls + k];
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, R[k * rs + col0 + c], acc, 0, 0, 0);
     }
+    return acc;
 }
 
-__device__ inline void acc_to_lds(double* X, const dm_f64x4 (&acc)[2][2], int wr, int wc, int h, int c) {
+// A sector's place in launch `round`: its own round index a, and whether it
+// takes part at all (sectors with fewer blocks than the largest sit out the
+// rest of a sweep of max_rounds).
+struct DmClock {
+    int a, t, t_prev;  // t: round of its sweep, t_prev: that of round a - 1
+    bool active;
+};
+
+__device__ inline DmClock dm_clock(int nb, int round, int max_rounds) {
+    const int sweep = round / max_rounds, t = round - sweep * max_rounds;
+    return {sweep * (nb - 1) + t, t, t ? t - 1 : nb - 2, t < nb - 1};
+}
+
+// Pair k in its sector's round ck.a.
+__device__ inline void dm_pair(const DmSector& s, int sec, int k, const DmClock& ck, DmPairLds& L,
+                               const DmBuffers& g) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int cur = ck.a & 1, old = cur ^ 1;
+    DmState* st = g.st + sec;
+    int* flags = g.flags + s.flag_off;
+    const int* flags_old = flags + old * g.f_round;
+    int* flag = flags + cur * g.f_round + k;
+    const int quiet = ck.a ? st->quiet[old] : 0;
+    const bool done = quiet >= s.nb - 1;
+    if (k == 0 && tid == 0) {
+        int any = ck.a == 0;
+        for (int x = 0; x < s.nb / 2 && ck.a && !done; x++) any |= flags_old[x];
+        st->quiet[cur] = done ? quiet : any ? 0 : quiet + 1;
+    }
+    if (done) {
+        if (tid == 0) *flag = 0;
+        return;
+    }
+    const double floor = st->floor;
+    const int expo = st->exponent;
+    const bool full = ck.t == 0;
+    int I, J;
+    circle_pair(s.nb, ck.t, k, I, J);
+    const int64_t np = s.npad;
+    const double* Sold = g.S + old * g.q_round + s.q_off;
+    if (tid == 0) L.any = L.work = 0;
+    constexpr int kPer = (kPair * kPair + kPairThreads - 1) / kPairThreads;
+    double sv[kPer];  // this thread's entries e = tid + kPairThreads j of S
+    bool mixed = false;  // the block between I and J comes from a product
+    int P1 = 0, P2 = 0, h1 = 0, h2 = 0;
+    if (ck.a == 0) {
+        const double* a = g.A + s.a_off;
 #pragma unroll
-    for (int bi = 0; bi < 2; bi++)
-#pragma unroll
-        for (int bj = 0; bj < 2; bj++) {
-            const int col = 32 * wc + 16 * bj + c;
-            X[(32 * wr + 16 * bi + h) * kLs + col] = acc[bi][bj].x;
-            X[(32 * wr + 16 * bi + 4 + h) * kLs + col] = acc[bi][bj].y;
-            X[(32 * wr + 16 * bi + 8 + h) * kLs + col] = acc[bi][bj].z;
-            X[(32 * wr + 16 * bi + 12 + h) * kLs + col] = acc[bi][bj].w;
+        for (int j = 0; j < kPer; j++) {
+            const int e = min(tid + kPairThreads * j, kPair * kPair - 1);
+            sv[j] = a[(int64_t)pair_row(I, J, e >> 6) * np + pair_row(I, J, e & 63)];
         }
-}
-
-// Applies the rotations of round t: A_{P1,P2} <- Q1^T A_{P1,P2} Q2 for pairs
-// P1 < P2 (written with its mirror), V_{R,P} <- V_{R,P} Q_P for every 64-row
-// tile R, and per sector the bookkeeping of quiet rounds.
-__global__ __launch_bounds__(256) void dm_update_kernel(const DmSector* __restrict__ secs,
-                                                        const DmItem* __restrict__ items, double* __restrict__ A,
-                                                        double* __restrict__ Vw, const double* __restrict__ Qw,
-                                                        DmState* __restrict__ st, const int* __restrict__ rotated,
-                                                        int round) {
-    const DmItem it = items[blockIdx.x];
-    const DmSector s = secs[it.sec];
-    const int* rf = rotated + s.flag_off;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int wr = w >> 1, wc = w & 1, h = lane >> 4, c = lane & 15;
-    if (it.kind == kItemBook) {
-        if (tid == 0) {
-            DmState x = st[it.sec];
-            if (!x.converged) {
-                int any = 0;
-                for (int k = 0; k < s.nb / 2; k++) any |= rf[k];
-                x.rounds++;
-                if (any) {
-                    x.quiet = 0;
-                } else if (++x.quiet >= s.nb - 1) {
-                    x.converged = 1;
-                }
-                st[it.sec] = x;
+    } else {
+        circle_where(s.nb, ck.t_prev, I, P1, h1);
+        circle_where(s.nb, ck.t_prev, J, P2, h2);
+        mixed = P1 != P2;
+        const double *s1 = Sold + (int64_t)P1 * kPair * kPair, *s2 = Sold + (int64_t)P2 * kPair * kPair;
+#pragma unroll
+        for (int j = 0; j < kPer; j++) {
+            const int e = min(tid + kPairThreads * j, kPair * kPair - 1), x = e >> 6, y = e & 63;
+            sv[j] = !mixed              ? s1[e]
+                    : y < kBlk          ? (x < kBlk ? s1[(kBlk * h1 + x) * kPair + kBlk * h1 + y] : 0.0)
+                    : x < kBlk          ? 0.0
+                                        : s2[(kBlk * (h2 - 1) + x) * kPair + kBlk * (h2 - 1) + y];
+        }
+    }
+    double cross[4] = {0.0, 0.0, 0.0, 0.0};  // waves 0..3: 16 x 16 of the block between I and J
+    if (mixed) {
+        int I1, J1, I2, J2;
+        circle_pair(s.nb, ck.t_prev, P1, I1, J1);
+        circle_pair(s.nb, ck.t_prev, P2, I2, J2);
+        const double* a = g.A + old * g.a_round + s.a_off;
+        const double* q1 = g.Q + old * g.q_round + s.q_off + (int64_t)P1 * kPair * kPair;
+        const double* q2 = g.Q + old * g.q_round + s.q_off + (int64_t)P2 * kPair * kPair;
+        const int r1 = flags_old[P1], r2 = flags_old[P2];
+        double xv[kPer], lv[kPer], rv[kPer];
+        constexpr int kPerH = (kPair * kBlk + kPairThreads - 1) / kPairThreads;
+#pragma unroll
+        for (int j = 0; j < kPer; j++) {
+            const int e = min(tid + kPairThreads * j, kPair * kPair - 1);
+            xv[j] = a[(int64_t)pair_row(I1, J1, e >> 6) * np + pair_row(I2, J2, e & 63)];
+        }
+#pragma unroll
+        for (int j = 0; j < kPerH; j++) {
+            const int e = min(tid + kPairThreads * j, kPair * kBlk - 1), x = e >> 5, y = e & 31;
+            lv[j] = r1 ? q1[x * kPair + kBlk * h1 + y] : x == kBlk * h1 + y ? 1.0 : 0.0;
+            rv[j] = r2 ? q2[x * kPair + kBlk * h2 + y] : x == kBlk * h2 + y ? 1.0 : 0.0;
+        }
+#pragma unroll
+        for (int j = 0; j < kPer; j++) {
+            const int e = tid + kPairThreads * j;
+            if (e < kPair * kPair) L.S[(e >> 6) * kLs + (e & 63)] = xv[j];
+        }
+#pragma unroll
+        for (int j = 0; j < kPerH; j++) {
+            const int e = tid + kPairThreads * j;
+            if (e < kPair * kBlk) {
+                L.L1[(e >> 5) * kHalf + (e & 31)] = lv[j];
+                L.R2[(e >> 5) * kHalf + (e & 31)] = rv[j];
             }
         }
+        __syncthreads();
+        dm_f64x4 z = {0.0, 0.0, 0.0, 0.0};
+        const int zr = 16 * (wave >> 1), zc = 16 * (wave & 1), h = lane >> 4, c = lane & 15;
+        if (wave < 8) z = mm16<false>(L.S, kLs, zr, L.R2, kHalf, zc, lane);
+        __syncthreads();
+        if (wave < 8)
+#pragma unroll
+            for (int v = 0; v < 4; v++) L.S[(zr + 4 * v + h) * kHalf + zc + c] = z[v];
+        __syncthreads();
+        if (wave < 4) {
+            const dm_f64x4 y = mm16<true>(L.L1, kHalf, zr, L.S, kHalf, zc, lane);
+#pragma unroll
+            for (int v = 0; v < 4; v++) cross[v] = y[v];
+        }
+    }
+    __syncthreads();
+    {
+        bool over = false;
+#pragma unroll
+        for (int j = 0; j < kPer; j++) {
+            const int e = tid + kPairThreads * j, x = e >> 6, y = e & 63;
+            const bool between = x < kBlk && y >= kBlk;
+            if (e >= kPair * kPair || x > y || (mixed && between)) continue;
+            const double v = ldexp(sv[j], -expo);
+            L.S[x * kLs + y] = v;
+            if (x != y && (full || between) && !(fabs(v) <= floor)) over = true;
+        }
+        if (mixed && wave < 4)
+#pragma unroll
+            for (int v = 0; v < 4; v++) {
+                const int x = 16 * (wave >> 1) + 4 * v + (lane >> 4), y = kBlk + 16 * (wave & 1) + (lane & 15);
+                const double w = ldexp(cross[v], -expo);
+                L.S[x * kLs + y] = w;
+                if (!(fabs(w) <= floor)) over = true;
+            }
+        if (over) L.work = 1;
+    }
+    __syncthreads();
+    double* Snew = g.S + cur * g.q_round + s.q_off + (int64_t)k * kPair * kPair;
+    double* diag = g.diag + s.d_off;
+    if (!L.work) {
+        for (int e = tid; e < kPair * kPair; e += kPairThreads) {
+            const int x = e >> 6, y = e & 63;
+            const double v = ldexp(L.S[su(x, y)], expo);
+            Snew[e] = v;
+            if (x == y) diag[pair_row(I, J, x)] = v;
+        }
+        if (tid == 0) *flag = 0;
         return;
     }
-    __shared__ double X[kPair * kLs];
-    __shared__ double L[kPair * kLs];
-    __shared__ double R[kPair * kLs];
-    const int64_t np = s.npad;
-    dm_f64x4 y[2][2];
-    if (it.kind == kItemA) {
-        const int P1 = it.a, P2 = it.b;
-        const int r1 = rf[P1], r2 = rf[P2];
-        if (!r1 && !r2) return;
-        int I1, J1, I2, J2;
-        circle_pair(s.nb, round, P1, I1, J1);
-        circle_pair(s.nb, round, P2, I2, J2);
-        double* a = A + s.a_off;
-        const double* q1 = Qw + s.q_off + (int64_t)P1 * kPair * kPair;
-        const double* q2 = Qw + s.q_off + (int64_t)P2 * kPair * kPair;
-        // all loads of a thread issued before the first LDS write
-        double xv[16], lv[16], rv[16];
+    if (tid < 32) {
+        const int p = slot_index(full, tid, false, 0), q = slot_index(full, tid, true, 0);
+        double app = L.S[p * kLs + p], aqq = L.S[q * kLs + q];
+        const DmRot r = dm_rotation(app, aqq, L.S[su(p, q)], floor);
+        L.rot[0][tid] = double2{r.c, r.s};
+        L.D[0][p] = app;
+        L.D[0][q] = aqq;
+        if (r.s != 0.0) L.any = 1;
+    }
+    // Q's columns of this wave's slots, row `lane`
+    double qt[8], qb[8];
 #pragma unroll
-        for (int j = 0; j < 16; j++) {
-            const int e = tid + 256 * j, x = e >> 6, z = e & 63;
-            xv[j] = a[(int64_t)pair_row(I1, J1, x) * np + pair_row(I2, J2, z)];
-            lv[j] = r1 ? q1[e] : 0.0;
-            rv[j] = r2 ? q2[e] : 0.0;
+    for (int j = 0; j < 8; j++) {
+        qt[j] = slot_index(full, 8 * (wave & 3) + j, false, 0) == lane ? 1.0 : 0.0;
+        qb[j] = slot_index(full, 8 * (wave & 3) + j, true, 0) == lane ? 1.0 : 0.0;
+    }
+    __syncthreads();
+    if (full) dm_sweep<true>(L, floor, tid, qt, qb);
+    else dm_sweep<false>(L, floor, tid, qt, qb);
+    const int last = (full ? kFull : kCross) & 1;
+    for (int e = tid; e < kPair * kPair; e += kPairThreads) {
+        const int x = e >> 6, y = e & 63;
+        const double v = ldexp(x == y ? L.D[last][x] : L.S[su(x, y)], expo);
+        Snew[e] = v;
+        if (x == y) diag[pair_row(I, J, x)] = v;
+    }
+    __syncthreads();
+    // Q through the LDS, so that its rows are written whole
+    if (wave < kQWaves)
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            L.S[lane * kLs + slot_index(full, 8 * wave + j, false, 0)] = qt[j];
+            L.S[lane * kLs + slot_index(full, 8 * wave + j, true, 0)] = qb[j];
         }
+    __syncthreads();
+    double* qw = g.Q + cur * g.q_round + s.q_off + (int64_t)k * kPair * kPair;
+    for (int e = tid; e < kPair * kPair; e += kPairThreads) qw[e] = L.S[(e >> 6) * kLs + (e & 63)];
+    if (tid == 0) *flag = L.any;
+}
+
+struct DmApplyLds {
+    double X[kPair * kLs], R[kPair * kLs];
+};
+
+// The rotations of a sector's last round on the block of pairs P1 <= P2 of its
+// matrix, from the old copy to the new one: Q1^T X Q2 and its mirror, or the
+// swept submatrix itself.
+__device__ inline void dm_apply_a(const DmSector& s, int P1, int P2, const DmClock& ck, DmApplyLds& L,
+                                  const DmBuffers& g) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 4, c = lane & 15;
+    const int cur = ck.a & 1, old = cur ^ 1;
+    const int64_t np = s.npad;
+    const double* from = g.A + old * g.a_round + s.a_off;
+    double* to = g.A + cur * g.a_round + s.a_off;
+    const int64_t qp = s.q_off + old * g.q_round;
+    int I1, J1, I2, J2;
+    circle_pair(s.nb, ck.t_prev, P1, I1, J1);
+    circle_pair(s.nb, ck.t_prev, P2, I2, J2);
+    if (P1 == P2) {
+        const double* sv = g.S + qp + (int64_t)P1 * kPair * kPair;
+        for (int e = tid; e < kPair * kPair; e += kPairThreads)
+            to[(int64_t)pair_row(I1, J1, e >> 6) * np + pair_row(I1, J1, e & 63)] = sv[e];
+        return;
+    }
+    const int* rf = g.flags + old * g.f_round + s.flag_off;
+    const int r1 = rf[P1], r2 = rf[P2];
+    const double *q1 = g.Q + qp + (int64_t)P1 * kPair * kPair, *q2 = g.Q + qp + (int64_t)P2 * kPair * kPair;
+    constexpr int kPer = (kPair * kPair + kPairThreads - 1) / kPairThreads;
+    double xv[kPer], lv[kPer], rv[kPer];
 #pragma unroll
-        for (int j = 0; j < 16; j++) {
-            const int e = tid + 256 * j, x = e >> 6, z = e & 63;
-            X[x * kLs + z] = xv[j];
-            L[x * kLs + z] = lv[j];
-            R[x * kLs + z] = rv[j];
+    for (int j = 0; j < kPer; j++) {
+        const int e = min(tid + kPairThreads * j, kPair * kPair - 1), x = e >> 6, z = e & 63;
+        xv[j] = from[(int64_t)pair_row(I1, J1, x) * np + pair_row(I2, J2, z)];
+        lv[j] = r1 ? q1[e] : 0.0;
+        rv[j] = r2 ? q2[e] : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; j++) {
+        const int e = tid + kPairThreads * j, x = e >> 6, z = e & 63;
+        if (e >= kPair * kPair) continue;
+        L.X[x * kLs + z] = xv[j];
+        L.R[x * kLs + z] = rv[j];
+    }
+    __syncthreads();
+    const int row0 = 16 * (w >> 1), col0 = 32 * (w & 1);  // eight waves of 16 x 32
+    auto put = [&](const dm_f64x4 (&y)[2]) {
+        __syncthreads();
+        if (w < 8)
+#pragma unroll
+            for (int bj = 0; bj < 2; bj++)
+#pragma unroll
+                for (int v = 0; v < 4; v++) L.X[(row0 + 4 * v + h) * kLs + col0 + 16 * bj + c] = y[bj][v];
+    };
+    dm_f64x4 y[2];
+    if (r2) {
+        if (w < 8)
+            for (int bj = 0; bj < 2; bj++) y[bj] = mm16<false>(L.X, kLs, row0, L.R, kLs, col0 + 16 * bj, lane);
+        put(y);
+        __syncthreads();
+    }
+    if (r1) {
+#pragma unroll
+        for (int j = 0; j < kPer; j++) {
+            const int e = tid + kPairThreads * j;
+            if (e < kPair * kPair) L.R[(e >> 6) * kLs + (e & 63)] = lv[j];
         }
         __syncthreads();
-        if (r2) {
-            mm64<false>(X, R, y, wr, wc, h, c);
-            __syncthreads();
-            acc_to_lds(X, y, wr, wc, h, c);
-            __syncthreads();
-        }
-        if (r1) {
-            mm64<true>(L, X, y, wr, wc, h, c);
-            __syncthreads();
-            acc_to_lds(X, y, wr, wc, h, c);
-            __syncthreads();
-        }
-        // the block and its mirror, both written along rows
-        for (int e = tid; e < kPair * kPair; e += 256) {
-            const int x = e >> 6, z = e & 63;
-            a[(int64_t)pair_row(I1, J1, x) * np + pair_row(I2, J2, z)] = X[x * kLs + z];
-            a[(int64_t)pair_row(I2, J2, x) * np + pair_row(I1, J1, z)] = X[z * kLs + x];
-        }
-        return;
+        if (w < 8)
+            for (int bj = 0; bj < 2; bj++) y[bj] = mm16<true>(L.R, kLs, row0, L.X, kLs, col0 + 16 * bj, lane);
+        put(y);
+        __syncthreads();
     }
-    // kItemV: rows it.a * 64 .. +64 of V, columns of pair it.b
-    const int P = it.b;
-    if (!rf[P]) return;
+    // the block and its mirror, both written along rows
+    for (int e = tid; e < kPair * kPair; e += kPairThreads) {
+        const int x = e >> 6, z = e & 63;
+        to[(int64_t)pair_row(I1, J1, x) * np + pair_row(I2, J2, z)] = L.X[x * kLs + z];
+        to[(int64_t)pair_row(I2, J2, x) * np + pair_row(I1, J1, z)] = L.X[z * kLs + x];
+    }
+}
+
+// V_{R,P} <- V_{R,P} Q_P of the last round for one 64-row tile R.
+__device__ inline void dm_apply_v(const DmSector& s, int tile, int P, const DmClock& ck, DmApplyLds& L,
+                                  const DmBuffers& g) {
+    const int old = (ck.a & 1) ^ 1;
+    if (!g.flags[old * g.f_round + s.flag_off + P]) return;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 4, c = lane & 15;
     int I, J;
-    circle_pair(s.nb, round, P, I, J);
-    double* v = Vw + s.a_off;
-    const double* qm = Qw + s.q_off + (int64_t)P * kPair * kPair;
-    const int64_t r0 = (int64_t)it.a * kPair;
-    double xv[16], rv[16];
+    circle_pair(s.nb, ck.t_prev, P, I, J);
+    double* v = g.V + s.a_off;
+    const double* qm = g.Q + old * g.q_round + s.q_off + (int64_t)P * kPair * kPair;
+    const int64_t r0 = (int64_t)tile * kPair, np = s.npad;
+    constexpr int kPer = (kPair * kPair + kPairThreads - 1) / kPairThreads;
+    double xv[kPer], rv[kPer];
 #pragma unroll
-    for (int j = 0; j < 16; j++) {
-        const int e = tid + 256 * j, x = e >> 6, z = e & 63;
+    for (int j = 0; j < kPer; j++) {
+        const int e = min(tid + kPairThreads * j, kPair * kPair - 1), x = e >> 6, z = e & 63;
         xv[j] = v[(r0 + x) * np + pair_row(I, J, z)];
         rv[j] = qm[e];
     }
 #pragma unroll
-    for (int j = 0; j < 16; j++) {
-        const int e = tid + 256 * j, x = e >> 6, z = e & 63;
-        X[x * kLs + z] = xv[j];
-        R[x * kLs + z] = rv[j];
+    for (int j = 0; j < kPer; j++) {
+        const int e = tid + kPairThreads * j, x = e >> 6, z = e & 63;
+        if (e >= kPair * kPair) continue;
+        L.X[x * kLs + z] = xv[j];
+        L.R[x * kLs + z] = rv[j];
     }
     __syncthreads();
-    mm64<false>(X, R, y, wr, wc, h, c);
+    if (w >= 8) return;
+    const int row0 = 16 * (w >> 1), col0 = 32 * (w & 1);
 #pragma unroll
-    for (int bi = 0; bi < 2; bi++)
+    for (int bj = 0; bj < 2; bj++) {
+        const dm_f64x4 y = mm16<false>(L.X, kLs, row0, L.R, kLs, col0 + 16 * bj, lane);
+        const int64_t col = pair_row(I, J, col0 + 16 * bj + c);
 #pragma unroll
-        for (int bj = 0; bj < 2; bj++) {
-            const int64_t col = pair_row(I, J, 32 * wc + 16 * bj + c);
-            const int64_t row = r0 + 32 * wr + 16 * bi + h;
-            v[row * np + col] = y[bi][bj].x;
-            v[(row + 4) * np + col] = y[bi][bj].y;
-            v[(row + 8) * np + col] = y[bi][bj].z;
-            v[(row + 12) * np + col] = y[bi][bj].w;
-        }
+        for (int e = 0; e < 4; e++) v[(r0 + row0 + 4 * e + h) * np + col] = y[e];
+    }
 }
 
-__global__ __launch_bounds__(256) void dm_count_kernel(const DmState* __restrict__ st, int n_sec,
-                                                       int* __restrict__ out) {
+// One round of every sector: its pairs first (they decide the launch's time),
+// then the last round's rotations on matrix and eigenvectors.
+__global__ __launch_bounds__(kPairThreads) void dm_round_kernel(const DmSector* __restrict__ secs,
+                                                                const DmItem* __restrict__ items, DmBuffers g,
+                                                                int round, int max_rounds) {
+    __shared__ __attribute__((aligned(16))) char lds[std::max(sizeof(DmPairLds), sizeof(DmApplyLds))];
+    const DmItem it = items[blockIdx.x];
+    const DmSector s = secs[it.sec];
+    const DmClock ck = dm_clock(s.nb, round, max_rounds);
+    if (!ck.active) return;
+    if (it.kind == kItemPair) {
+        dm_pair(s, it.sec, it.a, ck, *reinterpret_cast<DmPairLds*>(lds), g);
+        return;
+    }
+    if (ck.a == 0 || g.st[it.sec].quiet[(ck.a & 1) ^ 1] >= s.nb - 1) return;
+    DmApplyLds& L = *reinterpret_cast<DmApplyLds*>(lds);
+    if (it.kind == kItemA) dm_apply_a(s, it.a, it.b, ck, L, g);
+    else dm_apply_v(s, it.a, it.b, ck, L, g);
+}
+
+// Sectors that still rotate after launch `round` (the last of a sweep).
+__global__ __launch_bounds__(256) void dm_count_kernel(const DmSector* __restrict__ secs,
+                                                       const DmState* __restrict__ st,
+                                                       const int* __restrict__ flags, int f_round, int n_sec,
+                                                       int sweep, int* __restrict__ out) {
     __shared__ int red[256];
     int c = 0;
-    for (int k = threadIdx.x; k < n_sec; k += 256) c += st[k].converged ? 0 : 1;
+    for (int k = threadIdx.x; k < n_sec; k += 256) {
+        const int nb = secs[k].nb, par = ((sweep + 1) * (nb - 1) - 1) & 1;
+        const int* f = flags + par * f_round + secs[k].flag_off;
+        int quiet = st[k].quiet[par], any = 0;
+        for (int x = 0; x < nb / 2; x++) any |= f[x];
+        if (quiet < nb - 1) quiet = any ? 0 : quiet + 1;
+        c += quiet < nb - 1;
+    }
     red[threadIdx.x] = c;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
@@ -519,7 +812,7 @@ __device__ inline bool dm_before(double ka, int ia, double kb, int ib) {
 }
 
 __global__ __launch_bounds__(256) void dm_sort_kernel(const DmSector* __restrict__ secs,
-                                                      const double* __restrict__ A, const double* __restrict__ Vw,
+                                                      const double* __restrict__ diag, const double* __restrict__ Vw,
                                                       double* __restrict__ wall) {
     const DmSector s = secs[blockIdx.x];
     __shared__ double key[kSortMax];
@@ -528,7 +821,7 @@ __global__ __launch_bounds__(256) void dm_sort_kernel(const DmSector* __restrict
     int p2 = 1;
     while (p2 < s.n) p2 <<= 1;
     for (int i = tid; i < p2; i += 256) {
-        key[i] = i < s.n ? A[s.a_off + (int64_t)i * s.npad + i] + 0.0 : -INFINITY;
+        key[i] = i < s.n ? diag[s.d_off + i] + 0.0 : -INFINITY;
         idx[i] = i;
     }
     __syncthreads();
@@ -668,15 +961,19 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct DmLayout {
     std::vector<DmSector> secs;
-    std::vector<DmItem> rho_items, pair_items, upd_items;
-    size_t off_secs, off_state, off_rho, off_pair, off_upd, off_flags, off_count, off_above, off_equal, off_part;
-    size_t off_A, off_V, off_Q, off_W, total;
-    int max_rounds;  // rounds per sweep: max over sectors of nb - 1
+    std::vector<DmItem> rho_items, items;
+    size_t off_secs, off_state, off_rho, off_items, off_flags, off_count, off_above, off_equal, off_part;
+    size_t off_A, off_V, off_S, off_Q, off_D, off_W, total;
+    int64_t a_round, q_round;  // doubles of one copy of the matrices, of one round's submatrices
+    int f_round;               // flags of one round
+    int n_pair, n_apply_v;     // items: the pairs, then V updates, then A updates
+    int max_rounds;            // rounds per sweep: max over sectors of nb - 1
 };
 
 DmLayout dm_layout(const rot_dm_sector* in, int n_sec) {
     DmLayout L;
-    int64_t a_off = 0, q_off = 0, w_off = 0;
+    std::vector<DmItem> v_items, a_items;
+    int64_t a_off = 0, q_off = 0, w_off = 0, d_off = 0;
     int flag_off = 0;
     L.max_rounds = 1;
     for (int k = 0; k < n_sec; k++) {
@@ -693,23 +990,31 @@ DmLayout dm_layout(const rot_dm_sector* in, int n_sec) {
         s.a_off = a_off;
         s.q_off = q_off;
         s.w_off = w_off;
+        s.d_off = d_off;
         s.flag_off = flag_off;
         const int h = s.nb / 2, tiles = s.npad / kPair;
         a_off += (int64_t)s.npad * s.npad;
         q_off += (int64_t)h * kPair * kPair;
         w_off += s.n;
+        d_off += s.npad;
         flag_off += h;
         L.max_rounds = std::max(L.max_rounds, s.nb - 1);
         for (int j = 0; j < tiles; j++)
             for (int i = 0; i <= j; i++) L.rho_items.push_back({k, i, j, 0});
-        for (int p = 0; p < h; p++) L.pair_items.push_back({k, p, 0, 0});
+        for (int p = 0; p < h; p++) L.items.push_back({k, p, 0, kItemPair});
         for (int p2 = 0; p2 < h; p2++)
-            for (int p1 = 0; p1 < p2; p1++) L.upd_items.push_back({k, p1, p2, kItemA});
+            for (int p1 = 0; p1 <= p2; p1++) a_items.push_back({k, p1, p2, kItemA});
         for (int rt = 0; rt < tiles; rt++)
-            for (int p = 0; p < h; p++) L.upd_items.push_back({k, rt, p, kItemV});
-        L.upd_items.push_back({k, 0, 0, kItemBook});
+            for (int p = 0; p < h; p++) v_items.push_back({k, rt, p, kItemV});
         L.secs.push_back(s);
     }
+    L.n_pair = (int)L.items.size();
+    L.n_apply_v = (int)v_items.size();
+    L.items.insert(L.items.end(), v_items.begin(), v_items.end());
+    L.items.insert(L.items.end(), a_items.begin(), a_items.end());
+    L.a_round = a_off;
+    L.q_round = q_off;
+    L.f_round = flag_off;
     size_t o = 0;
     auto take = [&](size_t bytes) {
         const size_t at = o;
@@ -718,18 +1023,19 @@ DmLayout dm_layout(const rot_dm_sector* in, int n_sec) {
     };
     L.off_secs = take(sizeof(DmSector) * n_sec);
     L.off_rho = take(sizeof(DmItem) * L.rho_items.size());
-    L.off_pair = take(sizeof(DmItem) * L.pair_items.size());
-    L.off_upd = take(sizeof(DmItem) * L.upd_items.size());
+    L.off_items = take(sizeof(DmItem) * L.items.size());
     L.off_state = take(sizeof(DmState) * n_sec);
-    L.off_flags = take(sizeof(int) * (size_t)std::max(flag_off, 1));
+    L.off_flags = take(sizeof(int) * 2 * (size_t)flag_off);
     L.off_count = take(sizeof(int));
     L.off_above = take(sizeof(int) * n_sec);
     L.off_equal = take(sizeof(int) * n_sec);
     L.off_part = take(sizeof(double) * n_sec);
-    L.off_A = take(sizeof(double) * (size_t)a_off);
+    L.off_A = take(sizeof(double) * 2 * (size_t)a_off);
     L.off_V = take(sizeof(double) * (size_t)a_off);
-    L.off_Q = take(sizeof(double) * (size_t)q_off);
-    L.off_W = take(sizeof(double) * (size_t)std::max<int64_t>(w_off, 1));
+    L.off_S = take(sizeof(double) * 2 * (size_t)q_off);
+    L.off_Q = take(sizeof(double) * 2 * (size_t)q_off);
+    L.off_D = take(sizeof(double) * (size_t)d_off);
+    L.off_W = take(sizeof(double) * (size_t)w_off);
     L.total = o;
     return L;
 }
@@ -749,49 +1055,51 @@ hipError_t density_basis(const rot_dm_sector* sectors, int n_sec, int64_t m_keep
     std::vector<char> head(L.off_state, 0);
     std::memcpy(head.data() + L.off_secs, L.secs.data(), sizeof(DmSector) * n_sec);
     std::memcpy(head.data() + L.off_rho, L.rho_items.data(), sizeof(DmItem) * L.rho_items.size());
-    std::memcpy(head.data() + L.off_pair, L.pair_items.data(), sizeof(DmItem) * L.pair_items.size());
-    std::memcpy(head.data() + L.off_upd, L.upd_items.data(), sizeof(DmItem) * L.upd_items.size());
+    std::memcpy(head.data() + L.off_items, L.items.data(), sizeof(DmItem) * L.items.size());
     hipError_t e = hipMemcpyAsync(ws, head.data(), head.size(), hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return e;
     const DmSector* secs = reinterpret_cast<const DmSector*>(ws + L.off_secs);
     const DmItem* rho_items = reinterpret_cast<const DmItem*>(ws + L.off_rho);
-    const DmItem* pair_items = reinterpret_cast<const DmItem*>(ws + L.off_pair);
-    const DmItem* upd_items = reinterpret_cast<const DmItem*>(ws + L.off_upd);
-    DmState* st = reinterpret_cast<DmState*>(ws + L.off_state);
-    int* flags = reinterpret_cast<int*>(ws + L.off_flags);
+    const DmItem* items = reinterpret_cast<const DmItem*>(ws + L.off_items);
     int* count = reinterpret_cast<int*>(ws + L.off_count);
-    double* A = reinterpret_cast<double*>(ws + L.off_A);
-    double* Vw = reinterpret_cast<double*>(ws + L.off_V);
-    double* Qw = reinterpret_cast<double*>(ws + L.off_Q);
     double* W = reinterpret_cast<double*>(ws + L.off_W);
+    DmBuffers g{};
+    g.A = reinterpret_cast<double*>(ws + L.off_A);
+    g.V = reinterpret_cast<double*>(ws + L.off_V);
+    g.S = reinterpret_cast<double*>(ws + L.off_S);
+    g.Q = reinterpret_cast<double*>(ws + L.off_Q);
+    g.diag = reinterpret_cast<double*>(ws + L.off_D);
+    g.st = reinterpret_cast<DmState*>(ws + L.off_state);
+    g.flags = reinterpret_cast<int*>(ws + L.off_flags);
+    g.a_round = L.a_round;
+    g.q_round = L.q_round;
+    g.f_round = L.f_round;
 
     e = prof_timed("dm_rho", stream, [&] {
         hipLaunchKernelGGL(dm_rho_kernel, dim3((unsigned)L.rho_items.size()), dim3(256), 0, stream, secs,
-                           rho_items, A, Vw);
+                           rho_items, g.A, g.V);
         hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
-        hipLaunchKernelGGL(dm_prep_kernel, dim3(n_sec), dim3(256), 0, stream, secs, (const double*)A, st);
+        hipLaunchKernelGGL(dm_prep_kernel, dim3(n_sec), dim3(256), 0, stream, secs, (const double*)g.A, g.st);
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;
     *converged = false;
     int round = 0;
+    auto launch = [&](int first, int n) {
+        return prof_timed("dm_jacobi_round", stream, [&] {
+            hipLaunchKernelGGL(dm_round_kernel, dim3((unsigned)n), dim3(kPairThreads), 0, stream, secs, items + first, g,
+                               round, L.max_rounds);
+            return hipGetLastError();
+        });
+    };
     for (int sweep = 0; sweep < kMaxSweeps && !*converged; sweep++) {
         for (int r = 0; r < L.max_rounds; r++, round++) {
-            e = prof_timed("dm_jacobi_pairs", stream, [&] {
-                hipLaunchKernelGGL(dm_pair_kernel, dim3((unsigned)L.pair_items.size()), dim3(kPairThreads), 0, stream, secs,
-                                   pair_items, A, Qw, (const DmState*)st, flags, round);
-                return hipGetLastError();
-            });
-            if (e != hipSuccess) return e;
-            e = prof_timed("dm_jacobi_update", stream, [&] {
-                hipLaunchKernelGGL(dm_update_kernel, dim3((unsigned)L.upd_items.size()), dim3(256), 0, stream, secs,
-                                   upd_items, A, Vw, (const double*)Qw, st, (const int*)flags, round);
-                return hipGetLastError();
-            });
+            e = launch(0, (int)L.items.size());
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(dm_count_kernel, dim3(1), dim3(256), 0, stream, (const DmState*)st, n_sec, count);
+        hipLaunchKernelGGL(dm_count_kernel, dim3(1), dim3(256), 0, stream, secs, (const DmState*)g.st,
+                           (const int*)g.flags, L.f_round, n_sec, sweep, count);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         int host_count = -1;
@@ -800,11 +1108,16 @@ hipError_t density_basis(const rot_dm_sector* sectors, int n_sec, int64_t m_keep
         if (e != hipSuccess) return e;
         *converged = host_count == 0;
     }
+    if (!*converged) {
+        // the last round's rotations are still due on the eigenvectors
+        e = launch(L.n_pair, L.n_apply_v);
+        if (e != hipSuccess) return e;
+    }
     int64_t total = 0;
     for (int k = 0; k < n_sec; k++) total += sectors[k].n;
     return prof_timed("dm_sort_select", stream, [&] {
-        hipLaunchKernelGGL(dm_sort_kernel, dim3(n_sec), dim3(256), 0, stream, secs, (const double*)A,
-                           (const double*)Vw, W);
+        hipLaunchKernelGGL(dm_sort_kernel, dim3(n_sec), dim3(256), 0, stream, secs, (const double*)g.diag,
+                           (const double*)g.V, W);
         hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
         hipLaunchKernelGGL(dm_select_kernel, dim3(1), dim3(kSelThreads), 0, stream, secs, n_sec, (const double*)W, m_keep,
