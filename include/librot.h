@@ -300,8 +300,12 @@ ROT_API rot_status rot_expect_cross(const double* psi, int32_t m, int32_t d, int
  * Plans: repeated rotation of a fixed set of groups with different sizes (a
  * sweep step rotates the stored operators of many blocks; Sec. 3.2 counts
  * l(l+3)/2 of them per block).  rot_plan_create buckets the groups into size
- * classes (ceil log2 of m*d and of mp), packs their operators into chunks
- * whose stage-1 intermediates fit `workspace`, builds per-chunk work-lists for
+ * classes (ceil log2 of m*d and of mp).  Operators of 64 states and more run
+ * on FP16 pairs as in rot_batch, in chunks over all classes of at least 4
+ * GFLOP whose split operands fit `workspace`; one with an infinity, a NaN or
+ * rows of very different magnitude is left to the FP32 kernels at each
+ * execution.  The other operators are packed into chunks whose stage-1
+ * intermediates fit `workspace`: for them it builds per-chunk work-lists for
  * a grouped persistent kernel, picks per class the tile shape and the
  * schedule (static contiguous runs, like the paper's uniform-matrix
  * distribution, or an atomic tile queue, like its pool of tasks) from the
@@ -325,6 +329,13 @@ ROT_API rot_status rot_expect_cross(const double* psi, int32_t m, int32_t d, int
  * returns its full length (-1 for a null plan).
  */
 typedef struct rot_plan_s* rot_plan;
+/*
+ * Workspace with which a plan reaches its full speed: operators of all groups
+ * whose pairs (see rot_batch) fit the workspace together share launches.  With
+ * less, more chunks; at least rot_workspace_size's one operator is needed.
+ * At most 4 GiB unless one operator needs more.
+ */
+ROT_API size_t rot_plan_workspace_preferred(const rot_problem* groups, int32_t n_groups, rot_precision prec);
 #define ROT_PLAN_NO_GRAPH 1u
 #define ROT_PLAN_NO_TUNE 2u
 #define ROT_PLAN_RETUNE 4u

@@ -27,7 +27,7 @@ __all__ = [
     "ROT_FP64", "ROT_FP32", "ROT_SPLIT_BF16", "ROT_ASSUME_SYMMETRIC_O", "RotError",
     "RotProblem", "problem", "RotSector", "RotBlockedProblem", "lib", "library_path",
     "rot_batch", "rot_batch_fp32", "rot_batch_noalloc", "rot_backward", "rot_batch_blocked", "rot_pair_loss", "rot_check_isometry",
-    "rot_split_bf16", "rot_workspace_size", "rot_workspace_preferred", "rot_blocked_workspace_size",
+    "rot_split_bf16", "rot_workspace_size", "rot_workspace_preferred", "rot_plan_workspace_preferred", "rot_blocked_workspace_size",
     "rotate", "rotate_backward", "pair_loss", "check_isometry", "split_bf16",
     "RotateFn", "PairLossFn", "precision_code", "profile_enable", "profile_read",
     "blocked_problem", "rotate_blocked", "Plan", "ROT_PLAN_NO_GRAPH", "ROT_PLAN_NO_TUNE", "ROT_PLAN_RETUNE",
@@ -138,6 +138,8 @@ def lib() -> ctypes.CDLL:
         L.rot_workspace_size.restype = sz
         L.rot_workspace_preferred.argtypes = [ctypes.POINTER(RotProblem), i32, ctypes.c_int]
         L.rot_workspace_preferred.restype = sz
+        L.rot_plan_workspace_preferred.argtypes = [ctypes.POINTER(RotProblem), i32, ctypes.c_int]
+        L.rot_plan_workspace_preferred.restype = sz
         L.rot_backward.argtypes = [ctypes.POINTER(RotProblem), i32, ctypes.POINTER(vp), ctypes.POINTER(i64),
                                    ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.c_uint32, ctypes.c_int,
                                    vp, sz, vp]
@@ -254,6 +256,11 @@ def rot_workspace_size(groups, prec: int, ops_per_chunk: int = 0, for_backward: 
 def rot_workspace_preferred(groups, prec: int) -> int:
     arr = (RotProblem * len(groups))(*groups)
     return lib().rot_workspace_preferred(arr, len(groups), prec)
+
+
+def rot_plan_workspace_preferred(groups, prec: int) -> int:
+    arr = (RotProblem * max(1, len(groups)))(*groups)
+    return lib().rot_plan_workspace_preferred(arr, len(groups), prec)
 
 
 def rot_batch(groups, prec: int, workspace: int, workspace_bytes: int, stream: int, flags: int = 0) -> None:
@@ -777,7 +784,7 @@ class Plan:
             probs.append(_problem(U, O, out, d))
         self._probs = (RotProblem * len(probs))(*probs)
         if workspace_bytes is None:
-            workspace_bytes = rot_workspace_size(probs, ROT_FP32)  # everything in one chunk per class
+            workspace_bytes = rot_plan_workspace_preferred(probs, ROT_FP32)
         dev = self._groups[0][0].device if self._groups else torch.device("cuda")
         self.workspace = _workspace(workspace_bytes, dev)
         flags = (0 if graph else ROT_PLAN_NO_GRAPH) | (0 if tune else ROT_PLAN_NO_TUNE) | (

@@ -26,6 +26,8 @@
 #include <algorithm>
 #include <cmath>
 #include <functional>
+#include <queue>
+#include <vector>
 
 #include "buffer_rsrc.h"
 #include "lds_slice.h"
@@ -340,11 +342,37 @@ __global__ __launch_bounds__(512, 1) void gemm_flat_kernel(FlatDesc g) {
     else flat_tile<1, EPI_T, D4>(g, lds, m0, nt, part);
 }
 
+// One tile of a list of products (a plan's): rows m0 .. of 64 bi rows, column
+// tile nt.
+struct FlatTile {
+    int piece, m0, nt, bi;
+};
+
+// Tiles of many products in one launch, longest first (flat_list): the last
+// round of one product's tiles is filled by the next one's.
+template <bool EPI_T, bool D4>
+__global__ __launch_bounds__(512, 1) void gemm_flat_list_kernel(const FlatDesc* tab, const FlatTile* list) {
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[kFlatLds];
+    const FlatTile t = list[blockIdx.x];
+    const FlatDesc g = tab[t.piece];
+    switch (t.bi) {
+        case 4: flat_tile<4, EPI_T, D4>(g, lds, t.m0, t.nt, 0); break;
+        case 3: flat_tile<3, EPI_T, D4>(g, lds, t.m0, t.nt, 0); break;
+        case 2: flat_tile<2, EPI_T, D4>(g, lds, t.m0, t.nt, 0); break;
+        default: flat_tile<1, EPI_T, D4>(g, lds, t.m0, t.nt, 0); break;
+    }
+}
+
 constexpr int kF16MaxSite = 8;          // a split block holds 16 j of all site states
 constexpr int kF16RowSpread = 12;       // log2 of the accepted spread of row maxima
 constexpr int kPrepRows = 256;          // rows of U per partial column maximum
 constexpr int kPrepORows = 32;          // rows of O per partial maximum
 constexpr uint32_t kInfBits = 0x7f800000u;
+
+// A workgroup of the passes over a list of groups.
+struct PairBlock {
+    int piece, blk;
+};
 
 // Launch-time sizes and pointers of the scale pass.
 struct F16Scale {
@@ -362,6 +390,7 @@ struct F16Scale {
     int m32, mp32;     // rows of O_b's and T_b's layouts
     int* eo;           // [nb]
     int* skip;         // [nb]
+    int* any;          // plans: raised when an operator is skipped
     uint16_t *u1h, *u1l, *u2h, *u2l;
     uint16_t *oh, *ol;
     int64_t o_bs;
@@ -385,10 +414,9 @@ __device__ inline int scale_exp(uint32_t bits) {
 
 // Partial maxima of |U| per column and of |O| per operator.  Bound by the one
 // read of O and U.
-__global__ __launch_bounds__(256) void f16_scale_kernel(F16Scale g) {
+__device__ inline void f16_scale_block(const F16Scale& g, int blk) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     __shared__ uint32_t red[4][64];
-    int blk = blockIdx.x;
     if (blk < g.u_blocks) {
         const int cb = div_up(g.mp, 64);
         const int c = (blk % cb) * 64 + lane, r0 = (blk / cb) * kPrepRows;
@@ -455,6 +483,17 @@ __global__ __launch_bounds__(256) void f16_scale_kernel(F16Scale g) {
     }
 }
 
+__global__ __launch_bounds__(256) void f16_scale_kernel(F16Scale g) { f16_scale_block(g, blockIdx.x); }
+
+// The same over a list of groups (a plan's); the first workgroup clears the
+// flag that the split pass raises for a skipped operator.
+__global__ __launch_bounds__(256) void f16_scale_list_kernel(const F16Scale* tab, const PairBlock* list, int* any) {
+    const PairBlock b = list[blockIdx.x];
+    const F16Scale g = tab[b.piece];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *any = 0;
+    f16_scale_block(g, b.blk);
+}
+
 // U, O and T's K padding into the slab layout:
 //   U1 (d*mp rows, K = m):   element (beta*d + s, j) = U[j*d+s][beta] 2^eu[beta]
 //   U2 (mp rows, K = m*d):   element (alpha, r)      = U[r][alpha] 2^eu[alpha]
@@ -464,13 +503,12 @@ __global__ __launch_bounds__(256) void f16_scale_kernel(F16Scale g) {
 // chunk after chunk.  One on O takes a 64 x 64 block (split_o_kernel's
 // scheme).  The first block of each operator records eo[b] and skip[b].
 template <int DMAX>
-__global__ __launch_bounds__(256) void f16_split_kernel(F16Scale g) {
+__device__ inline void f16_split_block(const F16Scale& g, int blk) {
     static_assert(DMAX <= kF16MaxSite, "tile size");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     __shared__ __attribute__((aligned(16))) float tile[DMAX <= 4 ? 64 * 68 : 16 * DMAX * 65];
     __shared__ int s_e[64];
     __shared__ uint32_t s_mx[4][64];
-    int blk = blockIdx.x;
     const int u_chunks = div_up(g.rows, kPrepRows);
     auto store8 = [&](uint16_t* hi, uint16_t* lo, const float (&v)[8]) {
         const u32x2 p0 = split2_f16(v[0], v[1]), p1 = split2_f16(v[2], v[3]);
@@ -571,6 +609,7 @@ __global__ __launch_bounds__(256) void f16_split_kernel(F16Scale g) {
                 if (lane == 0) {
                     g.eo[b] = scale_exp(mx);
                     g.skip[b] = bad;
+                    if (bad && g.any) atomicOr(g.any, 1);
                 }
             }
         }
@@ -603,6 +642,23 @@ __global__ __launch_bounds__(256) void f16_split_kernel(F16Scale g) {
     *reinterpret_cast<u32x4*>(g.tl + off) = u32x4{0, 0, 0, 0};
 }
 
+template <int DMAX>
+__global__ __launch_bounds__(256) void f16_split_kernel(F16Scale g) {
+    f16_split_block<DMAX>(g, blockIdx.x);
+}
+
+template <int DMAX>
+__global__ __launch_bounds__(256) void f16_split_list_kernel(const F16Scale* tab, const PairBlock* list) {
+    const PairBlock b = list[blockIdx.x];
+    const F16Scale g = tab[b.piece];
+    f16_split_block<DMAX>(g, b.blk);
+}
+
+// us per slab of a tile of 64 bi rows with the chip full (1024-state batches
+// of 64 operators, stage 2), and around its K loop.
+constexpr double kFlatCost[5] = {0, 0.66, 0.74, 0.96, 1.22};
+constexpr double kFlatAround = 5;
+
 // Rows per tile (64 bi) and K parts of a flat product.
 struct FlatCfg {
     int bi, parts, part_slabs;
@@ -616,10 +672,8 @@ struct FlatCfg {
 // 128: 0.20; 256 states, 20 operators, stage 1: 25.0 against 18.3 us for
 // 128 rows).  At least min_parts.  out_bytes: bytes of the whole result, read and written once more per part.
 FlatCfg flat_cfg(int M, int blocks, int slabs, int min_parts, int max_parts, double out_bytes) {
-    // us per slab of a tile of 64 bi rows with the chip full (1024-state
-    // batches of 64 operators, stage 2), and around its K loop
-    static const double cost[5] = {0, 0.66, 0.74, 0.96, 1.22};
-    const double around = 5;
+    const double* cost = kFlatCost;
+    const double around = kFlatAround;
     FlatCfg best{4, 1, slabs};
     double best_t = 1e30;
     const int tn = div_up(blocks, 8);
@@ -715,43 +769,23 @@ size_t f16_o_bytes(const rot_problem& p, const F16Layout& L, int ops, int parts)
     return std::max(2 * al256(ops * L.o_op), parts > 1 ? al256((size_t)parts * ops * p.mp * p.mp * 4) : 0);
 }
 
-}  // namespace
-
-// Whether a group runs on FP16 pairs, `ops` operators at a time.  The passes
-// over U and O and the launches for skipped operators cost about 30 us, which
-// pays from about 4 GFLOP on (back to back, FP32 kernels against pairs: 80
-// operators of 128 states, 2.7 GFLOP, 52 / 52 us, 200 of them 97 / 78; 3 of
-// 403, 3.0 GFLOP, 59 / 59; 2 of 512, 4.3 GFLOP, 56 / 56, 4 of them 94 / 75).
-// Below 64 states the tiles are mostly padding; U's split takes d up to 8;
-// 32-bit offsets bound the operand arrays.
-bool f16_rotate_applies(const rot_problem& p, int ops) {
-    if (p.d > kF16MaxSite || p.m < 64 || p.mp < 64) return false;
-    const F16Layout L = f16_layout(p);
-    if (std::max(L.u1, L.u2) >= ((size_t)1 << 31) - 256 * kSlabK * 2) return false;
-    if (std::max(L.o_op, L.t_op) * ops >= (size_t)1 << 31) return false;
-    return 2.0 * p.m * p.d * p.mp * ((double)p.m + p.mp) * p.n_ops >= 4e9;
-}
-
-size_t f16_group_workspace(const rot_problem& p, int ops, bool symmetric) {
-    const F16Layout L = f16_layout(p);
-    const int parts = f16_stage2_cfg(p, ops, symmetric).parts;
-    return L.shared + f16_t_bytes(L, ops) + f16_o_bytes(p, L, ops, parts) + f16_scale_bytes(p, ops);
-}
-
-// Operators b0 .. b0 + nb - 1 of p (leading dimensions resolved) through FP16
-// pairs; `fallback` enqueues the FP32 kernels for the operators they skip
-// (T: FP32 intermediates, slot_elems apart; skip: the flags).
-hipError_t rotate_f16(const rot_problem& p, int b0, int nb, void* ws, bool symmetric,
-                      const std::function<hipError_t(void* T, int64_t slot_elems, const int* skip)>& fallback,
-                      hipStream_t stream) {
-    const F16Layout L = f16_layout(p);
+// Operators b0 .. b0 + nb - 1 of p (leading dimensions resolved) laid out in a
+// workspace: the scale and split passes' table (block counts left out), T's
+// place (pairs, and later the FP32 kernels' intermediates) and O's (pairs, and
+// later stage 2's partial results).
+struct F16Bound {
+    F16Scale g;
+    char *T, *O;
+};
+F16Bound f16_bind(const rot_problem& p, const F16Layout& L, int b0, int nb, int parts, void* ws) {
     char* base = static_cast<char*>(ws);
     auto take = [&](size_t bytes) {
         char* q = base;
         base += bytes;
         return q;
     };
-    F16Scale g{};
+    F16Bound r{};
+    F16Scale& g = r.g;
     g.U = static_cast<const float*>(p.U);
     g.rows = p.m * p.d;
     g.mp = p.mp;
@@ -771,35 +805,207 @@ hipError_t rotate_f16(const rot_problem& p, int b0, int nb, void* ws, bool symme
     g.upart = reinterpret_cast<uint32_t*>(take(L.part_u));
     g.ublk = reinterpret_cast<uint32_t*>(take(L.ublk));
     g.eu = reinterpret_cast<int*>(take(L.eu));
-    const FlatCfg c2 = f16_stage2_cfg(p, nb, symmetric);
-    char* T = take(f16_t_bytes(L, nb));
-    g.th = reinterpret_cast<uint16_t*>(T);
-    g.tl = reinterpret_cast<uint16_t*>(T + al256(nb * L.t_op));
+    r.T = take(f16_t_bytes(L, nb));
+    g.th = reinterpret_cast<uint16_t*>(r.T);
+    g.tl = reinterpret_cast<uint16_t*>(r.T + al256(nb * L.t_op));
     g.t_bs = (int64_t)(L.t_op / 2);
-    char* O = take(f16_o_bytes(p, L, nb, c2.parts));
-    g.oh = reinterpret_cast<uint16_t*>(O);
-    g.ol = reinterpret_cast<uint16_t*>(O + al256(nb * L.o_op));
+    r.O = take(f16_o_bytes(p, L, nb, parts));
+    g.oh = reinterpret_cast<uint16_t*>(r.O);
+    g.ol = reinterpret_cast<uint16_t*>(r.O + al256(nb * L.o_op));
     g.o_bs = (int64_t)(L.o_op / 2);
-    const int orb = div_up(p.m, kPrepORows), cb = div_up(p.mp, 64);
     g.opart = reinterpret_cast<uint32_t*>(base);
-    g.eo = reinterpret_cast<int*>(g.opart + 2 * (size_t)nb * orb);
+    g.eo = reinterpret_cast<int*>(g.opart + 2 * (size_t)nb * div_up(p.m, kPrepORows));
     g.skip = g.eo + nb;
-    g.n_ublk = cb * div_up(g.rows, kPrepRows);
+    g.n_ublk = div_up(p.mp, 64) * div_up(g.rows, kPrepRows);
+    return r;
+}
+
+// Workgroups of the two passes: on U (with_u), on O and on T's padding.
+void scale_blocks(F16Scale& g, bool with_u) {
+    g.u_blocks = with_u ? g.n_ublk : 0;
+    g.o_blocks = g.nb * div_up(g.m, kPrepORows);
+}
+int split_blocks(F16Scale& g, bool with_u) {
+    const int tb = div_up(g.m, 64);
+    g.u_blocks = with_u ? div_up(g.mp, 64) * div_up(g.m, kSlabK) : 0;
+    g.o_blocks = g.nb * tb * tb;
+    return g.u_blocks + g.o_blocks + (g.rows % kSlabK ? g.nb * div_up((int64_t)g.mp * 2, 256) : 0);
+}
+
+int f16_t_shift(int m) {
+    int log2m = 0;
+    while ((1 << log2m) < m) log2m++;
+    return 15 + log2m;
+}
+
+// Stage 1, transposed: C(beta*d + s, i) = sum_j U1(beta*d + s, j) O_b(i, j).
+FlatDesc f16_stage1(const F16Scale& g) {
+    FlatDesc a{};
+    a.M = g.d * g.mp;
+    a.N = g.m;
+    a.K = g.m;
+    a.batch = g.nb;
+    a.a_hi = g.u1h;
+    a.a_lo = g.u1l;
+    a.b_hi = g.oh;
+    a.b_lo = g.ol;
+    a.b_bs = g.o_bs;
+    a.n32 = g.m32;
+    a.t_hi = g.th;
+    a.t_lo = g.tl;
+    a.d = g.d;
+    a.t_rows = g.mp32;
+    a.t_bs = g.t_bs;
+    a.t_shift = f16_t_shift(g.m);
+    a.skip = g.skip;
+    a.parts = 1;
+    a.part_slabs = (int)n_slabs(a.K);
+    return a;
+}
+
+// Stage 2: out_b = U2 T_b^T.
+FlatDesc f16_stage2(const F16Scale& g, float* c, int64_t ldc, int64_t c_bs) {
+    FlatDesc b{};
+    b.M = g.mp;
+    b.N = g.mp;
+    b.K = g.rows;
+    b.batch = g.nb;
+    b.a_hi = g.u2h;
+    b.a_lo = g.u2l;
+    b.b_hi = g.th;
+    b.b_lo = g.tl;
+    b.b_bs = g.t_bs;
+    b.n32 = g.mp32;
+    b.c = c;
+    b.ldc = ldc;
+    b.c_bs = c_bs;
+    b.e0 = -f16_t_shift(g.m);
+    b.op_e = g.eo;
+    b.row_e = g.eu;
+    b.col_e = g.eu;
+    b.skip = g.skip;
+    b.parts = 1;
+    b.part_slabs = (int)n_slabs(b.K);
+    return b;
+}
+
+// Tiles of many products, longest first.  Each product takes the tallest
+// tiles that stay below a time limit; the limit is the one whose tiles,
+// handed out in this order to 256 CUs, end first by the estimate of flat_cfg
+// (a step's 17 groups of 128 to 1024 states: the 1024-state tiles of stage 2
+// alone last as long as the mean CU's share).
+struct FlatProduct {
+    int M, blocks, slabs;
+};
+std::vector<FlatTile> flat_list(const std::vector<FlatProduct>& prods) {
+    struct Run {
+        double t;
+        int piece, bi, m0, rows, cols;  // rows of tiles from m0 on, 64 bi each
+    };
+    auto tile_us = [](int bi, int slabs) { return kFlatCost[bi] * slabs + kFlatAround; };
+    std::vector<double> limits;
+    for (const FlatProduct& p : prods)
+        for (int bi = 1; bi <= 4; bi++) limits.push_back(tile_us(bi, p.slabs));
+    std::sort(limits.begin(), limits.end(), std::greater<double>());
+    limits.erase(std::unique(limits.begin(), limits.end()), limits.end());
+    if (limits.size() > 32) limits.resize(32);
+    auto runs_for = [&](double limit) {
+        std::vector<Run> runs;
+        for (int i = 0; i < (int)prods.size(); i++) {
+            const FlatProduct& p = prods[i];
+            int bi = 4;
+            while (bi > 1 && (tile_us(bi, p.slabs) > limit || 64 * (bi - 1) >= p.M)) bi--;
+            const int full = p.M / (64 * bi), rest = div_up(p.M - full * 64 * bi, 64), cols = div_up(p.blocks, 8);
+            if (full) runs.push_back({tile_us(bi, p.slabs), i, bi, 0, full, cols});
+            if (rest) runs.push_back({tile_us(rest, p.slabs), i, rest, full * 64 * bi, 1, cols});
+        }
+        std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.t > b.t; });
+        return runs;
+    };
+    std::vector<Run> best;
+    double best_t = 1e300;
+    for (double limit : limits) {
+        std::vector<Run> runs = runs_for(limit);
+        std::priority_queue<double, std::vector<double>, std::greater<double>> cu(std::greater<double>(),
+                                                                                  std::vector<double>(256, 0.0));
+        double end = 0, all = 0;  // latest CU, whole rounds given to every CU
+        for (const Run& r : runs) {
+            const int64_t n = (int64_t)r.rows * r.cols, rounds = std::max<int64_t>(0, n / 256 - 1);
+            all += rounds * r.t;
+            for (int64_t x = rounds * 256; x < n; x++) {
+                const double t = cu.top() + r.t;
+                cu.pop();
+                cu.push(t);
+                end = std::max(end, t);
+            }
+        }
+        end += all;
+        if (end < best_t * 0.97) {
+            best_t = end;
+            best = std::move(runs);
+        }
+    }
+    // Inside a run (alike tiles), M tiles fastest, in one stretch per XCD:
+    // workgroup w runs on XCD w % 8, and neighbours share panels in its L2.
+    std::vector<FlatTile> list;
+    for (const Run& r : best) {
+        const int n = r.rows * r.cols, w0 = (int)list.size();
+        list.resize(w0 + n);
+        int x = 0;
+        for (int xcd = 0; xcd < 8; xcd++)
+            for (int w = (xcd - w0 % 8 + 8) % 8; w < n; w += 8, x++)
+                list[w0 + w] = {r.piece, r.m0 + (x % r.rows) * 64 * r.bi, x / r.rows, r.bi};
+    }
+    return list;
+}
+
+}  // namespace
+
+// Whether `ops` operators of a group can run on FP16 pairs together: below 64
+// states the tiles are mostly padding; U's split takes d up to 8; 32-bit
+// offsets bound the operand arrays.
+bool f16_shape_supported(const rot_problem& p, int ops) {
+    if (p.d > kF16MaxSite || p.m < 64 || p.mp < 64) return false;
+    const F16Layout L = f16_layout(p);
+    if (std::max(L.u1, L.u2) >= ((size_t)1 << 31) - 256 * kSlabK * 2) return false;
+    return std::max(L.o_op, L.t_op) * ops < (size_t)1 << 31;
+}
+
+// Whether a group runs on FP16 pairs, `ops` operators at a time.  The passes
+// over U and O and the launches for skipped operators cost about 30 us, which
+// pays from about 4 GFLOP on (back to back, FP32 kernels against pairs: 80
+// operators of 128 states, 2.7 GFLOP, 52 / 52 us, 200 of them 97 / 78; 3 of
+// 403, 3.0 GFLOP, 59 / 59; 2 of 512, 4.3 GFLOP, 56 / 56, 4 of them 94 / 75).
+bool f16_rotate_applies(const rot_problem& p, int ops) {
+    return f16_shape_supported(p, ops) && 2.0 * p.m * p.d * p.mp * ((double)p.m + p.mp) * p.n_ops >= kPairsLeastFlop;
+}
+
+size_t f16_group_workspace(const rot_problem& p, int ops, bool symmetric) {
+    const F16Layout L = f16_layout(p);
+    const int parts = f16_stage2_cfg(p, ops, symmetric).parts;
+    return L.shared + f16_t_bytes(L, ops) + f16_o_bytes(p, L, ops, parts) + f16_scale_bytes(p, ops);
+}
+
+// Operators b0 .. b0 + nb - 1 of p (leading dimensions resolved) through FP16
+// pairs; `fallback` enqueues the FP32 kernels for the operators they skip
+// (T: FP32 intermediates, slot_elems apart; skip: the flags).
+hipError_t rotate_f16(const rot_problem& p, int b0, int nb, void* ws, bool symmetric,
+                      const std::function<hipError_t(void* T, int64_t slot_elems, const int* skip)>& fallback,
+                      hipStream_t stream) {
+    const F16Layout L = f16_layout(p);
+    const FlatCfg c2 = f16_stage2_cfg(p, nb, symmetric);
+    const F16Bound r = f16_bind(p, L, b0, nb, c2.parts, ws);
+    const F16Scale& g = r.g;
     hipError_t e = prof_timed("scale_f16x3", stream, [&] {
         F16Scale q = g;
-        q.u_blocks = b0 == 0 ? g.n_ublk : 0;
-        q.o_blocks = nb * orb;
+        scale_blocks(q, b0 == 0);
         hipLaunchKernelGGL(f16_scale_kernel, dim3((unsigned)(q.u_blocks + q.o_blocks)), dim3(256), 0, stream, q);
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;
     e = prof_timed("split_f16x3", stream, [&] {
         F16Scale q = g;
-        const int tb = div_up(p.m, 64);
-        q.u_blocks = b0 == 0 ? cb * div_up(p.m, kSlabK) : 0;
-        q.o_blocks = nb * tb * tb;
-        const int t_blocks = g.rows % kSlabK ? nb * div_up((int64_t)p.mp * 2, 256) : 0;
-        const dim3 grid((unsigned)(q.u_blocks + q.o_blocks + t_blocks));
+        const dim3 grid((unsigned)split_blocks(q, b0 == 0));
         if (p.d <= 4)
             hipLaunchKernelGGL(f16_split_kernel<4>, grid, dim3(256), 0, stream, q);
         else
@@ -807,64 +1013,176 @@ hipError_t rotate_f16(const rot_problem& p, int b0, int nb, void* ws, bool symme
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;
-    int log2m = 0;
-    while ((1 << log2m) < p.m) log2m++;
-    const int t_shift = 15 + log2m;
-    // stage 1, transposed: C(beta*d + s, i) = sum_j U1(beta*d + s, j) O_b(i, j)
-    FlatDesc a{};
-    a.M = p.d * p.mp;
-    a.N = p.m;
-    a.K = p.m;
-    a.batch = nb;
-    a.a_hi = g.u1h;
-    a.a_lo = g.u1l;
-    a.b_hi = g.oh;
-    a.b_lo = g.ol;
-    a.b_bs = g.o_bs;
-    a.n32 = L.m32;
-    a.t_hi = g.th;
-    a.t_lo = g.tl;
-    a.d = p.d;
-    a.t_rows = L.mp32;
-    a.t_bs = g.t_bs;
-    a.t_shift = t_shift;
-    a.skip = g.skip;
+    const FlatDesc a = f16_stage1(g);
     const FlatCfg c1 = flat_cfg(a.M, nb * (L.m32 / 32), (int)n_slabs(p.m), 1, 1, 0);
     e = prof_timed("stage1_f16x3", stream, [&] {
         return p.d == 4 ? launch_flat<true, true>(a, c1, stream) : launch_flat<true, false>(a, c1, stream);
     });
     if (e != hipSuccess) return e;
     float* out = static_cast<float*>(p.out) + (int64_t)b0 * p.stride_out;
-    {
-        FlatDesc b{};
-        b.M = p.mp;
-        b.N = p.mp;
-        b.K = g.rows;
-        b.batch = nb;
-        b.a_hi = g.u2h;
-        b.a_lo = g.u2l;
-        b.b_hi = g.th;
-        b.b_lo = g.tl;
-        b.b_bs = g.t_bs;
-        b.n32 = L.mp32;
-        b.c = c2.parts > 1 ? reinterpret_cast<float*>(O) : out;
-        b.ldc = c2.parts > 1 ? p.mp : p.ldout;
-        b.c_bs = c2.parts > 1 ? (int64_t)p.mp * p.mp : p.stride_out;
-        b.c_ps = (int64_t)nb * p.mp * p.mp;
-        b.e0 = -t_shift;
-        b.op_e = g.eo;
-        b.row_e = g.eu;
-        b.col_e = g.eu;
-        b.skip = g.skip;
-        b.upper = symmetric;
-        e = prof_timed(symmetric ? "stage2sym_f16x3" : "stage2_f16x3", stream, [&] { return launch_flat<false, true>(b, c2, stream); });
-        if (e == hipSuccess && c2.parts > 1)
-            e = prof_timed("stage2_sum", stream, [&] {
-                return sum_parts_2d(out, p.ldout, p.stride_out, O, p.mp, p.mp, nb, c2.parts, b.c_ps, false, stream);
-            });
-    }
+    FlatDesc b = c2.parts > 1 ? f16_stage2(g, reinterpret_cast<float*>(r.O), p.mp, (int64_t)p.mp * p.mp)
+                              : f16_stage2(g, out, p.ldout, p.stride_out);
+    b.c_ps = (int64_t)nb * p.mp * p.mp;
+    b.upper = symmetric;
+    e = prof_timed(symmetric ? "stage2sym_f16x3" : "stage2_f16x3", stream,
+                   [&] { return launch_flat<false, true>(b, c2, stream); });
+    if (e == hipSuccess && c2.parts > 1)
+        e = prof_timed("stage2_sum", stream, [&] {
+            return sum_parts_2d(out, p.ldout, p.stride_out, r.O, p.mp, p.mp, nb, c2.parts, b.c_ps, false, stream);
+        });
     if (e != hipSuccess) return e;
-    return fallback(T, (int64_t)(L.t32 / 4), g.skip);
+    return fallback(r.T, (int64_t)(L.t32 / 4), g.skip);
+}
+
+// ------------------------------------------------------------------ plans --
+// A chunk of a plan: operators of several groups ("pieces") through one
+// launch per pass and stage, from tables and lists in device memory.  Stage 2
+// is not split over K: the plan's FP32 kernels do not either, and the tiles
+// of all groups together fill the chip.  One execution, FP32 kernels before
+// -> pairs (rate of the products in brackets, TFLOP/s): 17 groups of 128 to
+// 1024 states, 8 operators each, 230 GFLOP, 2427 -> 748 us (95 -> 307); 8 of
+// 1000 states 1372 -> 397 us; 50 GFLOP in 7 groups of 101 to 900 states, 3
+// operators each, 826 -> 229 us.
+
+size_t pair_piece_workspace(const rot_problem& p, int ops) {
+    const F16Layout L = f16_layout(p);
+    return L.shared + f16_t_bytes(L, ops) + f16_o_bytes(p, L, ops, 1) + f16_scale_bytes(p, ops);
+}
+
+// The FP32 kernels' flag and intermediate of operator b0 + k of a piece.
+void pair_fallback(const rot_problem& p, const PairPiece& x, int k, const int** only, const float** T) {
+    const F16Layout L = f16_layout(p);
+    const F16Bound r = f16_bind(p, L, x.b0, x.nb, 1, x.ws);
+    *only = r.g.skip + k;
+    *T = reinterpret_cast<const float*>(r.T + k * L.t32);
+}
+
+namespace {
+struct PairTables {
+    F16Scale *scale, *split;
+    FlatDesc *s1, *s2;
+};
+PairTables pair_tables_at(void* mem, int n) {
+    PairTables t;
+    t.s1 = static_cast<FlatDesc*>(mem);
+    t.s2 = t.s1 + n;
+    t.scale = reinterpret_cast<F16Scale*>(t.s2 + n);
+    t.split = t.scale + n;
+    return t;
+}
+static_assert(sizeof(FlatDesc) % 8 == 0 && sizeof(F16Scale) % 8 == 0, "table alignment");
+}  // namespace
+
+size_t pair_table_bytes(int n) { return (size_t)n * 2 * (sizeof(F16Scale) + sizeof(FlatDesc)); }
+
+// The tables of a chunk's pieces (host memory of pair_table_bytes); `any` is
+// the chunk's device flag.
+void pair_fill_tables(const rot_problem* groups, const std::vector<PairPiece>& pieces, int* any, void* mem) {
+    const PairTables t = pair_tables_at(mem, (int)pieces.size());
+    for (size_t i = 0; i < pieces.size(); i++) {
+        const PairPiece& x = pieces[i];
+        const rot_problem& p = groups[x.group];
+        F16Scale g = f16_bind(p, f16_layout(p), x.b0, x.nb, 1, x.ws).g;
+        g.any = any;
+        t.s1[i] = f16_stage1(g);
+        t.s2[i] = f16_stage2(g, static_cast<float*>(p.out) + (int64_t)x.b0 * p.stride_out, p.ldout, p.stride_out);
+        scale_blocks(g, true);
+        t.scale[i] = g;
+        split_blocks(g, true);
+        t.split[i] = g;
+    }
+}
+
+// Lists of a chunk, and one device allocation for the tables (first), the
+// lists and the flag.
+hipError_t pair_build(const rot_problem* groups, const std::vector<PairPiece>& pieces, PairChunk* c) {
+    const int n = (int)pieces.size();
+    std::vector<char> host(pair_table_bytes(n));
+    pair_fill_tables(groups, pieces, nullptr, host.data());
+    const PairTables t = pair_tables_at(host.data(), n);
+    std::vector<PairBlock> scale, split;
+    std::vector<FlatProduct> p1, p2;
+    c->n_pieces = n;
+    c->d_max = 0;
+    c->all_d4 = true;
+    for (int i = 0; i < n; i++) {
+        const F16Scale& a = t.scale[i];
+        for (int x = 0; x < a.u_blocks + a.o_blocks; x++) scale.push_back({i, x});
+        F16Scale b = t.split[i];
+        const int nb = split_blocks(b, true);
+        for (int x = 0; x < nb; x++) split.push_back({i, x});
+        p1.push_back({t.s1[i].M, t.s1[i].batch * (t.s1[i].n32 / 32), (int)n_slabs(t.s1[i].K)});
+        p2.push_back({t.s2[i].M, t.s2[i].batch * (t.s2[i].n32 / 32), (int)n_slabs(t.s2[i].K)});
+        c->d_max = std::max(c->d_max, a.d);
+        c->all_d4 = c->all_d4 && a.d == 4;
+    }
+    const std::vector<FlatTile> l1 = flat_list(p1), l2 = flat_list(p2);
+    const size_t bytes[6] = {al256(host.size()), al256(scale.size() * sizeof(PairBlock)),
+                             al256(split.size() * sizeof(PairBlock)), al256(l1.size() * sizeof(FlatTile)),
+                             al256(l2.size() * sizeof(FlatTile)), 256};
+    size_t total = 0;
+    for (size_t x : bytes) total += x;
+    hipError_t e = hipMalloc(&c->mem, total);
+    if (e != hipSuccess) return e;
+    char* at = static_cast<char*>(c->mem);
+    c->scale = at += bytes[0];
+    c->split = at += bytes[1];
+    c->tiles1 = at += bytes[2];
+    c->tiles2 = at += bytes[3];
+    c->any = reinterpret_cast<int*>(at += bytes[4]);
+    c->n_scale = (int)scale.size();
+    c->n_split = (int)split.size();
+    c->n_tiles1 = (int)l1.size();
+    c->n_tiles2 = (int)l2.size();
+    pair_fill_tables(groups, pieces, c->any, host.data());
+    auto up = [&](void* dst, const void* src, size_t b) {
+        if (e == hipSuccess) e = hipMemcpy(dst, src, b, hipMemcpyHostToDevice);
+    };
+    up(c->mem, host.data(), host.size());
+    up(c->scale, scale.data(), scale.size() * sizeof(PairBlock));
+    up(c->split, split.data(), split.size() * sizeof(PairBlock));
+    up(c->tiles1, l1.data(), l1.size() * sizeof(FlatTile));
+    up(c->tiles2, l2.data(), l2.size() * sizeof(FlatTile));
+    return e;
+}
+
+// Enqueue a chunk's passes and stages; `timed` files each under the profiler.
+hipError_t pair_issue(const PairChunk& c, hipStream_t s, bool timed) {
+    const PairTables t = pair_tables_at(c.mem, c.n_pieces);
+    auto run = [&](const char* name, const std::function<void()>& launch) {
+        auto f = [&] {
+            launch();
+            return hipGetLastError();
+        };
+        return timed ? prof_timed(name, s, f) : f();
+    };
+    hipError_t e = run("scale_f16x3", [&] {
+        hipLaunchKernelGGL(f16_scale_list_kernel, dim3((unsigned)c.n_scale), dim3(256), 0, s, t.scale,
+                           static_cast<const PairBlock*>(c.scale), c.any);
+    });
+    if (e != hipSuccess) return e;
+    e = run("split_f16x3", [&] {
+        const dim3 grid((unsigned)c.n_split), block(256);
+        const PairBlock* list = static_cast<const PairBlock*>(c.split);
+        if (c.d_max <= 4)
+            hipLaunchKernelGGL(f16_split_list_kernel<4>, grid, block, 0, s, t.split, list);
+        else
+            hipLaunchKernelGGL(f16_split_list_kernel<kF16MaxSite>, grid, block, 0, s, t.split, list);
+    });
+    if (e != hipSuccess) return e;
+    e = run("plan_stage1_f16x3", [&] {
+        const dim3 grid((unsigned)c.n_tiles1), block(512);
+        const FlatTile* list = static_cast<const FlatTile*>(c.tiles1);
+        if (c.all_d4)
+            hipLaunchKernelGGL((gemm_flat_list_kernel<true, true>), grid, block, 0, s, t.s1, list);
+        else
+            hipLaunchKernelGGL((gemm_flat_list_kernel<true, false>), grid, block, 0, s, t.s1, list);
+    });
+    if (e != hipSuccess) return e;
+    return run("plan_stage2_f16x3", [&] {
+        hipLaunchKernelGGL((gemm_flat_list_kernel<false, true>), dim3((unsigned)c.n_tiles2), dim3(512), 0, s, t.s2,
+                           static_cast<const FlatTile*>(c.tiles2));
+    });
 }
 
 }  // namespace rot

@@ -47,6 +47,7 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(3))
     const int wm = wave / WN, wn = wave % WN;
     const int h = lane >> 5, c = lane & 31;
 
+    if (!DYN && L.any && !*L.any) return;
     // first tile
     int t;
     if (DYN) {
@@ -62,6 +63,10 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(3))
 
     while (t < L.n_tiles) {
         const GroupedTile tile = L.tiles[t];
+        if (!DYN && L.only && !*L.only[tile.prob]) {
+            t += gridDim.x;
+            continue;
+        }
         const GroupedProblem p = L.probs[tile.prob];
         // null base: the offset is an absolute address
         const float* Ab = L.a_base ? L.a_base + p.a_off : reinterpret_cast<const float*>(p.a_off);
@@ -332,6 +337,7 @@ int grouped_tile_edge(GroupedShape shape) {
 hipError_t grouped_gemm_f32(const GroupedLaunch& L, hipStream_t stream) {
     if (L.n_tiles <= 0) return hipSuccess;
     if (L.dynamic && !L.counter) return hipErrorInvalidValue;
+    if ((L.any || L.only) && (L.dynamic || L.shape == GroupedShape::k128d)) return hipErrorInvalidValue;
     const int grid = L.grid > 0 ? std::min(L.grid, L.n_tiles) : L.n_tiles;
     switch (L.shape) {
         case GroupedShape::k128: return launch_shape<128, 128, 2, 2>(L, grid, stream);

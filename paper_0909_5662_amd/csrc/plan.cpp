@@ -4,9 +4,12 @@
 //
 // rot_plan_create
 //   1. buckets groups into size classes (ceil log2 of m*d and of m'),
-//   2. packs each class's operators into chunks whose stage-1 intermediates
-//      fit the workspace (largest classes first),
-//   3. builds per-chunk work-lists (one problem per operator and stage, tiles
+//   2. packs operators, largest classes first, into chunks that run on FP16
+//      pairs (gemm_f16x3.hip) as far as the workspace holds their pairs: all
+//      sizes of a chunk share one launch per pass and stage, tiles longest
+//      first, followed by the FP32 kernels for operators that the pairs skip,
+//   3. packs each class's other operators into chunks whose stage-1
+//      intermediates fit the workspace and builds per-chunk work-lists (one problem per operator and stage, tiles
 //      in longest-processing-time order) in plan-owned device memory,
 //   4. picks, per class, the tile shape and the schedule (static contiguous
 //      runs, the uniform-matrix distribution of Sec. 3.2, or an atomic tile
@@ -43,6 +46,14 @@ struct rot_plan_s {
         double flops = 0;
         std::vector<std::pair<int, int>> src;  // (group, operator) of each problem
         std::vector<const float*> t;           // its stage-1 intermediate
+        const int* any = nullptr;              // FP32 kernels of a pair chunk: its flag
+        const int** only = nullptr;            // and the problems' flags (device)
+    };
+    // A chunk on FP16 pairs and the FP32 kernels for the operators it skips.
+    struct PairSet {
+        rot::PairChunk dev;
+        std::vector<rot::PairPiece> pieces;
+        Launch skipped[2];
     };
     struct Class {
         std::string key;
@@ -52,8 +63,10 @@ struct rot_plan_s {
         bool tuned = false;
         double flops = 0;
         int n_ops = 0;
+        int n_pairs = 0;  // of them on FP16 pairs
     };
     std::vector<Class> classes;
+    std::vector<PairSet> pairs;
     std::vector<Launch> launches;
     std::vector<std::vector<rot::GroupedProblem>> host_probs;  // per launch (tiles rebuilt on shape change)
     std::vector<rot_problem> groups;  // resolved shapes and the bound buffers
@@ -61,10 +74,10 @@ struct rot_plan_s {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     bool use_graph = true;
+    int n_cu = 256;
     // rot_plan_rebind: pinned staging of the problem tables and the event of
     // the last copy out of it
-    rot::GroupedProblem* staging = nullptr;
-    size_t staging_count = 0;
+    char* staging = nullptr;
     hipEvent_t staged = nullptr;
     std::string error;
 };
@@ -201,19 +214,80 @@ GroupedLaunch make_launch(const rot_plan_s::Launch& L, const rot_plan_s::Class& 
     g.shape = c.shape;
     g.grid = c.grid;
     g.counter = L.counter;
+    g.any = L.any;
+    g.only = L.only;
     return g;
+}
+
+// The FP32 launches behind a pair chunk: 128 x 128 tiles over all its sizes,
+// a few persistent workgroups that look at one flag and end.
+rot_plan_s::Class skipped_class(int n_cu) {
+    rot_plan_s::Class c;
+    c.shape = GroupedShape::k128;
+    c.dynamic = false;
+    c.grid = 2 * n_cu;
+    return c;
 }
 
 // Enqueue every launch of the plan; `timed` files each under the profiler
 // (never while capturing).
 hipError_t issue_all(rot_plan_s* P, hipStream_t s, bool timed) {
-    for (auto& L : P->launches) {
-        const GroupedLaunch g = make_launch(L, P->classes[L.cls]);
+    auto fp32 = [&](const rot_plan_s::Launch& L, const rot_plan_s::Class& c) {
+        const GroupedLaunch g = make_launch(L, c);
         const char* name = L.stage == 1 ? "plan_stage1_fp32" : "plan_stage2_fp32";
-        hipError_t e = timed ? prof_timed(name, s, [&] { return grouped_gemm_f32(g, s); }) : grouped_gemm_f32(g, s);
+        return timed ? prof_timed(name, s, [&] { return grouped_gemm_f32(g, s); }) : grouped_gemm_f32(g, s);
+    };
+    const rot_plan_s::Class sk = skipped_class(P->n_cu);
+    for (auto& c : P->pairs) {
+        hipError_t e = pair_issue(c.dev, s, timed);
+        for (int i = 0; i < 2 && e == hipSuccess; i++) e = fp32(c.skipped[i], sk);
+        if (e != hipSuccess) return e;
+    }
+    for (auto& L : P->launches) {
+        const hipError_t e = fp32(L, P->classes[L.cls]);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+// Frees a launch's device memory.
+void free_launch(rot_plan_s::Launch& L) {
+    (void)hipFree(L.probs);
+    (void)hipFree(L.tiles);
+    (void)hipFree(L.counter);
+}
+
+// Device tables of a pair chunk (pieces set) and of the FP32 launches behind it.
+hipError_t build_pair_set(const rot_plan_s* P, rot_plan_s::PairSet* c) {
+    hipError_t e = pair_build(P->groups.data(), c->pieces, &c->dev);
+    std::vector<const int*> only;
+    std::vector<GroupedProblem> probs[2];
+    for (const PairPiece& x : c->pieces)
+        for (int k = 0; k < x.nb; k++) {
+            const rot_problem& p = P->groups[x.group];
+            const int* flag;
+            const float* T;
+            pair_fallback(p, x, k, &flag, &T);
+            only.push_back(flag);
+            for (int i = 0; i < 2; i++) {
+                probs[i].push_back(stage_problem(p, x.b0 + k, T, i + 1));
+                c->skipped[i].src.emplace_back(x.group, x.b0 + k);
+                c->skipped[i].t.push_back(T);
+            }
+        }
+    for (int i = 0; i < 2 && e == hipSuccess; i++) {
+        rot_plan_s::Launch& L = c->skipped[i];
+        L.stage = i + 1;
+        L.any = c->dev.any;
+        const size_t bytes = sizeof(GroupedProblem) * probs[i].size(), fb = sizeof(int*) * only.size();
+        e = hipMalloc(&L.probs, bytes + fb);
+        if (e != hipSuccess) break;
+        L.only = reinterpret_cast<const int**>(L.probs + probs[i].size());
+        e = hipMemcpy(L.probs, probs[i].data(), bytes, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(L.only, only.data(), fb, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = upload_tiles(L, probs[i], GroupedShape::k128);
+    }
+    return e;
 }
 
 // Time the candidates for class `ci` on its first chunk (both stages).
@@ -292,10 +366,10 @@ void destroy(rot_plan_s* P) {
     if (!P) return;
     if (P->exec) (void)hipGraphExecDestroy(P->exec);
     if (P->graph) (void)hipGraphDestroy(P->graph);
-    for (auto& L : P->launches) {
-        (void)hipFree(L.probs);
-        (void)hipFree(L.tiles);
-        (void)hipFree(L.counter);
+    for (auto& L : P->launches) free_launch(L);
+    for (auto& c : P->pairs) {
+        (void)hipFree(c.dev.mem);
+        for (auto& L : c.skipped) free_launch(L);
     }
     if (P->staged) {
         (void)hipEventSynchronize(P->staged);
@@ -312,6 +386,28 @@ void destroy(rot_plan_s* P) {
 using namespace rot;
 
 extern "C" {
+
+size_t rot_plan_workspace_preferred(const rot_problem* groups, int32_t n_groups, rot_precision prec) {
+    const size_t least = rot_workspace_size(groups, n_groups, prec, 0, 0);
+    if (least == 0 || prec != ROT_FP32) return least;
+    size_t sum = 0, one = 0;
+    double flops = 0;
+    for (int gi = 0; gi < n_groups; gi++) {
+        rot_problem p = groups[gi];
+        if (p.ldu == 0) p.ldu = p.mp;
+        if (p.ldo == 0) p.ldo = p.m;
+        if (p.ldout == 0) p.ldout = p.mp;
+        int nb = p.n_ops;
+        while (nb > 0 && !f16_shape_supported(p, nb)) nb /= 2;
+        if (nb == 0) continue;
+        one = std::max(one, pair_piece_workspace(p, 1));
+        sum += (size_t)((p.n_ops + nb - 1) / nb) * ((pair_piece_workspace(p, nb) + 255) / 256 * 256);
+        flops += p.n_ops * (2.0 * p.m * p.m * p.d * p.mp + 2.0 * p.m * p.d * (double)p.mp * p.mp);
+    }
+    if (flops < kPairsLeastFlop) return least;
+    // chunks of 4 GiB last for milliseconds: nothing is gained beyond
+    return std::max({least, one, std::min(sum, (size_t)4 << 30)});
+}
 
 rot_status rot_plan_create(const rot_problem* groups, int32_t n_groups, rot_precision prec, void* workspace,
                            size_t workspace_bytes, uint32_t flags, void* stream, rot_plan* out) {
@@ -361,6 +457,7 @@ rot_status rot_plan_create(const rot_problem* groups, int32_t n_groups, rot_prec
         destroy(P);
         return perr(ROT_ERR_HIP, "plan setup: %s", hipGetErrorString(e));
     }
+    P->n_cu = n_cu;
     std::string arch = props.gcnArchName;
     arch = arch.substr(0, arch.find(':'));
 
@@ -392,9 +489,69 @@ rot_status rot_plan_create(const rot_problem* groups, int32_t n_groups, rot_prec
     std::stable_sort(order.begin(), order.end(),
                      [&](int a, int b) { return P->classes[a].flops > P->classes[b].flops; });
 
-    // 2-3. chunks and work-lists
+    // 2. chunks on FP16 pairs.  A chunk whose operators are worth less than
+    // kPairsLeastFlop goes to the FP32 kernels (at 4 GFLOP, FP32 kernels
+    // against pairs: 128 operators of 128 states 183 / 61 us, 10 of 300 98 /
+    // 76, 2 of 512 129 / 99: there the time is one tile's loop over K and the
+    // six launches), as does a group of which not one operator fits.
     char* ws = static_cast<char*>(workspace);
+    std::vector<std::vector<std::pair<int, int>>> rest(P->classes.size());  // (group, operator)
+    {
+        std::vector<PairPiece> pieces;
+        std::vector<int> piece_cls;
+        size_t used = 0;
+        double flops = 0;
+        auto flush = [&] {
+            if (pieces.empty()) return;
+            const bool keep = flops >= kPairsLeastFlop;
+            if (keep) {
+                P->pairs.emplace_back();
+                P->pairs.back().pieces = pieces;
+                e = build_pair_set(P, &P->pairs.back());
+            }
+            for (size_t i = 0; i < pieces.size(); i++) {
+                if (keep) P->classes[piece_cls[i]].n_pairs += pieces[i].nb;
+                else
+                    for (int k = 0; k < pieces[i].nb; k++) rest[piece_cls[i]].emplace_back(pieces[i].group, pieces[i].b0 + k);
+            }
+            pieces.clear();
+            piece_cls.clear();
+            used = 0;
+            flops = 0;
+        };
+        for (int ci : order)
+            for (int gi : members[ci]) {
+                const rot_problem& p = rg[gi];
+                int b = 0;
+                while (b < p.n_ops && e == hipSuccess) {
+                    // the most operators that fit
+                    int lo = 0, hi = p.n_ops - b;
+                    while (lo < hi) {
+                        const int mid = lo + (hi - lo + 1) / 2;
+                        if (f16_shape_supported(p, mid) && pair_piece_workspace(p, mid) <= workspace_bytes - used) lo = mid;
+                        else hi = mid - 1;
+                    }
+                    if (lo == 0) {
+                        if (!pieces.empty() && f16_shape_supported(p, 1) && pair_piece_workspace(p, 1) <= workspace_bytes) {
+                            flush();
+                            continue;
+                        }
+                        for (; b < p.n_ops; b++) rest[ci].emplace_back(gi, b);
+                        break;
+                    }
+                    pieces.push_back(PairPiece{gi, b, lo, ws + used});
+                    piece_cls.push_back(ci);
+                    used += std::min(workspace_bytes - used, (pair_piece_workspace(p, lo) + 255) / 256 * 256);
+                    flops += lo * (2.0 * p.m * p.m * p.d * p.mp + 2.0 * p.m * p.d * (double)p.mp * p.mp);
+                    b += lo;
+                }
+            }
+        if (e == hipSuccess) flush();
+    }
+
+    // 3. chunks and work-lists of the FP32 kernels
     for (int ci : order) {
+        if (e != hipSuccess) break;
         std::vector<GroupedProblem> s1, s2;
         std::vector<std::pair<int, int>> srcs;
         std::vector<const float*> ts;
@@ -426,25 +583,22 @@ rot_status rot_plan_create(const rot_problem* groups, int32_t n_groups, rot_prec
             chunk_flops = 0;
             return hipSuccess;
         };
-        for (int gi : members[ci]) {
+        for (const auto& [gi, b] : rest[ci]) {
             const rot_problem& p = rg[gi];
             // T_b takes U's row layout ((m*d) x ldu), so stage 1 reads U_r as
             // one matrix of row stride d*ldu over (d-1)*ldu + mp columns
             const size_t tb = ((size_t)p.m * p.d * p.ldu * 4 + 255) / 256 * 256;
-            for (int b = 0; b < p.n_ops; b++) {
-                if (used + tb > workspace_bytes) {
-                    e = flush();
-                    if (e != hipSuccess) break;
-                }
-                const float* T = reinterpret_cast<const float*>(ws + used);
-                s1.push_back(stage_problem(p, b, T, 1));
-                s2.push_back(stage_problem(p, b, T, 2));
-                srcs.emplace_back(gi, b);
-                ts.push_back(T);
-                used += tb;
-                chunk_flops += 2.0 * p.m * p.m * p.d * p.mp + 2.0 * p.m * p.d * (double)p.mp * p.mp;
+            if (used + tb > workspace_bytes) {
+                e = flush();
+                if (e != hipSuccess) break;
             }
-            if (e != hipSuccess) break;
+            const float* T = reinterpret_cast<const float*>(ws + used);
+            s1.push_back(stage_problem(p, b, T, 1));
+            s2.push_back(stage_problem(p, b, T, 2));
+            srcs.emplace_back(gi, b);
+            ts.push_back(T);
+            used += tb;
+            chunk_flops += 2.0 * p.m * p.m * p.d * p.mp + 2.0 * p.m * p.d * (double)p.mp * p.mp;
         }
         if (e == hipSuccess) e = flush();
         if (e != hipSuccess) break;
@@ -454,10 +608,11 @@ rot_status rot_plan_create(const rot_problem* groups, int32_t n_groups, rot_prec
         return perr(ROT_ERR_HIP, "plan work-lists: %s", hipGetErrorString(e));
     }
 
-    // 4. tile shape and schedule per class
+    // 4. tile shape and schedule per class (of those with FP32 operators)
     {
         for (int ci = 0; ci < (int)P->classes.size() && e == hipSuccess; ci++) {
             rot_plan_s::Class& c = P->classes[ci];
+            if (c.n_pairs == c.n_ops) continue;
             GroupedShape shape;
             bool dynamic;
             int grid;
@@ -479,6 +634,11 @@ rot_status rot_plan_create(const rot_problem* groups, int32_t n_groups, rot_prec
     }
     const int sched = forced_schedule();
     for (auto& c : P->classes) {
+        if (c.n_pairs == c.n_ops) {
+            c.dynamic = false;  // the hardware takes the tiles in the list's order
+            log_msg(2, "plan class %s: %d operators on FP16 pairs", c.key.c_str(), c.n_ops);
+            continue;
+        }
         if (sched >= 0) {
             c.dynamic = sched == 1;
             if (c.dynamic && c.grid <= 0) c.grid = 2 * n_cu;  // the queue needs persistent workgroups
@@ -536,13 +696,14 @@ rot_status rot_plan_rebind(rot_plan plan, const rot_problem* groups, int32_t n_g
         if (p.n_ops > 0 && (!p.U || !p.O || !p.out)) return perr(ROT_ERR_INVALID_ARG, "group %d: null buffer", gi);
     }
     size_t total = 0;
-    for (auto& L : plan->launches) total += L.src.size();
+    for (auto& c : plan->pairs)
+        total += pair_table_bytes((int)c.pieces.size()) + 2 * sizeof(GroupedProblem) * c.skipped[0].src.size();
+    for (auto& L : plan->launches) total += sizeof(GroupedProblem) * L.src.size();
     hipError_t e = hipSuccess;
     if (!plan->staging) {
-        e = hipHostMalloc(reinterpret_cast<void**>(&plan->staging), sizeof(GroupedProblem) * std::max<size_t>(total, 1));
+        e = hipHostMalloc(reinterpret_cast<void**>(&plan->staging), std::max<size_t>(total, 1));
         if (e == hipSuccess) e = hipEventCreateWithFlags(&plan->staged, hipEventDisableTiming);
         if (e != hipSuccess) return perr(ROT_ERR_HIP, "rot_plan_rebind setup: %s", hipGetErrorString(e));
-        plan->staging_count = total;
     }
     // the previous rebind's copies must have left the staging buffer
     e = hipEventSynchronize(plan->staged);
@@ -550,30 +711,45 @@ rot_status rot_plan_rebind(rot_plan plan, const rot_problem* groups, int32_t n_g
     hipStream_t s = static_cast<hipStream_t>(stream);
     // the new tables; a class tuned to the k128d shape needs every problem
     // whole (16-byte aligned U and O), checked before anything changes
-    size_t at = 0;
-    for (size_t li = 0; li < plan->launches.size(); li++) {
-        auto& L = plan->launches[li];
-        GroupedProblem* dst = plan->staging + at;
-        const bool need_whole = plan->classes[L.cls].shape == GroupedShape::k128d;
-        for (size_t k = 0; k < L.src.size(); k++) {
+    struct Copy {
+        void* dst;
+        const char* src;
+        size_t bytes;
+    };
+    std::vector<Copy> copies;
+    char* at = plan->staging;
+    auto problems = [&](const rot_plan_s::Launch& L) {
+        GroupedProblem* dst = reinterpret_cast<GroupedProblem*>(at);
+        for (size_t k = 0; k < L.src.size(); k++)
             dst[k] = stage_problem(rg[L.src[k].first], L.src[k].second, L.t[k], L.stage);
-            if (need_whole && !(dst[k].flags & kGroupedWhole))
+        copies.push_back({L.probs, at, sizeof(GroupedProblem) * L.src.size()});
+        at += sizeof(GroupedProblem) * L.src.size();
+        return dst;
+    };
+    for (auto& c : plan->pairs) {
+        const size_t bytes = pair_table_bytes((int)c.pieces.size());
+        pair_fill_tables(rg.data(), c.pieces, c.dev.any, at);
+        copies.push_back({c.dev.mem, at, bytes});
+        at += bytes;
+        for (auto& L : c.skipped) problems(L);
+    }
+    std::vector<const GroupedProblem*> fresh;
+    for (auto& L : plan->launches) {
+        const GroupedProblem* g = problems(L);
+        fresh.push_back(g);
+        if (plan->classes[L.cls].shape != GroupedShape::k128d) continue;
+        for (size_t k = 0; k < L.src.size(); k++)
+            if (!(g[k].flags & kGroupedWhole))
                 return perr(ROT_ERR_INVALID_ARG,
                             "rot_plan_rebind: group %d's U or O is not 16-byte aligned, which the plan's kernels for "
                             "its size class need (the plan was created with aligned buffers)",
                             L.src[k].first);
-        }
-        at += L.src.size();
     }
-    at = 0;
-    for (size_t li = 0; li < plan->launches.size() && e == hipSuccess; li++) {
-        auto& L = plan->launches[li];
-        GroupedProblem* dst = plan->staging + at;
-        plan->host_probs[li].assign(dst, dst + L.src.size());
-        // in stream order: replays enqueued before this call read the old tables
-        e = hipMemcpyAsync(L.probs, dst, sizeof(GroupedProblem) * L.src.size(), hipMemcpyHostToDevice, s);
-        at += L.src.size();
-    }
+    for (size_t li = 0; li < plan->launches.size(); li++)
+        plan->host_probs[li].assign(fresh[li], fresh[li] + plan->launches[li].src.size());
+    // in stream order: replays enqueued before this call read the old tables
+    for (const Copy& c : copies)
+        if (e == hipSuccess) e = hipMemcpyAsync(c.dst, c.src, c.bytes, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipEventRecord(plan->staged, s);
     if (e != hipSuccess) return perr(ROT_ERR_HIP, "rot_plan_rebind: %s", hipGetErrorString(e));
     plan->groups = rg;
@@ -592,12 +768,14 @@ rot_status rot_plan_execute(rot_plan plan, void* stream) {
 int32_t rot_plan_describe(rot_plan plan, char* buf, size_t len) {
     if (!plan) return -1;
     std::ostringstream os;
-    os << "{\"graph\": " << (plan->use_graph ? "true" : "false") << ", \"launches\": " << plan->launches.size()
+    os << "{\"graph\": " << (plan->use_graph ? "true" : "false")
+       << ", \"launches\": " << plan->launches.size() + 6 * plan->pairs.size()
        << ", \"classes\": [";
     for (size_t i = 0; i < plan->classes.size(); i++) {
         const auto& c = plan->classes[i];
-        os << (i ? ", " : "") << "{\"key\": \"" << c.key << "\", \"ops\": " << c.n_ops << ", \"gflop\": "
-           << c.flops / 1e9 << ", \"tile\": " << grouped_tile_edge(c.shape)
+        os << (i ? ", " : "") << "{\"key\": \"" << c.key << "\", \"ops\": " << c.n_ops << ", \"pairs\": " << c.n_pairs
+           << ", \"gflop\": " << c.flops / 1e9
+           << ", \"tile\": " << (c.n_pairs == c.n_ops ? 256 : grouped_tile_edge(c.shape))
            << ", \"lds_direct\": " << (c.shape == GroupedShape::k128d ? "true" : "false") << ", \"schedule\": \""
            << (c.dynamic ? "dynamic" : "static") << "\", \"grid\": " << c.grid << ", \"tuned_now\": "
            << (c.tuned ? "true" : "false") << "}";

@@ -77,9 +77,36 @@ struct GroupedLaunch {
     GroupedShape shape;
     int grid;                     // persistent workgroups (<= 0: one per tile)
     int* counter;                 // device int for the dynamic queue
+    // static schedule: run only if *any is set, and only the problems whose
+    // flag is (device; null: all)
+    const int* any;
+    const int* const* only;
 };
 int grouped_tile_edge(GroupedShape shape);
 hipError_t grouped_gemm_f32(const GroupedLaunch& L, hipStream_t stream);
+
+// FP32 rotations on FP16 pairs (gemm_f16x3.hip): the least work they pay for,
+// and the chunks of a plan that take them.
+constexpr double kPairsLeastFlop = 4e9;
+struct PairPiece {
+    int group, b0, nb;  // operators b0 .. b0 + nb - 1 of a group
+    char* ws;           // their part of the workspace (pair_piece_workspace bytes, 256-byte aligned)
+};
+struct PairChunk {
+    void* mem = nullptr;  // device: tables (first, pair_table_bytes), lists, flag
+    int n_pieces = 0, d_max = 0;
+    bool all_d4 = false;
+    void *scale = nullptr, *split = nullptr, *tiles1 = nullptr, *tiles2 = nullptr;
+    int n_scale = 0, n_split = 0, n_tiles1 = 0, n_tiles2 = 0;
+    int* any = nullptr;   // set when an operator is left to the FP32 kernels
+};
+bool f16_shape_supported(const rot_problem& p, int ops);
+size_t pair_piece_workspace(const rot_problem& p, int ops);
+size_t pair_table_bytes(int n_pieces);
+void pair_fill_tables(const rot_problem* groups, const std::vector<PairPiece>& pieces, int* any, void* mem);
+hipError_t pair_build(const rot_problem* groups, const std::vector<PairPiece>& pieces, PairChunk* c);
+hipError_t pair_issue(const PairChunk& c, hipStream_t s, bool timed);
+void pair_fallback(const rot_problem& p, const PairPiece& x, int k, const int** only, const float** T);
 
 // Records `msg` as the calling thread's last error (rot_last_error) and
 // returns `s`.
