@@ -254,6 +254,13 @@ typedef struct {
 
 ROT_API size_t rot_site_workspace_size(const rot_site_problem* groups, int32_t n_groups, rot_precision prec,
                                int32_t ops_per_chunk);
+/*
+ * Workspace with which FP32 groups of dense block operators reach their full
+ * speed: on FP16 pairs (see rot_batch), over the site states that S has
+ * non-zero columns for.  With less they take them in chunks, or the FP32
+ * kernels.
+ */
+ROT_API size_t rot_site_workspace_preferred(const rot_site_problem* groups, int32_t n_groups, rot_precision prec);
 ROT_API rot_status rot_batch_site(const rot_site_problem* groups, int32_t n_groups, rot_precision prec,
                           void* workspace, size_t workspace_bytes, void* stream);
 

@@ -32,7 +32,7 @@ __all__ = [
     "RotateFn", "PairLossFn", "precision_code", "profile_enable", "profile_read",
     "blocked_problem", "rotate_blocked", "Plan", "ROT_PLAN_NO_GRAPH", "ROT_PLAN_NO_TUNE", "ROT_PLAN_RETUNE",
     "RotSiteProblem", "ROT_BLOCK_IDENTITY", "ROT_BLOCK_DIAGONAL", "ROT_BLOCK_DENSE", "rot_batch_site",
-    "rot_site_workspace_size", "rotate_site", "expect_block", "expect_cross",
+    "rot_site_workspace_size", "rot_site_workspace_preferred", "rotate_site", "expect_block", "expect_cross",
     "RotDmSector", "rot_density_basis", "density_workspace_size", "density_basis",
     "RotSbTerm", "RotSbProblem", "SuperblockH",
 ]
@@ -146,6 +146,8 @@ def lib() -> ctypes.CDLL:
         L.rot_batch_site.argtypes = [ctypes.POINTER(RotSiteProblem), i32, ctypes.c_int, vp, sz, vp]
         L.rot_site_workspace_size.argtypes = [ctypes.POINTER(RotSiteProblem), i32, ctypes.c_int, i32]
         L.rot_site_workspace_size.restype = sz
+        L.rot_site_workspace_preferred.argtypes = [ctypes.POINTER(RotSiteProblem), i32, ctypes.c_int]
+        L.rot_site_workspace_preferred.restype = sz
         L.rot_expect_block_workspace_size.argtypes = [i32, i32, i64, i32]
         L.rot_expect_block_workspace_size.restype = sz
         L.rot_expect_block.argtypes = [vp, i32, i32, i64, vp, i32, i64, ctypes.c_int, vp, vp, sz, vp]
@@ -415,6 +417,11 @@ def rot_site_workspace_size(groups, prec: int, ops_per_chunk: int = 0) -> int:
     return lib().rot_site_workspace_size(arr, len(groups), prec, ops_per_chunk)
 
 
+def rot_site_workspace_preferred(groups, prec: int) -> int:
+    arr = (RotSiteProblem * len(groups))(*groups)
+    return lib().rot_site_workspace_preferred(arr, len(groups), prec)
+
+
 def rot_batch_site(groups, prec: int, workspace: int, workspace_bytes: int, stream: int) -> None:
     arr = (RotSiteProblem * len(groups))(*groups)
     _check(lib().rot_batch_site(arr, len(groups), prec, workspace, workspace_bytes, stream))
@@ -454,7 +461,7 @@ def rotate_site(U: torch.Tensor, X, S, precision="fp32", workspace: torch.Tensor
     p = RotSiteProblem(m, d, mp, n, kind, U.data_ptr(), S_host.ctypes.data_as(ctypes.POINTER(ctypes.c_double)),
                        xp, sx, out.data_ptr(), mp * mp)
     if workspace is None:
-        workspace = _workspace(rot_site_workspace_size([p], prec), U.device)
+        workspace = _workspace(rot_site_workspace_preferred([p], prec), U.device)
     rot_batch_site([p], prec, workspace.data_ptr(), workspace.numel(), _stream(stream))
     return out if kind == ROT_BLOCK_DENSE else out[0]
 

@@ -101,7 +101,8 @@ constexpr int kFlatLds = kFlatRing * 2 * kFlatArr;   // elements
 // into three register sets two slabs ahead.  A stage always holds 256 rows
 // (those past the tile are copied and not read), so every wave issues the
 // same number of loads and the waits stay immediate.
-template <int BI, bool EPI_T, bool D4>
+// DS: d of the transposed epilogue if it is 4 or 2, else 0.
+template <int BI, bool EPI_T, int DS>
 __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& g, uint16_t* lds, int m0, int nt,
                                                                 int part) {
     constexpr int BJ = 2, S = kFlatRing, ARR = kFlatArr, STAGE = 2 * ARR;
@@ -245,7 +246,36 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
 #pragma unroll
     for (int k = 0; k < BJ; k++) {
         const int col = cb[k] * 32 + c;
-        if (!live[k] || col >= g.N || g.skip[op[k]]) continue;
+        if (!live[k] || g.skip[op[k]]) continue;
+        if (EPI_T && DS == 2) {
+            // (33 operators of 500 states, kept 480, two states: single stores
+            // 120 us, exchanged 78 us for stage 1)
+            // rows row0 .. row0 + 3 are two beta of two states: lanes of two
+            // neighbouring columns exchange halves, so that each stores four
+            // k of one beta (a column past N holds zeros: k padding)
+            uint16_t* th = g.t_hi + op[k] * g.t_bs;
+            uint16_t* tl = g.t_lo + op[k] * g.t_bs;
+            const bool odd = c & 1, in = col < g.N, store = col - (odd ? 1 : 0) < g.N;
+#pragma unroll
+            for (int i = 0; i < BI; i++)
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    const int row0 = row0w + i * 32 + 8 * q + 4 * h;
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; e++) v[e] = in ? ldexpf(acc[i][k][4 * q + e], -g.t_shift) : 0.f;
+                    const u32x2 p0 = split2_f16(v[0], v[1]), p1 = split2_f16(v[2], v[3]);
+                    const uint32_t rh = __shfl_xor(odd ? p0[0] : p1[0], 1), rl = __shfl_xor(odd ? p0[1] : p1[1], 1);
+                    const int beta = (row0 >> 1) + (odd ? 1 : 0);
+                    if (store && beta * 2 < g.M) {
+                        const int64_t off = slab_off(beta, (int64_t)(col & ~1) * 2, g.t_rows);
+                        *reinterpret_cast<u32x2*>(th + off) = odd ? u32x2{rh, p1[0]} : u32x2{p0[0], rh};
+                        *reinterpret_cast<u32x2*>(tl + off) = odd ? u32x2{rl, p1[1]} : u32x2{p0[1], rl};
+                    }
+                }
+            continue;
+        }
+        if (col >= g.N) continue;
         if (EPI_T) {
             uint16_t* th = g.t_hi + op[k] * g.t_bs;
             uint16_t* tl = g.t_lo + op[k] * g.t_bs;
@@ -259,7 +289,7 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
                     for (int e = 0; e < 4; e++) v[e] = ldexpf(acc[i][k][4 * q + e], -g.t_shift);
                     const u32x2 p0 = split2_f16(v[0], v[1]), p1 = split2_f16(v[2], v[3]);
                     const u32x2 hv = {p0[0], p1[0]}, lv = {p0[1], p1[1]};
-                    if (D4) {
+                    if (DS == 4) {
                         if (row0 < g.M) {
                             const int64_t off = slab_off(row0 >> 2, (int64_t)col * 4, g.t_rows);
                             *reinterpret_cast<u32x2*>(th + off) = hv;
@@ -321,7 +351,7 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
     }
 }
 
-template <int BI, bool EPI_T, bool D4>
+template <int BI, bool EPI_T, int DS>
 __global__ __launch_bounds__(512, 1) void gemm_flat_kernel(FlatDesc g) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[kFlatLds];
     const int lin = xcd_linear_id();
@@ -336,10 +366,10 @@ __global__ __launch_bounds__(512, 1) void gemm_flat_kernel(FlatDesc g) {
     }
     // M tiles fastest: neighbouring workgroups share the B panel
     const int rest = min(BI, (g.M - m0 + 63) / 64);
-    if (rest == BI) flat_tile<BI, EPI_T, D4>(g, lds, m0, nt, part);
-    else if (BI > 3 && rest == 3) flat_tile<BI < 3 ? BI : 3, EPI_T, D4>(g, lds, m0, nt, part);
-    else if (BI > 2 && rest == 2) flat_tile<BI < 2 ? BI : 2, EPI_T, D4>(g, lds, m0, nt, part);
-    else flat_tile<1, EPI_T, D4>(g, lds, m0, nt, part);
+    if (rest == BI) flat_tile<BI, EPI_T, DS>(g, lds, m0, nt, part);
+    else if (BI > 3 && rest == 3) flat_tile<BI < 3 ? BI : 3, EPI_T, DS>(g, lds, m0, nt, part);
+    else if (BI > 2 && rest == 2) flat_tile<BI < 2 ? BI : 2, EPI_T, DS>(g, lds, m0, nt, part);
+    else flat_tile<1, EPI_T, DS>(g, lds, m0, nt, part);
 }
 
 // One tile of a list of products (a plan's): rows m0 .. of 64 bi rows, column
@@ -350,16 +380,16 @@ struct FlatTile {
 
 // Tiles of many products in one launch, longest first (flat_list): the last
 // round of one product's tiles is filled by the next one's.
-template <bool EPI_T, bool D4>
+template <bool EPI_T, int DS>
 __global__ __launch_bounds__(512, 1) void gemm_flat_list_kernel(const FlatDesc* tab, const FlatTile* list) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[kFlatLds];
     const FlatTile t = list[blockIdx.x];
     const FlatDesc g = tab[t.piece];
     switch (t.bi) {
-        case 4: flat_tile<4, EPI_T, D4>(g, lds, t.m0, t.nt, 0); break;
-        case 3: flat_tile<3, EPI_T, D4>(g, lds, t.m0, t.nt, 0); break;
-        case 2: flat_tile<2, EPI_T, D4>(g, lds, t.m0, t.nt, 0); break;
-        default: flat_tile<1, EPI_T, D4>(g, lds, t.m0, t.nt, 0); break;
+        case 4: flat_tile<4, EPI_T, DS>(g, lds, t.m0, t.nt, 0); break;
+        case 3: flat_tile<3, EPI_T, DS>(g, lds, t.m0, t.nt, 0); break;
+        case 2: flat_tile<2, EPI_T, DS>(g, lds, t.m0, t.nt, 0); break;
+        default: flat_tile<1, EPI_T, DS>(g, lds, t.m0, t.nt, 0); break;
     }
 }
 
@@ -398,6 +428,15 @@ struct F16Scale {
     int64_t t_bs;
     int u_blocks;      // workgroups that work on U (0: done by an earlier chunk)
     int o_blocks;      // and on O
+    // Blocked with a site (f16_site): U2 is made of Up (packed) instead of U,
+    // and both of the d site states listed in sel (4 bits each) out of d_all;
+    // the passes' first half of workgroups on U takes U, the second Up, with
+    // partial maxima and exponents of its own
+    const float* Up;
+    int d_all;
+    uint32_t sel;
+    uint32_t* upart2;
+    int* eu2;
 };
 
 inline __host__ __device__ int div_up(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
@@ -412,25 +451,39 @@ __device__ inline int scale_exp(uint32_t bits) {
     return 14 - ilogbf(__uint_as_float(bits));
 }
 
-// Partial maxima of |U| per column and of |O| per operator.  Bound by the one
-// read of O and U.
+// Partial maxima of |U| per column (of the listed site states) and of |O| per
+// operator, and of all of U per workgroup.  Bound by the one read of O and U.
+template <bool SITE>
 __device__ inline void f16_scale_block(const F16Scale& g, int blk) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    __shared__ uint32_t red[4][64];
+    __shared__ uint32_t red[4][64], red2[SITE ? 4 : 1][64];
     if (blk < g.u_blocks) {
-        const int cb = div_up(g.mp, 64);
-        const int c = (blk % cb) * 64 + lane, r0 = (blk / cb) * kPrepRows;
-        const int r1 = min(r0 + kPrepRows, g.rows);
-        uint32_t mx = 0;
+        const int cb = div_up(g.mp, 64), half = g.u_blocks / 2;
+        const bool up = SITE && blk >= half;
+        const int x = up ? blk - half : blk;
+        const float* U = up ? g.Up : g.U;
+        const int64_t ldu = up ? g.mp : g.ldu;
+        const int c = (x % cb) * 64 + lane, r0 = (x / cb) * kPrepRows;
+        const int r1 = min(r0 + kPrepRows, SITE ? g.m * g.d_all : g.rows);
+        uint32_t mx = 0, all = 0, listed = 0;
+        if (SITE)
+            for (int k = 0; k < g.d; k++) listed |= 1u << ((g.sel >> (4 * k)) & 15);
         if (c < g.mp) {
 #pragma unroll 16
-            for (int r = r0 + wave; r < r1; r += 4) mx = umax32(mx, abs_bits(g.U[(int64_t)r * g.ldu + c]));
+            for (int r = r0 + wave; r < r1; r += 4) {
+                const uint32_t v = abs_bits(U[(int64_t)r * ldu + c]);
+                mx = umax32(mx, !SITE || (listed >> (r % g.d_all)) & 1 ? v : 0u);
+                if (SITE) all = umax32(all, v);
+            }
         }
         red[wave][lane] = mx;
+        if (SITE) red2[wave][lane] = all;
         __syncthreads();
         if (wave == 0) {
             mx = umax32(umax32(red[0][lane], red[1][lane]), umax32(red[2][lane], red[3][lane]));
-            if (c < g.mp) g.upart[(int64_t)(blk / cb) * g.mp + c] = mx;
+            if (c < g.mp) (up ? g.upart2 : g.upart)[(int64_t)(x / cb) * g.mp + c] = mx;
+            if (SITE)
+                mx = umax32(umax32(red2[0][lane], red2[1][lane]), umax32(red2[2][lane], red2[3][lane]));
 #pragma unroll
             for (int s = 32; s; s >>= 1) mx = umax32(mx, __shfl_xor(mx, s));
             if (lane == 0) g.ublk[blk] = mx;
@@ -483,7 +536,10 @@ __device__ inline void f16_scale_block(const F16Scale& g, int blk) {
     }
 }
 
-__global__ __launch_bounds__(256) void f16_scale_kernel(F16Scale g) { f16_scale_block(g, blockIdx.x); }
+template <bool SITE>
+__global__ __launch_bounds__(256) void f16_scale_kernel(F16Scale g) {
+    f16_scale_block<SITE>(g, blockIdx.x);
+}
 
 // The same over a list of groups (a plan's); the first workgroup clears the
 // flag that the split pass raises for a skipped operator.
@@ -491,7 +547,7 @@ __global__ __launch_bounds__(256) void f16_scale_list_kernel(const F16Scale* tab
     const PairBlock b = list[blockIdx.x];
     const F16Scale g = tab[b.piece];
     if (blockIdx.x == 0 && threadIdx.x == 0) *any = 0;
-    f16_scale_block(g, b.blk);
+    f16_scale_block<false>(g, b.blk);
 }
 
 // U, O and T's K padding into the slab layout:
@@ -502,14 +558,16 @@ __global__ __launch_bounds__(256) void f16_scale_list_kernel(const F16Scale* tab
 // of U1's rows and d slabs of U2's, both written in whole 16-byte chunks,
 // chunk after chunk.  One on O takes a 64 x 64 block (split_o_kernel's
 // scheme).  The first block of each operator records eo[b] and skip[b].
-template <int DMAX>
+// With a site, the first half of the workgroups on U writes U1 from U and the
+// second U2 from Up.
+template <int DMAX, bool SITE>
 __device__ inline void f16_split_block(const F16Scale& g, int blk) {
     static_assert(DMAX <= kF16MaxSite, "tile size");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     __shared__ __attribute__((aligned(16))) float tile[DMAX <= 4 ? 64 * 68 : 16 * DMAX * 65];
     __shared__ int s_e[64];
     __shared__ uint32_t s_mx[4][64];
-    const int u_chunks = div_up(g.rows, kPrepRows);
+    const int u_chunks = div_up(SITE ? g.m * g.d_all : g.rows, kPrepRows);
     auto store8 = [&](uint16_t* hi, uint16_t* lo, const float (&v)[8]) {
         const u32x2 p0 = split2_f16(v[0], v[1]), p1 = split2_f16(v[2], v[3]);
         const u32x2 p2 = split2_f16(v[4], v[5]), p3 = split2_f16(v[6], v[7]);
@@ -517,6 +575,11 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
         *reinterpret_cast<u32x4*>(lo) = u32x4{p0[1], p1[1], p2[1], p3[1]};
     };
     if (blk < g.u_blocks) {
+        const bool up = SITE && blk >= g.u_blocks / 2;
+        if (up) blk -= g.u_blocks / 2;
+        const float* U = up ? g.Up : g.U;
+        const int64_t ldu = up ? g.mp : g.ldu;
+        const uint32_t* upart = up ? g.upart2 : g.upart;
         const int cb = div_up(g.mp, 64), d = g.d;
         const int a0 = (blk % cb) * 64, q = blk / cb, r0 = q * 16 * d, nr = 16 * d;
         const int a = a0 + lane;
@@ -524,11 +587,17 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
         const int ac = min(a, g.mp - 1);
         uint32_t mx = 0;
 #pragma unroll 4
-        for (int x = wave; x < u_chunks; x += 4) mx = umax32(mx, g.upart[(int64_t)x * g.mp + ac]);
+        for (int x = wave; x < u_chunks; x += 4) mx = umax32(mx, upart[(int64_t)x * g.mp + ac]);
         float v[DMAX * 4];
 #pragma unroll
-        for (int k = 0; k < DMAX * 4; k++)
-            v[k] = g.U[(int64_t)min(r0 + wave + 4 * k, g.rows - 1) * g.ldu + ac];
+        for (int k = 0; k < DMAX * 4; k++) {
+            int64_t row = min(r0 + wave + 4 * k, g.rows - 1);
+            if (SITE) {
+                const int j = (int)row / d, t = (int)row - j * d;
+                row = (int64_t)j * g.d_all + ((g.sel >> (4 * t)) & 15);
+            }
+            v[k] = U[row * ldu + ac];
+        }
         s_mx[wave][lane] = mx;
 #pragma unroll
         for (int k = 0; k < DMAX * 4; k++)
@@ -537,13 +606,13 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
         if (wave == 0) {
             mx = umax32(umax32(s_mx[0][lane], s_mx[1][lane]), umax32(s_mx[2][lane], s_mx[3][lane]));
             s_e[lane] = scale_exp(mx);
-            if (q == 0 && a < g.mp) g.eu[a] = scale_exp(mx);
+            if (q == 0 && a < g.mp) (up ? g.eu2 : g.eu)[a] = scale_exp(mx);
         }
         __syncthreads();
         const int na = min(64, g.mp - a0);
         // U1: rows a*d + s of slab q, chunk (row, slot)
         const int64_t rows1 = (int64_t)d * g.mp;
-        for (int x = tid; x < na * d * 2; x += 256) {
+        for (int x = up ? na * d * 2 : tid; x < na * d * 2; x += 256) {
             const int row = x >> 1, slot = x & 1, al = row / d, s = row - al * d;
             const int64_t gr = (int64_t)a0 * d + row;
             const int half = slot ^ (int)((gr >> 3) & 1), e = s_e[al];
@@ -555,7 +624,7 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
         }
         // U2: rows a of slabs q*d .. q*d + d - 1
         const int64_t ns2 = n_slabs(g.rows);
-        for (int x = tid; x < na * d * 2; x += 256) {
+        for (int x = SITE && !up ? na * d * 2 : tid; x < na * d * 2; x += 256) {
             const int sl = x / (na * 2), y = x - sl * (na * 2), al = y >> 1, slot = y & 1;
             const int64_t sq = (int64_t)q * d + sl;
             if (sq >= ns2) break;
@@ -642,16 +711,16 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
     *reinterpret_cast<u32x4*>(g.tl + off) = u32x4{0, 0, 0, 0};
 }
 
-template <int DMAX>
+template <int DMAX, bool SITE>
 __global__ __launch_bounds__(256) void f16_split_kernel(F16Scale g) {
-    f16_split_block<DMAX>(g, blockIdx.x);
+    f16_split_block<DMAX, SITE>(g, blockIdx.x);
 }
 
 template <int DMAX>
 __global__ __launch_bounds__(256) void f16_split_list_kernel(const F16Scale* tab, const PairBlock* list) {
     const PairBlock b = list[blockIdx.x];
     const F16Scale g = tab[b.piece];
-    f16_split_block<DMAX>(g, b.blk);
+    f16_split_block<DMAX, false>(g, b.blk);
 }
 
 // us per slab of a tile of 64 bi rows with the chip full (1024-state batches
@@ -699,7 +768,7 @@ FlatCfg flat_cfg(int M, int blocks, int slabs, int min_parts, int max_parts, dou
 
 constexpr int kF16MaxParts = 8;
 
-template <bool EPI_T, bool D4>
+template <bool EPI_T, int DS>
 hipError_t launch_flat(FlatDesc g, const FlatCfg& c, hipStream_t s) {
     g.bi = c.bi;
     g.parts = c.parts;
@@ -710,10 +779,10 @@ hipError_t launch_flat(FlatDesc g, const FlatCfg& c, hipStream_t s) {
     if (tiles > 0x7fffffff || n_slabs(g.K) - (int64_t)(g.parts - 1) * g.part_slabs < 3) return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles), block(512);
     switch (c.bi) {
-        case 1: hipLaunchKernelGGL((gemm_flat_kernel<1, EPI_T, D4>), grid, block, 0, s, g); break;
-        case 2: hipLaunchKernelGGL((gemm_flat_kernel<2, EPI_T, D4>), grid, block, 0, s, g); break;
-        case 3: hipLaunchKernelGGL((gemm_flat_kernel<3, EPI_T, D4>), grid, block, 0, s, g); break;
-        default: hipLaunchKernelGGL((gemm_flat_kernel<4, EPI_T, D4>), grid, block, 0, s, g); break;
+        case 1: hipLaunchKernelGGL((gemm_flat_kernel<1, EPI_T, DS>), grid, block, 0, s, g); break;
+        case 2: hipLaunchKernelGGL((gemm_flat_kernel<2, EPI_T, DS>), grid, block, 0, s, g); break;
+        case 3: hipLaunchKernelGGL((gemm_flat_kernel<3, EPI_T, DS>), grid, block, 0, s, g); break;
+        default: hipLaunchKernelGGL((gemm_flat_kernel<4, EPI_T, DS>), grid, block, 0, s, g); break;
     }
     return hipGetLastError();
 }
@@ -727,21 +796,21 @@ struct F16Layout {
     size_t shared;
 };
 
-F16Layout f16_layout(const rot_problem& p) {
+F16Layout f16_layout(const rot_problem& p, int d_all = 0) {
     F16Layout L;
-    const int64_t md = (int64_t)p.m * p.d;
+    const int64_t md = (int64_t)p.m * p.d, all = d_all ? (int64_t)p.m * d_all : md;
     L.m32 = div_up(p.m, 32) * 32;
     L.mp32 = div_up(p.mp, 32) * 32;
     L.u1 = al256((size_t)(n_slabs(p.m) * p.d * p.mp * kSlabK * 2));
     L.u2 = al256((size_t)(n_slabs(md) * p.mp * kSlabK * 2));
     L.o_op = (size_t)(n_slabs(p.m) * L.m32 * kSlabK * 2);
     L.t_op = (size_t)(n_slabs(md) * L.mp32 * kSlabK * 2);
-    L.t32 = al256((size_t)md * p.ldu * 4);
-    const size_t chunks = div_up(md, kPrepRows);
+    L.t32 = al256((size_t)all * p.ldu * 4);
+    const size_t chunks = div_up(all, kPrepRows);
     L.part_u = al256(chunks * p.mp * 4);
-    L.ublk = al256(chunks * div_up(p.mp, 64) * 4);
+    L.ublk = al256((d_all ? 2 : 1) * chunks * div_up(p.mp, 64) * 4);
     L.eu = al256((size_t)(p.mp + 256) * 4);  // read in groups of four up to a tile's last row
-    L.shared = 2 * L.u1 + 2 * L.u2 + L.part_u + L.ublk + L.eu;
+    L.shared = 2 * L.u1 + 2 * L.u2 + (d_all ? 2 : 1) * (L.part_u + L.eu) + L.ublk;
     return L;
 }
 
@@ -827,7 +896,7 @@ void scale_blocks(F16Scale& g, bool with_u) {
 }
 int split_blocks(F16Scale& g, bool with_u) {
     const int tb = div_up(g.m, 64);
-    g.u_blocks = with_u ? div_up(g.mp, 64) * div_up(g.m, kSlabK) : 0;
+    g.u_blocks = with_u ? (g.Up ? 2 : 1) * div_up(g.mp, 64) * div_up(g.m, kSlabK) : 0;
     g.o_blocks = g.nb * tb * tb;
     return g.u_blocks + g.o_blocks + (g.rows % kSlabK ? g.nb * div_up((int64_t)g.mp * 2, 256) : 0);
 }
@@ -986,6 +1055,87 @@ size_t f16_group_workspace(const rot_problem& p, int ops, bool symmetric) {
     return L.shared + f16_t_bytes(L, ops) + f16_o_bytes(p, L, ops, parts) + f16_scale_bytes(p, ops);
 }
 
+namespace {
+// The passes and both stages of operators b0 .. b0 + nb - 1 of p, bound in r.
+hipError_t run_pairs(const rot_problem& p, const F16Bound& r, int b0, int nb, bool with_u, bool symmetric,
+                     const FlatCfg& c2, hipStream_t stream) {
+    const F16Scale& g = r.g;
+    const bool site = g.Up != nullptr;
+    const dim3 block(256);
+    hipError_t e = prof_timed("scale_f16x3", stream, [&] {
+        F16Scale q = g;
+        scale_blocks(q, with_u);
+        const dim3 grid((unsigned)(q.u_blocks + q.o_blocks));
+        if (site)
+            hipLaunchKernelGGL(f16_scale_kernel<true>, grid, block, 0, stream, q);
+        else
+            hipLaunchKernelGGL(f16_scale_kernel<false>, grid, block, 0, stream, q);
+        return hipGetLastError();
+    });
+    if (e != hipSuccess) return e;
+    e = prof_timed("split_f16x3", stream, [&] {
+        F16Scale q = g;
+        const dim3 grid((unsigned)split_blocks(q, with_u));
+        if (site && p.d <= 4)
+            hipLaunchKernelGGL((f16_split_kernel<4, true>), grid, block, 0, stream, q);
+        else if (site)
+            hipLaunchKernelGGL((f16_split_kernel<kF16MaxSite, true>), grid, block, 0, stream, q);
+        else if (p.d <= 4)
+            hipLaunchKernelGGL((f16_split_kernel<4, false>), grid, block, 0, stream, q);
+        else
+            hipLaunchKernelGGL((f16_split_kernel<kF16MaxSite, false>), grid, block, 0, stream, q);
+        return hipGetLastError();
+    });
+    if (e != hipSuccess) return e;
+    const FlatDesc a = f16_stage1(g);
+    const FlatCfg c1 = flat_cfg(a.M, nb * (g.m32 / 32), (int)n_slabs(p.m), 1, 1, 0);
+    e = prof_timed("stage1_f16x3", stream, [&] {
+        return p.d == 4   ? launch_flat<true, 4>(a, c1, stream)
+               : p.d == 2 ? launch_flat<true, 2>(a, c1, stream)
+                          : launch_flat<true, 0>(a, c1, stream);
+    });
+    if (e != hipSuccess) return e;
+    float* out = static_cast<float*>(p.out) + (int64_t)b0 * p.stride_out;
+    FlatDesc b = c2.parts > 1 ? f16_stage2(g, reinterpret_cast<float*>(r.O), p.mp, (int64_t)p.mp * p.mp)
+                              : f16_stage2(g, out, p.ldout, p.stride_out);
+    if (g.Up) b.row_e = g.eu2;
+    b.c_ps = (int64_t)nb * p.mp * p.mp;
+    b.upper = symmetric;
+    e = prof_timed(symmetric ? "stage2sym_f16x3" : "stage2_f16x3", stream,
+                   [&] { return launch_flat<false, 0>(b, c2, stream); });
+    if (e == hipSuccess && c2.parts > 1)
+        e = prof_timed("stage2_sum", stream, [&] {
+            return sum_parts_2d(out, p.ldout, p.stride_out, r.O, p.mp, p.mp, nb, c2.parts, b.c_ps, false, stream);
+        });
+    if (e != hipSuccess) return e;
+    return hipSuccess;
+}
+
+// Operators b0 .. of a site group: the flags, then the pairs and, over them,
+// the FP32 kernels' intermediates.
+F16Bound f16_site_bind(const rot_problem& p, const F16Site& x, const F16Layout& L, int b0, int nb, int parts,
+                       void* ws, char** T32) {
+    char* base = static_cast<char*>(ws);
+    int* skip = reinterpret_cast<int*>(base);
+    base += al256((size_t)nb * 4);
+    *T32 = base;
+    F16Scale extra{};
+    extra.upart2 = reinterpret_cast<uint32_t*>(base);
+    base += L.part_u;
+    extra.eu2 = reinterpret_cast<int*>(base);
+    base += L.eu;
+    F16Bound r = f16_bind(p, L, b0, nb, parts, base);
+    r.g.skip = skip;
+    r.g.Up = x.Up;
+    r.g.d_all = x.d_all;
+    r.g.sel = x.sel;
+    r.g.upart2 = extra.upart2;
+    r.g.eu2 = extra.eu2;
+    r.g.n_ublk = 2 * div_up(p.mp, 64) * div_up((int64_t)p.m * x.d_all, kPrepRows);
+    return r;
+}
+}  // namespace
+
 // Operators b0 .. b0 + nb - 1 of p (leading dimensions resolved) through FP16
 // pairs; `fallback` enqueues the FP32 kernels for the operators they skip
 // (T: FP32 intermediates, slot_elems apart; skip: the flags).
@@ -995,43 +1145,34 @@ hipError_t rotate_f16(const rot_problem& p, int b0, int nb, void* ws, bool symme
     const F16Layout L = f16_layout(p);
     const FlatCfg c2 = f16_stage2_cfg(p, nb, symmetric);
     const F16Bound r = f16_bind(p, L, b0, nb, c2.parts, ws);
-    const F16Scale& g = r.g;
-    hipError_t e = prof_timed("scale_f16x3", stream, [&] {
-        F16Scale q = g;
-        scale_blocks(q, b0 == 0);
-        hipLaunchKernelGGL(f16_scale_kernel, dim3((unsigned)(q.u_blocks + q.o_blocks)), dim3(256), 0, stream, q);
-        return hipGetLastError();
-    });
-    if (e != hipSuccess) return e;
-    e = prof_timed("split_f16x3", stream, [&] {
-        F16Scale q = g;
-        const dim3 grid((unsigned)split_blocks(q, b0 == 0));
-        if (p.d <= 4)
-            hipLaunchKernelGGL(f16_split_kernel<4>, grid, dim3(256), 0, stream, q);
-        else
-            hipLaunchKernelGGL(f16_split_kernel<kF16MaxSite>, grid, dim3(256), 0, stream, q);
-        return hipGetLastError();
-    });
-    if (e != hipSuccess) return e;
-    const FlatDesc a = f16_stage1(g);
-    const FlatCfg c1 = flat_cfg(a.M, nb * (L.m32 / 32), (int)n_slabs(p.m), 1, 1, 0);
-    e = prof_timed("stage1_f16x3", stream, [&] {
-        return p.d == 4 ? launch_flat<true, true>(a, c1, stream) : launch_flat<true, false>(a, c1, stream);
-    });
-    if (e != hipSuccess) return e;
-    float* out = static_cast<float*>(p.out) + (int64_t)b0 * p.stride_out;
-    FlatDesc b = c2.parts > 1 ? f16_stage2(g, reinterpret_cast<float*>(r.O), p.mp, (int64_t)p.mp * p.mp)
-                              : f16_stage2(g, out, p.ldout, p.stride_out);
-    b.c_ps = (int64_t)nb * p.mp * p.mp;
-    b.upper = symmetric;
-    e = prof_timed(symmetric ? "stage2sym_f16x3" : "stage2_f16x3", stream,
-                   [&] { return launch_flat<false, true>(b, c2, stream); });
-    if (e == hipSuccess && c2.parts > 1)
-        e = prof_timed("stage2_sum", stream, [&] {
-            return sum_parts_2d(out, p.ldout, p.stride_out, r.O, p.mp, p.mp, nb, c2.parts, b.c_ps, false, stream);
-        });
-    if (e != hipSuccess) return e;
-    return fallback(r.T, (int64_t)(L.t32 / 4), g.skip);
+    const hipError_t e = run_pairs(p, r, b0, nb, b0 == 0, symmetric, c2, stream);
+    return e == hipSuccess ? fallback(r.T, (int64_t)(L.t32 / 4), r.g.skip) : e;
+}
+
+// Block operators times a site operator, out_b = U'^T (X_b U_r): stage 2's A
+// is the mixed Up instead of U, and only the site states t that Up has rows
+// for (S's non-zero columns; p.d of them, x.sel) enter either stage.  An
+// annihilator has two of the Hubbard site's four: half the products.  33
+// operators of 500 states, kept 480: 635 us for all four on the FP32 kernels,
+// 172 us for two on pairs (stage 1 78, stage 2 57, the passes 29).
+size_t f16_site_workspace(const rot_problem& p, const F16Site& x, int ops) {
+    const F16Layout L = f16_layout(p, x.d_all);
+    const int parts = f16_stage2_cfg(p, ops, false).parts;
+    return al256((size_t)ops * 4) + std::max(L.shared + 2 * al256(ops * L.t_op) + f16_o_bytes(p, L, ops, parts) +
+                                                 f16_scale_bytes(p, ops),
+                                             ops * L.t32);
+}
+hipError_t rotate_f16_site(const rot_problem& p, const F16Site& x, int b0, int nb, void* ws,
+                           const std::function<hipError_t(void* T, int64_t slot_elems, const int* skip)>& fallback,
+                           hipStream_t stream) {
+    F16Layout L = f16_layout(p, x.d_all);
+    const int64_t t32 = (int64_t)(L.t32 / 4);
+    L.t32 = 0;  // laid over everything instead of beside T's pairs
+    const FlatCfg c2 = f16_stage2_cfg(p, nb, false);
+    char* T32;
+    const F16Bound r = f16_site_bind(p, x, L, b0, nb, c2.parts, ws, &T32);
+    const hipError_t e = run_pairs(p, r, b0, nb, true, false, c2, stream);
+    return e == hipSuccess ? fallback(T32, t32, r.g.skip) : e;
 }
 
 // ------------------------------------------------------------------ plans --
@@ -1104,7 +1245,7 @@ hipError_t pair_build(const rot_problem* groups, const std::vector<PairPiece>& p
     std::vector<FlatProduct> p1, p2;
     c->n_pieces = n;
     c->d_max = 0;
-    c->all_d4 = true;
+    c->same_d = groups[pieces[0].group].d;
     for (int i = 0; i < n; i++) {
         const F16Scale& a = t.scale[i];
         for (int x = 0; x < a.u_blocks + a.o_blocks; x++) scale.push_back({i, x});
@@ -1114,7 +1255,7 @@ hipError_t pair_build(const rot_problem* groups, const std::vector<PairPiece>& p
         p1.push_back({t.s1[i].M, t.s1[i].batch * (t.s1[i].n32 / 32), (int)n_slabs(t.s1[i].K)});
         p2.push_back({t.s2[i].M, t.s2[i].batch * (t.s2[i].n32 / 32), (int)n_slabs(t.s2[i].K)});
         c->d_max = std::max(c->d_max, a.d);
-        c->all_d4 = c->all_d4 && a.d == 4;
+        if (a.d != c->same_d) c->same_d = 0;
     }
     const std::vector<FlatTile> l1 = flat_list(p1), l2 = flat_list(p2);
     const size_t bytes[6] = {al256(host.size()), al256(scale.size() * sizeof(PairBlock)),
@@ -1173,14 +1314,16 @@ hipError_t pair_issue(const PairChunk& c, hipStream_t s, bool timed) {
     e = run("plan_stage1_f16x3", [&] {
         const dim3 grid((unsigned)c.n_tiles1), block(512);
         const FlatTile* list = static_cast<const FlatTile*>(c.tiles1);
-        if (c.all_d4)
-            hipLaunchKernelGGL((gemm_flat_list_kernel<true, true>), grid, block, 0, s, t.s1, list);
+        if (c.same_d == 4)
+            hipLaunchKernelGGL((gemm_flat_list_kernel<true, 4>), grid, block, 0, s, t.s1, list);
+        else if (c.same_d == 2)
+            hipLaunchKernelGGL((gemm_flat_list_kernel<true, 2>), grid, block, 0, s, t.s1, list);
         else
-            hipLaunchKernelGGL((gemm_flat_list_kernel<true, false>), grid, block, 0, s, t.s1, list);
+            hipLaunchKernelGGL((gemm_flat_list_kernel<true, 0>), grid, block, 0, s, t.s1, list);
     });
     if (e != hipSuccess) return e;
     return run("plan_stage2_f16x3", [&] {
-        hipLaunchKernelGGL((gemm_flat_list_kernel<false, true>), dim3((unsigned)c.n_tiles2), dim3(512), 0, s, t.s2,
+        hipLaunchKernelGGL((gemm_flat_list_kernel<false, 0>), dim3((unsigned)c.n_tiles2), dim3(512), 0, s, t.s2,
                            static_cast<const FlatTile*>(c.tiles2));
     });
 }

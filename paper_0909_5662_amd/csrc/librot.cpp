@@ -27,6 +27,10 @@ size_t f16_group_workspace(const rot_problem& p, int ops, bool symmetric);
 hipError_t rotate_f16(const rot_problem& p, int b0, int nb, void* ws, bool symmetric,
                       const std::function<hipError_t(void* T, int64_t slot_elems, const int* skip)>& fallback,
                       hipStream_t stream);
+size_t f16_site_workspace(const rot_problem& p, const F16Site& x, int ops);
+hipError_t rotate_f16_site(const rot_problem& p, const F16Site& x, int b0, int nb, void* ws,
+                           const std::function<hipError_t(void* T, int64_t slot_elems, const int* skip)>& fallback,
+                           hipStream_t stream);
 bool bf16_backward_supported(int m, int d, int mp);
 size_t bf16_backward_workspace(int m, int d, int mp, int ops);
 hipError_t backward_bf16(const rot_problem& p, int b0, int nb, const float* dout, int64_t sd, float* dO, float* dU,
@@ -265,6 +269,22 @@ hipError_t gemm(rot_precision prec, const GemmDesc& g, hipStream_t s, const char
     return timed(name.c_str(), s, [&] { return f64 ? gemm_f64(g, s) : gemm_f32(g, s); });
 }
 
+// Operators per chunk on FP16 pairs, if `fits` says which counts may go
+// together; 0: FP32 kernels.  Chunks of a group that does not fit whole are of
+// equal size and pay from `least` on: 8 GFLOP in rot_batch (a chunk's passes
+// and launches cost 40 us; the pairs gain 5 us per GFLOP on the FP32 kernels'
+// full rate).
+template <typename F>
+int pair_chunk_if(int n_ops, double op_flop, double least, F fits) {
+    if (!fits(1)) return 0;
+    if (fits(n_ops)) return n_ops;
+    int fit = 1, over = n_ops;
+    while (over - fit > 1) (fits((fit + over) / 2) ? fit : over) = (fit + over) / 2;
+    const int chunks = (n_ops + fit - 1) / fit, size = (n_ops + chunks - 1) / chunks;
+    return op_flop * size >= least ? size : 0;
+}
+double rotation_flop(const rot_problem& p) { return 2.0 * p.m * p.d * p.mp * ((double)p.m + p.mp); }
+
 // Split-K for a single GEMM whose output has too few 128 x 128 tiles to fill
 // the chip: K is cut into parts of a multiple of 16 (the last one shorter),
 // each part's product goes to its own partial sum (parts x M x N), and the
@@ -424,18 +444,10 @@ size_t rot_workspace_preferred(const rot_problem* groups, int32_t n_groups, rot_
 
 namespace {
 
-// Operators per chunk on FP16 pairs within `bytes` of workspace; 0: FP32
-// kernels.  Chunks of a group that does not fit whole are of equal size and
-// pay from about 8 GFLOP on (a chunk's passes and launches cost 40 us; the
-// pairs gain 5 us per GFLOP on the FP32 kernels' full rate).
 int pair_chunk(const rot_problem& p, bool sym, size_t bytes) {
-    auto fits = [&](int ops) { return f16_rotate_applies(p, ops) && f16_group_workspace(p, ops, sym) <= bytes; };
-    if (!fits(1)) return 0;
-    if (fits(p.n_ops)) return p.n_ops;
-    int fit = 1, over = p.n_ops;
-    while (over - fit > 1) (fits((fit + over) / 2) ? fit : over) = (fit + over) / 2;
-    const int chunks = (p.n_ops + fit - 1) / fit, size = (p.n_ops + chunks - 1) / chunks;
-    return 2.0 * p.m * p.d * p.mp * ((double)p.m + p.mp) * size >= 8e9 ? size : 0;
+    return pair_chunk_if(p.n_ops, rotation_flop(p), 8e9, [&](int ops) {
+        return f16_rotate_applies(p, ops) && f16_group_workspace(p, ops, sym) <= bytes;
+    });
 }
 
 // rot_batch_ex; `pairs`: FP32 batches may run on FP16 pairs.
@@ -610,6 +622,40 @@ size_t site_up_bytes(const rot_site_problem& p, rot_precision prec) {
     return align_up((size_t)p.m * p.d * p.mp * elem_size(prec));
 }
 
+// The same shapes as a dense group: X_b in place of O_b, packed U, X and out.
+rot_problem site_as_dense(const rot_site_problem& sp) {
+    rot_problem p{};
+    p.m = sp.m;
+    p.d = sp.d;
+    p.mp = sp.mp;
+    p.n_ops = sp.n_ops;
+    p.U = sp.U;
+    p.O = sp.X;
+    p.stride_o = sp.stride_x;
+    p.out = sp.out;
+    p.stride_out = sp.stride_out;
+    return resolved(p);
+}
+
+// The group as it runs on FP16 pairs: d counts S's non-zero columns.  False:
+// FP32 kernels (a zero S; less work than the pairs pay for, rot_batch's rule;
+// shapes that they do not take).
+bool site_pairs(const rot_site_problem& sp, rot_problem* p, F16Site* x) {
+    *p = site_as_dense(sp);
+    if (sp.block_kind != ROT_BLOCK_DENSE || rotation_flop(*p) * sp.n_ops < kPairsLeastFlop) return false;
+    *x = F16Site{nullptr, sp.d, 0};
+    int n = 0;
+    for (int t = 0; t < sp.d; t++) {
+        bool any = false;
+        for (int s = 0; s < sp.d; s++) any |= sp.site[s * sp.d + t] != 0.0;
+        if (!any) continue;
+        if (n < 8) x->sel |= (uint32_t)t << (4 * n);
+        n++;
+    }
+    p->d = n;
+    return n > 0 && f16_shape_supported(*p, 1);
+}
+
 }  // namespace
 
 size_t rot_site_workspace_size(const rot_site_problem* groups, int32_t n_groups, rot_precision prec,
@@ -628,6 +674,18 @@ size_t rot_site_workspace_size(const rot_site_problem* groups, int32_t n_groups,
         }
         const int ops = ops_per_chunk > 0 ? std::min(ops_per_chunk, p.n_ops) : p.n_ops;
         need = std::max(need, slot * (size_t)(1 + ops));
+    }
+    return need;
+}
+
+size_t rot_site_workspace_preferred(const rot_site_problem* groups, int32_t n_groups, rot_precision prec) {
+    size_t need = rot_site_workspace_size(groups, n_groups, prec, 0);
+    if (need == 0 || prec != ROT_FP32) return need;
+    for (int gi = 0; gi < n_groups; gi++) {
+        rot_problem p;
+        F16Site x;
+        if (groups[gi].n_ops > 0 && site_pairs(groups[gi], &p, &x) && f16_shape_supported(p, p.n_ops))
+            need = std::max(need, site_up_bytes(groups[gi], prec) + f16_site_workspace(p, x, p.n_ops));
     }
     return need;
 }
@@ -664,18 +722,7 @@ rot_status rot_batch_site(const rot_site_problem* groups, int32_t n_groups, rot_
             return site_mix(sp.U, sp.m, sp.d, sp.mp, S, x, up, prec == ROT_FP64, s);
         });
         if (e != hipSuccess) return hip_fail(e, "rot_batch_site mix");
-        // the same shapes as a dense group: X_b in place of O_b
-        rot_problem p{};
-        p.m = sp.m;
-        p.d = sp.d;
-        p.mp = sp.mp;
-        p.n_ops = sp.n_ops;
-        p.U = sp.U;
-        p.O = sp.X;
-        p.stride_o = sp.stride_x;
-        p.out = sp.out;
-        p.stride_out = sp.stride_out;
-        p = resolved(p);  // packed U, X and out
+        const rot_problem p = site_as_dense(sp);
         if (sp.block_kind != ROT_BLOCK_DENSE) {
             // out = U'^T U: stage 2 with U' as A and U itself as B (split over K
             // when its mp x mp output has few tiles)
@@ -689,6 +736,31 @@ rot_status rot_batch_site(const rot_site_problem* groups, int32_t n_groups, rot_
         }
         const size_t slot = site_up_bytes(sp, prec);
         char* T = up + slot;
+        rot_problem q;
+        F16Site site;
+        if (prec == ROT_FP32 && site_pairs(sp, &q, &site)) {
+            site.Up = reinterpret_cast<const float*>(up);
+            // chunks pay from less on the fewer states are listed: the FP32
+            // kernels take them all (7.5 us gained per GFLOP for half of them)
+            const double least = 4e9 * (1.0 + (double)q.d / p.d);
+            const int fit = pair_chunk_if(q.n_ops, rotation_flop(p), least, [&](int ops) {
+                return f16_shape_supported(q, ops) && slot + f16_site_workspace(q, site, ops) <= workspace_bytes;
+            });
+            for (int b0 = 0; fit > 0 && b0 < q.n_ops; b0 += fit) {
+                const int nb = std::min(fit, q.n_ops - b0);
+                auto fp32 = [&](void* T32, int64_t slot_elems, const int* skip) {
+                    GemmDesc g1 = stage1(p, b0, nb, T32, es), g2 = stage2(p, b0, nb, T32, es);
+                    g1.c_bs = g2.b_bs = slot_elems;
+                    g1.only = g2.only = skip;
+                    g2.A = up;
+                    const hipError_t err = gemm(prec, g1, s, "rest1");
+                    return err == hipSuccess ? gemm(prec, g2, s, "rest2") : err;
+                };
+                e = rotate_f16_site(q, site, b0, nb, T, fp32, s);
+                if (e != hipSuccess) return hip_fail(e, "rot_batch_site launch");
+            }
+            if (fit > 0) continue;
+        }
         const int chunk = (int)std::min<size_t>((size_t)sp.n_ops, workspace_bytes / slot - 1);
         for (int b0 = 0; b0 < sp.n_ops; b0 += chunk) {
             const int nb = std::min(chunk, sp.n_ops - b0);

@@ -88,6 +88,11 @@ hipError_t grouped_gemm_f32(const GroupedLaunch& L, hipStream_t stream);
 // FP32 rotations on FP16 pairs (gemm_f16x3.hip): the least work they pay for,
 // and the chunks of a plan that take them.
 constexpr double kPairsLeastFlop = 4e9;
+struct F16Site {
+    const float* Up;  // (diag(x) (x) S^T) U, packed
+    int d_all;        // site states; the group's d counts those listed
+    uint32_t sel;     // 4 bits each
+};
 struct PairPiece {
     int group, b0, nb;  // operators b0 .. b0 + nb - 1 of a group
     char* ws;           // their part of the workspace (pair_piece_workspace bytes, 256-byte aligned)
@@ -95,7 +100,7 @@ struct PairPiece {
 struct PairChunk {
     void* mem = nullptr;  // device: tables (first, pair_table_bytes), lists, flag
     int n_pieces = 0, d_max = 0;
-    bool all_d4 = false;
+    int same_d = 0;       // d of all pieces, 0 if they differ
     void *scale = nullptr, *split = nullptr, *tiles1 = nullptr, *tiles2 = nullptr;
     int n_scale = 0, n_split = 0, n_tiles1 = 0, n_tiles2 = 0;
     int* any = nullptr;   // set when an operator is left to the FP32 kernels
