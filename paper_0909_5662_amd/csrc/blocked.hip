@@ -17,6 +17,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <list>
 #include <map>
 #include <memory>
@@ -1407,6 +1408,7 @@ struct DeviceLists {
 struct Plan {
     DeviceLists s1, s2;
     int64_t counter_off = 0;  // bytes into the caller's workspace: the tile queue of this call
+    size_t ws_bytes = 0;      // the workspace that the tables need
     int64_t x_elems = 0;
     BlkTask* f_tasks = nullptr;
     BlkTerm* f_terms = nullptr;
@@ -1532,6 +1534,17 @@ int64_t counter_offset(int64_t x_elems, int64_t ut_elems) {
     return ((x_elems + 63) / 64 * 64 + ut_elems) * (int64_t)sizeof(float) / 256 * 256 + 256;
 }
 
+size_t structure_workspace(const rot_blocked_problem* p, const Structure& st) {
+    const UtLayout ut = ut_layout(p, st);
+    return (size_t)counter_offset(x_elements(p, st, ut), ut.elems) + 256;
+}
+
+// Whether every table that a signature reads is there.
+bool tables_present(const rot_blocked_problem* p) {
+    return p->d > 0 && p->n_old > 0 && p->n_new > 0 && p->n_ops > 0 && p->site_qn && p->old_sec && p->new_sec &&
+           p->U_off && p->shift && p->O_off && p->out_off && p->O_blk && p->out_blk && p->U_blk;
+}
+
 }  // namespace
 
 // X of the grouped path, then the transposed U blocks of the fused path, then
@@ -1541,13 +1554,7 @@ size_t blocked_workspace_bytes(const rot_blocked_problem* p) {
     Structure st;
     std::string why;
     if (!build_structure(p, &st, &why)) return 0;
-    const UtLayout ut = ut_layout(p, st);
-    return (size_t)counter_offset(x_elements(p, st, ut), ut.elems) + 256;
-}
-
-rot_status blocked_validate(const rot_blocked_problem* p, std::string* why) {
-    Structure st;
-    return build_structure(p, &st, why) ? ROT_OK : ROT_ERR_INVALID_ARG;
+    return structure_workspace(p, st);
 }
 
 namespace {
@@ -1711,19 +1718,39 @@ hipError_t run_path(const rot_blocked_problem* p, Plan* plan, void* ws, GroupedS
 
 }  // namespace
 
-hipError_t rotate_blocked(const rot_blocked_problem* p, void* ws, size_t ws_bytes, hipStream_t stream) {
-    (void)ws_bytes;
-    if (p->n_ops == 0) return hipSuccess;
+// Tables equal to a cached entry's were valid when it was made and need the
+// workspace it holds, so they are compared with it first and examined only
+// when there is none (400 operators over 45 sectors: 18000 offsets, examined
+// twice by every call before; 2 x 160 us of host time against 250 us on the
+// device).  `check` judges the workspace; a refusal comes back in *status.
+hipError_t rotate_blocked(const rot_blocked_problem* p, void* ws, hipStream_t stream,
+                          const std::function<rot_status(size_t need)>& check, rot_status* status) {
     const GroupedShape shape = blocked_shape();
     const int forced = forced_path();
+    std::lock_guard<std::mutex> lk(g_mu);
+    Plan* plan = nullptr;
+    if (tables_present(p))
+        plan = g_plans.find_if(
+            [&](const std::vector<unsigned char>& key) { return signature_matches(p, ws, shape, key); });
+    Structure st;
+    size_t need;
+    if (plan) {
+        need = plan->ws_bytes;
+    } else {
+        std::string why;
+        if (!build_structure(p, &st, &why)) {
+            *status = set_error(ROT_ERR_INVALID_ARG, why.c_str());
+            return hipSuccess;
+        }
+        need = structure_workspace(p, st);
+    }
+    *status = check(need);
+    if (*status != ROT_OK || p->n_ops == 0) return hipSuccess;
     // Under stream capture the graph keeps the plan's device work-lists: the
     // plan is pinned (never evicted), and a structure not seen before cannot
     // be planned (its lists are copied to the device synchronously).
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     const bool capturing = hipStreamIsCapturing(stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone;
-    std::lock_guard<std::mutex> lk(g_mu);
-    Plan* plan = g_plans.find_if(
-        [&](const std::vector<unsigned char>& key) { return signature_matches(p, ws, shape, key); });
     if (!plan && capturing) {
         set_error(ROT_ERR_UNSUPPORTED,
                   "rot_batch_blocked: the first call for a block structure must run outside stream capture "
@@ -1731,9 +1758,6 @@ hipError_t rotate_blocked(const rot_blocked_problem* p, void* ws, size_t ws_byte
         return hipErrorStreamCaptureUnsupported;
     }
     if (!plan) {
-        Structure st;
-        std::string why;
-        if (!build_structure(p, &st, &why)) return hipErrorInvalidValue;  // validated by the caller
         Lists L;
         build_lists(p, st, static_cast<const float*>(ws), &L);
         const UtLayout ut = ut_layout(p, st);
@@ -1742,6 +1766,7 @@ hipError_t rotate_blocked(const rot_blocked_problem* p, void* ws, size_t ws_byte
         StackedLists S;
         build_stacked(p, st, ut, &S);
         auto np = std::make_unique<Plan>();
+        np->ws_bytes = need;
         np->x_elems = std::max(L.x_elems, S.x_elems);
         const int edge = grouped_tile_edge(shape);
         hipError_t e = upload(L.p1, make_tiles(L.p1, edge), &np->s1);

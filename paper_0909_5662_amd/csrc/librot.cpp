@@ -36,8 +36,8 @@ size_t bf16_backward_workspace(int m, int d, int mp, int ops);
 hipError_t backward_bf16(const rot_problem& p, int b0, int nb, const float* dout, int64_t sd, float* dO, float* dU,
                          bool sym, void* ws, hipStream_t s);
 size_t blocked_workspace_bytes(const rot_blocked_problem* p);
-rot_status blocked_validate(const rot_blocked_problem* p, std::string* why);
-hipError_t rotate_blocked(const rot_blocked_problem* p, void* ws, size_t ws_bytes, hipStream_t stream);
+hipError_t rotate_blocked(const rot_blocked_problem* p, void* ws, hipStream_t stream,
+                          const std::function<rot_status(size_t need)>& check, rot_status* status);
 size_t density_workspace_bytes(const rot_dm_sector* sectors, int n_sectors);
 hipError_t density_basis(const rot_dm_sector* sectors, int n_sec, int64_t m_keep, int32_t* kept, double* eps,
                          void* workspace, hipStream_t stream, bool* converged);
@@ -1252,9 +1252,7 @@ rot_status rot_split_bf16(const float* x, int64_t n, uint16_t* hi, uint16_t* lo,
 }
 
 size_t rot_blocked_workspace_size(const rot_blocked_problem* p) {
-    std::string why;
-    if (!p || blocked_validate(p, &why) != ROT_OK) return 0;
-    return blocked_workspace_bytes(p);
+    return p ? blocked_workspace_bytes(p) : 0;
 }
 
 rot_status rot_batch_blocked(const rot_blocked_problem* p, rot_precision prec, void* workspace,
@@ -1262,15 +1260,16 @@ rot_status rot_batch_blocked(const rot_blocked_problem* p, rot_precision prec, v
     rot::TraceRange trace_("rot_batch_blocked");
     if (!p) return fail(ROT_ERR_INVALID_ARG, "null problem");
     if (prec != ROT_FP32) return fail(ROT_ERR_UNSUPPORTED, "rot_batch_blocked supports ROT_FP32 only");
-    std::string why;
-    rot_status st = blocked_validate(p, &why);
-    if (st != ROT_OK) return fail(st, "%s", why.c_str());
-    const size_t need = blocked_workspace_bytes(p);
-    if (need > 0 && (!workspace || workspace_bytes < need))
-        return fail(ROT_ERR_WORKSPACE, "workspace %zu bytes < minimum %zu", workspace_bytes, need);
-    if (reinterpret_cast<uintptr_t>(workspace) % kAlign)
-        return fail(ROT_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
-    hipError_t e = rotate_blocked(p, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
+    rot_status st = ROT_OK;
+    auto check = [&](size_t need) {
+        if (need > 0 && (!workspace || workspace_bytes < need))
+            return fail(ROT_ERR_WORKSPACE, "workspace %zu bytes < minimum %zu", workspace_bytes, need);
+        if (reinterpret_cast<uintptr_t>(workspace) % kAlign)
+            return fail(ROT_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
+        return ROT_OK;
+    };
+    const hipError_t e = rotate_blocked(p, workspace, static_cast<hipStream_t>(stream), check, &st);
+    if (st != ROT_OK) return st;
     if (e == hipErrorStreamCaptureUnsupported) return ROT_ERR_UNSUPPORTED;  // message already set
     return e == hipSuccess ? ROT_OK : hip_fail(e, "rot_batch_blocked");
 }
