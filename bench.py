@@ -495,7 +495,7 @@ def bench_density(args, rot, torch, workloads):
     torch.cuda.synchronize()
     kernels = rot.profile_read()
     rot.profile_enable(False)
-    rounds = kernels.get("dm_jacobi_pairs", (0, 0.0))[0] / calls
+    rounds = kernels.get("dm_jacobi_round", (0, 0.0))[0] / calls
 
     def torch_eigh():
         for p in psi:

@@ -36,6 +36,7 @@ constexpr int kBlk = 32;        // Jacobi block edge
 constexpr int kPair = 64;       // two blocks
 constexpr int kLs = kPair + 1;  // LDS row stride (doubles)
 constexpr int kMaxSweeps = 80;
+constexpr int kFirstCheck = 6, kCheckEvery = 3;  // sweeps after which the host asks whether all sectors are done
 constexpr int kSortMax = 4096;  // largest sector (states)
 
 struct DmSector {
@@ -114,63 +115,80 @@ __device__ inline int pair_row(int I, int J, int l) { return l < kBlk ? I * kBlk
 
 // ---------------------------------------------------------------------------
 // rho tile (ti, tj), ti <= tj, of sector it.sec: rho[x][y] = sum_k psi[x][k] psi[y][k]
-// over 64 x 64 outputs (4 x 4 per thread), K in slices of 16 through LDS;
-// written to both (ti, tj) and its mirror.  The eigenvector matrix is set to
-// the identity on the same tiles.
+// over 64 x 64 outputs, one 32 x 32 quarter per wave on v_mfma_f64_16x16x4f64
+// (lane l: A(l%16, l/16), B(l/16, l%16); element v of the result is row
+// 4 v + l/16, column l%16); written to both (ti, tj) and its mirror.  The
+// eigenvector matrix is set to the identity on the same tiles.  K in slices of
+// 16 through two LDS buffers, the next slice in registers: with one workgroup
+// per CU the loads' latency is the bound (60 sectors of up to 246 states: one
+// buffer and vector arithmetic 80 us, now 25).
 __global__ __launch_bounds__(256) void dm_rho_kernel(const DmSector* __restrict__ secs,
                                                      const DmItem* __restrict__ items, double* __restrict__ A,
                                                      double* __restrict__ Vw) {
     const DmItem it = items[blockIdx.x];
     const DmSector s = secs[it.sec];
     const int ti = it.a, tj = it.b;
-    __shared__ double pa[16][kPair + 1];
-    __shared__ double pb[16][kPair + 1];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    double acc[4][4];
+    constexpr int kRow = 18;  // LDS row of a slice (doubles): 16 rows' reads spread over the banks
+    __shared__ double pa[2][kPair * kRow], pb[2][kPair * kRow];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 4, c = lane & 15;
+    const int wr = 32 * (wave >> 1), wc = 32 * (wave & 1);
+    const int kk = tid & 15, row = tid >> 4;
+    double va[4], vb[4];
+    auto load = [&](int k0) {
+        const int gk = k0 + kk;
 #pragma unroll
-    for (int p = 0; p < 4; p++)
+        for (int j = 0; j < 4; j++) {
+            const int gi = ti * kPair + row + 16 * j, gj = tj * kPair + row + 16 * j;
+            va[j] = (gk < s.r && gi < s.n) ? s.psi[(int64_t)gi * s.ld_psi + gk] : 0.0;
+            vb[j] = (gk < s.r && gj < s.n) ? s.psi[(int64_t)gj * s.ld_psi + gk] : 0.0;
+        }
+    };
+    typedef double f64x4 __attribute__((ext_vector_type(4)));
+    f64x4 acc[2][2];
 #pragma unroll
-        for (int q = 0; q < 4; q++) acc[p][q] = 0.0;
-    for (int k0 = 0; k0 < s.r; k0 += 16) {
-        for (int e = tid; e < kPair * 16; e += 256) {
-            const int row = e >> 4, kk = e & 15;
-            const int gi = ti * kPair + row, gj = tj * kPair + row, gk = k0 + kk;
-            const bool kin = gk < s.r;
-            pa[kk][row] = (kin && gi < s.n) ? s.psi[(int64_t)gi * s.ld_psi + gk] : 0.0;
-            pb[kk][row] = (kin && gj < s.n) ? s.psi[(int64_t)gj * s.ld_psi + gk] : 0.0;
+    for (int p = 0; p < 2; p++)
+#pragma unroll
+        for (int q = 0; q < 2; q++) acc[p][q] = f64x4{0.0, 0.0, 0.0, 0.0};
+    load(0);
+    for (int k0 = 0, cur = 0; k0 < s.r; k0 += 16, cur ^= 1) {
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            pa[cur][(row + 16 * j) * kRow + kk] = va[j];
+            pb[cur][(row + 16 * j) * kRow + kk] = vb[j];
         }
         __syncthreads();
-#pragma unroll 4
-        for (int kk = 0; kk < 16; kk++) {
-            double a[4], b[4];
+        if (k0 + 16 < s.r) load(k0 + 16);
 #pragma unroll
-            for (int p = 0; p < 4; p++) a[p] = pa[kk][ty * 4 + p];
+        for (int k4 = 0; k4 < 16; k4 += 4) {
+            double x[2], y[2];
 #pragma unroll
-            for (int q = 0; q < 4; q++) b[q] = pb[kk][tx * 4 + q];
+            for (int p = 0; p < 2; p++) {
+                x[p] = pa[cur][(wr + 16 * p + c) * kRow + k4 + h];
+                y[p] = pb[cur][(wc + 16 * p + c) * kRow + k4 + h];
+            }
 #pragma unroll
-            for (int p = 0; p < 4; p++)
+            for (int p = 0; p < 2; p++)
 #pragma unroll
-                for (int q = 0; q < 4; q++) acc[p][q] = fma(a[p], b[q], acc[p][q]);
+                for (int q = 0; q < 2; q++) acc[p][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[p], y[q], acc[p][q], 0, 0, 0);
         }
-        __syncthreads();
     }
     double* a = A + s.a_off;
     double* v = Vw + s.a_off;
     const int64_t np = s.npad;
 #pragma unroll
-    for (int p = 0; p < 4; p++) {
-        const int64_t row = ti * kPair + ty * 4 + p;
+    for (int p = 0; p < 2; p++)
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const int64_t col = tj * kPair + tx * 4 + q;
-            a[row * np + col] = acc[p][q];
-            v[row * np + col] = row == col ? 1.0 : 0.0;
-            if (ti != tj) {
-                a[col * np + row] = acc[p][q];
-                v[col * np + row] = 0.0;
+        for (int q = 0; q < 2; q++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const int64_t r0 = ti * kPair + wr + 16 * p + 4 * e + h, c0 = tj * kPair + wc + 16 * q + c;
+                a[r0 * np + c0] = acc[p][q][e];
+                v[r0 * np + c0] = r0 == c0 ? 1.0 : 0.0;
+                if (ti != tj) {
+                    a[c0 * np + r0] = acc[p][q][e];
+                    v[c0 * np + r0] = 0.0;
+                }
             }
-        }
-    }
 }
 
 // Per sector: the threshold 2^-52 tr(rho) (trace summed in a fixed order) and
@@ -805,15 +823,15 @@ __global__ __launch_bounds__(256) void dm_count_kernel(const DmSector* __restric
 
 // ---------------------------------------------------------------------------
 // Per sector: the diagonal sorted descending (equal values by position, a
-// bitonic network in LDS), written to w and to the concatenated list, and the
-// eigenvector columns gathered in that order into the caller's V.
+// bitonic network in LDS), written to w and to the concatenated list, with the
+// positions it came from.
 __device__ inline bool dm_before(double ka, int ia, double kb, int ib) {
     return ka > kb || (ka == kb && ia < ib);
 }
 
 __global__ __launch_bounds__(256) void dm_sort_kernel(const DmSector* __restrict__ secs,
-                                                      const double* __restrict__ diag, const double* __restrict__ Vw,
-                                                      double* __restrict__ wall) {
+                                                      const double* __restrict__ diag, double* __restrict__ wall,
+                                                      int* __restrict__ order) {
     const DmSector s = secs[blockIdx.x];
     __shared__ double key[kSortMax];
     __shared__ int idx[kSortMax];
@@ -848,15 +866,25 @@ __global__ __launch_bounds__(256) void dm_sort_kernel(const DmSector* __restrict
     for (int k = tid; k < s.n; k += 256) {
         s.w[k] = key[k];
         wall[s.w_off + k] = key[k];
-    }
-    const double* v = Vw + s.a_off;
-    for (int64_t e = tid; e < (int64_t)s.n * s.n; e += 256) {
-        const int64_t row = e / s.n;
-        const int col = (int)(e - row * s.n);
-        // idx[col] < n for finite diagonals; the clamp keeps the read in the
+        // idx[k] < n for finite diagonals; the clamp keeps the reads in the
         // sector's block should a non-finite value reorder the padding
-        const int src = idx[col] < s.n ? idx[col] : col;
-        s.V[row * s.ld_v + col] = v[row * s.npad + src];
+        order[s.w_off + k] = idx[k] < s.n ? idx[k] : k;
+    }
+}
+
+// The eigenvector columns in descending order into the caller's V, kGatherRows
+// rows of a sector per workgroup (one workgroup per sector: 104 us for 60
+// sectors of up to 246 states, now 7).
+constexpr int kGatherRows = 16;
+__global__ __launch_bounds__(256) void dm_gather_kernel(const DmSector* __restrict__ secs,
+                                                        const double* __restrict__ Vw, const int* __restrict__ order) {
+    const DmSector s = secs[blockIdx.x];
+    const int row0 = blockIdx.y * kGatherRows, rows = min(kGatherRows, s.n - row0);
+    const double* v = Vw + s.a_off;
+    for (int col = threadIdx.x & 63; col < s.n; col += 64) {
+        const int src = order[s.w_off + col];
+        for (int r = threadIdx.x >> 6; r < rows; r += 4)
+            s.V[(int64_t)(row0 + r) * s.ld_v + col] = v[(int64_t)(row0 + r) * s.npad + src];
     }
 }
 
@@ -878,14 +906,18 @@ __device__ inline int dm_count_ge(const double* w, int n, uint64_t c) {
 }
 
 // The m_keep largest eigenvalues over all sectors: the m_keep-th largest key T
-// found bit by bit (largest T with #(key >= T) >= m_keep; each thread counts
-// its share of the concatenated lists, held in registers when they fit), all
-// entries above T kept, entries equal to T handed out in sector order; then
-// the weight left out, per sector by one wave (strided lanes, then a fixed
-// butterfly) and over sectors in sector order.
+// found eight bits at a time (a histogram of the keys that share T's higher
+// bits; 64 counting passes, one per bit, took 70 us for 3 939 values, now
+// 25), all entries above T kept, entries equal to T handed out in sector
+// order; then the weight left out, per sector by one wave (strided lanes, then
+// a fixed butterfly) and over sectors in sector order.
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kSelCache = 16;
+
+__device__ inline long long dm_wave_sum(long long x) {
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    return x;
+}
 
 __global__ __launch_bounds__(kSelThreads) void dm_select_kernel(const DmSector* __restrict__ secs, int n_sec,
                                                                 const double* __restrict__ wall, int64_t m_keep,
@@ -893,36 +925,57 @@ __global__ __launch_bounds__(kSelThreads) void dm_select_kernel(const DmSector* 
                                                                 int* __restrict__ equal, double* __restrict__ part,
                                                                 int32_t* __restrict__ kept,
                                                                 double* __restrict__ eps) {
-    __shared__ long long red[2][kSelWaves];
+    __shared__ unsigned hist[256];
+    __shared__ uint64_t s_T;
+    __shared__ long long s_need;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (m_keep >= total || m_keep == 0) {
         for (int k = tid; k < n_sec; k += kSelThreads) kept[k] = m_keep == 0 ? 0 : secs[k].n;
     } else {
-        const bool cached = total <= (int64_t)kSelThreads * kSelCache;
-        uint64_t kc[kSelCache];
-#pragma unroll
-        for (int j = 0; j < kSelCache; j++) {
-            const int64_t e = tid + (int64_t)kSelThreads * j;
-            kc[j] = (cached && e < total) ? dm_key(wall[e]) : 0;  // key 0 is never counted (c >= 1)
+        if (tid == 0) {
+            s_T = 0;
+            s_need = m_keep;
         }
-        uint64_t T = 0;
-        for (int bit = 63; bit >= 0; bit--) {
-            const uint64_t c = T | (1ull << bit);
-            int cnt = 0;
-            if (cached) {
-#pragma unroll
-                for (int j = 0; j < kSelCache; j++) cnt += kc[j] >= c ? 1 : 0;
-            } else {
-                for (int64_t e = tid; e < total; e += kSelThreads) cnt += dm_key(wall[e]) >= c ? 1 : 0;
-            }
-            for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-            const int buf = bit & 1;
-            if (lane == 0) red[buf][wave] = cnt;
+        for (int shift = 56; shift >= 0; shift -= 8) {
+            if (tid < 256) hist[tid] = 0;
             __syncthreads();
-            long long tot = 0;
-            for (int w = 0; w < kSelWaves; w++) tot += red[buf][w];
-            if (tot >= m_keep) T = c;
+            const uint64_t T = s_T;
+            for (int64_t e = tid; e < (total + 63) / 64 * 64; e += kSelThreads) {
+                const uint64_t key = e < total ? dm_key(wall[e]) : 0;
+                const bool in = e < total && (shift == 56 || (key >> (shift + 8)) == (T >> (shift + 8)));
+                const unsigned digit = (unsigned)(key >> shift) & 255;
+                // the lanes that share the first one's digit add together
+                const unsigned long long lanes = __ballot(in);
+                if (lanes == 0) continue;
+                const int lead = __builtin_ctzll(lanes);
+                const bool same = in && digit == (unsigned)__shfl((int)digit, lead);
+                const unsigned long long alike = __ballot(same);
+                if (lane == lead) atomicAdd(&hist[digit], (unsigned)__popcll(alike));
+                else if (in && !same) atomicAdd(&hist[digit], 1u);
+            }
+            __syncthreads();
+            if (wave == 0) {
+                // four digits per lane, from the largest down
+                unsigned h[4], own = 0;
+#pragma unroll
+                for (int j = 0; j < 4; j++) own += h[j] = hist[255 - 4 * lane - j];
+                long long upto = own;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const long long x = __shfl_up(upto, o);
+                    if (lane >= o) upto += x;
+                }
+                const long long need = s_need;
+                long long before = upto - own;  // keys with larger digits than this lane's
+                if (before < need && need <= upto) {
+                    int j = 0;
+                    while (j < 3 && before + h[j] < need) before += h[j++];
+                    s_T = T | (uint64_t)(255 - 4 * lane - j) << shift;
+                    s_need = need - before;
+                }
+            }
+            __syncthreads();
         }
+        const uint64_t T = s_T;
         for (int k = tid; k < n_sec; k += kSelThreads) {
             const double* w = wall + secs[k].w_off;
             const int ge = dm_count_ge(w, secs[k].n, T);
@@ -931,13 +984,21 @@ __global__ __launch_bounds__(kSelThreads) void dm_select_kernel(const DmSector* 
             equal[k] = ge - gt;
         }
         __syncthreads();
-        if (tid == 0) {
-            long long need = m_keep;
-            for (int k = 0; k < n_sec; k++) need -= above[k];
-            for (int k = 0; k < n_sec; k++) {
-                const long long take = need < equal[k] ? need : equal[k];
-                kept[k] = above[k] + (int)take;
-                need -= take;
+        if (wave == 0) {
+            long long need = m_keep, sum = 0;
+            for (int k = lane; k < n_sec; k += 64) sum += above[k];
+            need -= dm_wave_sum(sum);
+            for (int k0 = 0; k0 < n_sec; k0 += 64) {
+                const int k = k0 + lane, eq = k < n_sec ? equal[k] : 0;
+                long long upto = eq;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const long long x = __shfl_up(upto, o);
+                    if (lane >= o) upto += x;
+                }
+                const long long left = need - (upto - eq);
+                if (k < n_sec) kept[k] = above[k] + (int)(left < 0 ? 0 : left < eq ? left : eq);
+                need -= __shfl(upto, 63);
+                if (need < 0) need = 0;
             }
         }
     }
@@ -950,10 +1011,14 @@ __global__ __launch_bounds__(kSelThreads) void dm_select_kernel(const DmSector* 
         if (lane == 0) part[k] = acc;
     }
     __syncthreads();
-    if (tid == 0) {
+    if (wave == 0) {
         double acc = 0.0;
-        for (int k = 0; k < n_sec; k++) acc += part[k];
-        eps[0] = acc;
+        for (int k0 = 0; k0 < n_sec; k0 += 64) {
+            const double p = k0 + lane < n_sec ? part[k0 + lane] : 0.0;
+            const int m = min(64, n_sec - k0);
+            for (int i = 0; i < m; i++) acc += __shfl(p, i);
+        }
+        if (lane == 0) eps[0] = acc;
     }
 }
 
@@ -963,11 +1028,12 @@ struct DmLayout {
     std::vector<DmSector> secs;
     std::vector<DmItem> rho_items, items;
     size_t off_secs, off_state, off_rho, off_items, off_flags, off_count, off_above, off_equal, off_part;
-    size_t off_A, off_V, off_S, off_Q, off_D, off_W, total;
+    size_t off_A, off_V, off_S, off_Q, off_D, off_W, off_order, total;
     int64_t a_round, q_round;  // doubles of one copy of the matrices, of one round's submatrices
     int f_round;               // flags of one round
     int n_pair, n_apply_v;     // items: the pairs, then V updates, then A updates
     int max_rounds;            // rounds per sweep: max over sectors of nb - 1
+    int max_n;
 };
 
 DmLayout dm_layout(const rot_dm_sector* in, int n_sec) {
@@ -976,6 +1042,7 @@ DmLayout dm_layout(const rot_dm_sector* in, int n_sec) {
     int64_t a_off = 0, q_off = 0, w_off = 0, d_off = 0;
     int flag_off = 0;
     L.max_rounds = 1;
+    L.max_n = 0;
     for (int k = 0; k < n_sec; k++) {
         DmSector s{};
         s.n = in[k].n;
@@ -999,6 +1066,7 @@ DmLayout dm_layout(const rot_dm_sector* in, int n_sec) {
         d_off += s.npad;
         flag_off += h;
         L.max_rounds = std::max(L.max_rounds, s.nb - 1);
+        L.max_n = std::max(L.max_n, s.n);
         for (int j = 0; j < tiles; j++)
             for (int i = 0; i <= j; i++) L.rho_items.push_back({k, i, j, 0});
         for (int p = 0; p < h; p++) L.items.push_back({k, p, 0, kItemPair});
@@ -1036,6 +1104,7 @@ DmLayout dm_layout(const rot_dm_sector* in, int n_sec) {
     L.off_Q = take(sizeof(double) * 2 * (size_t)q_off);
     L.off_D = take(sizeof(double) * (size_t)d_off);
     L.off_W = take(sizeof(double) * (size_t)w_off);
+    L.off_order = take(sizeof(int) * (size_t)w_off);
     L.total = o;
     return L;
 }
@@ -1098,6 +1167,9 @@ hipError_t density_basis(const rot_dm_sector* sectors, int n_sec, int64_t m_keep
             e = launch(0, (int)L.items.size());
             if (e != hipSuccess) return e;
         }
+        // asking costs 25 us of idle device, a sweep after the last one (its
+        // workgroups find their sector done) 3 us a launch
+        if (sweep + 1 < kMaxSweeps && (sweep + 1 < kFirstCheck || (sweep + 1 - kFirstCheck) % kCheckEvery)) continue;
         hipLaunchKernelGGL(dm_count_kernel, dim3(1), dim3(256), 0, stream, secs, (const DmState*)g.st,
                            (const int*)g.flags, L.f_round, n_sec, sweep, count);
         e = hipGetLastError();
@@ -1116,9 +1188,13 @@ hipError_t density_basis(const rot_dm_sector* sectors, int n_sec, int64_t m_keep
     int64_t total = 0;
     for (int k = 0; k < n_sec; k++) total += sectors[k].n;
     return prof_timed("dm_sort_select", stream, [&] {
-        hipLaunchKernelGGL(dm_sort_kernel, dim3(n_sec), dim3(256), 0, stream, secs, (const double*)g.diag,
-                           (const double*)g.V, W);
+        int* order = reinterpret_cast<int*>(ws + L.off_order);
+        hipLaunchKernelGGL(dm_sort_kernel, dim3(n_sec), dim3(256), 0, stream, secs, (const double*)g.diag, W, order);
         hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+        hipLaunchKernelGGL(dm_gather_kernel, dim3(n_sec, (unsigned)((L.max_n + kGatherRows - 1) / kGatherRows)), dim3(256),
+                           0, stream, secs, (const double*)g.V, (const int*)order);
+        err = hipGetLastError();
         if (err != hipSuccess) return err;
         hipLaunchKernelGGL(dm_select_kernel, dim3(1), dim3(kSelThreads), 0, stream, secs, n_sec, (const double*)W, m_keep,
                            total, reinterpret_cast<int*>(ws + L.off_above), reinterpret_cast<int*>(ws + L.off_equal),
