@@ -228,21 +228,26 @@ __global__ __launch_bounds__(256) void dm_prep_kernel(const DmSector* __restrict
 // Both return every index to its first slot at the end.
 //
 // Rotation (p, q) zeroes a_pq of J^T S J, J = [[c, s], [-s, c]] on rows and
-// columns (p, q): with d = a_qq - a_pp and r = sqrt(d^2 + 4 a_pq^2),
-// c^2 = (1 + |d| / r) / 2, s = sign(d) a_pq / (r c), t = s / c (|t| <= 1).
+// columns (p, q): with d = a_qq - a_pp, t = s / c = 2 a_pq / (d + sign(d)
+// sqrt(d^2 + 4 a_pq^2)) (|t| <= 1).
 //
-// A step is bound by its chain of LDS round trips and dependent FP64
+// A full step is bound by its chain of LDS round trips and dependent FP64
 // operations, so it has one barrier: each of the 496 two-slot blocks is
 // rotated by one thread, and the 32 blocks that hold the next step's a_pq
 // belong to the lanes of one wave, which go on from the updated entry to the
-// next rotation (square roots by Newton steps from the hardware's estimate;
-// the diagonal lives apart, double-buffered, written by those lanes only).
-// S is held as its upper triangle.  The accumulated Q never touches the LDS:
-// four waves hold 8 slots of every row each in registers and hand one value
-// per neighbour and step on.  1.1 us per step with two barriers and Q in LDS,
-// 0.5 us so; what is left is the LDS: after each barrier all waves read their
-// blocks at once (about 700 of 1250 cycles).  60 sectors of up to 246 states
-// (3 939 in all, 13 sweeps): 7.1 ms before, 3.5 ms now.
+// next rotation (the diagonal lives apart, double-buffered, written by those
+// lanes only).  S is held as its upper triangle.  A cross step holds S in
+// registers (dm_sweep_cross).  The accumulated Q never touches the LDS: four
+// waves hold 8 slots of every row each in registers and hand one value per
+// neighbour and step on.
+// Time of a step, and of 60 sectors of up to 246 states (3 939 in all, 13
+// sweeps): two barriers and Q in the LDS 1.1 us, 7.1 ms; one barrier, Q in
+// registers 0.5 us, 3.5 ms; cross steps in registers and short rotation chains
+// 0.37 us (cross) and 0.6 us (full), 2.7 ms.  A cross step is now bound by the
+// issue of FP64 instructions (890 cycles; 560 for the wave of the rotations
+// alone, 700 without the other waves of S, 770 without those of Q); a round's
+// other 13 us are the launch, the loads and two 64-deep products before the
+// sweep and the stores after it.
 constexpr int kQWaves = 4;
 constexpr int kSWaves = 9;
 constexpr int kPairThreads = 64 * (kQWaves + kSWaves);
@@ -252,37 +257,31 @@ constexpr int kFull = kPair - 1;
 
 struct DmBlocks {
     // blocks (kx, ky), kx <= ky, by thread of the 8 plain S waves, then those of
-    // the next step's pairs by lane, for a full (0) and a cross (1) sweep;
-    // 255: none.  entry: which of (top, top), (top, bottom), (bottom, top),
-    // (bottom, bottom) of (kx, ky) is the next pair's a_pq.
-    unsigned char x[2][512], y[2][512], nx[2][32], ny[2][32], entry[2][32];
+    // the next step's pairs by lane, for a full sweep; 255: none.  entry: which
+    // of (top, top), (top, bottom), (bottom, top), (bottom, bottom) of (kx, ky)
+    // is the next pair's a_pq.
+    unsigned char x[512], y[512], nx[32], ny[32], entry[32];
 };
 
 constexpr DmBlocks dm_blocks() {
     DmBlocks b{};
     for (int k = 0; k < 32; k++) {
-        // full: (top 0, top 1); (top 2, bottom 0); (top k+1, bottom k-1); (bottom 31, bottom 30)
-        b.nx[0][k] = (unsigned char)(k == 0 ? 0 : k == 31 ? 30 : k - 1);
-        b.ny[0][k] = (unsigned char)(k == 0 ? 1 : k == 31 ? 31 : k + 1);
-        b.entry[0][k] = (unsigned char)(k == 0 ? 0 : k == 31 ? 3 : 2);
-        // cross: (top k, bottom k+1); (top 31, bottom 0)
-        b.nx[1][k] = (unsigned char)(k == 31 ? 0 : k);
-        b.ny[1][k] = (unsigned char)(k == 31 ? 31 : k + 1);
-        b.entry[1][k] = (unsigned char)(k == 31 ? 2 : 1);
+        // (top 0, top 1); (top 2, bottom 0); (top k+1, bottom k-1); (bottom 31, bottom 30)
+        b.nx[k] = (unsigned char)(k == 0 ? 0 : k == 31 ? 30 : k - 1);
+        b.ny[k] = (unsigned char)(k == 0 ? 1 : k == 31 ? 31 : k + 1);
+        b.entry[k] = (unsigned char)(k == 0 ? 0 : k == 31 ? 3 : 2);
     }
-    for (int m = 0; m < 2; m++) {
-        int n = 0;
-        for (int ky = 0; ky < 32; ky++)
-            for (int kx = 0; kx <= ky; kx++) {
-                bool next = false;
-                for (int k = 0; k < 32; k++) next = next || (b.nx[m][k] == kx && b.ny[m][k] == ky);
-                if (next) continue;
-                b.x[m][n] = (unsigned char)kx;
-                b.y[m][n] = (unsigned char)ky;
-                n++;
-            }
-        for (; n < 512; n++) b.x[m][n] = b.y[m][n] = 255;
-    }
+    int n = 0;
+    for (int ky = 0; ky < 32; ky++)
+        for (int kx = 0; kx <= ky; kx++) {
+            bool next = false;
+            for (int k = 0; k < 32; k++) next = next || (b.nx[k] == kx && b.ny[k] == ky);
+            if (next) continue;
+            b.x[n] = (unsigned char)kx;
+            b.y[n] = (unsigned char)ky;
+            n++;
+        }
+    for (; n < 512; n++) b.x[n] = b.y[n] = 255;
     return b;
 }
 
@@ -298,31 +297,33 @@ __device__ inline int slot_index(bool full, int k, bool bottom, int u) {
 
 __device__ inline int su(unsigned a, unsigned b) { return (int)(__umul24(min(a, b), kLs) + max(a, b)); }
 
-// 1 / sqrt(x), x in a range without under- or overflow: the hardware's
-// estimate and two Newton steps.
-__device__ inline double dm_rsqrt(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    const double h = 0.5 * x;
-    y = fma(y, fma(-h * y, y, 0.5), y);
-    return fma(y, fma(-h * y, y, 0.5), y);
-}
-
 struct DmRot {
     double c, s;
 };
 
-// The rotation that zeroes apq; the diagonal becomes app - t apq, aqq + t apq.
-__device__ inline DmRot dm_rotation(double& app, double& aqq, double apq, double floor) {
-    DmRot r{1.0, 0.0};
-    if (fabs(apq) > floor) {
-        const double d = aqq - app, y = dm_rsqrt(fma(d, d, 4.0 * apq * apq));
-        const double c2 = fma(0.5 * fabs(d), y, 0.5), z = dm_rsqrt(c2);
-        r.c = c2 * z;
-        r.s = copysign(apq, d < 0.0 ? -apq : apq) * (y * z);
-        const double t = r.s * z;
-        app = fma(-t, apq, app);
-        aqq = fma(t, apq, aqq);
-    }
+// The rotation that zeroes apq, the diagonal entries after it and what is left
+// of apq.  Only c^2 + s^2 = 1 has to hold to the last bit: t comes from single
+// precision (apq and the diagonal's difference are above 2^-52 of a trace in
+// [1, 2), or do not matter) and c = 1 / sqrt(1 + t^2) from that very t in
+// double, by one third-order step from a single-precision start (an error of
+// 2^-22 becomes 2^-66); the 2^-23 of apq that t's rounding leaves behind is
+// kept, not dropped.  The chain through the next pair's entry sets the time of
+// a step: 25 dependent FP64 operations with exact t, 9 so.
+__device__ inline DmRot dm_rotation(double& app, double& aqq, double apq, double floor, double& left) {
+    const double d = aqq - app;
+    const float df = (float)d, af = (float)apq;
+    const float den = fabsf(df) + __builtin_amdgcn_sqrtf(fmaf(df, df, 4.0f * af * af));
+    const float tf = 2.0f * af * __builtin_amdgcn_rcpf(copysignf(den, df));
+    const double t = (double)tf, x = fma(t, t, 1.0), y = (double)__builtin_amdgcn_rsqf(fmaf(tf, tf, 1.0f));
+    const double e = fma(-x, y * y, 1.0);
+    const bool on = fabs(apq) > floor;
+    DmRot r;
+    r.c = on ? fma(y * e, fma(0.375, e, 0.5), y) : 1.0;
+    r.s = on ? t * r.c : 0.0;
+    const double g = fma(r.c, apq, -r.s * d), w = fma(r.c, apq, g);
+    app = fma(-r.s, w, app);
+    aqq = fma(r.s, w, aqq);
+    left = fma(r.c, g, -r.s * r.s * apq);
     return r;
 }
 
@@ -337,76 +338,192 @@ struct DmPairLds {
     int any, work;
 };
 
+// The accumulated Q through a sweep: this wave's eight slots of row `lane`.
 template <bool FULL>
-__device__ __attribute__((always_inline)) inline void dm_sweep(DmPairLds& L, double floor, int tid,
-                                                               double (&qt)[8], double (&qb)[8]) {
-    constexpr int NS = FULL ? kFull : kCross, M = FULL ? 0 : 1;
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (wave < kQWaves) {
-        for (int u = 0; u < NS; u++) {
-            const int cur = u & 1;
+__device__ __attribute__((always_inline)) inline void dm_sweep_q(DmPairLds& L, int wave, int lane, double (&qt)[8],
+                                                                 double (&qb)[8]) {
+    constexpr int NS = FULL ? kFull : kCross;
+    for (int u = 0; u < NS; u++) {
+        const int cur = u & 1;
 #pragma unroll
-            for (int j = 0; j < 8; j++) {
-                const double2 r = L.rot[cur][8 * wave + j];
-                const double a = qt[j], b = qb[j];
-                qt[j] = fma(r.x, a, -r.y * b);
-                qb[j] = fma(r.y, a, r.x * b);
-            }
-            // hand on to the neighbours, move the own ones
-            L.hand[cur][wave][0][lane] = FULL ? qt[0] : qb[0];
-            if (FULL) L.hand[cur][wave][1][lane] = qb[7];
-            __syncthreads();
-            const double up = L.hand[cur][(wave + 1) & 3][0][lane];
-            if (FULL) {
-                const double down = L.hand[cur][(wave + 3) & 3][1][lane];
-                const double t0 = qt[0], t1 = qt[1], last = qb[7];
-#pragma unroll
-                for (int j = 0; j < 7; j++) qt[j] = qt[j + 1];
-                qt[7] = wave == 3 ? last : up;
-#pragma unroll
-                for (int j = 7; j > 0; j--) qb[j] = qb[j - 1];
-                qb[0] = down;
-                if (wave == 0) {
-                    qt[0] = t0;
-                    qb[0] = t1;
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 7; j++) qb[j] = qb[j + 1];
-                qb[7] = up;
-            }
+        for (int j = 0; j < 8; j++) {
+            const double2 r = L.rot[cur][8 * wave + j];
+            const double a = qt[j], b = qb[j];
+            qt[j] = fma(r.x, a, -r.y * b);
+            qb[j] = fma(r.y, a, r.x * b);
         }
+        // hand on to the neighbours, move the own ones
+        L.hand[cur][wave][0][lane] = FULL ? qt[0] : qb[0];
+        if (FULL) L.hand[cur][wave][1][lane] = qb[7];
+        __syncthreads();
+        const double up = L.hand[cur][(wave + 1) & 3][0][lane];
+        if (FULL) {
+            const double down = L.hand[cur][(wave + 3) & 3][1][lane];
+            const double t0 = qt[0], t1 = qt[1], last = qb[7];
+#pragma unroll
+            for (int j = 0; j < 7; j++) qt[j] = qt[j + 1];
+            qt[7] = wave == 3 ? last : up;
+#pragma unroll
+            for (int j = 7; j > 0; j--) qb[j] = qb[j - 1];
+            qb[0] = down;
+            if (wave == 0) {
+                qt[0] = t0;
+                qb[0] = t1;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 7; j++) qb[j] = qb[j + 1];
+            qb[7] = up;
+        }
+    }
+}
+
+// Lane i's x from lane i + 1 (i - 1) of 64, cyclically.
+template <int CTRL>
+__device__ inline double dm_wave_rotate(double x) {
+    const int64_t b = __builtin_bit_cast(int64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, (int64_t)hi << 32 | lo);
+}
+__device__ inline double from_next(double x) { return dm_wave_rotate<0x134>(x); }
+__device__ inline double from_prev(double x) { return dm_wave_rotate<0x13C>(x); }
+
+// S through a cross sweep, in registers: the block between slots ky - m and ky
+// (mod 32) is lane ky's, m = 1..16 spread two to a wave (lanes 32..63 repeat
+// 0..31, which makes the wave's rotation one of 32; m = 16 holds every block
+// twice, once transposed).  A step's moves of the bottoms then are: bottom x
+// bottom to the lane before; top x bottom there too, from m + 1 to m; bottom x
+// top from m to m + 1 in its lane.  Only what crosses from wave to wave goes
+// through the LDS, one value each way.  The wave of m = 1, 2 sees every next
+// a_pq first and goes on from its own rotations without the LDS.
+struct DmCrossBlock {
+    double tt, tb, bt, bb;
+};
+__device__ inline void dm_rotate_block(DmCrossBlock& x, double cx, double sx, double cy, double sy) {
+    const double u1 = fma(cx, x.tt, -sx * x.bt), x1 = fma(sx, x.tt, cx * x.bt);
+    const double v1 = fma(cx, x.tb, -sx * x.bb), y1 = fma(sx, x.tb, cx * x.bb);
+    x.tt = fma(cy, u1, -sy * v1);
+    x.tb = fma(sy, u1, cy * v1);
+    x.bt = fma(cy, x1, -sy * y1);
+    x.bb = fma(sy, x1, cy * y1);
+}
+
+constexpr int kCrossWaves = 8;
+
+__device__ __attribute__((always_inline)) inline void dm_sweep_cross(DmPairLds& L, double floor, int wave, int lane) {
+    const int w = wave == kParamWave ? 0 : wave < kParamWave ? wave - kQWaves + 1 : wave - kQWaves;
+    if (w >= kCrossWaves) {
+        for (int u = 0; u < kCross; u++) __syncthreads();
         return;
     }
+    const int l = lane & 31, ma = 2 * w + 1, ka = (l - ma) & 31, kb = (l - ma - 1) & 31;
+    // what waves hand on: bottom x top up to the next m, top x bottom down
+    double(*up)[kCrossWaves][32] = reinterpret_cast<double(*)[kCrossWaves][32]>(L.L1);
+    double(*down)[kCrossWaves][32] = reinterpret_cast<double(*)[kCrossWaves][32]>(L.R2);
+    static_assert(2 * kCrossWaves * 32 <= kPair * kHalf, "handing on fits the operands' place");
+    auto get = [&](int k) {
+        return DmCrossBlock{L.S[su(k, l)], L.S[su(k, 32 + l)], L.S[su(32 + k, l)], L.S[su(32 + k, 32 + l)]};
+    };
+    DmCrossBlock a = get(ka), b = get(kb);
+    if (w == 0) {
+        __builtin_amdgcn_s_setprio(3);  // the step waits for this wave
+        const double2 r0 = L.rot[0][l];
+        double c = r0.x, sn = r0.y, app = L.D[0][l], aqq = L.D[0][32 + l];
+        double left = L.S[su(l, 32 + l)], apq = 0.0;  // the pair's entry after its rotation, the next one's before
+        for (int u = 0; u < kCross; u++) {
+            const int cur = u & 1;
+            const double c1 = from_prev(c), s1 = from_prev(sn), c2 = from_prev(c1), s2 = from_prev(s1);
+            if (u) b.tb = down[cur][1][(l + 1) & 31];
+            dm_rotate_block(a, c1, s1, c, sn);
+            apq = from_next(a.tb);
+            aqq = from_next(aqq);
+            a.bb = from_next(a.bb);
+            dm_rotate_block(b, c2, s2, c, sn);
+            a.tb = from_next(b.tb);
+            b.bb = from_next(b.bb);
+            up[cur ^ 1][0][l] = b.bt;
+            b.bt = a.bt;
+            a.bt = left;
+            if (u + 1 < kCross) {
+                const DmRot r = dm_rotation(app, aqq, apq, floor, left);
+                c = r.c;
+                sn = r.s;
+                L.rot[cur ^ 1][l] = double2{c, sn};
+                if (sn != 0.0) L.any = 1;
+            }
+            __syncthreads();
+        }
+        b.tb = down[kCross & 1][1][(l + 1) & 31];
+        __builtin_amdgcn_s_setprio(0);
+        L.D[kCross & 1][l] = app;
+        L.D[kCross & 1][32 + l] = aqq;
+        L.S[su(l, 32 + l)] = apq;
+    } else {
+        const bool end = w == kCrossWaves - 1;
+        const double* above = end ? &up[0][w][0] : &down[0][w + 1][0];
+        const int at = end ? l ^ 16 : (l + 1) & 31;
+        constexpr int kStep = kCrossWaves * 32;  // from one step's values to the other's
+        for (int u = 0; u < kCross; u++) {
+            const int cur = u & 1;
+            const double2 ry = L.rot[cur][l], ra = L.rot[cur][ka], rb = L.rot[cur][kb];
+            if (u) {
+                a.bt = up[cur][w - 1][l];
+                b.tb = above[cur * kStep + at];
+            }
+            dm_rotate_block(a, ra.x, ra.y, ry.x, ry.y);
+            dm_rotate_block(b, rb.x, rb.y, ry.x, ry.y);
+            // the end hands its own bottom x top over transposed
+            up[cur ^ 1][w][l] = end ? a.bt : b.bt;
+            down[cur ^ 1][w][l] = a.tb;
+            a.bb = from_next(a.bb);
+            a.tb = from_next(b.tb);
+            b.bb = from_next(b.bb);
+            b.bt = a.bt;
+            __syncthreads();
+        }
+        a.bt = up[kCross & 1][w - 1][l];
+        b.tb = above[(kCross & 1) * kStep + at];
+    }
+    auto put = [&](int k, const DmCrossBlock& x) {
+        L.S[su(k, l)] = x.tt;
+        L.S[su(k, 32 + l)] = x.tb;
+        L.S[su(32 + k, l)] = x.bt;
+        L.S[su(32 + k, 32 + l)] = x.bb;
+    };
+    if (lane < 32) {
+        put(ka, a);
+        if (w + 1 < kCrossWaves || l >= 16) put(kb, b);
+    }
+}
+
+// S through a full sweep, in the LDS.
+__device__ __attribute__((always_inline)) inline void dm_sweep_full(DmPairLds& L, double floor, int wave, int lane) {
+    constexpr int NS = kFull;
     const bool param = wave == kParamWave;
     const int plain = (wave - kQWaves - (wave > kParamWave ? 1 : 0)) * 64 + lane;
     unsigned kx, ky, entry = 0;
     if (param) {
-        kx = lane < 32 ? kDmBlocks.nx[M][lane] : 255;
-        ky = lane < 32 ? kDmBlocks.ny[M][lane] : 255;
-        entry = kDmBlocks.entry[M][lane & 31];
+        kx = lane < 32 ? kDmBlocks.nx[lane] : 255;
+        ky = lane < 32 ? kDmBlocks.ny[lane] : 255;
+        entry = kDmBlocks.entry[lane & 31];
         __builtin_amdgcn_s_setprio(3);  // the step waits for this wave
     } else {
-        kx = kDmBlocks.x[M][plain];
-        ky = kDmBlocks.y[M][plain];
+        kx = kDmBlocks.x[plain];
+        ky = kDmBlocks.y[plain];
     }
     const bool live = kx < 32, diagonal = kx == ky;
     if (!live) kx = ky = 0;
     // this thread's indices, and (lanes of the next rotations) the next pair's,
     // carried from step to step
-    unsigned px = slot_index(FULL, kx, false, 0), qx = slot_index(FULL, kx, true, 0);
-    unsigned py = slot_index(FULL, ky, false, 0), qy = slot_index(FULL, ky, true, 0);
-    unsigned p = slot_index(FULL, lane & 31, false, 1), q = slot_index(FULL, lane & 31, true, 1);
-    auto advance = [](unsigned i, bool bottom) -> unsigned {
-        if (FULL) return i == 0 ? 0 : i == 63 ? 1 : i + 1;
-        return bottom ? 32 + ((i + 1) & 31) : i;
-    };
+    unsigned px = slot_index(true, kx, false, 0), qx = slot_index(true, kx, true, 0);
+    unsigned py = slot_index(true, ky, false, 0), qy = slot_index(true, ky, true, 0);
+    unsigned p = slot_index(true, lane & 31, false, 1), q = slot_index(true, lane & 31, true, 1);
+    auto advance = [](unsigned i) -> unsigned { return i == 0 ? 0 : i == 63 ? 1 : i + 1; };
     for (int u = 0; u < NS; u++) {
         const int cur = u & 1;
         if (live) {
-            if (diagonal) {
-                if (L.rot[cur][kx].y != 0.0) L.S[su(px, qx)] = 0.0;
-            } else {
+            if (!diagonal) {
                 const int iu = su(px, py), iv = su(px, qy), ix = su(qx, py), iy = su(qx, qy);
                 const double2 rx = L.rot[cur][kx], ry = L.rot[cur][ky];
                 double u0 = L.S[iu], v0 = L.S[iv], x0 = L.S[ix], y0 = L.S[iy];
@@ -430,19 +547,23 @@ __device__ __attribute__((always_inline)) inline void dm_sweep(DmPairLds& L, dou
                 if (param) {
                     const double apq = entry & 2 ? (entry & 1 ? y0 : x0) : (entry & 1 ? v0 : u0);
                     DmRot r{1.0, 0.0};
-                    if (u + 1 < NS) r = dm_rotation(app, aqq, apq, floor);
+                    if (u + 1 < NS) {
+                        double left;
+                        r = dm_rotation(app, aqq, apq, floor, left);
+                        L.S[su(p, q)] = left;
+                    }
                     L.rot[cur ^ 1][lane] = double2{r.c, r.s};
                     L.D[cur ^ 1][p] = app;
                     L.D[cur ^ 1][q] = aqq;
                     if (r.s != 0.0) L.any = 1;
-                    p = advance(p, false);
-                    q = advance(q, true);
+                    p = advance(p);
+                    q = advance(q);
                 }
             }
-            px = advance(px, false);
-            qx = advance(qx, true);
-            py = advance(py, false);
-            qy = advance(qy, true);
+            px = advance(px);
+            qx = advance(qx);
+            py = advance(py);
+            qy = advance(qy);
         }
         __syncthreads();
     }
@@ -622,7 +743,9 @@ __device__ inline void dm_pair(const DmSector& s, int sec, int k, const DmClock&
     if (tid < 32) {
         const int p = slot_index(full, tid, false, 0), q = slot_index(full, tid, true, 0);
         double app = L.S[p * kLs + p], aqq = L.S[q * kLs + q];
-        const DmRot r = dm_rotation(app, aqq, L.S[su(p, q)], floor);
+        double left;
+        const DmRot r = dm_rotation(app, aqq, L.S[su(p, q)], floor, left);
+        L.S[su(p, q)] = left;
         L.rot[0][tid] = double2{r.c, r.s};
         L.D[0][p] = app;
         L.D[0][q] = aqq;
@@ -636,8 +759,15 @@ __device__ inline void dm_pair(const DmSector& s, int sec, int k, const DmClock&
         qb[j] = slot_index(full, 8 * (wave & 3) + j, true, 0) == lane ? 1.0 : 0.0;
     }
     __syncthreads();
-    if (full) dm_sweep<true>(L, floor, tid, qt, qb);
-    else dm_sweep<false>(L, floor, tid, qt, qb);
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    if (full) {
+        if (wv < kQWaves) dm_sweep_q<true>(L, wv, lane, qt, qb);
+        else dm_sweep_full(L, floor, wv, lane);
+    } else {
+        if (wv < kQWaves) dm_sweep_q<false>(L, wv, lane, qt, qb);
+        else dm_sweep_cross(L, floor, wv, lane);
+        __syncthreads();
+    }
     const int last = (full ? kFull : kCross) & 1;
     for (int e = tid; e < kPair * kPair; e += kPairThreads) {
         const int x = e >> 6, y = e & 63;
