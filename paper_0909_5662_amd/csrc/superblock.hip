@@ -10,10 +10,10 @@
 //   operator on B:  out_seg += w coef O_B(q' <- q) psi_seg        (K = dim q)
 //   operator on B~: out_seg += w coef psi_seg O_B~(p' <- p)^T      (K = dim p)
 //   site terms only: out_seg += w coef psi_seg
-// The plan cuts every output segment into 32 x 32 tiles and lists, per tile and
-// in term order, every contribution reaching it; one workgroup computes one
-// tile from its list and writes it once, so the sum has a fixed order and
-// needs no atomics.
+// The plan lists, per output segment and in term order, every contribution
+// reaching it, and cuts the segment into square tiles; one wave computes one
+// tile from the segment's list and writes it once, so the sum has a fixed order
+// and needs no atomics.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -31,186 +31,215 @@
 namespace rot {
 namespace {
 
-constexpr int kSbTile = 32;
 constexpr int kSbMaxSite = 16;
 
 enum : int { kFromLeft = 0, kFromRight = 1, kCopy = 2 };
 
-struct SbContrib {
-    int kind, K;
+constexpr int kSbKs = 16;  // k per step
+
+// A step of a segment's sum: 16 k of a product, or a scaled copy.  Offsets are
+// those of the segment's first row and column and of the step's first k.
+struct SbStep {
     double alpha;
-    int64_t a_off, lda;  // left: operator block (rows of the tile); right, copy: psi
-    int64_t b_off, ldb;  // left: psi (columns of the tile); right: operator block (rows = tile columns)
+    int64_t a_off;  // left: operator block (rows of the segment); right, copy: psi
+    int64_t b_off;  // left: psi (columns of the segment); right: operator block (rows = segment columns)
+    int lda, ldb;
+    // kind; k below lo and from hi on count as zero (a last step of a longer
+    // product starts 16 before its end, and lo cuts what the step before it
+    // took); hi < 16: shorter products, nothing is read from hi on
+    int kind, lo_hi;
 };
 
 struct SbTile {
-    int64_t out_off, ldo;
-    int rows, cols;
-    int c_begin, c_end;
+    int64_t out_off, ldo;  // of the tile
+    int r0, c0, rows, cols;
+    int s_begin, s_end;
 };
-
-// C (rows x cols, 32 x 32 at most) = sum of the tile's contributions.  Wave w
-// owns the 16 x 16 quarter (w / 2, w % 2) and multiplies with
-// v_mfma_f64_16x16x4f64 (lane l supplies A(row l%16, k l/16) and B(k l/16,
-// col l%16); accumulator element v is C(4v + l/16, l%16)).  The contributions
-// are walked as one sequence of steps (a 32-wide K slice of a product, or a
-// scaled copy); the raw operands of the steps one and two ahead are loaded into
-// two register sets while the current one is multiplied from LDS (two LDS
-// buffers, one barrier per product step), and the step descriptors are read
-// from LDS.
-constexpr int kSbKs = 32;
-constexpr int kSbMaxC = 128;  // contribution descriptors held in LDS at a time
 
 typedef double sb_f64x4 __attribute__((ext_vector_type(4)));
+typedef double sb_f64x2 __attribute__((ext_vector_type(2)));
+typedef sb_f64x2 sb_f64x2u __attribute__((aligned(8)));
+typedef int sb_i32x4 __attribute__((ext_vector_type(4)));
 
-struct SbStep {
-    int ci, k0;
+// One step's operands of a wave: for a product, four consecutive k per lane of
+// NB 16-row blocks of A and of B; for a copy, the psi entries of the lane's
+// accumulator rows (those of blocks (0, j) in a[j], of (1, j) in b[j]).
+template <int NB>
+struct SbSet {
+    sb_f64x4 a[NB], b[NB];
+    double alpha;
+    int kind, lo_hi;
 };
 
-// Raw operands of step (c, k0) into registers: for a product, this thread's
-// four elements of the A slice (tile row r, slice column k) and of the B
-// slice; for a copy, the psi entries of this lane's four accumulator rows (in
-// av).  Every load is unconditional, from the element's own address when it
-// lies inside the slice and from the slice's first element otherwise, and
-// nothing is computed from the values here, so the loads stay in flight until
-// the step is used; scaling and zeroing happen then (sb_stage, sb_copy).
-__device__ __attribute__((always_inline)) inline void sb_load(const SbContrib& c, int k0, const SbTile& tl,
-                                                              const double* left_blk, const double* right_blk,
-                                                              const double* psi, int tid, int wr, int wc, int h,
-                                                              int cl, sb_f64x4& av, sb_f64x4& bv) {
-    if (c.kind == kCopy) {
-        const int col = wc * 16 + cl, r0 = wr * 16 + h;
-        const bool cin = col < tl.cols;
-        const double* src = psi + c.a_off;
-        av.x = src[(cin && r0 < tl.rows) ? (int64_t)r0 * c.lda + col : 0];
-        av.y = src[(cin && r0 + 4 < tl.rows) ? (int64_t)(r0 + 4) * c.lda + col : 0];
-        av.z = src[(cin && r0 + 8 < tl.rows) ? (int64_t)(r0 + 8) * c.lda + col : 0];
-        av.w = src[(cin && r0 + 12 < tl.rows) ? (int64_t)(r0 + 12) * c.lda + col : 0];
-        return;
-    }
-    const double* A = c.kind == kFromLeft ? left_blk + c.a_off : psi + c.a_off;
-    const double* B = c.kind == kFromLeft ? psi + c.b_off : right_blk + c.b_off;
-    const bool left = c.kind == kFromLeft;
-    // element j of this thread: e = tid + 256 j, A row e >> 5 (col e & 31);
-    // B: left, slice row e >> 5 and tile column e & 31; right (B^T stored),
-    // tile column e >> 5 and slice row e & 31
-    const int hi = tid >> 5, lo = tid & 31;
-    double a[4], b[4];
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const int r = hi + 8 * j;
-        a[j] = A[(r < tl.rows && k0 + lo < c.K) ? (int64_t)r * c.lda + k0 + lo : 0];
-        b[j] = B[left ? ((lo < tl.cols && k0 + r < c.K) ? (int64_t)(k0 + r) * c.ldb + lo : 0)
-                      : ((r < tl.cols && k0 + lo < c.K) ? (int64_t)r * c.ldb + k0 + lo : 0)];
-    }
-    av = sb_f64x4{a[0], a[1], a[2], a[3]};
-    bv = sb_f64x4{b[0], b[1], b[2], b[3]};
+__device__ inline int64_t sb_lane64(int lo, int hi, int l) {
+    return (int64_t)(uint32_t)__builtin_amdgcn_readlane(lo, l) | (int64_t)__builtin_amdgcn_readlane(hi, l) << 32;
 }
 
-// A copy step: alpha times the raw psi entries of this lane's accumulator rows
-// (zero outside the tile), as loaded by sb_load.
-__device__ __attribute__((always_inline)) inline sb_f64x4 sb_copy(const SbContrib& c, const SbTile& tl,
-                                                                  const sb_f64x4& av, int wr, int wc, int h,
-                                                                  int cl) {
-    const int col = wc * 16 + cl, r0 = wr * 16 + h;
-    const bool cin = col < tl.cols;
-    return sb_f64x4{(cin && r0 < tl.rows) ? c.alpha * av.x : 0.0, (cin && r0 + 4 < tl.rows) ? c.alpha * av.y : 0.0,
-                    (cin && r0 + 8 < tl.rows) ? c.alpha * av.z : 0.0,
-                    (cin && r0 + 12 < tl.rows) ? c.alpha * av.w : 0.0};
-}
-
-// A product step's slices into LDS: A scaled by alpha, both zero outside the
-// slice (the raw values there came from the slice's first element).
-__device__ __attribute__((always_inline)) inline void sb_stage(double (*As)[kSbTile + 1], double (*Bs)[kSbTile + 1],
-                                                              const SbContrib& c, int k0, const SbTile& tl,
-                                                              const sb_f64x4& av, const sb_f64x4& bv, int tid) {
-    const int hi = tid >> 5, lo = tid & 31;
-    const bool left = c.kind == kFromLeft;
-    const double a[4] = {av.x, av.y, av.z, av.w}, b[4] = {bv.x, bv.y, bv.z, bv.w};
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const int r = hi + 8 * j;
-        As[lo][r] = (r < tl.rows && k0 + lo < c.K) ? c.alpha * a[j] : 0.0;
-        if (left)
-            Bs[r][lo] = (lo < tl.cols && k0 + r < c.K) ? b[j] : 0.0;
-        else
-            Bs[lo][r] = (r < tl.cols && k0 + lo < c.K) ? b[j] : 0.0;
-    }
-}
-
-// position after step x of the chunk [.., ce) whose descriptors start at cd[0] (index cb)
-__device__ __attribute__((always_inline)) inline SbStep sb_next(const SbContrib* cd, int cb, int ce, SbStep x) {
-    if (x.ci >= ce) return x;
-    const SbContrib& c = cd[x.ci - cb];
-    return (c.kind == kCopy || x.k0 + kSbKs >= c.K) ? SbStep{x.ci + 1, 0} : SbStep{x.ci, x.k0 + kSbKs};
-}
-
-__global__ __launch_bounds__(256) void sb_tile_kernel(const SbTile* __restrict__ tiles,
-                                                      const SbContrib* __restrict__ contribs,
+// C (16 NB x 16 NB at most) = sum of the segment's steps, one wave per tile.
+// A state of 1024 + 1024 states has short segments and about 19 steps per tile,
+// so the waves share nothing and meet at no barrier: operands go straight from
+// the L2 to the registers of v_mfma_f64_16x16x4f64 in its own layout (lane l
+// supplies A(l%16, k) and B(k, l%16), k = 4 (l/16) + j at instruction j, so that
+// k-contiguous operands are read 32 bytes per lane; element v of the result is
+// C(4 v + l/16, l%16)), and three register sets keep as many steps in flight.
+// The plan lists the steps; 64 at a time are fetched, one per lane, and handed
+// out by lane reads.  Rows and columns past the tile repeat its last one and are
+// not stored.  Bound by the instructions around a step's four (NB = 2: sixteen)
+// products.  Before, one 32 x 32 tile per workgroup through the LDS, 32 k per
+// barrier; now, at 400 / 1024 / 2000 / 3500 states: 17.2 / 32.1 / 113 / 337 ->
+// 10.8 / 25.0 / 95 / 229 us.  Not faster at 1024 states: loads through bounded
+// descriptors instead of clamped addresses 26.9 us, turning k-contiguous
+// operands through the wave's own LDS 37.0, 16 k per barrier with four steps in
+// flight 29.4, tiles grouped by XCD 26.8.
+template <int NB>
+__global__ __launch_bounds__(256) void sb_tile_kernel(const SbTile* __restrict__ tiles, int n_tiles,
+                                                      const SbStep* __restrict__ steps,
                                                       const double* __restrict__ left_blk,
                                                       const double* __restrict__ right_blk,
                                                       const double* __restrict__ psi, double* __restrict__ out) {
-    const SbTile tl = tiles[blockIdx.x];
-    __shared__ double As[2][kSbKs][kSbTile + 1];  // [buf][k][row]
-    __shared__ double Bs[2][kSbKs][kSbTile + 1];  // [buf][k][col]
-    __shared__ SbContrib cd[kSbMaxC];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int wr = w >> 1, wc = w & 1, h = lane >> 4, cl = lane & 15;
-    sb_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-    sb_f64x4 a0, b0, a1, b1;
-    int buf = 0;
-// one step from register set (A, B); the set is then refilled with step REFILL
-#define SB_RUN(A, B, X, REFILL)                                                                            \
-    do {                                                                                                      \
-        const SbContrib& c_ = cd[(X).ci - cb];                                                                \
-        if (c_.kind == kCopy) {                                                                               \
-            acc += sb_copy(c_, tl, A, wr, wc, h, cl);                                                         \
-            if ((REFILL).ci < ce)                                                                             \
-                sb_load(cd[(REFILL).ci - cb], (REFILL).k0, tl, left_blk, right_blk, psi, tid, wr, wc, h, cl, A, \
-                        B);                                                                                \
-        } else {                                                                                              \
-            sb_stage(As[buf], Bs[buf], c_, (X).k0, tl, A, B, tid);                                            \
-            __syncthreads();                                                                                  \
-            const int kq = (min(kSbKs, c_.K - (X).k0) + 3) >> 2;                                              \
-            if ((REFILL).ci < ce)                                                                             \
-                sb_load(cd[(REFILL).ci - cb], (REFILL).k0, tl, left_blk, right_blk, psi, tid, wr, wc, h, cl, A, \
-                        B);                                                                                \
-            for (int q = 0; q < kq; q++) {                                                                    \
-                const double a_ = As[buf][4 * q + h][wr * 16 + cl];                                           \
-                const double b_ = Bs[buf][4 * q + h][wc * 16 + cl];                                           \
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a_, b_, acc, 0, 0, 0);                             \
-            }                                                                                                 \
-            buf ^= 1;                                                                                         \
-        }                                                                                                     \
-    } while (0)
-    for (int cb = tl.c_begin; cb < tl.c_end; cb += kSbMaxC) {
-        const int ce = min(cb + kSbMaxC, tl.c_end);
-        __syncthreads();  // the previous chunk's descriptors are no longer read
-        for (int i = tid; i < ce - cb; i += 256) cd[i] = contribs[cb + i];
-        __syncthreads();
-        SbStep cur{cb, 0};
-        SbStep s1 = sb_next(cd, cb, ce, cur);
-        sb_load(cd[0], 0, tl, left_blk, right_blk, psi, tid, wr, wc, h, cl, a0, b0);
-        if (s1.ci < ce) sb_load(cd[s1.ci - cb], s1.k0, tl, left_blk, right_blk, psi, tid, wr, wc, h, cl, a1, b1);
-        SbStep ld = sb_next(cd, cb, ce, s1);
-        while (true) {
-            SB_RUN(a0, b0, cur, ld);
-            cur = sb_next(cd, cb, ce, cur);
-            ld = sb_next(cd, cb, ce, ld);
-            if (cur.ci >= ce) break;
-            SB_RUN(a1, b1, cur, ld);
-            cur = sb_next(cd, cb, ce, cur);
-            ld = sb_next(cd, cb, ce, ld);
-            if (cur.ci >= ce) break;
-        }
-    }
-#undef SB_RUN
+    const int t = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (t >= n_tiles) return;
+    const SbTile tl = tiles[t];
+    const int lane = threadIdx.x & 63, h = lane >> 4, cl = lane & 15;
+    int row[NB], col[NB];  // operand rows of this lane, inside the segment
 #pragma unroll
-    for (int v = 0; v < 4; v++) {
-        const int r = wr * 16 + 4 * v + h, col = wc * 16 + cl;
-        if (r < tl.rows && col < tl.cols) out[tl.out_off + r * tl.ldo + col] = acc[v];
+    for (int i = 0; i < NB; i++) {
+        row[i] = tl.r0 + min(16 * i + cl, tl.rows - 1);
+        col[i] = tl.c0 + min(16 * i + cl, tl.cols - 1);
     }
+    sb_f64x4 acc[NB][NB];
+#pragma unroll
+    for (int i = 0; i < NB; i++)
+#pragma unroll
+        for (int j = 0; j < NB; j++) acc[i][j] = sb_f64x4{0.0, 0.0, 0.0, 0.0};
+    // lane l's step: the l-th of the 64 from `base` on
+    sb_i32x4 d0 = {0, 0, 0, 0}, d1 = {0, 0, 0, 0};
+    int d8 = 0, d9 = 0;
+    int base = tl.s_begin, next = tl.s_begin;
+    auto fetch = [&]() __attribute__((always_inline)) {
+        const int* p = reinterpret_cast<const int*>(steps + min(base + lane, tl.s_end - 1));
+        d0 = sb_i32x4{p[0], p[1], p[2], p[3]};
+        d1 = sb_i32x4{p[4], p[5], p[6], p[7]};
+        d8 = p[8];
+        d9 = p[9];
+    };
+    if (next < tl.s_end) fetch();
+    auto load = [&](SbSet<NB>& s) __attribute__((always_inline)) {
+        if (next >= tl.s_end) return;
+        if (next - base == 64) {
+            base += 64;
+            fetch();
+        }
+        const int l = next - base;
+        next++;
+        s.alpha = __builtin_bit_cast(double, sb_lane64(d0[0], d0[1], l));
+        const int64_t a_off = sb_lane64(d0[2], d0[3], l), b_off = sb_lane64(d1[0], d1[1], l);
+        const int lda = __builtin_amdgcn_readlane(d1[2], l), ldb = __builtin_amdgcn_readlane(d1[3], l);
+        s.kind = __builtin_amdgcn_readlane(d8, l);
+        s.lo_hi = __builtin_amdgcn_readlane(d9, l);
+        if (s.kind == kCopy) {
+            const double* p = psi + a_off;
+#pragma unroll
+            for (int i = 0; i < NB; i++)
+#pragma unroll
+                for (int j = 0; j < NB; j++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        const int r = tl.r0 + min(16 * i + 4 * e + h, tl.rows - 1);
+                        (i == 0 ? s.a[j] : s.b[j])[e] = p[(int64_t)r * lda + col[j]];
+                    }
+            return;
+        }
+        const bool left = s.kind == kFromLeft;
+        const double *A = (left ? left_blk : psi) + a_off, *B = (left ? psi : right_blk) + b_off;
+        const int hi = s.lo_hi >> 8;
+        if (hi == kSbKs) {
+            auto four = [&](const double* q) __attribute__((always_inline)) {
+                const sb_f64x2 x = *reinterpret_cast<const sb_f64x2u*>(q), y = *reinterpret_cast<const sb_f64x2u*>(q + 2);
+                return sb_f64x4{x[0], x[1], y[0], y[1]};
+            };
+#pragma unroll
+            for (int i = 0; i < NB; i++) s.a[i] = four(A + (int64_t)row[i] * lda + 4 * h);
+            if (left) {
+                const double* q = B + (int64_t)(4 * h) * ldb;
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+#pragma unroll
+                    for (int i = 0; i < NB; i++) s.b[i][e] = q[(int64_t)e * ldb + col[i]];
+            } else {
+#pragma unroll
+                for (int i = 0; i < NB; i++) s.b[i] = four(B + (int64_t)col[i] * ldb + 4 * h);
+            }
+        } else {
+            const int64_t bk = left ? ldb : 1, br = left ? 1 : ldb;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const int k = min(4 * h + e, hi - 1);
+#pragma unroll
+                for (int i = 0; i < NB; i++) {
+                    s.a[i][e] = A[(int64_t)row[i] * lda + k];
+                    s.b[i][e] = B[k * bk + col[i] * br];
+                }
+            }
+        }
+    };
+    auto run = [&](SbSet<NB>& s) __attribute__((always_inline)) {
+        if (s.kind == kCopy) {
+#pragma unroll
+            for (int i = 0; i < NB; i++)
+#pragma unroll
+                for (int j = 0; j < NB; j++) acc[i][j] += s.alpha * (i == 0 ? s.a[j] : s.b[j]);
+            return;
+        }
+        if (s.lo_hi != kSbKs << 8) {
+            const int lo = s.lo_hi & 255, hi = s.lo_hi >> 8;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const bool in = 4 * h + e >= lo && 4 * h + e < hi;
+#pragma unroll
+                for (int i = 0; i < NB; i++) {
+                    s.a[i][e] = in ? s.a[i][e] : 0.0;
+                    s.b[i][e] = in ? s.b[i][e] : 0.0;
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+#pragma unroll
+            for (int i = 0; i < NB; i++)
+#pragma unroll
+                for (int j = 0; j < NB; j++)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(s.alpha * s.a[i][e], s.b[j][e], acc[i][j], 0, 0, 0);
+    };
+    SbSet<NB> s0, s1, s2;
+    load(s0);
+    load(s1);
+    load(s2);
+    for (int n = tl.s_end - tl.s_begin; n > 0; n -= 3) {
+        run(s0);
+        load(s0);
+        if (n == 1) break;
+        run(s1);
+        load(s1);
+        if (n == 2) break;
+        run(s2);
+        load(s2);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; i++)
+#pragma unroll
+        for (int j = 0; j < NB; j++)
+#pragma unroll
+            for (int v = 0; v < 4; v++) {
+                const int r = 16 * i + 4 * v + h, c = 16 * j + cl;
+                if (r < tl.rows && c < tl.cols) out[tl.out_off + r * tl.ldo + c] = acc[i][j][v];
+            }
 }
+
+// 32 x 32 tiles read half as much and issue less per product, and pay once
+// there are two waves of them for each SIMD (16 / 32 wide: 1024 states, 1076
+// tiles, 25 / 34 us; 2000 states, 111 / 95; 3500 states, 6880 tiles, 314 / 229).
+constexpr int64_t kSbWideTiles = 2048;
 
 rot_status sberr(rot_status s, const char* fmt, ...) {
     char buf[512];
@@ -344,9 +373,9 @@ rot_status validate_sb(const rot_sb_problem* p) {
     return ROT_OK;
 }
 
-// Output tiles and their contributions, in block, segment, tile and then term
-// order (site states of the term's sums in ascending order).
-void build_work(const rot_sb_problem* p, std::vector<SbTile>& tiles, std::vector<SbContrib>& cs, double& flops,
+// Output segments (as one tile each) and their contributions, in block, segment
+// and then term order (site states of the term's sums in ascending order).
+void build_work(const rot_sb_problem* p, std::vector<SbTile>& segments, std::vector<SbStep>& st, double& flops,
                 int64_t& total) {
     const Enlarged sys = enlarge(p->d, p->site_qn, p->n_left, p->left);
     const Enlarged env = enlarge(p->d, p->site_qn, p->n_right, p->right);
@@ -374,74 +403,77 @@ void build_work(const rot_sb_problem* p, std::vector<SbTile>& tiles, std::vector
             const Qn qo{p->left[rs.sec].n_up, p->left[rs.sec].n_dn};
             for (const Seg& csg : env.segs.at(P)) {
                 const Qn po{p->right[csg.sec].n_up, p->right[csg.sec].n_dn};
-                for (int r0 = 0; r0 < rs.dim; r0 += kSbTile)
-                    for (int c0 = 0; c0 < csg.dim; c0 += kSbTile) {
-                        SbTile tl{};
-                        tl.out_off = ob.offset + (int64_t)(rs.start + r0) * ob.cols + csg.start + c0;
-                        tl.ldo = ob.cols;
-                        tl.rows = std::min(kSbTile, rs.dim - r0);
-                        tl.cols = std::min(kSbTile, csg.dim - c0);
-                        tl.c_begin = (int)cs.size();
-                        for (int l = 0; l < p->n_terms; l++) {
-                            const rot_sb_term& t = p->terms[l];
-                            const int lo = t.left_op, ro = t.right_op;
-                            const Qn qs{qo.first - (lo >= 0 ? p->left_shift[2 * lo] : 0),
-                                        qo.second - (lo >= 0 ? p->left_shift[2 * lo + 1] : 0)};
-                            const Qn ps{po.first - (ro >= 0 ? p->right_shift[2 * ro] : 0),
-                                        po.second - (ro >= 0 ? p->right_shift[2 * ro + 1] : 0)};
-                            auto kq = lsec.find(qs);
-                            auto kp = rsec.find(ps);
-                            if (kq == lsec.end() || kp == rsec.end()) continue;
-                            int64_t op_off = -1;
-                            if (lo >= 0) op_off = p->left_off[(int64_t)lo * p->n_left + kq->second];
-                            if (ro >= 0) op_off = p->right_off[(int64_t)ro * p->n_right + kp->second];
-                            if ((lo >= 0 || ro >= 0) && op_off < 0) continue;
-                            for (int sa = 0; sa < d; sa++) {
-                                const double wa = t.site_a ? t.site_a[rs.site * d + sa] : (sa == rs.site ? 1.0 : 0.0);
-                                if (wa == 0.0) continue;
-                                for (int ta = 0; ta < d; ta++) {
-                                    const double wt = t.site_at ? t.site_at[csg.site * d + ta] : (ta == csg.site ? 1.0 : 0.0);
-                                    if (wt == 0.0) continue;
-                                    const Qn Qs{qs.first + qn[2 * sa], qs.second + qn[2 * sa + 1]};
-                                    const Qn Ps{ps.first + qn[2 * ta], ps.second + qn[2 * ta + 1]};
-                                    auto sb = block_of.find(Qs);
-                                    if (sb == block_of.end()) continue;
-                                    const Block& src = *sb->second;
-                                    const int rstart = seg_start(sys, Qs, sa, kq->second);
-                                    const int cstart = seg_start(env, Ps, ta, kp->second);
-                                    if (rstart < 0 || cstart < 0) continue;
-                                    SbContrib c{};
-                                    c.alpha = t.coef * wa * wt;
-                                    if (lo >= 0) {
-                                        const int K = p->left[kq->second].dim;
-                                        c.kind = kFromLeft;
-                                        c.K = K;
-                                        c.a_off = op_off + (int64_t)r0 * K;
-                                        c.lda = K;
-                                        c.b_off = src.offset + (int64_t)rstart * src.cols + cstart + c0;
-                                        c.ldb = src.cols;
-                                    } else if (ro >= 0) {
-                                        const int K = p->right[kp->second].dim;
-                                        c.kind = kFromRight;
-                                        c.K = K;
-                                        c.a_off = src.offset + (int64_t)(rstart + r0) * src.cols + cstart;
-                                        c.lda = src.cols;
-                                        c.b_off = op_off + (int64_t)c0 * K;
-                                        c.ldb = K;
-                                    } else {
-                                        c.kind = kCopy;
-                                        c.K = 1;
-                                        c.a_off = src.offset + (int64_t)(rstart + r0) * src.cols + cstart + c0;
-                                        c.lda = src.cols;
-                                    }
-                                    flops += 2.0 * tl.rows * tl.cols * c.K;
-                                    cs.push_back(c);
-                                }
+                SbTile tl{};
+                tl.out_off = ob.offset + (int64_t)rs.start * ob.cols + csg.start;
+                tl.ldo = ob.cols;
+                tl.rows = rs.dim;
+                tl.cols = csg.dim;
+                tl.s_begin = (int)st.size();
+                for (int l = 0; l < p->n_terms; l++) {
+                    const rot_sb_term& t = p->terms[l];
+                    const int lo = t.left_op, ro = t.right_op;
+                    const Qn qs{qo.first - (lo >= 0 ? p->left_shift[2 * lo] : 0),
+                                qo.second - (lo >= 0 ? p->left_shift[2 * lo + 1] : 0)};
+                    const Qn ps{po.first - (ro >= 0 ? p->right_shift[2 * ro] : 0),
+                                po.second - (ro >= 0 ? p->right_shift[2 * ro + 1] : 0)};
+                    auto kq = lsec.find(qs);
+                    auto kp = rsec.find(ps);
+                    if (kq == lsec.end() || kp == rsec.end()) continue;
+                    int64_t op_off = -1;
+                    if (lo >= 0) op_off = p->left_off[(int64_t)lo * p->n_left + kq->second];
+                    if (ro >= 0) op_off = p->right_off[(int64_t)ro * p->n_right + kp->second];
+                    if ((lo >= 0 || ro >= 0) && op_off < 0) continue;
+                    for (int sa = 0; sa < d; sa++) {
+                        const double wa = t.site_a ? t.site_a[rs.site * d + sa] : (sa == rs.site ? 1.0 : 0.0);
+                        if (wa == 0.0) continue;
+                        for (int ta = 0; ta < d; ta++) {
+                            const double wt = t.site_at ? t.site_at[csg.site * d + ta] : (ta == csg.site ? 1.0 : 0.0);
+                            if (wt == 0.0) continue;
+                            const Qn Qs{qs.first + qn[2 * sa], qs.second + qn[2 * sa + 1]};
+                            const Qn Ps{ps.first + qn[2 * ta], ps.second + qn[2 * ta + 1]};
+                            auto sb = block_of.find(Qs);
+                            if (sb == block_of.end()) continue;
+                            const Block& src = *sb->second;
+                            const int rstart = seg_start(sys, Qs, sa, kq->second);
+                            const int cstart = seg_start(env, Ps, ta, kp->second);
+                            if (rstart < 0 || cstart < 0) continue;
+                            SbStep c{};
+                            int K = 1;
+                            c.alpha = t.coef * wa * wt;
+                            if (lo >= 0) {
+                                K = p->left[kq->second].dim;
+                                c.kind = kFromLeft;
+                                c.a_off = op_off;
+                                c.lda = K;
+                                c.b_off = src.offset + (int64_t)rstart * src.cols + cstart;
+                                c.ldb = src.cols;
+                            } else if (ro >= 0) {
+                                K = p->right[kp->second].dim;
+                                c.kind = kFromRight;
+                                c.a_off = src.offset + (int64_t)rstart * src.cols + cstart;
+                                c.lda = src.cols;
+                                c.b_off = op_off;
+                                c.ldb = K;
+                            } else {
+                                c.kind = kCopy;
+                                c.a_off = src.offset + (int64_t)rstart * src.cols + cstart;
+                                c.lda = src.cols;
+                            }
+                            flops += 2.0 * tl.rows * tl.cols * K;
+                            const int64_t bk = c.kind == kFromLeft ? c.ldb : 1;
+                            for (int k0 = 0; k0 < K; k0 += kSbKs) {
+                                SbStep x = c;
+                                const int at = K - k0 >= kSbKs ? k0 : std::max(0, K - kSbKs);
+                                x.a_off += c.kind == kCopy ? 0 : at;
+                                x.b_off += at * bk;
+                                x.lo_hi = (k0 - at) | std::min(K, kSbKs) << 8;
+                                st.push_back(x);
                             }
                         }
-                        tl.c_end = (int)cs.size();
-                        tiles.push_back(tl);
                     }
+                }
+                tl.s_end = (int)st.size();
+                segments.push_back(tl);
             }
         }
     }
@@ -452,8 +484,9 @@ void build_work(const rot_sb_problem* p, std::vector<SbTile>& tiles, std::vector
 
 struct rot_sb_plan_s {
     rot::SbTile* tiles = nullptr;
-    rot::SbContrib* contribs = nullptr;
+    rot::SbStep* steps = nullptr;
     int n_tiles = 0;
+    int edge = 16;
     const double* left_blk = nullptr;
     const double* right_blk = nullptr;
     int64_t total = 0;
@@ -493,23 +526,30 @@ rot_status rot_sb_plan_create(const rot_sb_problem* p, rot_sb_plan* plan) {
     *plan = nullptr;
     const rot_status v = validate_sb(p);
     if (v != ROT_OK) return v;
-    std::vector<SbTile> tiles;
-    std::vector<SbContrib> cs;
+    std::vector<SbTile> segments, tiles;
+    std::vector<SbStep> steps;
     auto* P = new rot_sb_plan_s();
-    build_work(p, tiles, cs, P->flops, P->total);
+    build_work(p, segments, steps, P->flops, P->total);
+    int64_t n32 = 0;
+    for (const SbTile& g : segments) n32 += (int64_t)((g.rows + 31) / 32) * ((g.cols + 31) / 32);
+    P->edge = n32 >= kSbWideTiles ? 32 : 16;
     // heaviest tiles first: all tiles do not fit on the chip at once, and the
     // ones dispatched last should be short
-    {
-        std::vector<std::pair<int64_t, int>> order(tiles.size());
-        for (size_t i = 0; i < tiles.size(); i++) {
-            int64_t w = 0;
-            for (int c = tiles[i].c_begin; c < tiles[i].c_end; c++) w += cs[c].kind == kCopy ? 1 : (cs[c].K + 31) / 32;
-            order[i] = {-w, (int)i};
-        }
-        std::stable_sort(order.begin(), order.end());
-        std::vector<SbTile> sorted(tiles.size());
-        for (size_t i = 0; i < tiles.size(); i++) sorted[i] = tiles[order[i].second];
-        tiles.swap(sorted);
+    std::vector<std::pair<int64_t, int>> order(segments.size());
+    for (size_t i = 0; i < segments.size(); i++) order[i] = {segments[i].s_begin - segments[i].s_end, (int)i};
+    std::stable_sort(order.begin(), order.end());
+    for (const auto& o : order) {
+        const SbTile& g = segments[o.second];
+        for (int r0 = 0; r0 < g.rows; r0 += P->edge)
+            for (int c0 = 0; c0 < g.cols; c0 += P->edge) {
+                SbTile t = g;
+                t.out_off += r0 * g.ldo + c0;
+                t.r0 = r0;
+                t.c0 = c0;
+                t.rows = std::min(P->edge, g.rows - r0);
+                t.cols = std::min(P->edge, g.cols - c0);
+                tiles.push_back(t);
+            }
     }
     P->n_tiles = (int)tiles.size();
     P->left_blk = p->left_blk;
@@ -517,10 +557,10 @@ rot_status rot_sb_plan_create(const rot_sb_problem* p, rot_sb_plan* plan) {
     hipError_t e = hipSuccess;
     if (!tiles.empty()) {
         e = hipMalloc(&P->tiles, sizeof(SbTile) * tiles.size());
-        if (e == hipSuccess) e = hipMalloc(&P->contribs, sizeof(SbContrib) * std::max<size_t>(cs.size(), 1));
+        if (e == hipSuccess) e = hipMalloc(&P->steps, sizeof(SbStep) * std::max<size_t>(steps.size(), 1));
         if (e == hipSuccess) e = hipMemcpy(P->tiles, tiles.data(), sizeof(SbTile) * tiles.size(), hipMemcpyHostToDevice);
-        if (e == hipSuccess && !cs.empty())
-            e = hipMemcpy(P->contribs, cs.data(), sizeof(SbContrib) * cs.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess && !steps.empty())
+            e = hipMemcpy(P->steps, steps.data(), sizeof(SbStep) * steps.size(), hipMemcpyHostToDevice);
     }
     if (e != hipSuccess) {
         rot_sb_plan_destroy(P);
@@ -538,8 +578,13 @@ rot_status rot_sb_apply(rot_sb_plan plan, const double* psi, double* out, void* 
     if (out < psi + plan->total && psi < out + plan->total) return sberr(ROT_ERR_INVALID_ARG, "out overlaps psi");
     hipStream_t s = static_cast<hipStream_t>(stream);
     const hipError_t e = prof_timed("sb_matvec", s, [&] {
-        hipLaunchKernelGGL(sb_tile_kernel, dim3(plan->n_tiles), dim3(256), 0, s, plan->tiles, plan->contribs,
-                           plan->left_blk, plan->right_blk, psi, out);
+        const dim3 grid((plan->n_tiles + 3) / 4), block(256);
+        if (plan->edge == 32)
+            hipLaunchKernelGGL(sb_tile_kernel<2>, grid, block, 0, s, plan->tiles, plan->n_tiles, plan->steps,
+                               plan->left_blk, plan->right_blk, psi, out);
+        else
+            hipLaunchKernelGGL(sb_tile_kernel<1>, grid, block, 0, s, plan->tiles, plan->n_tiles, plan->steps,
+                               plan->left_blk, plan->right_blk, psi, out);
         return hipGetLastError();
     });
     return e == hipSuccess ? ROT_OK : sberr(ROT_ERR_HIP, "rot_sb_apply: %s", hipGetErrorString(e));
@@ -550,7 +595,7 @@ double rot_sb_plan_flops(rot_sb_plan plan) { return plan ? plan->flops : 0.0; }
 rot_status rot_sb_plan_destroy(rot_sb_plan plan) {
     if (!plan) return ROT_OK;
     if (plan->tiles) (void)hipFree(plan->tiles);
-    if (plan->contribs) (void)hipFree(plan->contribs);
+    if (plan->steps) (void)hipFree(plan->steps);
     delete plan;
     return ROT_OK;
 }
