@@ -275,7 +275,7 @@ hipError_t gemm_any(const GemmDesc& g, bool is_double, hipStream_t stream) {
     if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
     if (g.upper && (g.M != g.N || g.accumulate)) return hipErrorInvalidValue;
     const int parts = g.parts > 1 ? g.parts : 1;
-    if (parts > 1 && (g.upper || g.accumulate || g.kbatch != 1 || g.kp <= 0 || g.kp % kSlice != 0 ||
+    if (parts > 1 && ((g.upper && !is_double) || g.accumulate || g.kbatch != 1 || g.kp <= 0 || g.kp % kSlice != 0 ||
                       (int64_t)g.kp * (parts - 1) >= g.K))
         return hipErrorInvalidValue;
     const int tm = (g.M + kTile - 1) / kTile, tn = (g.N + kTile - 1) / kTile;

@@ -809,6 +809,7 @@ rot_status rot_expect_block(const double* psi, int32_t m, int32_t d, int64_t nco
     g.A = psi; g.lda = d * ncols; g.a_kcontig = true;
     g.B = psi; g.ldb = d * ncols; g.b_kcontig = true;
     g.C = rho; g.ldc = m;
+    g.upper = true;
     hipError_t err = gemm_split_k(ROT_FP64, g, split, workspace_bytes - (split - static_cast<char*>(workspace)), s,
                                   "expect_rho");
     if (err == hipSuccess)
@@ -907,12 +908,19 @@ rot_status rot_expect_cross(const double* psi, int32_t m, int32_t d, int32_t mR,
     }
     if (err == hipSuccess) {
         // c[b][k] = sum_e q_b[e] W_k[e]
-        GemmDesc g{};
-        g.M = n_left; g.N = n_right; g.K = mR * mR; g.batch = 1; g.kbatch = 1;
-        g.A = q; g.lda = (int64_t)mR * mR; g.a_kcontig = true;
-        g.B = W; g.ldb = stride_w; g.b_kcontig = true;
-        g.C = c; g.ldc = n_right;
-        err = gemm_split_k(ROT_FP64, g, split, split_bytes, s, "expect_pairs");
+        const int64_t n = (int64_t)mR * mR;
+        if (few_pairs(n_left, n_right)) {
+            err = prof_timed("expect_pairs", s, [&] {
+                return cross_dots(q, n, n_left, W, stride_w, n_right, n, c, split, split_bytes, s);
+            });
+        } else {
+            GemmDesc g{};
+            g.M = n_left; g.N = n_right; g.K = (int)n; g.batch = 1; g.kbatch = 1;
+            g.A = q; g.lda = n; g.a_kcontig = true;
+            g.B = W; g.ldb = stride_w; g.b_kcontig = true;
+            g.C = c; g.ldc = n_right;
+            err = gemm_split_k(ROT_FP64, g, split, split_bytes, s, "expect_pairs");
+        }
     }
     return err == hipSuccess ? ROT_OK : hip_fail(err, "rot_expect_cross");
 }

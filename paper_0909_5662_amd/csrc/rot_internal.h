@@ -179,6 +179,12 @@ hipError_t fill_zero(void* p, int64_t bytes, hipStream_t stream);
 // (n elements per operator, fixed summation order; partial needs
 // expect_dot_scratch(n_ops) bytes).
 size_t expect_dot_scratch(int n_ops);
+// Pairs of operators of the two blocks for which cross_dots beats a matrix
+// product split over K: up to eight 8 x 8 tiles of them (380 states, 6 x 7 /
+// 16 x 16 / 32 x 32 pairs: 13 / 24 / 59 us, the product and its sum 59).
+inline bool few_pairs(int nl, int nr) { return (int64_t)((nl + 7) / 8) * ((nr + 7) / 8) <= 8; }
+hipError_t cross_dots(const double* Q, int64_t stride_q, int nl, const double* W, int64_t stride_w, int nr, int64_t n,
+                      double* c, void* scratch, size_t scratch_bytes, hipStream_t s);
 hipError_t expect_dots(const void* Z, bool z_double, int64_t stride_z, int64_t n, int n_ops, const double* rho,
                        double* partial, double* e, hipStream_t s);
 // dst[b][i] = sum over x < groups of src[(b*groups + x)*count + i], i < count,
