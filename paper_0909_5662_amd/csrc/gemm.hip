@@ -88,7 +88,6 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_dl_kernel(GemmDesc g, int t
         lin -= part * per;
     }
     const TileCoord tc = tile_coord(lin, tiles_m, tiles_n, UPPER);
-    if (g.only && !g.only[tc.g]) return;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -280,7 +279,7 @@ hipError_t gemm_any(const GemmDesc& g, bool is_double, hipStream_t stream) {
         return hipErrorInvalidValue;
     const int tm = (g.M + kTile - 1) / kTile, tn = (g.N + kTile - 1) / kTile;
     const int64_t tiles = (g.upper ? (int64_t)tm * (tm + 1) / 2 : (int64_t)tm * tn) * g.batch * parts;
-    if (is_double || tiles < kWideTiles || !direct_lds_ok(g)) return gemm_tile64(g, is_double, stream);
+    if (is_double || g.only || tiles < kWideTiles || !direct_lds_ok(g)) return gemm_tile64(g, is_double, stream);
     if (tiles > 0x7fffffff) return hipErrorInvalidValue;
     const bool edge = g.M % kTile != 0 || g.N % kTile != 0;
     auto pick = [&](auto mode, auto e) {

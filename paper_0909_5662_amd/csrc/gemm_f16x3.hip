@@ -420,7 +420,7 @@ struct F16Scale {
     int m32, mp32;     // rows of O_b's and T_b's layouts
     int* eo;           // [nb]
     int* skip;         // [nb]
-    int* any;          // plans: raised when an operator is skipped
+    int* any;          // raised when an operator is skipped (behind skip; plans: one per chunk)
     uint16_t *u1h, *u1l, *u2h, *u2l;
     uint16_t *oh, *ol;
     int64_t o_bs;
@@ -538,6 +538,7 @@ __device__ inline void f16_scale_block(const F16Scale& g, int blk) {
 
 template <bool SITE>
 __global__ __launch_bounds__(256) void f16_scale_kernel(F16Scale g) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *g.any = 0;
     f16_scale_block<SITE>(g, blockIdx.x);
 }
 
@@ -678,7 +679,7 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
                 if (lane == 0) {
                     g.eo[b] = scale_exp(mx);
                     g.skip[b] = bad;
-                    if (bad && g.any) atomicOr(g.any, 1);
+                    if (bad) atomicOr(g.any, 1);
                 }
             }
         }
@@ -816,7 +817,7 @@ F16Layout f16_layout(const rot_problem& p, int d_all = 0) {
 
 size_t f16_t_bytes(const F16Layout& L, int ops) { return std::max(2 * al256(ops * L.t_op), ops * L.t32); }
 size_t f16_scale_bytes(const rot_problem& p, int ops) {
-    return al256((size_t)ops * (div_up(p.m, kPrepORows) * 8 + 8));
+    return al256((size_t)ops * (div_up(p.m, kPrepORows) * 8 + 8) + 4);
 }
 // Stage 2 of `ops` operators of the group.  The K parts are those of the
 // whole group, so that results do not depend on the chunks.  Symmetric output
@@ -885,6 +886,7 @@ F16Bound f16_bind(const rot_problem& p, const F16Layout& L, int b0, int nb, int 
     g.opart = reinterpret_cast<uint32_t*>(base);
     g.eo = reinterpret_cast<int*>(g.opart + 2 * (size_t)nb * div_up(p.m, kPrepORows));
     g.skip = g.eo + nb;
+    g.any = g.skip + nb;
     g.n_ublk = div_up(p.mp, 64) * div_up(g.rows, kPrepRows);
     return r;
 }
@@ -1117,7 +1119,7 @@ F16Bound f16_site_bind(const rot_problem& p, const F16Site& x, const F16Layout& 
                        void* ws, char** T32) {
     char* base = static_cast<char*>(ws);
     int* skip = reinterpret_cast<int*>(base);
-    base += al256((size_t)nb * 4);
+    base += al256((size_t)(nb + 1) * 4);
     *T32 = base;
     F16Scale extra{};
     extra.upart2 = reinterpret_cast<uint32_t*>(base);
@@ -1126,6 +1128,7 @@ F16Bound f16_site_bind(const rot_problem& p, const F16Site& x, const F16Layout& 
     base += L.eu;
     F16Bound r = f16_bind(p, L, b0, nb, parts, base);
     r.g.skip = skip;
+    r.g.any = skip + nb;
     r.g.Up = x.Up;
     r.g.d_all = x.d_all;
     r.g.sel = x.sel;
@@ -1138,7 +1141,8 @@ F16Bound f16_site_bind(const rot_problem& p, const F16Site& x, const F16Layout& 
 
 // Operators b0 .. b0 + nb - 1 of p (leading dimensions resolved) through FP16
 // pairs; `fallback` enqueues the FP32 kernels for the operators they skip
-// (T: FP32 intermediates, slot_elems apart; skip: the flags).
+// (T: FP32 intermediates, slot_elems apart; skip: their flags, and behind them
+// one that is set if any is).
 hipError_t rotate_f16(const rot_problem& p, int b0, int nb, void* ws, bool symmetric,
                       const std::function<hipError_t(void* T, int64_t slot_elems, const int* skip)>& fallback,
                       hipStream_t stream) {
@@ -1158,7 +1162,7 @@ hipError_t rotate_f16(const rot_problem& p, int b0, int nb, void* ws, bool symme
 size_t f16_site_workspace(const rot_problem& p, const F16Site& x, int ops) {
     const F16Layout L = f16_layout(p, x.d_all);
     const int parts = f16_stage2_cfg(p, ops, false).parts;
-    return al256((size_t)ops * 4) + std::max(L.shared + 2 * al256(ops * L.t_op) + f16_o_bytes(p, L, ops, parts) +
+    return al256((size_t)(ops + 1) * 4) + std::max(L.shared + 2 * al256(ops * L.t_op) + f16_o_bytes(p, L, ops, parts) +
                                                  f16_scale_bytes(p, ops),
                                              ops * L.t32);
 }

@@ -232,17 +232,18 @@ template <> struct Acc<double> {
     }
 };
 
+// Tile `lin` of the launch.
 template <typename T, bool AK, bool BK, Addr ADDR>
-__global__ __launch_bounds__(256, 4) void gemm_tile64_kernel(GemmDesc g, int tiles_m, int tiles_n) {
+__device__ __attribute__((always_inline)) inline void gemm_tile64_tile(const GemmDesc& g, int lin, int per_part,
+                                                                       int tiles_m, int tiles_n) {
     typedef Slice<T, AK, ADDR> SA;
     typedef Slice<T, BK, ADDR> SB;
     __shared__ __attribute__((aligned(16))) T As[2][SA::ELEMS];
     __shared__ __attribute__((aligned(16))) T Bs[2][SB::ELEMS];
-    int lin = xcd_linear_id(), part = 0;
+    int part = 0;
     if (g.parts > 1) {
-        const int per = gridDim.x / g.parts;
-        part = lin / per;
-        lin -= part * per;
+        part = lin / per_part;
+        lin -= part * per_part;
     }
     int gb, m0, n0;
     if (g.upper) {
@@ -338,6 +339,21 @@ __global__ __launch_bounds__(256, 4) void gemm_tile64_kernel(GemmDesc g, int til
     }
 }
 
+template <typename T, bool AK, bool BK, Addr ADDR>
+__global__ __launch_bounds__(256, 4) void gemm_tile64_kernel(GemmDesc g, int tiles_m, int tiles_n) {
+    gemm_tile64_tile<T, AK, BK, ADDR>(g, xcd_linear_id(), g.parts > 1 ? gridDim.x / g.parts : 0, tiles_m, tiles_n);
+}
+
+// The products of flagged batch entries (g.only), normally none: a few
+// workgroups look at one flag and end, or walk all tiles.  (65 operators of 403
+// states: one workgroup per tile 10.1 us for stage 1 with its 11375, now 4.6.)
+template <typename T, bool AK, bool BK, Addr ADDR>
+__global__ __launch_bounds__(256, 4) void gemm_tile64_only_kernel(GemmDesc g, int tiles_m, int tiles_n, int tiles) {
+    if (!*g.any) return;
+    for (int lin = blockIdx.x; lin < tiles; lin += gridDim.x)
+        gemm_tile64_tile<T, AK, BK, ADDR>(g, lin, 0, tiles_m, tiles_n);
+}
+
 template <typename T>
 hipError_t launch(const GemmDesc& g, hipStream_t stream) {
     const int tm = (g.M + kT - 1) / kT, tn = (g.N + kT - 1) / kT;
@@ -350,6 +366,19 @@ hipError_t launch(const GemmDesc& g, hipStream_t stream) {
         return g.kbatch == 1 && (kc ? (rows + kT) * ld : (g.K + kS) * ld + kT) < lim ? kNear : kRebase;
     };
     const Addr a = std::max(addr(g.a_kcontig, g.lda, g.M), addr(g.b_kcontig, g.ldb, g.N));
+    if (g.only) {
+        // rotations only: A is O (K-contiguous) or U, B is M/N-contiguous
+        if (!g.any || g.b_kcontig || g.parts > 1 || sizeof(T) != 4) return hipErrorInvalidValue;
+        auto only = [&](auto ak) {
+            constexpr bool AK = decltype(ak)::value;
+            return a == kNear     ? gemm_tile64_only_kernel<float, AK, false, kNear>
+                   : a == kRebase ? gemm_tile64_only_kernel<float, AK, false, kRebase>
+                                  : gemm_tile64_only_kernel<float, AK, false, kFar>;
+        };
+        hipLaunchKernelGGL((g.a_kcontig ? only(std::true_type{}) : only(std::false_type{})),
+                           dim3((unsigned)std::min<int64_t>(tiles, 1024)), dim3(256), 0, stream, g, tm, tn, (int)tiles);
+        return hipGetLastError();
+    }
     auto pick = [&](auto ak, auto bk) {
         constexpr bool AK = decltype(ak)::value, BK = decltype(bk)::value;
         return a == kNear     ? gemm_tile64_kernel<T, AK, BK, kNear>

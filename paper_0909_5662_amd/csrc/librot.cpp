@@ -517,6 +517,7 @@ rot_status batch(const rot_problem* groups, int32_t n_groups, rot_precision prec
                         GemmDesc g1 = stage1(p, b0, nb, T, es), g2 = stage2(p, b0, nb, T, es);
                         g1.c_bs = g2.b_bs = slot;
                         g1.only = g2.only = skip;
+                        g1.any = g2.any = skip + nb;
                         g2.upper = sym;
                         const hipError_t e = gemm(prec, g1, s, "rest1");
                         return e == hipSuccess ? gemm(prec, g2, s, "rest2") : e;
@@ -752,6 +753,7 @@ rot_status rot_batch_site(const rot_site_problem* groups, int32_t n_groups, rot_
                     GemmDesc g1 = stage1(p, b0, nb, T32, es), g2 = stage2(p, b0, nb, T32, es);
                     g1.c_bs = g2.b_bs = slot_elems;
                     g1.only = g2.only = skip;
+                    g1.any = g2.any = skip + nb;
                     g2.A = up;
                     const hipError_t err = gemm(prec, g1, s, "rest1");
                     return err == hipSuccess ? gemm(prec, g2, s, "rest2") : err;

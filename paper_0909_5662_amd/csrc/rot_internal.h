@@ -37,8 +37,9 @@ struct GemmDesc {
     // C + p*c_ps; the caller adds the parts
     int parts, kp;
     int64_t c_ps;
-    // when set, batch elements b with only[b] == 0 are left alone
-    const int* only;
+    // when set (FP32 rotations), batch elements b with only[b] == 0 are left
+    // alone, and all of them if *any == 0
+    const int *only, *any;
     // with inner > 1, batch element g reads A at (g / inner)*a_bs +
     // (g % inner)*a_is (B likewise)
     int inner;
