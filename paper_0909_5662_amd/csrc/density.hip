@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256) void dm_prep_kernel(const DmSector* __restrict
 // registers (dm_sweep_cross).  The accumulated Q never touches the LDS: four
 // waves hold 8 slots of every row each in registers and hand one value per
 // neighbour and step on.
-// Time of a step, and of 60 sectors of up to 246 states (3 939 in all, 13
+// Time of a step, and of 60 sectors of up to 246 states (4 096 in all, 13
 // sweeps): two barriers and Q in the LDS 1.1 us, 7.1 ms; one barrier, Q in
 // registers 0.5 us, 3.5 ms; cross steps in registers and short rotation chains
 // 0.37 us (cross) and 0.6 us (full), 2.7 ms.  A cross step is now bound by the
@@ -1037,7 +1037,7 @@ __device__ inline int dm_count_ge(const double* w, int n, uint64_t c) {
 
 // The m_keep largest eigenvalues over all sectors: the m_keep-th largest key T
 // found eight bits at a time (a histogram of the keys that share T's higher
-// bits; 64 counting passes, one per bit, took 70 us for 3 939 values, now
+// bits; 64 counting passes, one per bit, took 70 us for 4 096 values, now
 // 25), all entries above T kept, entries equal to T handed out in sector
 // order; then the weight left out, per sector by one wave (strided lanes, then
 // a fixed butterfly) and over sectors in sector order.
