@@ -310,7 +310,10 @@ def bench_differentiated(args, rot, torch, workloads):
     f_fwd = n * flops_per_op(m, d, mp)
     # backward per symmetric operator: P = U dOut and (P + Q) = U (dOut + dOut^T)
     # (2 md mp^2 each), dO = P_r U_r^T and dU_r += O (P + Q)_r (2 m^2 d mp each)
+    # (the pair loss hands every operator the same dOut, so these products are
+    # executed for one operator)
     f_bwd = n * (4.0 * m * d * mp * mp + 4.0 * m * m * d * mp)
+    f_exec = f_fwd + f_bwd / n
 
     def run(precision):
         def step():
@@ -343,13 +346,14 @@ def bench_differentiated(args, rot, torch, workloads):
                       {"workload": "differentiated_m1024_n64", "m": m, "d": d, "mp": mp, "n_ops": n,
                        "precision": "fp32 forward/adjoint, fp64 loss"})
     rec.update({"tflop_per_step": round((f_fwd + f_bwd) / 1e12, 3), "tflops": round(tflops, 2),
-                "pct_fp32_mfma_peak": round(100 * tflops / 157.3, 2),
+                "tflop_executed_per_step": round(f_exec / 1e12, 3),
+                "pct_fp32_mfma_peak_executed": round(100 * f_exec / (ms / 1e3) / 1e12 / 157.3, 2),
                 "kernels_ms_avg": {k: round(v[1] / v[0], 4) for k, v in kernels.items()},
                 "kernels_ms_total_per_step": {k: round(v[1] / args.steps, 4) for k, v in kernels.items()}})
     ms_b, tflops_b, kernels_b = run("split_bf16")
     rec["split_bf16"] = {"value": round(n / (ms_b / 1e3), 2), "unit": "operator rotations/s (forward + loss + adjoint)",
                          "ms_per_step": round(ms_b, 4), "tflops_fp32_equivalent": round(tflops_b, 2),
-                         "pct_bf16_mfma_peak_executed": round(100 * 3 * tflops_b / 2516.6, 2),
+                         "pct_bf16_mfma_peak_executed": round(100 * 3 * f_exec / (ms_b / 1e3) / 1e12 / 2516.6, 2),
                          "speedup_vs_fp32": round(ms / ms_b, 3),
                          "kernels_ms_total_per_step": {k: round(v[1] / args.steps, 4) for k, v in kernels_b.items()}}
     return rec
@@ -391,7 +395,7 @@ def bench_site(args, rot, torch, workloads):
     p = rot.RotSiteProblem(case.m, 4, case.mp, n, rot.ROT_BLOCK_DENSE, U.data_ptr(),
                            S.ctypes.data_as(ctypes.POINTER(ctypes.c_double)), X.data_ptr(), case.m * case.m,
                            1 << 40, case.mp * case.mp)
-    ws = torch.empty(rot.rot_site_workspace_size([p], rot.ROT_FP32), dtype=torch.uint8, device=U.device)
+    ws = torch.empty(rot.rot_site_workspace_preferred([p], rot.ROT_FP32), dtype=torch.uint8, device=U.device)
     rot.profile_enable(True)
     ms_dense = timed_loop(torch, lambda: rot.rotate_site(U, X, C_UP, "fp32", workspace=ws), args.steps, args.warmup)
     kernels = rot.profile_read()
@@ -406,17 +410,21 @@ def bench_site(args, rot, torch, workloads):
     ms_new = timed_loop(torch, new_site, args.steps, args.warmup)
     F = flops_per_op(case.m, 4, case.mp)
     tflops = n * F / (ms_dense / 1e3) / 1e12
-    stage = {k: v for k, v in kernels.items() if k.startswith("site_stage")}
+    # on FP16 pairs: three 16-bit products per FP32 one, of the two site states of
+    # four that c_up has columns for
+    stage = {k: v for k, v in kernels.items() if k.startswith(("site_stage", "stage"))}
     dom, (cnt, tot) = max(stage.items(), key=lambda kv: kv[1][1])
-    achieved = n * F / 2 / (tot / cnt / 1e3) / 1e12
+    pairs = dom.endswith("_f16x3")
+    peak = PEAK_TFLOPS["split_bf16"] if pairs else 157.3
+    achieved = n * F / 2 * (1.5 if pairs else 1.0) / (tot / cnt / 1e3) / 1e12
     rec = base_record(args, n / (ms_dense / 1e3), "operator rotations/s (block-site products)", ms_dense,
                       {"workload": "site_m1024_n64", "m": case.m, "d": 4, "mp": case.mp, "n_ops": n,
                        "site_operator": "c_up", "precision": "fp32"})
     rec.update({"tflops": round(tflops, 2), "pct_fp32_mfma_peak": round(100 * tflops / 157.3, 2),
                 "new_site_operators_ms": round(ms_new, 4), "new_site_operators": 4,
                 "kernels_ms_avg": {k: round(v[1] / v[0], 4) for k, v in kernels.items()},
-                "roofline": {"bound": "mfma", "achieved": round(achieved, 2), "peak": 157.3, "unit": "TFLOP/s",
-                             "frac": round(achieved / 157.3, 4), "traffic": None, "kernel": dom,
+                "roofline": {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
+                             "frac": round(achieved / peak, 4), "traffic": None, "kernel": dom,
                              "avg_ms": round(tot / cnt, 4)}})
     return rec
 
@@ -444,8 +452,9 @@ def bench_measure(args, rot, torch, workloads):
     kernels = rot.profile_read()
     rot.profile_enable(False)
     mp = dR * mR
-    f_one = 2.0 * m * m * d * dR * mR + 2.0 * n * m * m
-    f_cross = 8 * (2.0 * m * m * d * mp + 2.0 * m * d * mp * mp) + 2.0 * 8 * 8 * mR * mR
+    # rho is symmetric; of psi^T T only the blocks on the diagonal in a~ are formed
+    f_one = m * (m + 1.0) * d * dR * mR + 2.0 * n * m * m
+    f_cross = 8 * (2.0 * m * m * d * mp + 2.0 * m * d * mp * mR) + 2.0 * 8 * 8 * mR * mR
     t_one = f_one / (ms_one / 1e3) / 1e12
     t_cross = f_cross / (ms_cross / 1e3) / 1e12
     rec = base_record(args, n / (ms_one / 1e3), "stored operators measured/s (one-point, FP64)", ms_one,
