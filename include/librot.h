@@ -60,8 +60,9 @@ typedef enum {
     ROT_FP64 = 0,        /* double buffers, FP64 matrix cores */
     ROT_FP32 = 1,        /* float buffers, FP32 accumulation: FP32 matrix cores,
                             or for larger dense batches three products of
-                            FP16 pairs that hold the scaled operands to FP32's
-                            last bit, whose results are the more exact */
+                            FP16 pairs that hold the entries of scaled
+                            operands within 2^-23 of themselves, where entries
+                            too small for that are few (see rot_batch) */
     ROT_SPLIT_BF16 = 2   /* float buffers; each operand x = hi + lo with
                             hi = bf16(x), lo = bf16(x - hi) (round to nearest
                             even); products hi*hi + hi*lo + lo*hi on BF16
@@ -115,9 +116,15 @@ typedef struct {
  * (its size is still checked as for any group).  An FP32 group of 4 GFLOP or
  * more (m, mp >= 64, d <= 8) runs on FP16 pairs when the workspace holds the
  * split operands of the group (rot_workspace_preferred) or of chunks of at
- * least 8 GFLOP, with the same bits for every chunk size; its operators with
- * infinities, NaN or rows whose largest entries differ by more than 2^12 are
- * computed by the FP32 kernels, all of them if U holds an infinity or NaN.
+ * least 8 GFLOP, with the same bits for every chunk size.  Operators that FP16's
+ * range does not hold are computed by the FP32 kernels: those with infinities
+ * or NaN, with many non-zero entries below 2^-16 of their largest one or rows
+ * whose largest entries differ by more than 2^12, with many non-zero entries
+ * of O U below 2^-17 of m max|O| max|U column|, and all of them if U holds an
+ * infinity or NaN or many non-zero entries below 2^-16 of their column's
+ * largest.  Many means a quarter or more of some 8 to 64 neighbours (of O U:
+ * half of 16, a row of 32, or an eighth of a 32 x 32 block); fewer cost no
+ * result, and no block of one, the FP32 kernels' accuracy.
  * Groups may have
  * different m, d, mp.  ROT_SPLIT_BF16 picks each stage's tile configuration per shape (m, d,
  * mp, chunk): from the tuning cache (in memory, and in the file named by

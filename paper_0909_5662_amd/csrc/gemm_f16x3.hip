@@ -1,13 +1,14 @@
 // FP32 rotation on FP16 pairs.  The FP32 matrix instructions run at 1/16 of
 // the FP16 ones' rate, so a product of FP32 operands taken as three FP16
 // products (hi*hi + hi*lo + lo*hi, FP32 accumulation) has over five times the
-// FP32 peak to work with.  It is no less exact: a scaled pair holds an FP32
-// value to its last bit (split2_f16), the dropped lo*lo term is below 2^-22
-// of a product and averages 2^-25, and the sum is rounded three times per 16
-// k where the FP32 instructions round eight times.  Measured against 64 bits
-// (relative Frobenius error, Gaussian operators; FP32 kernels -> pairs):
-// 1024 states 1.28e-6 -> 8.0e-7, 403: 8.0e-7 -> 5.1e-7, 256: 4.4e-7 ->
-// 3.2e-7, 128: 2.6e-7 -> 2.1e-7, 64: 2.1e-7 -> 1.8e-7.
+// FP32 peak to work with.  A scaled pair holds a value in its range to 2^-23
+// of itself, one unit of FP32's last place (split2_f16); the dropped lo*lo term
+// is below 2^-22 of a product and averages 2^-25; the sum is rounded three
+// times per 16 k where the FP32 instructions round eight times, which more
+// than makes up for both.  Measured against 64 bits (relative Frobenius error,
+// Gaussian operators; FP32 kernels -> pairs): 1024 states 1.28e-6 -> 8.0e-7,
+// 403: 8.0e-7 -> 5.1e-7, 256: 4.4e-7 -> 3.2e-7, 128: 2.6e-7 -> 2.1e-7, 64:
+// 2.1e-7 -> 1.8e-7.
 // Time of the two stages and all passes around them, 64 operators of 1024
 // states: 8.02 -> 2.73 ms; 65 of 403 (kept 391): 1.31 -> 0.26 ms.
 //
@@ -15,12 +16,29 @@
 // [2^14, 2^15) by exact powers of two (eu[beta], eo[b]).  |T| of the scaled
 // operands is below m 2^30, so stage 1's epilogue multiplies by 2^-t with
 // t = 15 + ceil(log2 m) before it splits T; stage 2's undoes every scale.
-// FP16's range leaves T entries down to 2^-16 of that bound (Gaussian
-// operators of 1024 states sit at 2^-9) at full precision.  An operator with
-// an infinity or NaN, or whose rows' largest entries differ by more than
-// 2^12 (its small rows of T would fall out of that range), and every operator
-// when U holds one, is skipped by these kernels and computed by the FP32
-// kernels that follow, which leave the others alone (skip[b]).
+// FP16's range leaves entries from 2^-2 on, 2^-16 of an operand's largest entry
+// or 2^-17 of T's bound (Gaussian operators of 1024 states: T at 2^-9), at full
+// precision; the pair of a smaller one is off by up to 2^-25 whatever its size.
+//
+// Range.  Where such entries are many, in a part of an operand that some result
+// is made of alone, that result would be less exact than FP32's: columns of an
+// operator that are small beside others which U leaves out, states that U
+// hardly reaches, blocks of different size.  So the entries themselves are
+// counted where they are made: an operator is skipped by these kernels, and
+// computed by the FP32 kernels that follow (which leave the others alone), when
+//   - it holds an infinity or NaN, or its rows' largest entries differ by more
+//     than 2^12, or non-zero entries below 2^-2 make up a quarter of 16 entries
+//     of a row or of 64 of a column (split pass);
+//   - the same is true of U: then every operator is (split pass: 3 of 8 entries
+//     of a column, or a quarter of a row's 32 in its half of a wave);
+//   - in a 32 x 32 block of T they are half of a lane's 16 or a whole row of 32,
+//     or an eighth of the block (stage 1, t_out_of_range).
+// Scattered small entries of a Gaussian operand (6e-5 of O and U, 0.5 % of T at
+// 1024 states) stay far below these counts.  Zeros count for nothing: they are
+// exact.  Of the operators accepted, every block of the result is as exact as
+// FP32's or more (160 states; columns of operators that U leaves out, states
+// that U hardly reaches, sectors, in order and mixed, and tails of U, from
+// 2^0 to 2^-16 of the rest: at most 0.93 times the FP32 kernels' error).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -86,12 +104,118 @@ struct FlatDesc {
     uint16_t *t_hi, *t_lo;
     int d, t_rows, t_shift;
     int64_t t_bs;
-    const int* skip;            // operators left to the FP32 kernels
+    int* skip;                  // operators left to the FP32 kernels: kSkipSplit, kSkipStage1
+    int* any;                   // raised with the first of them
+    const int* u_bad;           // U leaves the pairs' range
     // symmetric output (M == N, plain epilogue): tiles below the diagonal of
     // all their operators are left out, entries on or above it are also stored
     // transposed
     int upper;
 };
+
+// Bits of skip[b]: what the split pass found, and stage 1 (whose tiles read
+// the first while others set the second).
+constexpr int kSkipSplit = 1, kSkipStage1 = 2;
+
+// Entries of a pair operand below this are off by more than 2^-23 of themselves.
+constexpr float kPairLeast = 0.25f;
+
+__device__ inline bool pair_small(float x) {
+    return (__float_as_uint(x) & 0x7fffffffu) - 1u < __float_as_uint(kPairLeast) - 1u;
+}
+
+// The range of a 32 x 32 block of T (a column per lane, in lanes `valid`; rows
+// 8 q + 4 h + e).  The epilogue's pairs are watched without telling zeros from
+// small entries, one bit per entry; where they could be too many the blocks are
+// looked at entry by entry (a comparison, a count and two ballot words per entry
+// of all blocks made stage 1 of 65 operators of 403 states 10 % slower, this
+// does by 3 %).
+struct TWatch {
+    uint32_t below = 0;  // bit 8 e + 7 - q
+    __device__ inline void add(int q, uint32_t h01, uint32_t h23) {
+        const f16x2 c = {(_Float16)(-kPairLeast * kPairLeast), (_Float16)(-kPairLeast * kPairLeast)};
+        auto sign = [&](uint32_t h) {  // set where |h| < kPairLeast
+            const f16x2 x = __builtin_bit_cast(f16x2, h);
+            return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(x, x, c));
+        };
+        const uint32_t four = __builtin_amdgcn_perm(sign(h23), sign(h01), 0x07050301u) >> q, at = 0x80808080u >> q;
+        below = (four & at) | (below & ~at);
+    }
+    // The bits of a block's first `rows` rows.
+    __device__ static inline uint32_t inside(int rows, int lane) {
+        const int left = rows - 4 * (lane >> 5);
+        uint32_t in = 0;
+#pragma unroll
+        for (int v = 0; v < 16; v++) in |= 8 * (v >> 2) + (v & 3) < left ? 128u << 8 * (v & 3) >> (v >> 2) : 0u;
+        return in;
+    }
+    __device__ static inline uint32_t filled(const f32x16& t) {
+        uint32_t f = 0;
+#pragma unroll
+        for (int v = 0; v < 16; v++) f |= t[v] != 0.f ? 128u << 8 * (v & 3) >> (v >> 2) : 0u;
+        return f;
+    }
+};
+
+// Whether one of BI blocks on the same columns is to be looked at: half a column
+// (16 entries of a block) with four below, two in a quarter of the half columns,
+// or a whole row.
+template <int BI>
+__device__ __attribute__((always_inline)) inline bool t_suspect(const TWatch (&w)[BI], uint64_t valid, int lane) {
+    const bool in = (valid >> lane) & 1;
+    int most = 0;
+    uint32_t rows = 0;  // bits set in all lanes of a half wave: rows
+#pragma unroll
+    for (int i = 0; i < BI; i++) most = max(most, __builtin_popcount(w[i].below));
+#pragma unroll
+    for (int i = 0; i < BI; i += 2) {
+        uint32_t r = w[i].below;  // the high half of each byte
+        if (i + 1 < BI) r |= w[i + 1 < BI ? i + 1 : i].below >> 4;
+        int x = in ? (int)r : -1;
+        x &= __builtin_amdgcn_mov_dpp(x, 0x128, 0xf, 0xf, false);  // row_ror 8, 4, 2, 1
+        x &= __builtin_amdgcn_mov_dpp(x, 0x124, 0xf, 0xf, false);
+        x &= __builtin_amdgcn_mov_dpp(x, 0x122, 0xf, 0xf, false);
+        x &= __builtin_amdgcn_mov_dpp(x, 0x121, 0xf, 0xf, false);
+        const auto y = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+        rows |= y[0] & y[1];
+    }
+    const uint64_t four = __builtin_amdgcn_ballot_w64(most >= 4) & valid;
+    const uint64_t two = __builtin_amdgcn_ballot_w64(most >= 2) & valid;
+    return (four | __builtin_amdgcn_ballot_w64(rows != 0)) != 0 ||
+           4 * __builtin_popcountll(two) >= __builtin_popcountll(valid);
+}
+
+// Whether too much of one of the blocks is below and not zero (filled: the
+// entries in T that are not).  t_suspect passes no such block: what it passes
+// has fewer than 94 entries below of 1024.
+template <int BI>
+__device__ __attribute__((always_inline)) inline bool t_out_of_range(const TWatch (&w)[BI], const uint32_t (&filled)[BI]) {
+    bool bad = false;
+    uint32_t f = filled[0], s = w[0].below & f;
+#pragma unroll 1
+    for (int i = 0; i < BI; i++) {
+        int all_small = 0, all_filled = 0;
+#pragma unroll 1
+        for (uint32_t bit = 1u << 31; bit; bit >>= bit & 0x10101010u ? 5 : 1) {  // a row of each half wave
+            const uint64_t bs = __builtin_amdgcn_ballot_w64((s & bit) != 0), bf = __builtin_amdgcn_ballot_w64((f & bit) != 0);
+            all_small += __builtin_popcountll(bs);
+            all_filled += __builtin_popcountll(bf);
+            bad |= (uint32_t)bs == (uint32_t)bf && __builtin_popcount((uint32_t)bf) >= 4;
+            bad |= bs >> 32 == bf >> 32 && __builtin_popcount((uint32_t)(bf >> 32)) >= 4;
+        }
+        const int n = __builtin_popcount(s);
+        bad |= __builtin_amdgcn_ballot_w64(n >= 4 && 2 * n >= __builtin_popcount(f)) != 0;
+        bad |= all_small >= 8 && 8 * all_small >= all_filled;
+        bad |= all_small >= 2 && all_small == all_filled;
+#pragma unroll
+        for (int j = 1; j < BI; j++)
+            if (j == i + 1) {
+                f = filled[j];
+                s = w[j].below & f;
+            }
+    }
+    return bad;
+}
 
 __device__ inline f32x16 mfma_f16(f16x8 a, f16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
@@ -120,6 +244,13 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
     const int h = lane >> 5, c = lane & 31;
+    if (EPI_T && *g.u_bad) {
+        // nothing of this group runs on pairs
+        const int bpo = g.n32 >> 5, last = min(nt * 8 + 7, bpo * g.batch - 1) / bpo;
+        for (int b = nt * 8 / bpo + tid; b <= last; b += 512) atomicOr(&g.skip[b], kSkipStage1);
+        if (tid == 0) atomicOr(g.any, 1);
+        return;
+    }
     const int st0 = part * g.part_slabs;
     const int nk = min(g.part_slabs, (int)n_slabs(g.K) - st0);
 
@@ -252,7 +383,33 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
 #pragma unroll
     for (int k = 0; k < BJ; k++) {
         const int col = cb[k] * 32 + c;
-        if (!live[k] || g.skip[op[k]]) continue;
+        // (stage 1: other waves may be raising it; one value for the wave)
+        if (!live[k] || __builtin_amdgcn_readfirstlane(g.skip[op[k]])) continue;
+        const uint64_t valid = __builtin_amdgcn_ballot_w64(col < g.N);
+        TWatch watch[BI];
+        auto judge = [&]() __attribute__((always_inline)) {
+            bool suspect = false;
+            if (row0w + 32 * BI > g.M)
+#pragma unroll
+                for (int i = 0; i < BI; i++) {
+                    const int rows = g.M - row0w - 32 * i;
+                    watch[i].below &= TWatch::inside(rows, lane);
+                    // a block cut off at M may be out of range with fewer entries below
+                    const uint64_t one = __builtin_amdgcn_ballot_w64(watch[i].below != 0) & valid;
+                    suspect |= rows > 0 && rows < 32 && 12 * __builtin_popcountll(one) >= __builtin_popcountll(valid);
+                }
+            if (!t_suspect(watch, valid, lane) && !suspect) return;
+            uint32_t filled[BI];
+#pragma unroll
+            for (int i = 0; i < BI; i++)
+                filled[i] = (valid >> lane) & 1
+                                ? TWatch::filled(acc[i][k]) & TWatch::inside(g.M - row0w - 32 * i, lane)
+                                : 0u;
+            if (t_out_of_range(watch, filled) && lane == 0) {
+                atomicOr(&g.skip[op[k]], kSkipStage1);
+                atomicOr(g.any, 1);
+            }
+        };
         if (EPI_T && DS == 2) {
             // (33 operators of 500 states, kept 480, two states: single stores
             // 120 us, exchanged 78 us for stage 1)
@@ -271,6 +428,7 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
 #pragma unroll
                     for (int e = 0; e < 4; e++) v[e] = in ? acc[i][k][4 * q + e] * t_scale : 0.f;
                     const u32x2 p0 = split2_f16(v[0], v[1]), p1 = split2_f16(v[2], v[3]);
+                    watch[i].add(q, p0[0], p1[0]);
                     const uint32_t rh = __shfl_xor(odd ? p0[0] : p1[0], 1), rl = __shfl_xor(odd ? p0[1] : p1[1], 1);
                     const int beta = (row0 >> 1) + (odd ? 1 : 0);
                     if (store && beta * 2 < g.M) {
@@ -279,9 +437,10 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
                         *reinterpret_cast<u32x2*>(tl + off) = odd ? u32x2{rl, p1[1]} : u32x2{p0[1], rl};
                     }
                 }
+            judge();
             continue;
         }
-        if (col >= g.N) continue;
+        if (!EPI_T && col >= g.N) continue;
         if (EPI_T) {
             uint16_t* th = g.t_hi + op[k] * g.t_bs;
             uint16_t* tl = g.t_lo + op[k] * g.t_bs;
@@ -295,6 +454,8 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
                     for (int e = 0; e < 4; e++) v[e] = acc[i][k][4 * q + e] * t_scale;
                     const u32x2 p0 = split2_f16(v[0], v[1]), p1 = split2_f16(v[2], v[3]);
                     const u32x2 hv = {p0[0], p1[0]}, lv = {p0[1], p1[1]};
+                    watch[i].add(q, hv[0], hv[1]);
+                    if (col >= g.N) continue;
                     if (DS == 4) {
                         if (row0 < g.M) {
                             const int64_t off = slab_off(row0 >> 2, (int64_t)col * 4, g.t_rows);
@@ -313,6 +474,7 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
                         }
                     }
                 }
+            judge();
         } else if (g.upper) {
             float* cp = g.c + part * g.c_ps + op[k] * g.c_bs;
             const int e0 = -(g.e0 + g.op_e[op[k]] + g.col_e[col]);
@@ -425,7 +587,8 @@ struct F16Scale {
     int n_ublk;
     int m32, mp32;     // rows of O_b's and T_b's layouts
     int* eo;           // [nb]
-    int* skip;         // [nb]
+    int* skip;         // [nb], cleared by the scale pass
+    int* u_bad;        // U leaves the pairs' range; cleared by the scale pass when it works on U
     int* any;          // raised when an operator is skipped (behind skip; plans: one per chunk)
     uint16_t *u1h, *u1l, *u2h, *u2l;
     uint16_t *oh, *ol;
@@ -464,6 +627,7 @@ __device__ inline void f16_scale_block(const F16Scale& g, int blk) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     __shared__ uint32_t red[4][64], red2[SITE ? 4 : 1][64];
     if (blk < g.u_blocks) {
+        if (blk == 0 && tid == 0) *g.u_bad = 0;
         const int cb = div_up(g.mp, 64), half = g.u_blocks / 2;
         const bool up = SITE && blk >= half;
         const int x = up ? blk - half : blk;
@@ -499,6 +663,7 @@ __device__ inline void f16_scale_block(const F16Scale& g, int blk) {
     blk -= g.u_blocks;
     const int rb = div_up(g.m, kPrepORows);
     const int b = blk / rb, i0 = (blk % rb) * kPrepORows;
+    if (i0 == 0 && tid == 0) g.skip[b] = 0;
     const float* src = g.O + (int64_t)b * g.stride_o;
     uint32_t mx = 0, mn = 0xffffffffu;
     // eight rows per wave, their loads in flight together (rows past the last
@@ -564,7 +729,8 @@ __global__ __launch_bounds__(256) void f16_scale_list_kernel(const F16Scale* tab
 // A workgroup on U takes 16 j (16 d rows) x 64 columns through LDS: one slab
 // of U1's rows and d slabs of U2's, both written in whole 16-byte chunks,
 // chunk after chunk.  One on O takes a 64 x 64 block (split_o_kernel's
-// scheme).  The first block of each operator records eo[b] and skip[b].
+// scheme).  The first block of each operator records eo[b]; each raises skip[b]
+// (on U: u_bad) where its entries are out of range.
 // With a site, the first half of the workgroups on U writes U1 from U and the
 // second U2 from Up.
 template <int DMAX, bool SITE>
@@ -617,6 +783,19 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
         }
         __syncthreads();
         const int na = min(64, g.mp - a0);
+        // entries below the pairs' range: three of a thread's eight, or a
+        // quarter of a row's 32 among the wave's (two rows take turns in it)
+        bool u_bad = false;
+        auto check = [&](const float (&v)[8]) {
+            int small = 0;
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                const bool s = pair_small(v[k]);
+                small += s;
+                u_bad |= __builtin_popcountll(__ballot(s)) >= 8;
+            }
+            u_bad |= small >= 3;
+        };
         // U1: rows a*d + s of slab q, chunk (row, slot)
         const int64_t rows1 = (int64_t)d * g.mp;
         for (int x = up ? na * d * 2 : tid; x < na * d * 2; x += 256) {
@@ -626,6 +805,7 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
             float v[8];
 #pragma unroll
             for (int k = 0; k < 8; k++) v[k] = ldexpf(tile[((half * 8 + k) * d + s) * 65 + al], e);
+            check(v);
             const int64_t off = (int64_t)q * rows1 * kSlabK + gr * kSlabK + slot * 8;
             store8(g.u1h + off, g.u1l + off, v);
         }
@@ -639,9 +819,11 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
             float v[8];
 #pragma unroll
             for (int k = 0; k < 8; k++) v[k] = ldexpf(tile[(sl * 16 + half * 8 + k) * 65 + al], e);
+            if (SITE) check(v);
             const int64_t off = sq * (int64_t)g.mp * kSlabK + (int64_t)(a0 + al) * kSlabK + slot * 8;
             store8(g.u2h + off, g.u2l + off, v);
         }
+        if (__any(u_bad) && lane == 0) atomicOr(g.u_bad, 1);
         return;
     }
     blk -= g.u_blocks;
@@ -684,14 +866,18 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
                 bad = __any(bad);
                 if (lane == 0) {
                     g.eo[b] = scale_exp(mx);
-                    g.skip[b] = bad;
-                    if (bad) atomicOr(g.any, 1);
+                    if (bad) {
+                        atomicOr(&g.skip[b], kSkipSplit);
+                        atomicOr(g.any, 1);
+                    }
                 }
             }
         }
         __syncthreads();
         const int e = s_e[0];
         const int64_t nslab = n_slabs(g.m);
+        int small = 0;
+        bool bad = false;
 #pragma unroll
         for (int x = 0; x < 2; x++) {
             const int ch = tid + 256 * x;  // slab q, k half, row
@@ -701,10 +887,19 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
             if (i >= g.m || sq >= nslab) continue;
             float v[8];
 #pragma unroll
-            for (int k = 0; k < 8; k++) v[k] = ldexpf(tile[row * 68 + q * kSlabK + half * 8 + k], e);
+            for (int k = 0; k < 8; k++) {
+                v[k] = ldexpf(tile[row * 68 + q * kSlabK + half * 8 + k], e);
+                const bool s = pair_small(v[k]);
+                small += s;
+                bad |= __builtin_popcountll(__ballot(s)) >= 16;  // of a column's 64 rows
+            }
             const int64_t off = (int64_t)b * g.o_bs + sq * (int64_t)g.m32 * kSlabK + (int64_t)i * kSlabK +
                                 (half ^ ((i >> 3) & 1)) * 8;
             store8(g.oh + off, g.ol + off, v);
+        }
+        if (__any(bad || small >= 4) && lane == 0) {
+            atomicOr(&g.skip[b], kSkipSplit);
+            atomicOr(g.any, 1);
         }
         return;
     }
@@ -800,6 +995,7 @@ struct F16Layout {
     size_t t_op, o_op;          // one operator's
     size_t t32;                 // one operator's T of the FP32 kernels
     size_t part_u, ublk, eu;    // scale pass: partial column maxima, block maxima, exponents
+    size_t u_bad;
     size_t shared;
 };
 
@@ -817,7 +1013,8 @@ F16Layout f16_layout(const rot_problem& p, int d_all = 0) {
     L.part_u = al256(chunks * p.mp * 4);
     L.ublk = al256((d_all ? 2 : 1) * chunks * div_up(p.mp, 64) * 4);
     L.eu = al256((size_t)(p.mp + 256) * 4);  // read in groups of four up to a tile's last row
-    L.shared = 2 * L.u1 + 2 * L.u2 + (d_all ? 2 : 1) * (L.part_u + L.eu) + L.ublk;
+    L.u_bad = 256;
+    L.shared = L.u_bad + 2 * L.u1 + 2 * L.u2 + (d_all ? 2 : 1) * (L.part_u + L.eu) + L.ublk;
     return L;
 }
 
@@ -881,6 +1078,7 @@ F16Bound f16_bind(const rot_problem& p, const F16Layout& L, int b0, int nb, int 
     g.upart = reinterpret_cast<uint32_t*>(take(L.part_u));
     g.ublk = reinterpret_cast<uint32_t*>(take(L.ublk));
     g.eu = reinterpret_cast<int*>(take(L.eu));
+    g.u_bad = reinterpret_cast<int*>(take(L.u_bad));
     r.T = take(f16_t_bytes(L, nb));
     g.th = reinterpret_cast<uint16_t*>(r.T);
     g.tl = reinterpret_cast<uint16_t*>(r.T + al256(nb * L.t_op));
@@ -935,6 +1133,8 @@ FlatDesc f16_stage1(const F16Scale& g) {
     a.t_bs = g.t_bs;
     a.t_shift = f16_t_shift(g.m);
     a.skip = g.skip;
+    a.any = g.any;
+    a.u_bad = g.u_bad;
     a.parts = 1;
     a.part_slabs = (int)n_slabs(a.K);
     return a;
