@@ -73,7 +73,8 @@ __device__ inline TileCoord tile_coord(int lin, int tiles_m, int tiles_n, bool u
 // entry, whose extent bounds the descriptors); those values only reach rows
 // and columns of C that are not stored.
 template <bool AK, bool BK, int MODE, bool EDGE>
-__global__ __launch_bounds__(kThreads) void gemm_f32_dl_kernel(GemmDesc g, int tiles_m, int tiles_n) {
+__device__ __attribute__((always_inline)) inline void gemm_f32_dl_tile(const GemmDesc& g, int lin, int tiles_m,
+                                                                       int tiles_n) {
     constexpr bool UPPER = MODE == 1;
     typedef DmaSlice128<AK> DA;
     typedef DmaSlice128<BK> DB;
@@ -81,13 +82,14 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_dl_kernel(GemmDesc g, int t
     __shared__ __attribute__((aligned(1024))) float As[2][DA::ELEMS];
     __shared__ __attribute__((aligned(1024))) float Bs[2][DB::ELEMS];
 
-    int lin = xcd_linear_id(), part = 0;
+    int part = 0;
     if (MODE == 0 && g.parts > 1) {
         const int per = gridDim.x / g.parts;
         part = lin / per;
         lin -= part * per;
     }
     const TileCoord tc = tile_coord(lin, tiles_m, tiles_n, UPPER);
+    if (g.only && !g.only[tc.g]) return;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -240,6 +242,21 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_dl_kernel(GemmDesc g, int t
     }
 }
 
+template <bool AK, bool BK, int MODE, bool EDGE>
+__global__ __launch_bounds__(kThreads) void gemm_f32_dl_kernel(GemmDesc g, int tiles_m, int tiles_n) {
+    gemm_f32_dl_tile<AK, BK, MODE, EDGE>(g, xcd_linear_id(), tiles_m, tiles_n);
+}
+
+// The products of flagged batch entries (g.only), normally none: workgroups that
+// fit the chip at once look at one flag and end, or walk all tiles (64 operators
+// of 1024 states, all flagged: both stages 8.9 ms in 64 x 64 tiles, 8.0 here).
+template <bool AK, int MODE, bool EDGE>
+__global__ __launch_bounds__(kThreads) void gemm_f32_dl_only_kernel(GemmDesc g, int tiles_m, int tiles_n, int tiles) {
+    if (!*g.any) return;
+    for (int lin = xcd_linear_id(); lin < tiles; lin += gridDim.x)
+        gemm_f32_dl_tile<AK, false, MODE, EDGE>(g, lin, tiles_m, tiles_n);
+}
+
 // Conditions of the direct-to-LDS kernel: 16-byte aligned rows, whole K slices
 // (also of a part), no two-level batch, and every byte offset of an operand's
 // batch entry (over all K batches, and the rows or columns a last partial
@@ -279,9 +296,24 @@ hipError_t gemm_any(const GemmDesc& g, bool is_double, hipStream_t stream) {
         return hipErrorInvalidValue;
     const int tm = (g.M + kTile - 1) / kTile, tn = (g.N + kTile - 1) / kTile;
     const int64_t tiles = (g.upper ? (int64_t)tm * (tm + 1) / 2 : (int64_t)tm * tn) * g.batch * parts;
-    if (is_double || g.only || tiles < kWideTiles || !direct_lds_ok(g)) return gemm_tile64(g, is_double, stream);
+    if (is_double || tiles < kWideTiles || !direct_lds_ok(g)) return gemm_tile64(g, is_double, stream);
     if (tiles > 0x7fffffff) return hipErrorInvalidValue;
     const bool edge = g.M % kTile != 0 || g.N % kTile != 0;
+    if (g.only) {
+        // rotations only (as in gemm_tile64.hip)
+        if (!g.any || g.b_kcontig || parts > 1 || g.accumulate || g.kbatch != 1) return hipErrorInvalidValue;
+        auto only = [&](auto ak, auto mode) {
+            constexpr bool AK = decltype(ak)::value;
+            constexpr int MD = decltype(mode)::value;
+            return edge ? gemm_f32_dl_only_kernel<AK, MD, true> : gemm_f32_dl_only_kernel<AK, MD, false>;
+        };
+        auto only_mode = [&](auto ak) {
+            return g.upper ? only(ak, std::integral_constant<int, 1>{}) : only(ak, std::integral_constant<int, 0>{});
+        };
+        hipLaunchKernelGGL((g.a_kcontig ? only_mode(std::true_type{}) : only_mode(std::false_type{})),
+                           dim3((unsigned)kWideTiles), dim3(kThreads), 0, stream, g, tm, tn, (int)tiles);
+        return hipGetLastError();
+    }
     auto pick = [&](auto mode, auto e) {
         constexpr int MD = decltype(mode)::value;
         constexpr bool E = decltype(e)::value;

@@ -157,6 +157,14 @@ struct TWatch {
     }
 };
 
+// x of the lane 8, 4, 2 or 1 further in the same 16 lanes (cyclically): sums and
+// the like over these, which a swap of neighbouring sixteens completes to 32.
+constexpr int kRor8 = 0x128, kRor4 = 0x124, kRor2 = 0x122, kRor1 = 0x121;
+template <int CTRL>
+__device__ inline uint32_t lane_dpp(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, false);
+}
+
 // Whether one of BI blocks on the same columns is to be looked at: half a column
 // (16 entries of a block) with four below, two in a quarter of the half columns,
 // or a whole row.
@@ -171,12 +179,12 @@ __device__ __attribute__((always_inline)) inline bool t_suspect(const TWatch (&w
     for (int i = 0; i < BI; i += 2) {
         uint32_t r = w[i].below;  // the high half of each byte
         if (i + 1 < BI) r |= w[i + 1 < BI ? i + 1 : i].below >> 4;
-        int x = in ? (int)r : -1;
-        x &= __builtin_amdgcn_mov_dpp(x, 0x128, 0xf, 0xf, false);  // row_ror 8, 4, 2, 1
-        x &= __builtin_amdgcn_mov_dpp(x, 0x124, 0xf, 0xf, false);
-        x &= __builtin_amdgcn_mov_dpp(x, 0x122, 0xf, 0xf, false);
-        x &= __builtin_amdgcn_mov_dpp(x, 0x121, 0xf, 0xf, false);
-        const auto y = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+        uint32_t x = in ? r : ~0u;
+        x &= lane_dpp<kRor8>(x);
+        x &= lane_dpp<kRor4>(x);
+        x &= lane_dpp<kRor2>(x);
+        x &= lane_dpp<kRor1>(x);
+        const auto y = __builtin_amdgcn_permlane16_swap(x, x, false, false);
         rows |= y[0] & y[1];
     }
     const uint64_t four = __builtin_amdgcn_ballot_w64(most >= 4) & valid;
@@ -185,36 +193,65 @@ __device__ __attribute__((always_inline)) inline bool t_suspect(const TWatch (&w
            4 * __builtin_popcountll(two) >= __builtin_popcountll(valid);
 }
 
+// Per bit over the 32 lanes of each half wave: `left` ored, and the count as
+// ones, twos and "four or more".
+struct RowBits {
+    uint32_t left, one, two, four;
+    __device__ inline void add(const RowBits& o) {
+        const uint32_t carry = one & o.one;
+        left |= o.left;
+        four |= o.four | (two & o.two) | (carry & (two ^ o.two));
+        two ^= o.two ^ carry;
+        one ^= o.one;
+    }
+    template <int CTRL>
+    __device__ inline void step() {
+        add(RowBits{lane_dpp<CTRL>(left), lane_dpp<CTRL>(one), lane_dpp<CTRL>(two), lane_dpp<CTRL>(four)});
+    }
+    __device__ inline void reduce() {
+        step<kRor8>();
+        step<kRor4>();
+        step<kRor2>();
+        step<kRor1>();
+        const auto l = __builtin_amdgcn_permlane16_swap(left, left, false, false);
+        const auto o = __builtin_amdgcn_permlane16_swap(one, one, false, false);
+        const auto t = __builtin_amdgcn_permlane16_swap(two, two, false, false);
+        const auto f = __builtin_amdgcn_permlane16_swap(four, four, false, false);
+        *this = RowBits{l[0], o[0], t[0], f[0]};
+        add(RowBits{l[1], o[1], t[1], f[1]});
+    }
+};
+
 // Whether too much of one of the blocks is below and not zero (filled: the
 // entries in T that are not).  t_suspect passes no such block: what it passes
 // has fewer than 94 entries below of 1024.
 template <int BI>
 __device__ __attribute__((always_inline)) inline bool t_out_of_range(const TWatch (&w)[BI], const uint32_t (&filled)[BI]) {
     bool bad = false;
-    uint32_t f = filled[0], s = w[0].below & f;
-#pragma unroll 1
-    for (int i = 0; i < BI; i++) {
-        int all_small = 0, all_filled = 0;
-#pragma unroll 1
-        for (uint32_t bit = 1u << 31; bit; bit >>= bit & 0x10101010u ? 5 : 1) {  // a row of each half wave
-            const uint64_t bs = __builtin_amdgcn_ballot_w64((s & bit) != 0), bf = __builtin_amdgcn_ballot_w64((f & bit) != 0);
-            all_small += __builtin_popcountll(bs);
-            all_filled += __builtin_popcountll(bf);
-            bad |= (uint32_t)bs == (uint32_t)bf && __builtin_popcount((uint32_t)bf) >= 4;
-            bad |= bs >> 32 == bf >> 32 && __builtin_popcount((uint32_t)(bf >> 32)) >= 4;
-        }
-        const int n = __builtin_popcount(s);
-        bad |= __builtin_amdgcn_ballot_w64(n >= 4 && 2 * n >= __builtin_popcount(f)) != 0;
-        bad |= all_small >= 8 && 8 * all_small >= all_filled;
-        bad |= all_small >= 2 && all_small == all_filled;
 #pragma unroll
-        for (int j = 1; j < BI; j++)
-            if (j == i + 1) {
-                f = filled[j];
-                s = w[j].below & f;
-            }
+    for (int i = 0; i < BI; i += 2) {
+        // rows: two blocks' bits together
+        const int j = i + 1 < BI ? i + 1 : i;
+        const uint32_t f = filled[i] | (j > i ? filled[j] >> 4 : 0u), b = w[i].below | (j > i ? w[j].below >> 4 : 0u);
+        RowBits r{f & ~b, f, 0, 0};
+        r.reduce();
+        bad |= (r.four & ~r.left) != 0;
     }
-    return bad;
+#pragma unroll
+    for (int i = 0; i < BI; i++) {
+        const int f = __builtin_popcount(filled[i]), n = __builtin_popcount(filled[i] & w[i].below);
+        bad |= n >= 4 && 2 * n >= f;
+        int sum = n << 16 | f;  // over the wave
+        sum += (int)lane_dpp<kRor8>((uint32_t)sum);
+        sum += (int)lane_dpp<kRor4>((uint32_t)sum);
+        sum += (int)lane_dpp<kRor2>((uint32_t)sum);
+        sum += (int)lane_dpp<kRor1>((uint32_t)sum);
+        const int all = __builtin_amdgcn_readlane(sum, 0) + __builtin_amdgcn_readlane(sum, 16) +
+                        __builtin_amdgcn_readlane(sum, 32) + __builtin_amdgcn_readlane(sum, 48);
+        const int small = all >> 16, in = all & 0xffff;
+        bad |= (small >= 8 && 8 * small >= in) || (small >= 2 && small == in);
+    }
+    return __builtin_amdgcn_ballot_w64(bad) != 0;
 }
 
 __device__ inline f32x16 mfma_f16(f16x8 a, f16x8 b, f32x16 c) {
@@ -244,12 +281,22 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
     const int h = lane >> 5, c = lane & 31;
-    if (EPI_T && *g.u_bad) {
-        // nothing of this group runs on pairs
-        const int bpo = g.n32 >> 5, last = min(nt * 8 + 7, bpo * g.batch - 1) / bpo;
-        for (int b = nt * 8 / bpo + tid; b <= last; b += 512) atomicOr(&g.skip[b], kSkipStage1);
-        if (tid == 0) atomicOr(g.any, 1);
-        return;
+    if (EPI_T ? *g.any | *g.u_bad : *g.any) {
+        // nothing to do where all operators are skipped (64 of 1024 states, all
+        // skipped: 10.3 ms with these products and the 64-wide FP32 tiles, 8.4
+        // without and with the 128-wide ones; 7.96 on the FP32 kernels alone).
+        // Stage 1 looks at the split pass's bits only, which no tile changes, so
+        // that all waves decide alike; when U is out of range it marks the
+        // operators.
+        const int bpo = g.n32 >> 5, first = nt * 8 / bpo, last = min(nt * 8 + 7, bpo * g.batch - 1) / bpo;
+        if (EPI_T && *g.u_bad) {
+            for (int b = first + tid; b <= last; b += 512) atomicOr(&g.skip[b], kSkipStage1);
+            if (tid == 0) atomicOr(g.any, 1);
+            return;
+        }
+        bool all = true;
+        for (int b = first; b <= last; b++) all &= (g.skip[b] & (EPI_T ? kSkipSplit : ~0)) != 0;
+        if (all) return;
     }
     const int st0 = part * g.part_slabs;
     const int nk = min(g.part_slabs, (int)n_slabs(g.K) - st0);
@@ -1161,6 +1208,7 @@ FlatDesc f16_stage2(const F16Scale& g, float* c, int64_t ldc, int64_t c_bs) {
     b.row_e = g.eu;
     b.col_e = g.eu;
     b.skip = g.skip;
+    b.any = g.any;
     b.parts = 1;
     b.part_slabs = (int)n_slabs(b.K);
     return b;
