@@ -248,6 +248,17 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     return ws
 
 
+def _workspace_or_less(preferred: int, least: int, device) -> torch.Tensor:
+    """The preferred workspace, or where memory does not hold it the smaller one
+    that the library takes as well (more chunks, or the FP32 kernels)."""
+    try:
+        return _workspace(preferred, device)
+    except torch.OutOfMemoryError:
+        if least >= preferred:
+            raise
+        return _workspace(least, device)
+
+
 # --------------------------------------------------------------- raw C ABI --
 
 def rot_workspace_size(groups, prec: int, ops_per_chunk: int = 0, for_backward: bool = False) -> int:
@@ -406,7 +417,7 @@ def rotate(U: torch.Tensor, O: torch.Tensor, d: int, precision="fp32", out: torc
         _row_layout(out, "out")
     p = _problem(U, O, out, d)
     if workspace is None:
-        workspace = _workspace(rot_workspace_preferred([p], prec), U.device)
+        workspace = _workspace_or_less(rot_workspace_preferred([p], prec), rot_workspace_size([p], prec), U.device)
     rot_batch([p], prec, workspace.data_ptr(), workspace.numel(), _stream(stream),
               ROT_ASSUME_SYMMETRIC_O if symmetric_O else 0)
     return out
@@ -461,7 +472,8 @@ def rotate_site(U: torch.Tensor, X, S, precision="fp32", workspace: torch.Tensor
     p = RotSiteProblem(m, d, mp, n, kind, U.data_ptr(), S_host.ctypes.data_as(ctypes.POINTER(ctypes.c_double)),
                        xp, sx, out.data_ptr(), mp * mp)
     if workspace is None:
-        workspace = _workspace(rot_site_workspace_preferred([p], prec), U.device)
+        workspace = _workspace_or_less(rot_site_workspace_preferred([p], prec), rot_site_workspace_size([p], prec),
+                                       U.device)
     rot_batch_site([p], prec, workspace.data_ptr(), workspace.numel(), _stream(stream))
     return out if kind == ROT_BLOCK_DENSE else out[0]
 
@@ -790,10 +802,12 @@ class Plan:
             _check_inputs(U, O, d, ROT_FP32)
             probs.append(_problem(U, O, out, d))
         self._probs = (RotProblem * len(probs))(*probs)
-        if workspace_bytes is None:
-            workspace_bytes = rot_plan_workspace_preferred(probs, ROT_FP32)
         dev = self._groups[0][0].device if self._groups else torch.device("cuda")
-        self.workspace = _workspace(workspace_bytes, dev)
+        if workspace_bytes is None:
+            self.workspace = _workspace_or_less(rot_plan_workspace_preferred(probs, ROT_FP32),
+                                                rot_workspace_size(probs, ROT_FP32), dev)
+        else:
+            self.workspace = _workspace(workspace_bytes, dev)
         flags = (0 if graph else ROT_PLAN_NO_GRAPH) | (0 if tune else ROT_PLAN_NO_TUNE) | (
             ROT_PLAN_RETUNE if retune else 0)
         h = ctypes.c_void_p()
