@@ -248,15 +248,17 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     return ws
 
 
-def _workspace_or_less(preferred: int, least: int, device) -> torch.Tensor:
-    """The preferred workspace, or where memory does not hold it the smaller one
-    that the library takes as well (more chunks, or the FP32 kernels)."""
+def _workspace_or_less(preferred: int, device, least, *args) -> torch.Tensor:
+    """The preferred workspace, or where memory does not hold it the smaller one,
+    least(*args) bytes, that the library takes as well (more chunks, or the FP32
+    kernels)."""
     try:
         return _workspace(preferred, device)
     except torch.OutOfMemoryError:
-        if least >= preferred:
+        smaller = least(*args)
+        if smaller >= preferred:
             raise
-        return _workspace(least, device)
+        return _workspace(smaller, device)
 
 
 # --------------------------------------------------------------- raw C ABI --
@@ -417,7 +419,7 @@ def rotate(U: torch.Tensor, O: torch.Tensor, d: int, precision="fp32", out: torc
         _row_layout(out, "out")
     p = _problem(U, O, out, d)
     if workspace is None:
-        workspace = _workspace_or_less(rot_workspace_preferred([p], prec), rot_workspace_size([p], prec), U.device)
+        workspace = _workspace_or_less(rot_workspace_preferred([p], prec), U.device, rot_workspace_size, [p], prec)
     rot_batch([p], prec, workspace.data_ptr(), workspace.numel(), _stream(stream),
               ROT_ASSUME_SYMMETRIC_O if symmetric_O else 0)
     return out
@@ -472,8 +474,8 @@ def rotate_site(U: torch.Tensor, X, S, precision="fp32", workspace: torch.Tensor
     p = RotSiteProblem(m, d, mp, n, kind, U.data_ptr(), S_host.ctypes.data_as(ctypes.POINTER(ctypes.c_double)),
                        xp, sx, out.data_ptr(), mp * mp)
     if workspace is None:
-        workspace = _workspace_or_less(rot_site_workspace_preferred([p], prec), rot_site_workspace_size([p], prec),
-                                       U.device)
+        workspace = _workspace_or_less(rot_site_workspace_preferred([p], prec), U.device, rot_site_workspace_size, [p],
+                                       prec)
     rot_batch_site([p], prec, workspace.data_ptr(), workspace.numel(), _stream(stream))
     return out if kind == ROT_BLOCK_DENSE else out[0]
 
@@ -804,8 +806,8 @@ class Plan:
         self._probs = (RotProblem * len(probs))(*probs)
         dev = self._groups[0][0].device if self._groups else torch.device("cuda")
         if workspace_bytes is None:
-            self.workspace = _workspace_or_less(rot_plan_workspace_preferred(probs, ROT_FP32),
-                                                rot_workspace_size(probs, ROT_FP32), dev)
+            self.workspace = _workspace_or_less(rot_plan_workspace_preferred(probs, ROT_FP32), dev, rot_workspace_size,
+                                                probs, ROT_FP32)
         else:
             self.workspace = _workspace(workspace_bytes, dev)
         flags = (0 if graph else ROT_PLAN_NO_GRAPH) | (0 if tune else ROT_PLAN_NO_TUNE) | (

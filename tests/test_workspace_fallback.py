@@ -17,14 +17,14 @@ def test_smaller_workspace_when_memory_is_short(monkeypatch):
         return real((n + 255) // 256 * 256, **kw)
 
     monkeypatch.setattr(rot_mod, "_workspace", lambda n, device: short(n, dtype=torch.uint8, device=device))
-    assert rot_mod._workspace_or_less(2000, 500, "cpu").numel() >= 500
+    assert rot_mod._workspace_or_less(2000, "cpu", int, 500).numel() >= 500
     assert asked == [2000, 500]
-    assert rot_mod._workspace_or_less(900, 500, "cpu").numel() >= 900
+    assert rot_mod._workspace_or_less(900, "cpu", int, 500).numel() >= 900
     with pytest.raises(torch.OutOfMemoryError):
-        rot_mod._workspace_or_less(5000, 2000, "cpu")
+        rot_mod._workspace_or_less(5000, "cpu", int, 2000)
     asked.clear()
     with pytest.raises(torch.OutOfMemoryError):
-        rot_mod._workspace_or_less(2000, 2000, "cpu")
+        rot_mod._workspace_or_less(2000, "cpu", int, 2000)
     assert asked == [2000]
 
 
