@@ -91,7 +91,6 @@ struct FlatDesc {
     const uint16_t *b_hi, *b_lo;  // slab layout, n32 rows per operator, b_bs elements apart
     int64_t b_bs;
     int n32;                    // N rounded up to 32
-    int bi;                     // 32-row blocks per wave: 64 bi rows per tile
     int tiles_m, tiles_n, parts, part_slabs;
     // plain epilogue: C_b(row, col) 2^-(e0 + op_e[b] + row_e[row] + col_e[col])
     // at c + part*c_ps + b*c_bs + row*ldc + col
@@ -1019,7 +1018,6 @@ constexpr int kF16MaxParts = 8;
 
 template <bool EPI_T, int DS>
 hipError_t launch_flat(FlatDesc g, const FlatCfg& c, hipStream_t s) {
-    g.bi = c.bi;
     g.parts = c.parts;
     g.part_slabs = c.part_slabs;
     g.tiles_m = div_up(g.M, 64 * c.bi);

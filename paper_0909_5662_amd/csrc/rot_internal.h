@@ -32,13 +32,14 @@ struct GemmDesc {
     // symmetric output (M == N, no accumulation): only tiles on or above the
     // diagonal are computed, each off-diagonal one also stored transposed
     bool upper;
-    // split K (parts > 1; kbatch == 1, no upper, no accumulate): part p
+    // split K (parts > 1; kbatch == 1, no accumulate, upper in FP64 only): part p
     // multiplies K range [p*kp, min(K, (p+1)*kp)) and writes its product to
     // C + p*c_ps; the caller adds the parts
     int parts, kp;
     int64_t c_ps;
-    // when set (FP32 rotations), batch elements b with only[b] == 0 are left
-    // alone, and all of them if *any == 0
+    // when set, both, batch elements b with only[b] == 0 are left alone, and all
+    // of them if *any == 0 (FP32, M/N-contiguous B, kbatch == 1, no parts, no
+    // accumulate)
     const int *only, *any;
     // with inner > 1, batch element g reads A at (g / inner)*a_bs +
     // (g % inner)*a_is (B likewise)
