@@ -290,18 +290,19 @@ constexpr int64_t kWideTiles = 1024;
 hipError_t gemm_any(const GemmDesc& g, bool is_double, hipStream_t stream) {
     if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
     if (g.upper && (g.M != g.N || g.accumulate)) return hipErrorInvalidValue;
-    const int parts = g.parts > 1 ? g.parts : 1;
-    if (parts > 1 && ((g.upper && !is_double) || g.accumulate || g.kbatch != 1 || g.kp <= 0 || g.kp % kSlice != 0 ||
-                      (int64_t)g.kp * (parts - 1) >= g.K))
+    const int parts = g.parts > 1 && !g.only ? g.parts : 1;
+    if (g.parts > 1 && ((g.upper && !is_double) || g.accumulate || g.kbatch != 1 || g.kp <= 0 || g.kp % kSlice != 0 ||
+                      (int64_t)g.kp * (g.parts - 1) >= g.K))
         return hipErrorInvalidValue;
     const int tm = (g.M + kTile - 1) / kTile, tn = (g.N + kTile - 1) / kTile;
     const int64_t tiles = (g.upper ? (int64_t)tm * (tm + 1) / 2 : (int64_t)tm * tn) * g.batch * parts;
-    if (is_double || tiles < kWideTiles || !direct_lds_ok(g)) return gemm_tile64(g, is_double, stream);
+    if (is_double || tiles < kWideTiles || (g.only && g.parts > 1) || !direct_lds_ok(g))
+        return gemm_tile64(g, is_double, stream);
     if (tiles > 0x7fffffff) return hipErrorInvalidValue;
     const bool edge = g.M % kTile != 0 || g.N % kTile != 0;
     if (g.only) {
         // rotations only (as in gemm_tile64.hip)
-        if (!g.any || g.b_kcontig || parts > 1 || g.accumulate || g.kbatch != 1) return hipErrorInvalidValue;
+        if (!g.any || g.b_kcontig || g.accumulate || g.kbatch != 1) return hipErrorInvalidValue;
         auto only = [&](auto ak, auto mode) {
             constexpr bool AK = decltype(ak)::value;
             constexpr int MD = decltype(mode)::value;

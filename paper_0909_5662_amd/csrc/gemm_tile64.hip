@@ -232,8 +232,9 @@ template <> struct Acc<double> {
     }
 };
 
-// Tile `lin` of the launch.
-template <typename T, bool AK, bool BK, Addr ADDR>
+// Tile `lin` of the launch.  SUM: K parts one after the other, added as the pass
+// over their partial results would.
+template <typename T, bool AK, bool BK, Addr ADDR, bool SUM>
 __device__ __attribute__((always_inline)) inline void gemm_tile64_tile(const GemmDesc& g, int lin, int per_part,
                                                                        int tiles_m, int tiles_n) {
     typedef Slice<T, AK, ADDR> SA;
@@ -241,7 +242,7 @@ __device__ __attribute__((always_inline)) inline void gemm_tile64_tile(const Gem
     __shared__ __attribute__((aligned(16))) T As[2][SA::ELEMS];
     __shared__ __attribute__((aligned(16))) T Bs[2][SB::ELEMS];
     int part = 0;
-    if (g.parts > 1) {
+    if (!SUM && g.parts > 1) {
         part = lin / per_part;
         lin -= part * per_part;
     }
@@ -272,11 +273,10 @@ __device__ __attribute__((always_inline)) inline void gemm_tile64_tile(const Gem
     const T* Bb = static_cast<const T*>(g.B) + (int64_t)go * g.b_bs + (int64_t)gi * g.b_is;
     // slices: of one K batch after the other, or of this part's K range
     const int nk = (g.K + kS - 1) / kS;
-    const int s0 = g.parts > 1 ? part * (g.kp / kS) : 0;
-    const int total = g.parts > 1 ? min(g.kp / kS, nk - s0) : nk * g.kbatch;
+    int s0 = g.parts > 1 ? part * (g.kp / kS) : 0;
+    int total = g.parts > 1 ? min(g.kp / kS, nk - s0) : nk * g.kbatch;
 
     Acc<T> acc;
-    acc.clear();
     typename SA::Source sa;
     typename SB::Source sb;
     sa.init(Ab, g.lda, m0, g.M, g.K, tid);
@@ -303,17 +303,37 @@ __device__ __attribute__((always_inline)) inline void gemm_tile64_tile(const Gem
         }
         __syncthreads();
     };
-    if (total > 0) {
-        fetch(0, a0, b0);
-        if (total > 1) fetch(1, a1, b1);
-        a0.store(As[0], tid);
-        b0.store(Bs[0], tid);
-        __syncthreads();
+    auto walk = [&]() __attribute__((always_inline)) {
+        acc.clear();
+        if (total > 0) {
+            fetch(0, a0, b0);
+            if (total > 1) fetch(1, a1, b1);
+            a0.store(As[0], tid);
+            b0.store(Bs[0], tid);
+            __syncthreads();
+        }
+        for (int t = 0; t < total; t += 2) {
+            step(t, 0, a0, b0, a1, b1);
+            if (t + 1 < total) step(t + 1, 1, a1, b1, a0, b0);
+        }
+    };
+    T sum[SUM ? Acc<T>::N : 1];
+    if (SUM) {
+#pragma unroll
+        for (int v = 0; v < Acc<T>::N; v++) sum[SUM ? v : 0] = T(0);
+        for (int q = 0; q < max(g.parts, 1); q++) {
+            if (g.parts > 1) {
+                s0 = q * (g.kp / kS);
+                total = min(g.kp / kS, nk - s0);
+            }
+            walk();
+#pragma unroll
+            for (int v = 0; v < Acc<T>::N; v++) sum[SUM ? v : 0] += acc.at(v);
+        }
+    } else {
+        walk();
     }
-    for (int t = 0; t < total; t += 2) {
-        step(t, 0, a0, b0, a1, b1);
-        if (t + 1 < total) step(t + 1, 1, a1, b1, a0, b0);
-    }
+    auto value = [&](int v) __attribute__((always_inline)) { return SUM ? sum[SUM ? v : 0] : acc.at(v); };
 
     T* Cb = static_cast<T*>(g.C) + (int64_t)gb * g.c_bs + (int64_t)part * g.c_ps;
     // symmetric output: off-diagonal tiles are also stored transposed, a
@@ -332,7 +352,7 @@ __device__ __attribute__((always_inline)) inline void gemm_tile64_tile(const Gem
     for (int v = 0; v < Acc<T>::N; v++) {
         const int row = m0 + wm + Acc<T>::row(lane, v), col = n0 + wn + Acc<T>::col(lane, v);
         if (row < g.M && col < g.N && (!diag || row <= col)) {
-            const T x = g.accumulate ? old[v] + acc.at(v) : acc.at(v);
+            const T x = g.accumulate ? old[v] + value(v) : value(v);
             Cb[(int64_t)row * g.ldc + col] = x;
             if (mirror || (diag && row < col)) Cb[(int64_t)col * g.ldc + row] = x;
         }
@@ -341,24 +361,25 @@ __device__ __attribute__((always_inline)) inline void gemm_tile64_tile(const Gem
 
 template <typename T, bool AK, bool BK, Addr ADDR>
 __global__ __launch_bounds__(256, 4) void gemm_tile64_kernel(GemmDesc g, int tiles_m, int tiles_n) {
-    gemm_tile64_tile<T, AK, BK, ADDR>(g, xcd_linear_id(), g.parts > 1 ? gridDim.x / g.parts : 0, tiles_m, tiles_n);
+    gemm_tile64_tile<T, AK, BK, ADDR, false>(g, xcd_linear_id(), g.parts > 1 ? gridDim.x / g.parts : 0, tiles_m, tiles_n);
 }
 
 // The products of flagged batch entries (g.only), normally none: a few
-// workgroups look at one flag and end, or walk all tiles.  (65 operators of 403
+// workgroups look at one flag and end, or walk all tiles.  K parts are summed by
+// the workgroup, so that an entry has the bits of the split product.  (65 operators of 403
 // states: one workgroup per tile 10.1 us for stage 1 with its 11375, now 4.6.)
 template <typename T, bool AK, bool BK, Addr ADDR>
 __global__ __launch_bounds__(256, 4) void gemm_tile64_only_kernel(GemmDesc g, int tiles_m, int tiles_n, int tiles) {
     if (!*g.any) return;
     for (int lin = blockIdx.x; lin < tiles; lin += gridDim.x)
-        gemm_tile64_tile<T, AK, BK, ADDR>(g, lin, 0, tiles_m, tiles_n);
+        gemm_tile64_tile<T, AK, BK, ADDR, true>(g, lin, 0, tiles_m, tiles_n);
 }
 
 template <typename T>
 hipError_t launch(const GemmDesc& g, hipStream_t stream) {
     const int tm = (g.M + kT - 1) / kT, tn = (g.N + kT - 1) / kT;
     const int64_t tiles =
-        (g.upper ? (int64_t)tm * (tm + 1) / 2 : (int64_t)tm * tn) * g.batch * (g.parts > 1 ? g.parts : 1);
+        (g.upper ? (int64_t)tm * (tm + 1) / 2 : (int64_t)tm * tn) * g.batch * (g.parts > 1 && !g.only ? g.parts : 1);
     if (tiles > 0x7fffffff) return hipErrorInvalidValue;
     const int64_t lim = ((int64_t)1 << 32) / (int64_t)sizeof(T);
     auto addr = [&](bool kc, int64_t ld, int64_t rows) {
@@ -368,7 +389,7 @@ hipError_t launch(const GemmDesc& g, hipStream_t stream) {
     const Addr a = std::max(addr(g.a_kcontig, g.lda, g.M), addr(g.b_kcontig, g.ldb, g.N));
     if (g.only) {
         // rotations only: A is O (K-contiguous) or U, B is M/N-contiguous
-        if (!g.any || g.b_kcontig || g.parts > 1 || sizeof(T) != 4) return hipErrorInvalidValue;
+        if (!g.any || g.b_kcontig || sizeof(T) != 4) return hipErrorInvalidValue;
         auto only = [&](auto ak) {
             constexpr bool AK = decltype(ak)::value;
             return a == kNear     ? gemm_tile64_only_kernel<float, AK, false, kNear>

@@ -519,6 +519,8 @@ rot_status batch(const rot_problem* groups, int32_t n_groups, rot_precision prec
                         g1.only = g2.only = skip;
                         g1.any = g2.any = skip + nb;
                         g2.upper = sym;
+                        // in the K parts of the FP32 path
+                        g2.parts = sym ? 1 : stage2_parts(p, p.n_ops, &g2.kp);
                         const hipError_t e = gemm(prec, g1, s, "rest1");
                         return e == hipSuccess ? gemm(prec, g2, s, "rest2") : e;
                     };

@@ -38,8 +38,8 @@ struct GemmDesc {
     int parts, kp;
     int64_t c_ps;
     // when set, both, batch elements b with only[b] == 0 are left alone, and all
-    // of them if *any == 0 (FP32, M/N-contiguous B, kbatch == 1, no parts, no
-    // accumulate)
+    // of them if *any == 0 (FP32, M/N-contiguous B, kbatch == 1, no accumulate;
+    // parts are added by the kernel, to the bits of the caller's sum, into C)
     const int *only, *any;
     // with inner > 1, batch element g reads A at (g / inner)*a_bs +
     // (g % inner)*a_is (B likewise)

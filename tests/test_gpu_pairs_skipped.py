@@ -86,7 +86,8 @@ def test_skipped_in_later_chunks(rot, oracle_mod):
 
 
 def test_skipped_with_k_parts(rot, oracle_mod):
-    """Partial sums of a skipped operator are not its result."""
+    """Partial sums of a skipped operator are not its result; it has the FP32
+    path's K parts, and so its bits."""
     m, mp, n = 404, 391, 4
     U, O = inputs(m, mp, n, 7700)
     grade(O, [1])
@@ -96,6 +97,7 @@ def test_skipped_with_k_parts(rot, oracle_mod):
     kinds = rot.profile_read()
     rot.profile_enable(False)
     assert "stage1_f16x3" in kinds and "stage2_sum" in kinds
+    assert torch.equal(got[1], fp32_kernels(rot, U, O)[1])
     check(oracle_mod, U, O, got, list(range(n)))
 
 
