@@ -30,15 +30,18 @@
 //     than 2^12, or non-zero entries below 2^-2 make up a quarter of 16 entries
 //     of a row or of 64 of a column (split pass);
 //   - the same is true of U: then every operator is (split pass: 3 of 8 entries
-//     of a column, or a quarter of a row's 32 in its half of a wave);
+//     of a column, or a quarter of a row's 32 in its half of a wave), as where
+//     U's columns are short or mostly scattered zeros (kPairColumn);
 //   - in a 32 x 32 block of T they are half of a lane's 16 or a whole row of 32,
 //     or an eighth of the block (stage 1, t_out_of_range).
 // Scattered small entries of a Gaussian operand (6e-5 of O and U, 0.5 % of T at
 // 1024 states) stay far below these counts.  Zeros count for nothing: they are
-// exact.  Of the operators accepted, every block of the result is as exact as
-// FP32's or more (160 states; columns of operators that U leaves out, states
-// that U hardly reaches, sectors, in order and mixed, and tails of U, from
-// 2^0 to 2^-16 of the rest: at most 0.93 times the FP32 kernels' error).
+// exact.  Blocks of the results of accepted operators against the FP32 kernels'
+// error: columns of operators that U leaves out, states that U hardly reaches,
+// sectors, in order and mixed, and tails of U, from 2^0 to 2^-16 of the rest, at
+// most 0.93 times it (160 states); sectors, sites, rows, columns and sparsity
+// drawn at random (64 to 330 states, d 1 to 8, 16 500 blocks), at most 1.0e-7
+// more (sparse operators between short sectors).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -76,6 +79,13 @@ __device__ inline u32x2 split2_f16(float a, float b) {
     return u32x2{h, __builtin_bit_cast(uint32_t, l)};
 }
 
+// What the split pass finds in U (cleared by the scale pass).
+struct UState {
+    int bad;         // leaves the pairs' range
+    uint32_t filled; // entries that are not zero
+    int runs;        // groups of eight of a column with five and more of them less those with one to four
+};
+
 // Rotation products with one A for every operator (U1 or U2) and one B per
 // operator: the operators' B rows, each padded to whole blocks of 32, are laid
 // end to end, and a tile takes 8 consecutive blocks (256 columns) whatever
@@ -105,7 +115,8 @@ struct FlatDesc {
     int64_t t_bs;
     int* skip;                  // operators left to the FP32 kernels: kSkipSplit, kSkipStage1
     int* any;                   // raised with the first of them
-    const int* u_bad;           // U leaves the pairs' range
+    const UState* u;            // stage 1: what the split pass found in U
+    uint32_t u_least;           // entries that U needs
     // symmetric output (M == N, plain epilogue): tiles below the diagonal of
     // all their operators are left out, entries on or above it are also stored
     // transposed
@@ -115,6 +126,18 @@ struct FlatDesc {
 // Bits of skip[b]: what the split pass found, and stage 1 (whose tiles read
 // the first while others set the second).
 constexpr int kSkipSplit = 1, kSkipStage1 = 2;
+
+// U's columns hold at least this many entries on average (three quarters of
+// shorter ones, 64 at least), mostly five and more of eight neighbours, or the
+// FP32 instructions' sums, which round once per entry or two of them (two k)
+// where these kernels round three times per 16 k, are the more exact ones: 128
+// states with 1 / 16 / 64 / 128 / 256 of 512 entries per column, scattered, 0 /
+// 0.85e-7 / 1.6e-7 / 2.3e-7 / 3.2e-7 against 0.4e-7 / 1.7e-7 / 2.4e-7 / 2.8e-7 /
+// 2.9e-7; 74 of 369 in a row, sparse operators, 0.8e-7 against 1.9e-7.  Zeros of
+// an operator do not matter: with such a U diagonal ones, permutations and ones
+// of 1 entry in 20 have 0.61 to 1.01 times the FP32 kernels' error from 64 states
+// on.
+constexpr int kPairColumn = 128, kPairShortColumn = 64;
 
 // Entries of a pair operand below this are off by more than 2^-23 of themselves.
 constexpr float kPairLeast = 0.25f;
@@ -280,15 +303,16 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
     const int h = lane >> 5, c = lane & 31;
-    if (EPI_T ? *g.any | *g.u_bad : *g.any) {
+    const bool u_bad = EPI_T && (g.u->bad || g.u->runs <= 0 || g.u->filled < g.u_least);
+    if (u_bad || *g.any) {
         // nothing to do where all operators are skipped (64 of 1024 states, all
         // skipped: 10.3 ms with these products and the 64-wide FP32 tiles, 8.4
         // without and with the 128-wide ones; 7.96 on the FP32 kernels alone).
         // Stage 1 looks at the split pass's bits only, which no tile changes, so
-        // that all waves decide alike; when U is out of range it marks the
+        // that all waves decide alike; when U is not for the pairs it marks the
         // operators.
         const int bpo = g.n32 >> 5, first = nt * 8 / bpo, last = min(nt * 8 + 7, bpo * g.batch - 1) / bpo;
-        if (EPI_T && *g.u_bad) {
+        if (u_bad) {
             for (int b = first + tid; b <= last; b += 512) atomicOr(&g.skip[b], kSkipStage1);
             if (tid == 0) atomicOr(g.any, 1);
             return;
@@ -634,7 +658,7 @@ struct F16Scale {
     int m32, mp32;     // rows of O_b's and T_b's layouts
     int* eo;           // [nb]
     int* skip;         // [nb], cleared by the scale pass
-    int* u_bad;        // U leaves the pairs' range; cleared by the scale pass when it works on U
+    UState* u;         // cleared by the scale pass when it works on U
     int* any;          // raised when an operator is skipped (behind skip; plans: one per chunk)
     uint16_t *u1h, *u1l, *u2h, *u2l;
     uint16_t *oh, *ol;
@@ -673,7 +697,7 @@ __device__ inline void f16_scale_block(const F16Scale& g, int blk) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     __shared__ uint32_t red[4][64], red2[SITE ? 4 : 1][64];
     if (blk < g.u_blocks) {
-        if (blk == 0 && tid == 0) *g.u_bad = 0;
+        if (blk == 0 && tid == 0) *g.u = UState{0, 0, 0};
         const int cb = div_up(g.mp, 64), half = g.u_blocks / 2;
         const bool up = SITE && blk >= half;
         const int x = up ? blk - half : blk;
@@ -776,7 +800,7 @@ __global__ __launch_bounds__(256) void f16_scale_list_kernel(const F16Scale* tab
 // of U1's rows and d slabs of U2's, both written in whole 16-byte chunks,
 // chunk after chunk.  One on O takes a 64 x 64 block (split_o_kernel's
 // scheme).  The first block of each operator records eo[b]; each raises skip[b]
-// (on U: u_bad) where its entries are out of range.
+// (on U: u->bad) where its entries are out of range.
 // With a site, the first half of the workgroups on U writes U1 from U and the
 // second U2 from Up.
 template <int DMAX, bool SITE>
@@ -830,17 +854,22 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
         __syncthreads();
         const int na = min(64, g.mp - a0);
         // entries below the pairs' range: three of a thread's eight, or a
-        // quarter of a row's 32 among the wave's (two rows take turns in it)
+        // quarter of a row's 32 among the wave's (two rows take turns in it);
+        // and how full the eights are
         bool u_bad = false;
+        int filled = 0, runs = 0;
         auto check = [&](const float (&v)[8]) {
-            int small = 0;
+            int small = 0, n = 0;
 #pragma unroll
             for (int k = 0; k < 8; k++) {
                 const bool s = pair_small(v[k]);
                 small += s;
+                n += v[k] != 0.f;
                 u_bad |= __builtin_popcountll(__ballot(s)) >= 8;
             }
             u_bad |= small >= 3;
+            filled += n;
+            runs += n >= 5 ? 1 : n ? -1 : 0;
         };
         // U1: rows a*d + s of slab q, chunk (row, slot)
         const int64_t rows1 = (int64_t)d * g.mp;
@@ -869,7 +898,22 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
             const int64_t off = sq * (int64_t)g.mp * kSlabK + (int64_t)(a0 + al) * kSlabK + slot * 8;
             store8(g.u2h + off, g.u2l + off, v);
         }
-        if (__any(u_bad) && lane == 0) atomicOr(g.u_bad, 1);
+        if (__any(u_bad) && lane == 0) atomicOr(&g.u->bad, 1);
+#pragma unroll
+        for (int s = 32; s; s >>= 1) {
+            filled += __shfl_xor(filled, s);
+            runs += __shfl_xor(runs, s);
+        }
+        if (lane == 0) {
+            s_mx[wave][0] = (uint32_t)filled;
+            s_mx[wave][1] = (uint32_t)runs;
+        }
+        __syncthreads();
+        if (tid < 2) {
+            const uint32_t x = s_mx[0][tid] + s_mx[1][tid] + s_mx[2][tid] + s_mx[3][tid];
+            if (tid == 0) atomicAdd(&g.u->filled, x);
+            else atomicAdd(&g.u->runs, (int)x);
+        }
         return;
     }
     blk -= g.u_blocks;
@@ -1040,7 +1084,7 @@ struct F16Layout {
     size_t t_op, o_op;          // one operator's
     size_t t32;                 // one operator's T of the FP32 kernels
     size_t part_u, ublk, eu;    // scale pass: partial column maxima, block maxima, exponents
-    size_t u_bad;
+    size_t u_state;
     size_t shared;
 };
 
@@ -1058,8 +1102,8 @@ F16Layout f16_layout(const rot_problem& p, int d_all = 0) {
     L.part_u = al256(chunks * p.mp * 4);
     L.ublk = al256((d_all ? 2 : 1) * chunks * div_up(p.mp, 64) * 4);
     L.eu = al256((size_t)(p.mp + 256) * 4);  // read in groups of four up to a tile's last row
-    L.u_bad = 256;
-    L.shared = L.u_bad + 2 * L.u1 + 2 * L.u2 + (d_all ? 2 : 1) * (L.part_u + L.eu) + L.ublk;
+    L.u_state = al256(sizeof(UState));
+    L.shared = L.u_state + 2 * L.u1 + 2 * L.u2 + (d_all ? 2 : 1) * (L.part_u + L.eu) + L.ublk;
     return L;
 }
 
@@ -1123,7 +1167,7 @@ F16Bound f16_bind(const rot_problem& p, const F16Layout& L, int b0, int nb, int 
     g.upart = reinterpret_cast<uint32_t*>(take(L.part_u));
     g.ublk = reinterpret_cast<uint32_t*>(take(L.ublk));
     g.eu = reinterpret_cast<int*>(take(L.eu));
-    g.u_bad = reinterpret_cast<int*>(take(L.u_bad));
+    g.u = reinterpret_cast<UState*>(take(L.u_state));
     r.T = take(f16_t_bytes(L, nb));
     g.th = reinterpret_cast<uint16_t*>(r.T);
     g.tl = reinterpret_cast<uint16_t*>(r.T + al256(nb * L.t_op));
@@ -1179,7 +1223,10 @@ FlatDesc f16_stage1(const F16Scale& g) {
     a.t_shift = f16_t_shift(g.m);
     a.skip = g.skip;
     a.any = g.any;
-    a.u_bad = g.u_bad;
+    a.u = g.u;
+    // both halves of a site's split count
+    const int column = std::min(kPairColumn, std::max(kPairShortColumn, g.rows / 4 * 3));
+    a.u_least = (uint32_t)((int64_t)column * g.mp * (g.Up ? 2 : 1));
     a.parts = 1;
     a.part_slabs = (int)n_slabs(a.K);
     return a;

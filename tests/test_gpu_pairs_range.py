@@ -168,6 +168,50 @@ def test_single_rows_and_columns_are_found(rot):
     assert same == [2 * k for k in range(len(kept))] + [20 + 2 * k for k in range(len(rows))]
 
 
+def picked(per_column, rng):
+    """U with a few entries per column, anywhere (one: states picked out)."""
+    U = np.zeros((M * D, MP))
+    for beta in range(MP):
+        rows = rng.permutation(M * D)[:per_column]
+        U[rows, beta] = 1 if per_column == 1 else rng.standard_normal(per_column) / np.sqrt(per_column)
+    return U.reshape(M, D, MP), rng.standard_normal((2, M, M)), [(ALL, ALL)]
+
+
+@pytest.mark.parametrize("per_column", [1, 5, 40, 160])
+def test_sparse_U(rot, oracle_mod, per_column):
+    """Short sums are exact, or nearly, on the FP32 instructions: batches, site
+    products and plans with such a U stay there."""
+    U, O, _ = inputs(lambda size, rng: picked(per_column, rng), 0, 7260)
+    got, fp32 = rot.rotate(U, O, D, "fp32"), fp32_kernels(rot, U, O)
+    assert torch.equal(got, fp32)
+    if per_column == 1:
+        assert np.array_equal(host(got[:3]), oracle_mod.rotate(host(U), host(O[:3]), D))
+    S = np.eye(D)
+    assert torch.equal(rot.rotate_site(U, O, S, "fp32")[:3], rot.rotate_site(U, O[:3].contiguous(), S, "fp32"))
+    out = torch.empty_like(got)
+    plan = rot.Plan([(U, O, out, D)])
+    assert sum(c["pairs"] for c in plan.describe()["classes"]) == N
+    plan.execute()
+    torch.cuda.synchronize()
+    check(host(out[:3]), host(fp32[:3]), oracle_mod.rotate(host(U), host(O[:3]), D), [(ALL, ALL)])
+    if per_column == 1:
+        assert torch.equal(out, got)
+    plan.close()
+
+
+def test_sectors_in_order_stay_on_pairs(rot):
+    """Four sectors, operators between neighbours: runs of entries and zeros."""
+    rng = np.random.default_rng(7270)
+    U, O, n, k = np.zeros((M, D, MP)), np.zeros((N, M, M)), M // 4, MP // 4
+    for q in range(4):
+        U[q * n:(q + 1) * n, :, q * k:(q + 1) * k] = isometry(n * D, k, rng).reshape(n, D, k)
+        r = (q + 1) % 4
+        O[:, q * n:(q + 1) * n, r * n:(r + 1) * n] = rng.standard_normal((N, n, n))
+    U, O = dev(U.reshape(M * D, MP)), dev(O)
+    got, fp32 = rot.rotate(U, O, D, "fp32"), fp32_kernels(rot, U, O)
+    assert not any(torch.equal(got[b], fp32[b]) for b in range(N))
+
+
 @pytest.mark.parametrize("kind", [left_out, hardly_kept, sectors])
 def test_plan_of_uneven_entries(rot, oracle_mod, kind):
     """Two groups, one of even operators: each is judged by itself, at every
