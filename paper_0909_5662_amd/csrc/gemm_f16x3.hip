@@ -10,7 +10,7 @@
 // 403: 8.0e-7 -> 5.1e-7, 256: 4.4e-7 -> 3.2e-7, 128: 2.6e-7 -> 2.1e-7, 64:
 // 2.1e-7 -> 1.8e-7.
 // Time of the two stages and all passes around them, 64 operators of 1024
-// states: 8.02 -> 2.73 ms; 65 of 403 (kept 391): 1.31 -> 0.26 ms.
+// states: 8.02 -> 2.79 ms; 65 of 403 (kept 391): 1.31 -> 0.27 ms.
 //
 // Scaling.  U's columns and each operator are brought to a largest entry in
 // [2^14, 2^15) by exact powers of two (eu[beta], eo[b]).  |T| of the scaled
@@ -1262,7 +1262,7 @@ FlatDesc f16_stage2(const F16Scale& g, float* c, int64_t ldc, int64_t c_bs) {
 // Tiles of many products, longest first.  Each product takes the tallest
 // tiles that stay below a time limit; the limit is the one whose tiles,
 // handed out in this order to 256 CUs, end first by the estimate of flat_cfg
-// (a step's 17 groups of 128 to 1024 states: the 1024-state tiles of stage 2
+// (a step's 16 groups of 128 to 1024 states: the 1024-state tiles of stage 2
 // alone last as long as the mean CU's share).
 struct FlatProduct {
     int M, blocks, slabs;
@@ -1483,8 +1483,8 @@ hipError_t rotate_f16_site(const rot_problem& p, const F16Site& x, int b0, int n
 // launch per pass and stage, from tables and lists in device memory.  Stage 2
 // is not split over K: the plan's FP32 kernels do not either, and the tiles
 // of all groups together fill the chip.  One execution, FP32 kernels before
-// -> pairs (rate of the products in brackets, TFLOP/s): 17 groups of 128 to
-// 1024 states, 8 operators each, 230 GFLOP, 2427 -> 748 us (95 -> 307); 8 of
+// -> pairs (rate of the products in brackets, TFLOP/s): 16 groups of 128 to
+// 1024 states, 8 operators each, 230 GFLOP, 2427 -> 738 us (95 -> 312); 8 of
 // 1000 states 1372 -> 397 us; 50 GFLOP in 7 groups of 101 to 900 states, 3
 // operators each, 826 -> 229 us.
 

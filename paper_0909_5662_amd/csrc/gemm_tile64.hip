@@ -10,9 +10,9 @@
 // CU); the small tile leaves room for four and more workgroups per CU, which
 // hide each other's loads and barriers, and a ragged extent wastes at most
 // 63 rows.  128 x 128 tiles before it, one or two workgroups per CU: FP64 rotation of
-// 8 operators of 1024 states 2.33 -> 1.99 ms (69 of the 73 TFLOP/s that a
-// large library product reaches here), 12 of 400: 464 -> 255 us, 16 of 128:
-// 57.7 -> 30.9 us.
+// 8 operators of 1024 states 2.33 -> 2.04 ms (67 of the 73 TFLOP/s that a
+// large library product reaches here), 12 of 400: 464 -> 261 us, 16 of 128:
+// 57.7 -> 30.6 us.
 //
 // Loads are 16-byte buffer loads through registers.  They need 4-byte
 // alignment only, and a descriptor that ends with the operand returns zero,
