@@ -120,12 +120,12 @@ typedef struct {
  * range does not hold are computed by the FP32 kernels: those with infinities
  * or NaN, with many non-zero entries below 2^-16 of their largest one or rows
  * whose largest entries differ by more than 2^12, with many non-zero entries
- * of O U below 2^-17 of m max|O| max|U column|, and all of them if U holds an
- * infinity or NaN, many non-zero entries below 2^-16 of their column's largest,
- * or columns of few entries (128 on average, or mostly fewer than five of eight
- * neighbours).  Many means a quarter or more of some 8 to 64 neighbours (of O U:
- * half of 16, a row of 32, or an eighth of a 32 x 32 block); fewer cost no block
- * of a result the FP32 kernels' accuracy (1e-7 at most).
+ * of O U below 2^-17 of O's largest row sum times max|U column|, and all of
+ * them if U holds an infinity or NaN, many non-zero entries below 2^-16 of their
+ * column's largest, or columns of few entries (128 on average, or mostly fewer
+ * than five of eight neighbours).  Many means a quarter or more of some 8 to 64
+ * neighbours (of O U: half of 16, a row of 32, or an eighth of a 32 x 32 block);
+ * fewer cost no block of a result the FP32 kernels' accuracy (1.3e-7 at most).
  * Groups may have
  * different m, d, mp.  ROT_SPLIT_BF16 picks each stage's tile configuration per shape (m, d,
  * mp, chunk): from the tuning cache (in memory, and in the file named by

@@ -14,11 +14,13 @@
 //
 // Scaling.  U's columns and each operator are brought to a largest entry in
 // [2^14, 2^15) by exact powers of two (eu[beta], eo[b]).  |T| of the scaled
-// operands is below m 2^30, so stage 1's epilogue multiplies by 2^-t with
-// t = 15 + ceil(log2 m) before it splits T; stage 2's undoes every scale.
-// FP16's range leaves entries from 2^-2 on, 2^-16 of an operand's largest entry
-// or 2^-17 of T's bound (Gaussian operators of 1024 states: T at 2^-9), at full
-// precision; the pair of a smaller one is off by up to 2^-25 whatever its size.
+// operands is below 2^15 times the largest row sum of |O_b|, so stage 1's
+// epilogue multiplies by 2^-t with that sum below 2^t before it splits T; stage
+// 2's undoes every scale.  FP16's range leaves entries from 2^-2 on, 2^-16 of an
+// operand's largest entry or 2^-17 of T's bound (Gaussian operators of 1024
+// states: T at 2^-7; by m max|O| instead of the row sum it was at 2^-10, and large
+// operators had blocks of T below it by chance), at full precision; the pair of
+// a smaller one is off by up to 2^-25 whatever its size.
 //
 // Range.  Where such entries are many, in a part of an operand that some result
 // is made of alone, that result would be less exact than FP32's: columns of an
@@ -34,13 +36,13 @@
 //     U's columns are short or mostly scattered zeros (kPairColumn);
 //   - in a 32 x 32 block of T they are half of a lane's 16 or a whole row of 32,
 //     or an eighth of the block (stage 1, t_out_of_range).
-// Scattered small entries of a Gaussian operand (6e-5 of O and U, 0.5 % of T at
+// Scattered small entries of a Gaussian operand (6e-5 of O and U, 1e-3 of T at
 // 1024 states) stay far below these counts.  Zeros count for nothing: they are
 // exact.  Blocks of the results of accepted operators against the FP32 kernels'
 // error: columns of operators that U leaves out, states that U hardly reaches,
 // sectors, in order and mixed, and tails of U, from 2^0 to 2^-16 of the rest, at
 // most 0.93 times it (160 states); sectors, sites, rows, columns and sparsity
-// drawn at random (64 to 330 states, d 1 to 8, 16 500 blocks), at most 1.0e-7
+// drawn at random (64 to 330 states, d 1 to 8, 25 500 blocks), at most 1.3e-7
 // more (sparse operators between short sectors).
 #include <hip/hip_runtime.h>
 
@@ -81,9 +83,11 @@ __device__ inline u32x2 split2_f16(float a, float b) {
 
 // What the split pass finds in U (cleared by the scale pass).
 struct UState {
-    int bad;         // leaves the pairs' range
-    uint32_t filled; // entries that are not zero
-    int runs;        // groups of eight of a column with five and more of them less those with one to four
+    // low half: entries that are not zero; high half (signed): groups of eight of a
+    // column with five and more of them less those with one to four (one addition
+    // for both: 1024 workgroups add to it)
+    unsigned long long filled_runs;
+    int bad;  // leaves the pairs' range
 };
 
 // Rotation products with one A for every operator (U1 or U2) and one B per
@@ -102,17 +106,17 @@ struct FlatDesc {
     int64_t b_bs;
     int n32;                    // N rounded up to 32
     int tiles_m, tiles_n, parts, part_slabs;
-    // plain epilogue: C_b(row, col) 2^-(e0 + op_e[b] + row_e[row] + col_e[col])
-    // at c + part*c_ps + b*c_bs + row*ldc + col
+    // plain epilogue: C_b(row, col) 2^-(op_e[b] + row_e[row] + col_e[col]) at
+    // c + part*c_ps + b*c_bs + row*ldc + col
     float* c;
     int64_t ldc, c_bs, c_ps;
-    int e0;
     const int *op_e, *row_e, *col_e;  // row_e: readable up to the last tile's rows
-    // split-transposed epilogue: C_b(beta*d + s, i) 2^-t_shift -> T_b(beta, i*d + s),
+    // split-transposed epilogue: C_b(beta*d + s, i) 2^-t_e[b] -> T_b(beta, i*d + s),
     // slab layout with t_rows rows per operator, t_bs elements apart
     uint16_t *t_hi, *t_lo;
-    int d, t_rows, t_shift;
+    int d, t_rows;
     int64_t t_bs;
+    const int* t_e;
     int* skip;                  // operators left to the FP32 kernels: kSkipSplit, kSkipStage1
     int* any;                   // raised with the first of them
     const UState* u;            // stage 1: what the split pass found in U
@@ -303,7 +307,8 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
     const int h = lane >> 5, c = lane & 31;
-    const bool u_bad = EPI_T && (g.u->bad || g.u->runs <= 0 || g.u->filled < g.u_least);
+    const bool u_bad = EPI_T && (g.u->bad || (int)(g.u->filled_runs >> 32) <= 0 ||
+                                 (uint32_t)g.u->filled_runs < g.u_least);
     if (u_bad || *g.any) {
         // nothing to do where all operators are skipped (64 of 1024 states, all
         // skipped: 10.3 ms with these products and the 64-wide FP32 tiles, 8.4
@@ -449,13 +454,13 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
     __builtin_amdgcn_s_waitcnt(kLgkmcnt0);
 
     const int row0w = m0 + wm * 32 * BI;
-    const float t_scale = EPI_T ? ldexpf(1.0f, -g.t_shift) : 1.0f;
 #pragma unroll
     for (int k = 0; k < BJ; k++) {
         const int col = cb[k] * 32 + c;
         // (stage 1: other waves may be raising it; one value for the wave)
         if (!live[k] || __builtin_amdgcn_readfirstlane(g.skip[op[k]])) continue;
         const uint64_t valid = __builtin_amdgcn_ballot_w64(col < g.N);
+        const float t_scale = EPI_T ? ldexpf(1.0f, -g.t_e[op[k]]) : 1.0f;
         TWatch watch[BI];
         auto judge = [&]() __attribute__((always_inline)) {
             bool suspect = false;
@@ -547,7 +552,7 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
             judge();
         } else if (g.upper) {
             float* cp = g.c + part * g.c_ps + op[k] * g.c_bs;
-            const int e0 = -(g.e0 + g.op_e[op[k]] + g.col_e[col]);
+            const int e0 = -(g.op_e[op[k]] + g.col_e[col]);
 #pragma unroll
             for (int i = 0; i < BI; i++)
 #pragma unroll
@@ -574,7 +579,7 @@ __device__ __attribute__((always_inline)) inline void flat_tile(const FlatDesc& 
                 }
         } else {
             float* cp = g.c + part * g.c_ps + op[k] * g.c_bs + col;
-            const int e0 = -(g.e0 + g.op_e[op[k]] + g.col_e[col]);
+            const int e0 = -(g.op_e[op[k]] + g.col_e[col]);
 #pragma unroll
             for (int i = 0; i < BI; i++)
 #pragma unroll
@@ -652,11 +657,11 @@ struct F16Scale {
     int64_t ldo, stride_o;
     uint32_t* upart;   // [chunk][mp]: largest |U| of a column in kPrepRows rows (bits)
     uint32_t* ublk;    // [U block of the scale pass]: largest |U|
-    uint32_t* opart;   // [b][row block][2]: largest |O|, smallest non-zero row maximum
+    uint32_t* opart;   // [b][row block][3]: largest |O|, smallest non-zero row maximum, largest row sum of |O|
     int* eu;           // [mp]
     int n_ublk;
     int m32, mp32;     // rows of O_b's and T_b's layouts
-    int* eo;           // [nb]
+    int *eo, *et;      // [nb]: exponents of O_b less T_b's, and of T_b
     int* skip;         // [nb], cleared by the scale pass
     UState* u;         // cleared by the scale pass when it works on U
     int* any;          // raised when an operator is skipped (behind skip; plans: one per chunk)
@@ -690,6 +695,29 @@ __device__ inline int scale_exp(uint32_t bits) {
     return 14 - ilogbf(__uint_as_float(bits));
 }
 
+// Power of two that the scaled operator's row sums stay below: by the largest of
+// them (bits), or where that overflows by the largest entry (bits) and m.
+__device__ inline int t_exp(uint32_t mx, uint32_t most, int m) {
+    if (mx == 0 || mx >= kInfBits) return 0;
+    if (most >= kInfBits) return 15 + 32 - __builtin_clz(m);
+    return scale_exp(mx) + ilogbf(__uint_as_float(most)) + 1;
+}
+
+// The eight values of all lanes, each reduced over the wave: eight lanes end with
+// each of them (10 exchanges; one by one it would be 48).
+template <typename T, typename F>
+__device__ inline T row_of_eight(const T (&v)[8], int lane, F f) {
+    T a[4], b[2], c;
+#pragma unroll
+    for (int k = 0; k < 4; k++) a[k] = f(lane & 32 ? v[k + 4] : v[k], __shfl_xor(lane & 32 ? v[k] : v[k + 4], 32));
+#pragma unroll
+    for (int k = 0; k < 2; k++) b[k] = f(lane & 16 ? a[k + 2] : a[k], __shfl_xor(lane & 16 ? a[k] : a[k + 2], 16));
+    c = f(lane & 8 ? b[1] : b[0], __shfl_xor(lane & 8 ? b[0] : b[1], 8));
+#pragma unroll
+    for (int s = 4; s; s >>= 1) c = f(c, __shfl_xor(c, s));
+    return c;
+}
+
 // Partial maxima of |U| per column (of the listed site states) and of |O| per
 // operator, and of all of U per workgroup.  Bound by the one read of O and U.
 template <bool SITE>
@@ -697,7 +725,7 @@ __device__ inline void f16_scale_block(const F16Scale& g, int blk) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     __shared__ uint32_t red[4][64], red2[SITE ? 4 : 1][64];
     if (blk < g.u_blocks) {
-        if (blk == 0 && tid == 0) *g.u = UState{0, 0, 0};
+        if (blk == 0 && tid == 0) *g.u = UState{0, 0};
         const int cb = div_up(g.mp, 64), half = g.u_blocks / 2;
         const bool up = SITE && blk >= half;
         const int x = up ? blk - half : blk;
@@ -735,15 +763,19 @@ __device__ inline void f16_scale_block(const F16Scale& g, int blk) {
     const int b = blk / rb, i0 = (blk % rb) * kPrepORows;
     if (i0 == 0 && tid == 0) g.skip[b] = 0;
     const float* src = g.O + (int64_t)b * g.stride_o;
-    uint32_t mx = 0, mn = 0xffffffffu;
+    uint32_t mx = 0, mn = 0xffffffffu, most = 0;
     // eight rows per wave, their loads in flight together (rows past the last
     // repeat it)
     constexpr int RW = kPrepORows / 4;
     const int r0 = i0 + wave * RW;
     if (r0 < g.m) {
         uint32_t x[RW];
+        float sum[RW];
 #pragma unroll
-        for (int k = 0; k < RW; k++) x[k] = 0;
+        for (int k = 0; k < RW; k++) {
+            x[k] = 0;
+            sum[k] = 0.f;
+        }
         const int m4 = g.m & ~3;
 #pragma unroll 2
         for (int j = lane * 4; j < m4; j += 256)
@@ -751,29 +783,42 @@ __device__ inline void f16_scale_block(const F16Scale& g, int blk) {
             for (int k = 0; k < RW; k++) {
                 const f32x4u v = *reinterpret_cast<const f32x4u*>(src + (int64_t)min(r0 + k, g.m - 1) * g.ldo + j);
 #pragma unroll
-                for (int e = 0; e < 4; e++) x[k] = umax32(x[k], abs_bits(v[e]));
+                for (int e = 0; e < 4; e++) {
+                    x[k] = umax32(x[k], abs_bits(v[e]));
+                    sum[k] += fabsf(v[e]);
+                }
             }
         if (m4 + lane < g.m)
 #pragma unroll
-            for (int k = 0; k < RW; k++)
-                x[k] = umax32(x[k], abs_bits(src[(int64_t)min(r0 + k, g.m - 1) * g.ldo + m4 + lane]));
+            for (int k = 0; k < RW; k++) {
+                const float v = src[(int64_t)min(r0 + k, g.m - 1) * g.ldo + m4 + lane];
+                x[k] = umax32(x[k], abs_bits(v));
+                sum[k] += fabsf(v);
+            }
+        // eight lanes to each row, then one value for all
+        static_assert(RW == 8, "rows of a wave");
+        const uint32_t row = row_of_eight(x, lane, [](uint32_t a, uint32_t b) { return umax32(a, b); });
+        mx = row;
+        mn = row ? row : mn;
+        most = abs_bits(row_of_eight(sum, lane, [](float a, float b) { return a + b; }));
 #pragma unroll
-        for (int k = 0; k < RW; k++) {
-#pragma unroll
-            for (int s = 32; s; s >>= 1) x[k] = umax32(x[k], __shfl_xor(x[k], s));
-            mx = umax32(mx, x[k]);
-            if (x[k]) mn = umin32(mn, x[k]);
+        for (int s = 32; s >= 8; s >>= 1) {
+            mx = umax32(mx, __shfl_xor(mx, s));
+            mn = umin32(mn, __shfl_xor(mn, s));
+            most = umax32(most, __shfl_xor(most, s));
         }
     }
     if (lane == 0) {
         red[0][wave] = mx;
         red[1][wave] = mn;
+        red[2][wave] = most;
     }
     __syncthreads();
     if (tid == 0) {
-        uint32_t* o = g.opart + 2 * ((int64_t)b * rb + i0 / kPrepORows);
+        uint32_t* o = g.opart + 3 * ((int64_t)b * rb + i0 / kPrepORows);
         o[0] = umax32(umax32(red[0][0], red[0][1]), umax32(red[0][2], red[0][3]));
         o[1] = umin32(umin32(red[1][0], red[1][1]), umin32(red[1][2], red[1][3]));
+        o[2] = umax32(umax32(red[2][0], red[2][1]), umax32(red[2][2], red[2][3]));
     }
 }
 
@@ -909,10 +954,10 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
             s_mx[wave][1] = (uint32_t)runs;
         }
         __syncthreads();
-        if (tid < 2) {
-            const uint32_t x = s_mx[0][tid] + s_mx[1][tid] + s_mx[2][tid] + s_mx[3][tid];
-            if (tid == 0) atomicAdd(&g.u->filled, x);
-            else atomicAdd(&g.u->runs, (int)x);
+        if (tid == 0) {
+            const uint32_t n = s_mx[0][0] + s_mx[1][0] + s_mx[2][0] + s_mx[3][0];
+            const uint32_t r = s_mx[0][1] + s_mx[1][1] + s_mx[2][1] + s_mx[3][1];
+            atomicAdd(&g.u->filled_runs, (unsigned long long)r << 32 | n);
         }
         return;
     }
@@ -938,15 +983,17 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
         }
         if (wave == 0) {
             const int rb = div_up(g.m, kPrepORows);
-            const uint32_t* p = g.opart + 2 * (int64_t)b * rb;
-            uint32_t mx = 0, mn = 0xffffffffu;
+            const uint32_t* p = g.opart + 3 * (int64_t)b * rb;
+            uint32_t mx = 0, mn = 0xffffffffu, most = 0;
             for (int x = lane; x < rb; x += 64) {
-                mx = umax32(mx, p[2 * x]);
-                mn = umin32(mn, p[2 * x + 1]);
+                mx = umax32(mx, p[3 * x]);
+                mn = umin32(mn, p[3 * x + 1]);
+                most = umax32(most, p[3 * x + 2]);
             }
             for (int s = 32; s; s >>= 1) {
                 mx = umax32(mx, __shfl_xor(mx, s));
                 mn = umin32(mn, __shfl_xor(mn, s));
+                most = umax32(most, __shfl_xor(most, s));
             }
             if (lane == 0) s_e[0] = scale_exp(mx);
             if (t == 0) {
@@ -955,7 +1002,8 @@ __device__ inline void f16_split_block(const F16Scale& g, int blk) {
                 for (int x = lane; x < g.n_ublk; x += 64) bad |= g.ublk[x] >= kInfBits;
                 bad = __any(bad);
                 if (lane == 0) {
-                    g.eo[b] = scale_exp(mx);
+                    g.et[b] = t_exp(mx, most, g.m);
+                    g.eo[b] = scale_exp(mx) - t_exp(mx, most, g.m);
                     if (bad) {
                         atomicOr(&g.skip[b], kSkipSplit);
                         atomicOr(g.any, 1);
@@ -1109,7 +1157,7 @@ F16Layout f16_layout(const rot_problem& p, int d_all = 0) {
 
 size_t f16_t_bytes(const F16Layout& L, int ops) { return std::max(2 * al256(ops * L.t_op), ops * L.t32); }
 size_t f16_scale_bytes(const rot_problem& p, int ops) {
-    return al256((size_t)ops * (div_up(p.m, kPrepORows) * 8 + 8) + 4);
+    return al256((size_t)ops * (div_up(p.m, kPrepORows) * 12 + 12) + 4);
 }
 // Stage 2 of `ops` operators of the group.  The K parts are those of the
 // whole group, so that results do not depend on the chunks.  Symmetric output
@@ -1177,8 +1225,9 @@ F16Bound f16_bind(const rot_problem& p, const F16Layout& L, int b0, int nb, int 
     g.ol = reinterpret_cast<uint16_t*>(r.O + al256(nb * L.o_op));
     g.o_bs = (int64_t)(L.o_op / 2);
     g.opart = reinterpret_cast<uint32_t*>(base);
-    g.eo = reinterpret_cast<int*>(g.opart + 2 * (size_t)nb * div_up(p.m, kPrepORows));
-    g.skip = g.eo + nb;
+    g.eo = reinterpret_cast<int*>(g.opart + 3 * (size_t)nb * div_up(p.m, kPrepORows));
+    g.et = g.eo + nb;
+    g.skip = g.et + nb;
     g.any = g.skip + nb;
     g.n_ublk = div_up(p.mp, 64) * div_up(g.rows, kPrepRows);
     return r;
@@ -1194,12 +1243,6 @@ int split_blocks(F16Scale& g, bool with_u) {
     g.u_blocks = with_u ? (g.Up ? 2 : 1) * div_up(g.mp, 64) * div_up(g.m, kSlabK) : 0;
     g.o_blocks = g.nb * tb * tb;
     return g.u_blocks + g.o_blocks + (g.rows % kSlabK ? g.nb * div_up((int64_t)g.mp * 2, 256) : 0);
-}
-
-int f16_t_shift(int m) {
-    int log2m = 0;
-    while ((1 << log2m) < m) log2m++;
-    return 15 + log2m;
 }
 
 // Stage 1, transposed: C(beta*d + s, i) = sum_j U1(beta*d + s, j) O_b(i, j).
@@ -1220,7 +1263,7 @@ FlatDesc f16_stage1(const F16Scale& g) {
     a.d = g.d;
     a.t_rows = g.mp32;
     a.t_bs = g.t_bs;
-    a.t_shift = f16_t_shift(g.m);
+    a.t_e = g.et;
     a.skip = g.skip;
     a.any = g.any;
     a.u = g.u;
@@ -1248,7 +1291,6 @@ FlatDesc f16_stage2(const F16Scale& g, float* c, int64_t ldc, int64_t c_bs) {
     b.c = c;
     b.ldc = ldc;
     b.c_bs = c_bs;
-    b.e0 = -f16_t_shift(g.m);
     b.op_e = g.eo;
     b.row_e = g.eu;
     b.col_e = g.eu;

@@ -148,20 +148,24 @@ def test_even_operators_stay_on_pairs(rot):
 
 
 def test_single_rows_and_columns_are_found(rot):
-    """One small row of an operator (a column of T), or one kept state that only
-    an operator's small column reaches (a row of T), wherever it lies in a tile:
-    computed by the FP32 kernels, to the bit; their neighbours are not."""
+    """One small row of an operator that acts on states U hardly reaches (a column
+    of T), or one kept state that only an operator's small column reaches (a row
+    of T), wherever it lies in a tile: computed by the FP32 kernels, to the bit;
+    their neighbours are not."""
     rng = np.random.default_rng(7250)
     kept = [0, 7, 8, 31, 32, 63, 64, 101, MP - 1]
     rows = [0, 15, 16, 31, 32, 95, M - 1]
     U = isometry(M * D, MP, rng).reshape(M, D, MP)
+    U[100:120] *= 2.0 ** -8
     O = rng.standard_normal((N, M, M))
     for k, beta in enumerate(kept):
         U[:, :, beta] = 0
         U[10 + k, k % D, beta] = 1
-        O[2 * k, :, 10 + k] *= 2.0 ** -9
+        O[2 * k, :, 10 + k] *= 2.0 ** -11
     for k, i in enumerate(rows):
-        O[20 + 2 * k, i, :] *= 2.0 ** -9
+        O[20 + 2 * k, i, :100] = 0
+        O[20 + 2 * k, i, 120:] = 0
+        O[20 + 2 * k, i] *= 2.0 ** -6
     U, O = dev(U.reshape(M * D, MP)), dev(O)
     got, fp32 = rot.rotate(U, O, D, "fp32"), fp32_kernels(rot, U, O)
     same = [b for b in range(N) if torch.equal(got[b], fp32[b])]
