@@ -147,6 +147,17 @@ def test_even_operators_stay_on_pairs(rot):
     assert [b for b in range(N) if same[b]] == [1, N - 2]
 
 
+def test_operators_whose_row_sums_overflow(rot, oracle_mod):
+    """T's scale comes from row sums of |O|; near FP32's largest value it comes
+    from the largest entry."""
+    U, O, blocks = inputs(left_out, 1.0, 7240)
+    O[3] *= 2.0 ** 124
+    O[4] *= 2.0 ** -100
+    got, fp32 = rot.rotate(U, O, D, "fp32"), fp32_kernels(rot, U, O)
+    assert not torch.equal(got[3], fp32[3]) and not torch.equal(got[4], fp32[4])
+    check(host(got[2:5]), host(fp32[2:5]), oracle_mod.rotate(host(U), host(O[2:5]), D), blocks)
+
+
 def test_single_rows_and_columns_are_found(rot):
     """One small row of an operator that acts on states U hardly reaches (a column
     of T), or one kept state that only an operator's small column reaches (a row
