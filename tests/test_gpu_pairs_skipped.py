@@ -101,6 +101,34 @@ def test_skipped_with_k_parts(rot, oracle_mod):
     check(oracle_mod, U, O, got, list(range(n)))
 
 
+def test_skipped_in_a_graph(rot):
+    """A captured batch judges its operators and U at each replay."""
+    U, O = inputs(200, 150, 90, 7750)
+    out = torch.empty((90, 150, 150), device="cuda")
+    ws = torch.empty(rot.rot_workspace_preferred([rot._problem(U, O, out, D)], rot.ROT_FP32), dtype=torch.uint8,
+                     device="cuda")
+    rot.rotate(U, O, D, "fp32", out=out, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rot.rotate(U, O, D, "fp32", out=out, workspace=ws)
+    U0, O0 = U.clone(), O.clone()
+    for step in range(4):
+        U.copy_(U0)
+        O.copy_(O0)
+        if step == 1:
+            grade(O, [3, 88])
+        if step == 2:
+            U[:400] *= 2.0 ** -20
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, rot.rotate(U, O, D, "fp32"))
+        fp32 = fp32_kernels(rot, U, O)
+        same = [b for b in range(90) if torch.equal(out[b], fp32[b])]
+        assert same == ([], [3, 88], list(range(90)), [])[step]
+
+
 @pytest.mark.parametrize("which", ["U", "O"])
 def test_skipped_batch_runs_no_products_on_pairs(rot, which):
     """The pairs' stages of a batch that is skipped whole take less than half of
